@@ -288,6 +288,7 @@ fs_status plan_create_impl(const fs_op_desc* ops, int32_t n_ops, const fs_plan_o
           // caller fixes no launch shape; the hand-written one serves the prebuilt mode.
           if (p->match.row.gelu && lo.codegen && lo.wg_size == 0 && lo.rows_per_wave == 0 && lo.grid == 0 && fall_back_to_generated()) break;
           if (fs::row_stitch_plan(p->match.row, lo, &p->row, &err)) {
+            p->lds_bytes = p->row.lds_bytes;
             p->description = fs::row_stitch_describe(p->match.row, p->row);
           } else if (err.find("wg_size") != std::string::npos || err.find("rows_per_wave") != std::string::npos) {
             delete p;
@@ -298,7 +299,7 @@ fs_status plan_create_impl(const fs_op_desc* ops, int32_t n_ops, const fs_plan_o
             p->lds_bytes = 2 * 16 * 4;
             p->description = fs::row_team_describe(p->match.row, p->row_team);
           } else {
-            // unaligned or very long row: block-composed form, row cached in LDS
+            // a row shorter than one vector, or too long for a team: block-composed form, row cached in LDS
             int st = FS_OK;
             fs::LaunchOpts lb = lo;
             if (!fs::row_block_plan(p->match.row, lb, &p->row_block, &st, &err)) {

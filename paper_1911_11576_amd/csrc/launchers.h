@@ -8,7 +8,7 @@
 
 namespace fs {
 
-struct RowLaunch { int variant = 0, K = 1, L = 64, U = 1, wg = 256, grid = 1; };
+struct RowLaunch { int variant = 0, K = 1, L = 64, U = 1, wg = 256, grid = 1; bool ragged = false; int64_t lds_bytes = 0; };
 bool row_stitch_plan(const RowSpec&, const LaunchOpts&, RowLaunch*, std::string* err);
 std::string row_stitch_describe(const RowSpec&, const RowLaunch&);
 int row_stitch_launch(const RowSpec&, const RowLaunch&, const void* const* in, void* const* out,
@@ -16,7 +16,7 @@ int row_stitch_launch(const RowSpec&, const RowLaunch&, const void* const* in, v
 
 // Wavefront-team form of the row schedule: a register-resident row spread over the
 // wavefronts of one workgroup (2049..32768 elements).
-struct RowTeamLaunch { int variant = 0, K = 1, wg = 128, grid = 1; };
+struct RowTeamLaunch { int variant = 0, K = 1, wg = 128, grid = 1; bool ragged = false; };
 bool row_team_plan(const RowSpec&, const LaunchOpts&, RowTeamLaunch*, std::string* err);
 std::string row_team_describe(const RowSpec&, const RowTeamLaunch&);
 int row_team_launch(const RowSpec&, const RowTeamLaunch&, const void* const* in, void* const* out,

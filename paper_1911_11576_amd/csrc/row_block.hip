@@ -1,7 +1,7 @@
 // Schedule 1, block-composed form (paper Section 5.1: a reduction schedule may use warp or
-// block composition, Section 5.3): the same groups as row_stitch, for rows that do not
-// fit one wavefront's register tile (cols > 2048) or whose length is not a multiple of the
-// 16-byte vector width.  One workgroup owns a row: the prologue's result is cached in LDS
+// block composition, Section 5.3): the same groups as row_stitch and row_team, for what those leave: rows
+// shorter than one 16-byte vector, rows beyond a team's registers (32769..40000 elements), and workgroup sizes
+// they do not take.  One workgroup owns a row: the prologue's result is cached in LDS
 // as fp32 (the `S` attribute), the two row reductions are wavefront all-reduces combined
 // across wavefronts through LDS, and the epilogue reads the row back from LDS.  Every
 // element of HBM is still touched exactly once.

@@ -26,12 +26,16 @@ int max_U(int K, int V) { return K * V <= 8 ? 4 : K * V <= 16 ? 2 : 1; }
 
 bool row_stitch_plan(const RowSpec& sp, const LaunchOpts& opt, RowLaunch* out, std::string* err) {
   const int V = 16 / dtype_size(sp.dtype);
-  if (sp.cols % V != 0) { *err = "row schedule: cols must be a multiple of the 16-byte vector width"; return false; }
-  const int64_t nvec = sp.cols / V;
+  if (sp.cols < V) { *err = "row schedule: row shorter than a 16-byte vector"; return false; }
+  const int64_t nvec = (sp.cols + V - 1) / V;
   // one wavefront holds a whole row in registers: at most 32 fp32 values per lane
   if (sp.cols > 2048) { *err = "row schedule: row longer than one wavefront's register tile (cols > 2048)"; return false; }
   if (sp.rows >= (int64_t)1 << 31) { *err = "row schedule: rows >= 2^31"; return false; }
   RowLaunch rl;
+  rl.ragged = sp.cols % V != 0;
+  // (launch options that only the block-composed form of a ragged row takes are left to it)
+  if (rl.ragged && opt.wg_size && (opt.wg_size < 64 || opt.wg_size > 512 || opt.wg_size % 64)) { *err = "row schedule: a ragged row with a workgroup of the block form"; return false; }
+  if (rl.ragged && opt.rows_per_wave > 8) { *err = "row schedule: a ragged row with an option of another form"; return false; }
   rl.K = pick_K((int)nvec);
   rl.L = pick_L((int)nvec);
   rl.wg = opt.wg_size ? opt.wg_size : 256;
@@ -52,6 +56,7 @@ bool row_stitch_plan(const RowSpec& sp, const LaunchOpts& opt, RowLaunch* out, s
   if (grid > 0x7fffffff) grid = 0x7fffffff;
   rl.grid = (int)grid;
   const bool mask_bcast = !(sp.mask_d1 == 1 && sp.mask_d2 == 1 && sp.mask_stride[0] == 1);
+  rl.lds_bytes = rl.ragged ? (int64_t)waves * rl.U * G * sp.cols * dtype_size(sp.dtype) : 0;      // at most 8 rows of 8188 bytes
   rl.variant = sp.core == CORE_LAYERNORM ? (sp.gelu ? 1 : 0) : (sp.in_mask < 0 ? 2 : mask_bcast ? 4 : 3);
   *out = rl;
   return true;
@@ -60,15 +65,17 @@ bool row_stitch_plan(const RowSpec& sp, const LaunchOpts& opt, RowLaunch* out, s
 std::string row_stitch_describe(const RowSpec& sp, const RowLaunch& rl) {
   // one schedule per reduction and per output, in the template notation of Section 5.2:
   // rows are tiled GRID then WARP (U row groups of 64/L rows per wavefront), columns are
-  // WARP-parallel with K vectors per lane; nothing carries the S attribute
+  // WARP-parallel with K vectors per lane; ragged rows leave through LDS (the S attribute)
   char buf[512];
   const int G = 64 / rl.L;
   const char* r1 = sp.core == CORE_LAYERNORM ? "reduce_mean" : "reduce_max";
   const char* r2 = sp.core == CORE_LAYERNORM ? "reduce_var" : "reduce_sum";
+  char lds[64] = "";
+  if (rl.ragged) snprintf(lds, sizeof lds, ", lds=%lld", (long long)rl.lds_bytes);
   snprintf(buf, sizeof buf,
-           "%s[GRID-WARP_%d,WARP]; %s[GRID-WARP_%d,WARP]; out[GRID-WARP_%d,WARP-THREAD_%d]; "
-           "cta_num=%d, cta_size=%d",
-           r1, rl.U * G, r2, rl.U * G, rl.U * G, rl.K * (16 / dtype_size(sp.dtype)), rl.grid, rl.wg);
+           "%s[GRID-WARP_%d,WARP]; %s[GRID-WARP_%d,WARP]; out[GRID-WARP_%d,%s-THREAD_%d]%s; "
+           "cta_num=%d, cta_size=%d%s",
+           r1, rl.U * G, r2, rl.U * G, rl.U * G, rl.ragged ? "CTA" : "WARP", rl.K * (16 / dtype_size(sp.dtype)), rl.ragged ? "S" : "", rl.grid, rl.wg, lds);
   return buf;
 }
 
@@ -83,7 +90,8 @@ void row_fill_args(const RowSpec& sp, const void* const* in, void* const* out, R
   a.y = out[0];
   a.rows = sp.rows;
   a.cols = (int)sp.cols;
-  a.nvec = (int)(sp.cols / (16 / dtype_size(sp.dtype)));
+  const int V = 16 / dtype_size(sp.dtype);
+  a.nvec = (int)((sp.cols + V - 1) / V);
   a.scale = sp.scale; a.eps = sp.eps; a.inv_n = (float)(1.0 / (double)sp.cols);
   // c*h*(1 + tanh(k0*(h + k1*h^3))) == 2c*h / (1 + exp2(h*(a0 + a1*h^2))), a0 = -2*k0*log2(e)
   a.g_mul = 2.f * sp.gelu_half;

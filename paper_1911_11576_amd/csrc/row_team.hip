@@ -1,5 +1,4 @@
-// Schedule 1, wavefront-team form: rows of 2049..32768 elements (a multiple of the
-// 16-byte vector width) stay register-resident like in row_stitch, but one row is held by a
+// Schedule 1, wavefront-team form: rows of 2049..32768 elements stay register-resident like in row_stitch, but one row is held by a
 // team of W wavefronts (one workgroup).  Wavefront w of the team owns the 1 KB chunks
 // w, w+W, w+2W, ... of the row (K chunks per wavefront), so the team reads W consecutive
 // kilobytes per step.  Each row reduction is a wave64 all-reduce followed by one exchange
@@ -19,9 +18,10 @@ __device__ __forceinline__ float team_allreduce(float v, float* slot, int waves,
   return r;
 }
 
-template <typename T, int VARIANT, int K, bool EXACT>
+template <typename T, int VARIANT, int K, int FIT>
 __global__ __launch_bounds__(1024) void row_team_kernel(const RowArgs a) {
   constexpr int V = Vec<T>::V;
+  constexpr bool EXACT = FIT == FIT_EXACT, RAGGED = FIT == FIT_RAGGED;
   constexpr bool kLN = VARIANT <= 1, kGelu = VARIANT == 1, kMask = VARIANT >= 3, kMaskBcast = VARIANT == 4;
   // two exchange buffers used alternately: a buffer is rewritten only after the barrier of
   // the other reduction has been passed by every wavefront
@@ -32,26 +32,29 @@ __global__ __launch_bounds__(1024) void row_team_kernel(const RowArgs a) {
   constexpr uint32_t kOne = sizeof(T) == 4 ? 0x3F800000u : (Vec<T>::kOneBits | (Vec<T>::kOneBits << 16));
 
   bool vld[K];
-  int voff[K];
+  int voff[K], dup[K];
 #pragma unroll
   for (int k = 0; k < K; ++k) {
     const int vi = (k * waves + w) * 64 + lane;
     vld[k] = EXACT || vi < a.nvec;
     voff[k] = (vld[k] ? vi : 0) * V;
+    dup[k] = 0;
+    if (RAGGED && vi == a.nvec - 1) { dup[k] = a.nvec * V - a.cols; voff[k] = a.cols - V; }
   }
+  auto counts = [&](int k, int j) { return EXACT || (vld[k] && (!RAGGED || j >= dup[k])); };
 
   for (int64_t row = blockIdx.x; row < a.rows; row += gridDim.x) {
     float v[K][V];
     u32x4 raw[K], aux[K];
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-      raw[k] = stream_load16(x + row * a.cols + voff[k]);
+      raw[k] = stream_load<T, !RAGGED>(x + row * a.cols + voff[k]);
       aux[k] = u32x4{0u, 0u, 0u, 0u};
     }
     if constexpr (kGelu) {
       if (a.res) {
 #pragma unroll
-        for (int k = 0; k < K; ++k) aux[k] = stream_load16(static_cast<const T*>(a.res) + row * a.cols + voff[k]);
+        for (int k = 0; k < K; ++k) aux[k] = stream_load<T, !RAGGED>(static_cast<const T*>(a.res) + row * a.cols + voff[k]);
       }
     }
     if constexpr (kMask) {
@@ -65,7 +68,7 @@ __global__ __launch_bounds__(1024) void row_team_kernel(const RowArgs a) {
       }
 #pragma unroll
       for (int k = 0; k < K; ++k)
-        aux[k] = kMaskBcast ? Vec<T>::load_raw(mk + mrow * a.cols + voff[k]) : stream_load16(mk + mrow * a.cols + voff[k]);
+        aux[k] = kMaskBcast ? cached_load<T, !RAGGED>(mk + mrow * a.cols + voff[k]) : stream_load<T, !RAGGED>(mk + mrow * a.cols + voff[k]);
     }
     // ---- thread-composed prologue ------------------------------------------------------
 #pragma unroll
@@ -76,7 +79,7 @@ __global__ __launch_bounds__(1024) void row_team_kernel(const RowArgs a) {
       if constexpr (kGelu) {
         float b[V];
         u32x4 braw = u32x4{0u, 0u, 0u, 0u};
-        if (a.bias) braw = Vec<T>::load_raw(static_cast<const T*>(a.bias) + voff[k]);
+        if (a.bias) braw = cached_load<T, !RAGGED>(static_cast<const T*>(a.bias) + voff[k]);
         Vec<T>::unpack(braw, b);
 #pragma unroll
         for (int j = 0; j < V; ++j) {
@@ -98,7 +101,7 @@ __global__ __launch_bounds__(1024) void row_team_kernel(const RowArgs a) {
 #pragma unroll
       for (int k = 0; k < K; ++k)
 #pragma unroll
-        for (int j = 0; j < V; ++j) s += vld[k] ? v[k][j] : 0.f;
+        for (int j = 0; j < V; ++j) s += counts(k, j) ? v[k][j] : 0.f;
       const float mean = team_allreduce<SumOp>(s, exch[0], waves, 0.f) * a.inv_n;
       float q = 0.f;
 #pragma unroll
@@ -106,21 +109,21 @@ __global__ __launch_bounds__(1024) void row_team_kernel(const RowArgs a) {
 #pragma unroll
         for (int j = 0; j < V; ++j) {
           v[k][j] -= mean;
-          q += vld[k] ? v[k][j] * v[k][j] : 0.f;
+          q += counts(k, j) ? v[k][j] * v[k][j] : 0.f;
         }
       const float var = team_allreduce<SumOp>(q, exch[1], waves, 0.f) * a.inv_n;
       const float rstd = 1.f / sqrtf(var + a.eps);
 #pragma unroll
       for (int k = 0; k < K; ++k) {
         u32x4 graw = u32x4{kOne, kOne, kOne, kOne}, braw = u32x4{0u, 0u, 0u, 0u};
-        if (a.gamma) graw = Vec<T>::load_raw(static_cast<const T*>(a.gamma) + voff[k]);
-        if (a.beta) braw = Vec<T>::load_raw(static_cast<const T*>(a.beta) + voff[k]);
+        if (a.gamma) graw = cached_load<T, !RAGGED>(static_cast<const T*>(a.gamma) + voff[k]);
+        if (a.beta) braw = cached_load<T, !RAGGED>(static_cast<const T*>(a.beta) + voff[k]);
         float o[V], gk[V], bk[V];
         Vec<T>::unpack(graw, gk);
         Vec<T>::unpack(braw, bk);
 #pragma unroll
         for (int j = 0; j < V; ++j) o[j] = (v[k][j] * rstd) * gk[j] + bk[j];
-        if (vld[k]) stream_store16(y + row * a.cols + voff[k], pack16<T>(o));
+        if (vld[k]) stream_store<T, !RAGGED>(y + row * a.cols + voff[k], pack16<T>(o));
       }
     } else {
       float mx = -INFINITY;
@@ -137,7 +140,7 @@ __global__ __launch_bounds__(1024) void row_team_kernel(const RowArgs a) {
         for (int j = 0; j < V; ++j) {
           const float e = vld[k] ? __builtin_amdgcn_exp2f(fmaf(v[k][j], kLog2e, nmx)) : 0.f;
           v[k][j] = e;
-          s += e;
+          s += !RAGGED || counts(k, j) ? e : 0.f;
         }
       s = team_allreduce<SumOp>(s, exch[1], waves, 0.f);
       const float inv = 1.f / s;
@@ -146,7 +149,7 @@ __global__ __launch_bounds__(1024) void row_team_kernel(const RowArgs a) {
         float o[V];
 #pragma unroll
         for (int j = 0; j < V; ++j) o[j] = v[k][j] * inv;
-        if (vld[k]) stream_store16(y + row * a.cols + voff[k], pack16<T>(o));
+        if (vld[k]) stream_store<T, !RAGGED>(y + row * a.cols + voff[k], pack16<T>(o));
       }
     }
   }
@@ -155,37 +158,38 @@ __global__ __launch_bounds__(1024) void row_team_kernel(const RowArgs a) {
 namespace {
 
 template <typename T, int VARIANT, int K>
-hipError_t team_launch_exact(const RowArgs& a, bool exact, int grid, int wg, hipStream_t s) {
-  if (exact) hipLaunchKernelGGL((row_team_kernel<T, VARIANT, K, true>), dim3(grid), dim3(wg), 0, s, a);
-  else hipLaunchKernelGGL((row_team_kernel<T, VARIANT, K, false>), dim3(grid), dim3(wg), 0, s, a);
+hipError_t team_launch_fit(const RowArgs& a, int fit, int grid, int wg, hipStream_t s) {
+  if (fit == FIT_EXACT) hipLaunchKernelGGL((row_team_kernel<T, VARIANT, K, FIT_EXACT>), dim3(grid), dim3(wg), 0, s, a);
+  else if (fit == FIT_VECTORS) hipLaunchKernelGGL((row_team_kernel<T, VARIANT, K, FIT_VECTORS>), dim3(grid), dim3(wg), 0, s, a);
+  else hipLaunchKernelGGL((row_team_kernel<T, VARIANT, K, FIT_RAGGED>), dim3(grid), dim3(wg), 0, s, a);
   return hipGetLastError();
 }
 
 template <typename T, int VARIANT>
-hipError_t team_launch_K(const RowArgs& a, int K, bool exact, int grid, int wg, hipStream_t s) {
+hipError_t team_launch_K(const RowArgs& a, int K, int fit, int grid, int wg, hipStream_t s) {
   switch (K) {
-    case 1: return team_launch_exact<T, VARIANT, 1>(a, exact, grid, wg, s);
-    case 2: return team_launch_exact<T, VARIANT, 2>(a, exact, grid, wg, s);
-    case 3: return team_launch_exact<T, VARIANT, 3>(a, exact, grid, wg, s);
-    case 4: return team_launch_exact<T, VARIANT, 4>(a, exact, grid, wg, s);
+    case 1: return team_launch_fit<T, VARIANT, 1>(a, fit, grid, wg, s);
+    case 2: return team_launch_fit<T, VARIANT, 2>(a, fit, grid, wg, s);
+    case 3: return team_launch_fit<T, VARIANT, 3>(a, fit, grid, wg, s);
+    case 4: return team_launch_fit<T, VARIANT, 4>(a, fit, grid, wg, s);
     default: break;
   }
   if constexpr (Vec<T>::V == 4) {
-    if (K == 6) return team_launch_exact<T, VARIANT, 6>(a, exact, grid, wg, s);
-    if (K == 8) return team_launch_exact<T, VARIANT, 8>(a, exact, grid, wg, s);
+    if (K == 6) return team_launch_fit<T, VARIANT, 6>(a, fit, grid, wg, s);
+    if (K == 8) return team_launch_fit<T, VARIANT, 8>(a, fit, grid, wg, s);
   }
   return hipErrorInvalidValue;
 }
 
 template <typename T>
 hipError_t team_launch_variant(const RowArgs& a, const RowTeamLaunch& l, hipStream_t s) {
-  const bool exact = a.nvec == l.K * (l.wg / 64) * 64;
+  const int fit = l.ragged ? FIT_RAGGED : a.nvec == l.K * (l.wg / 64) * 64 ? FIT_EXACT : FIT_VECTORS;
   switch (l.variant) {
-    case 0: return team_launch_K<T, 0>(a, l.K, exact, l.grid, l.wg, s);
-    case 1: return team_launch_K<T, 1>(a, l.K, exact, l.grid, l.wg, s);
-    case 2: return team_launch_K<T, 2>(a, l.K, exact, l.grid, l.wg, s);
-    case 3: return team_launch_K<T, 3>(a, l.K, exact, l.grid, l.wg, s);
-    default: return team_launch_K<T, 4>(a, l.K, exact, l.grid, l.wg, s);
+    case 0: return team_launch_K<T, 0>(a, l.K, fit, l.grid, l.wg, s);
+    case 1: return team_launch_K<T, 1>(a, l.K, fit, l.grid, l.wg, s);
+    case 2: return team_launch_K<T, 2>(a, l.K, fit, l.grid, l.wg, s);
+    case 3: return team_launch_K<T, 3>(a, l.K, fit, l.grid, l.wg, s);
+    default: return team_launch_K<T, 4>(a, l.K, fit, l.grid, l.wg, s);
   }
 }
 
@@ -198,12 +202,13 @@ int pick_team_K(int need, int kmax) {
 
 bool row_team_plan(const RowSpec& sp, const LaunchOpts& opt, RowTeamLaunch* out, std::string* err) {
   const int V = 16 / dtype_size(sp.dtype);
-  if (sp.cols % V != 0) { *err = "row schedule (team form): cols must be a multiple of the 16-byte vector width"; return false; }
+  if (sp.cols < V) { *err = "row schedule (team form): row shorter than a 16-byte vector"; return false; }
   if (sp.rows >= (int64_t)1 << 31) { *err = "row schedule: rows >= 2^31"; return false; }
-  const int64_t nvec = sp.cols / V;
+  const int64_t nvec = (sp.cols + V - 1) / V;
   const int kmax = V == 4 ? 8 : 4;       // at most 32 fp32 values of a row per lane
   // smallest team whose lanes hold at most 16 values each, else the smallest that fits at all
   RowTeamLaunch l;
+  l.ragged = sp.cols % V != 0;
   int waves = 0;
   if (opt.wg_size) {
     if (opt.wg_size < 128 || opt.wg_size > 1024 || (opt.wg_size & (opt.wg_size - 1))) {

@@ -158,6 +158,29 @@ def test_softmax_long_or_unaligned_rows(shape, mask):
                          inputs.scaled_masked_softmax(shape, mask), what=f"softmax block {shape} {mask}")
 
 
+# rows whose length is no multiple of the 16-byte vector: one vector and a bit, the edges of the lane tiles (8 .. 64 lanes, 1 .. 8
+# vectors), of a wavefront (2048) and of a team; row counts that leave the last workgroup partly empty
+RAGGED = [(5, 9), (70, 31), (131, 33), (67, 129), (1000, 197), (37, 255), (41, 513), (29, 999), (9, 1025), (5, 2047), (3, 2049), (4, 3001), (2, 8193),
+          (2, 32767)]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
+@pytest.mark.parametrize("rows,cols", RAGGED)
+def test_ragged_rows(dtype, rows, cols):
+    announce(f"ragged rows {dtype} {rows}x{cols}")
+    check_against_oracle(graphs.layernorm_fwd(rows, cols, dtype), inputs.layernorm_fwd(rows, cols, dtype), what=f"ln ragged {rows}x{cols}")
+    check_against_oracle(graphs.bias_gelu_residual_layernorm(rows, cols, dtype), inputs.bias_gelu_residual_layernorm(rows, cols, dtype), "prebuilt",
+                         what=f"cfg4 ragged {rows}x{cols}")
+    for mask in ("none", "full"):
+        check_against_oracle(graphs.scaled_masked_softmax((rows, cols), 0.125, mask, dtype), inputs.scaled_masked_softmax((rows, cols), mask, dtype),
+                             what=f"softmax ragged {rows}x{cols} {mask}")
+    shape = (2, 2, rows, cols)
+    ops, ins = graphs.scaled_masked_softmax(shape, 0.125, "key_padding", dtype), inputs.scaled_masked_softmax(shape, "key_padding", dtype)
+    ref, _ = check_against_oracle(ops, ins, what=f"softmax ragged {shape}")
+    for opts in (dict(grid=3), dict(wg_size=128), dict(rows_per_wave=4, grid=2)):       # several trips of the row loop, other tiles
+        assert np.array_equal(run_gpu(ops, ins, **opts)[0], ref[0]) or cols > 2048
+
+
 @pytest.mark.parametrize("rows,cols", [(3, 2052), (5, 5000), (4, 8192), (2, 32768), (3, 20480)])
 def test_layernorm_team_form_f32(rows, cols):
     announce(f"layernorm team form f32 {rows}x{cols}")
