@@ -133,7 +133,7 @@ template <> struct Unaligned16<bf16_t> { typedef uint32_t type __attribute__((ex
 template <> struct Unaligned16<f16_t> { typedef uint32_t type __attribute__((ext_vector_type(4), aligned(2))); };
 template <typename T, bool ALIGNED> __device__ __forceinline__ u32x4 stream_load(const T* p) {
   if constexpr (ALIGNED) return stream_load16(p);
-  else return __builtin_nontemporal_load(reinterpret_cast<const typename Unaligned16<T>::type*>(p));
+  else return *reinterpret_cast<const typename Unaligned16<T>::type*>(p);      // (lines at row ends are shared with the neighbour: cached)
 }
 template <typename T, bool ALIGNED> __device__ __forceinline__ u32x4 cached_load(const T* p) {
   if constexpr (ALIGNED) return Vec<T>::load_raw(p);
