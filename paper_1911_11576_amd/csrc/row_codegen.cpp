@@ -731,9 +731,45 @@ int chunk_elements(const Analysis& A, bool* fast) {
   return 0;
 }
 
+// Elements per 16-byte access where no width above two divides the row (or an operand's strides): accesses are
+// aligned to the element only, and the row's last chunk is moved back to end with the row, so that its first
+// elements are its neighbour's too (they count in no reduction and are not stored).  0: the row is too short for
+// it, or an operand is strided along the last dim.  With column reductions a lane's running sums have to stay
+// within 16 per reduction set.
+// The memory system takes 16-byte accesses at any address at nearly the aligned rate, and one- or two-element ones
+// cost four to eight times the instructions; but a row of a few chunks leaves lanes idle that single elements fill.
+// Measured, single elements against ragged chunks: LayerNorm over 32768 rows of 333 fp16 8.3 against 8.9 us, 94 fp32
+// columns (the motivating pattern) 47 against 52; 8192 x 999 fp32 12.1 against 11.0, 8192 x 2047 bf16 14.1 against
+// 12.4, 4096 x 3001 fp32 22.2 against 16.3, LayerNorm backward over 4096 x 3001 40.8 against 35.1.  So from 512 on.
+// Neighbouring rows share lines: ragged chunks are loaded through the caches (that last figure is 40.4 with
+// nontemporal loads).
+constexpr int64_t kRaggedCols = 512;
+int ragged_chunk_elements(const Analysis& A) {
+  bool any32 = false;
+  for (const RView& v : A.views) {
+    if (v.cls != CLS_FULL) continue;
+    const int64_t ls = v.stride[A.rank - 1];
+    if (ls != 0 && ls != 1) return 0;
+    if (ls == 1 && v.dtype == FS_F32) any32 = true;
+  }
+  for (const RNode& n : A.nodes) if (n.out_ord >= 0 && n.cls == CLS_FULL && n.out_dtype == FS_F32) any32 = true;
+  for (int w : {8, 4})
+    if (!(w == 8 && any32) && A.cols >= kRaggedCols && (A.n_col == 0 || w * A.n_col <= 16)) return w;
+  return 0;
+}
+
+// what a ragged kernel adds: the vector types aligned to their element
+const char* kRaggedPreamble = R"SRC(
+typedef float f32x4e __attribute__((ext_vector_type(4), aligned(4)));
+typedef unsigned u32x2e __attribute__((ext_vector_type(2), aligned(2)));
+typedef unsigned u32x4e __attribute__((ext_vector_type(4), aligned(2)));
+)SRC";
+
 struct Gen {
   const Analysis& A;
   int L = 64, K = 1, W = 4;
+  bool ragged = false;        // chunks are aligned to the element only and the last one overlaps its neighbour
+  bool allow_ragged = true;
   bool exact = true;          // K*L chunks cover the row exactly
   bool fast = false;          // 16-bit group: short tanh
   std::vector<int> splat;     // per view: 1 if one scalar per row (last stride 0 or row view)
@@ -897,9 +933,19 @@ struct Gen {
 
   bool geometry(std::string* err) {
     if (A.mma_in >= 0) return geometry_mma(err);
+    if (geometry_rows(err)) return true;
+    if (!ragged) return false;
+    // what only narrow chunks fit (running sums of several column reductions over long rows)
+    allow_ragged = ragged = persistent = false;
+    L = 64;
+    return geometry_rows(err);
+  }
+  bool geometry_rows(std::string* err) {
     W = chunk_elements(A, &fast);
     if (W == 0) { *err = "generated row schedule: an operand strided along the last dim"; return false; }
-    const int64_t nvec = A.cols / W;
+    const int rw = allow_ragged && W <= 2 ? ragged_chunk_elements(A) : 0;
+    if (rw > W) { W = rw; ragged = true; }
+    const int64_t nvec = (A.cols + W - 1) / W;
     auto pow2_at_least = [](int64_t v) { int p = 1; while (p < v && p < 64) p *= 2; return p; };
     if (lanes_per_row > 0) {
       // the caller's template
@@ -937,7 +983,7 @@ struct Gen {
                                : "generated row schedule: row longer than 32768 elements";
       return false;
     }
-    exact = (int64_t)K * L == nvec;
+    exact = (int64_t)K * L == nvec && !ragged;
     // Short rows that do not fill whole 128-byte lines: a workgroup's rows are contiguous in
     // memory, so its full outputs are first laid out in LDS and then stored as one dense run
     // of 16-byte accesses (stores of separate row pieces straddle lines and measured 2x slower).
@@ -947,7 +993,7 @@ struct Gen {
         // running sums (two registers per column and reduction) stay few by spreading the row wider
         while ((int64_t)K * W * A.n_col > 16 && L < 1024) { L *= 2; K = (int)((nvec + L - 1) / L); }
         if ((int64_t)K * W * A.n_col > 16) { *err = "generated row schedule: column reductions over rows too long for their running sums to stay in registers"; return false; }
-        exact = (int64_t)K * L == nvec;
+        exact = (int64_t)K * L == nvec && !ragged;
       } else if ((int64_t)A.n_col * A.cols * 8 > 96 * 1024) {
         *err = "generated row schedule: column accumulators exceed the LDS";
         return false;
@@ -1163,6 +1209,9 @@ struct Gen {
     e.s = ew_preamble();
     e.s += kReducePreamble;
     if (mma) e.s += kMmaPreamble;
+    if (ragged) e.s += kRaggedPreamble;
+    const std::string al = ragged ? "e" : "";       // the vector types' suffix
+    const char* if_counts = ragged ? "if (j >= lo[k]) " : "";   // an element of a chunk that is its own
     const int T = L > 64 ? L / 64 : 1;      // wavefronts per row
     // (matrix-unit kernels: two wavefronts per SIMD asked for, so that the register budget is the 256 ordinary
     // registers and the compiler keeps the accumulators there instead of copying through the accumulation file)
@@ -1189,15 +1238,27 @@ struct Gen {
     }
     if (stage) {
       e.line("  constexpr int RPW = %d, N = %lld;            // rows per workgroup, row length", wg / L, (long long)A.cols);
-      e.line("  __shared__ float stage[RPW * N];");
+      e.line("  __shared__ __attribute__((aligned(16))) float stage[RPW * N];");
       e.line("  const int row_local = threadIdx.x / L;");
       e.line("  const long long wg_row0 = (long long)blockIdx.x * RPW;");
       e.line("  const long long left = %lldll - wg_row0;", (long long)A.rows);
       e.line("  const int wg_count = (int)(left < RPW ? left : RPW) * N;   // elements this workgroup owns");
     }
-    e.line("  int col[K]; bool ok[K];");
-    e.line("  UNROLL for (int k = 0; k < K; ++k) { const int c = k * L + lane; ok[k] = c < %lld; col[k] = (ok[k] ? c : 0) * W; }",
-           (long long)(A.cols / W));
+    if (ragged) {
+      // lo: elements of the chunk that its neighbour holds too (the row's last chunk ends with the row)
+      const int64_t nvec = (A.cols + W - 1) / W;
+      e.line("  int col[K], lo[K]; bool ok[K];");
+      e.line("  UNROLL for (int k = 0; k < K; ++k) {");
+      e.line("    const int c = k * L + lane;");
+      e.line("    ok[k] = c < %lld;", (long long)nvec);
+      e.line("    col[k] = c == %lld ? %lld : (ok[k] ? c : 0) * W;", (long long)nvec - 1, (long long)A.cols - W);
+      e.line("    lo[k] = c == %lld ? %lld : 0;", (long long)nvec - 1, (long long)(nvec * W - A.cols));
+      e.line("  }");
+    } else {
+      e.line("  int col[K]; bool ok[K];");
+      e.line("  UNROLL for (int k = 0; k < K; ++k) { const int c = k * L + lane; ok[k] = c < %lld; col[k] = (ok[k] ? c : 0) * W; }",
+             (long long)(A.cols / W));
+    }
     if (persistent) {
       // Column reductions: every lane keeps a double-precision running sum for each of its
       // columns while the workgroups loop over the rows; the sums of a workgroup meet in LDS
@@ -1339,23 +1400,26 @@ struct Gen {
         const RView& v = A.views[q];
         const char* ty = v.dtype == FS_F32 ? "float" : "unsigned short";
         const char* rt = raw_type(v);
+        const std::string pt_s = rt + al;
+        const char* pt = pt_s.c_str();
+        const char* ld = ragged ? "*" : "__builtin_nontemporal_load";
         bool dummy = false;
         const std::string offp = row_offset(v, &dummy, "rowp"), offn = row_offset(v, &dummy, "rown");
         if (rotating) {
           snprintf(buf, sizeof buf, "  %s raw%zux[%d][K];\n", rt, q, nb);
           pro += buf;
-          snprintf(buf, sizeof buf, "    UNROLL for (int k = 0; k < K; ++k) raw%zux[pp][k] = __builtin_nontemporal_load(reinterpret_cast<const %s*>(static_cast<const %s*>(a.in[%zu]) + (%s) + col[k]));\n",
-                   q, rt, ty, q, offp.c_str());
+          snprintf(buf, sizeof buf, "    UNROLL for (int k = 0; k < K; ++k) raw%zux[pp][k] = %s(reinterpret_cast<const %s*>(static_cast<const %s*>(a.in[%zu]) + (%s) + col[k]));\n",
+                   q, ld, pt, ty, q, offp.c_str());
           pro_req += buf;
-          snprintf(buf, sizeof buf, "  UNROLL for (int k = 0; k < K; ++k) raw%zux[(ph + %d) %% %d][k] = __builtin_nontemporal_load(reinterpret_cast<const %s*>(static_cast<const %s*>(a.in[%zu]) + (%s) + col[k]));\n",
-                   q, depth, nb, rt, ty, q, offn.c_str());
+          snprintf(buf, sizeof buf, "  UNROLL for (int k = 0; k < K; ++k) raw%zux[(ph + %d) %% %d][k] = %s(reinterpret_cast<const %s*>(static_cast<const %s*>(a.in[%zu]) + (%s) + col[k]));\n",
+                   q, depth, nb, ld, pt, ty, q, offn.c_str());
           nxt += buf;
         } else {
-          snprintf(buf, sizeof buf, "  %s raw%zu[K];\n  UNROLL for (int k = 0; k < K; ++k) raw%zu[k] = __builtin_nontemporal_load(reinterpret_cast<const %s*>(static_cast<const %s*>(a.in[%zu]) + (%s) + col[k]));\n",
-                   rt, q, q, rt, ty, q, offp.c_str());
+          snprintf(buf, sizeof buf, "  %s raw%zu[K];\n  UNROLL for (int k = 0; k < K; ++k) raw%zu[k] = %s(reinterpret_cast<const %s*>(static_cast<const %s*>(a.in[%zu]) + (%s) + col[k]));\n",
+                   rt, q, q, ld, pt, ty, q, offp.c_str());
           pro += buf;
-          snprintf(buf, sizeof buf, "  %s nraw%zu[K];\n  UNROLL for (int k = 0; k < K; ++k) nraw%zu[k] = __builtin_nontemporal_load(reinterpret_cast<const %s*>(static_cast<const %s*>(a.in[%zu]) + (%s) + col[k]));\n",
-                   rt, q, q, rt, ty, q, offn.c_str());
+          snprintf(buf, sizeof buf, "  %s nraw%zu[K];\n  UNROLL for (int k = 0; k < K; ++k) nraw%zu[k] = %s(reinterpret_cast<const %s*>(static_cast<const %s*>(a.in[%zu]) + (%s) + col[k]));\n",
+                   rt, q, q, ld, pt, ty, q, offn.c_str());
           nxt += buf;
           snprintf(buf, sizeof buf, "  UNROLL for (int k = 0; k < K; ++k) raw%zu[k] = nraw%zu[k];\n", q, q);
           adv += buf;
@@ -1432,7 +1496,7 @@ struct Gen {
       // tensors of the group's own shape stream through once; per-column operands are shared by all rows
       bool dense = true;
       for (int d = 0; d < nrow; ++d) if (A.S[d] != 1 && v.stride[d] == 0) dense = false;
-      const char* ld = dense ? "__builtin_nontemporal_load" : "*";
+      const char* ld = dense && !ragged ? "__builtin_nontemporal_load" : "*";
       e.line("  float v%zu[K][W];", q);
       e.line("  UNROLL for (int k = 0; k < K; ++k) {");
       e.line("    const %s* p = static_cast<const %s*>(a.in[%zu]) + (%s) + col[k];", ty, ty, q, roff[q].c_str());
@@ -1443,7 +1507,7 @@ struct Gen {
         e.line("    v%zu[k][0] = x[0]; v%zu[k][1] = x[1];", q, q);
       } else if (v.dtype == FS_F32) {
         for (int h = 0; h < W / 4; ++h) {
-          e.line("    { const f32x4 x = %s(reinterpret_cast<const f32x4*>(p) + %d);", ld, h);
+          e.line("    { const f32x4 x = %s(reinterpret_cast<const f32x4%s*>(p) + %d);", ld, al.c_str(), h);
           e.line("      UNROLL for (int j = 0; j < 4; ++j) v%zu[k][%d + j] = x[j]; }", q, 4 * h);
         }
       } else {
@@ -1453,7 +1517,7 @@ struct Gen {
           e.line("    const unsigned x1 = %s(reinterpret_cast<const unsigned*>(p));", ld);
           e.line("    const unsigned x[1] = {x1};");
         } else {
-          e.line("    const %s x = %s(reinterpret_cast<const %s*>(p));", W == 8 ? "u32x4" : "u32x2", ld, W == 8 ? "u32x4" : "u32x2");
+          e.line("    const %s x = %s(reinterpret_cast<const %s%s*>(p));", W == 8 ? "u32x4" : "u32x2", ld, W == 8 ? "u32x4" : "u32x2", al.c_str());
         }
         e.line("    UNROLL for (int j = 0; j < W / 2; ++j) { v%zu[k][2 * j] = %s(x[j]); v%zu[k][2 * j + 1] = %s(x[j]); }", q, lo, q, hi);
       }
@@ -1484,7 +1548,7 @@ struct Gen {
         const std::string x = opnd(n.o[0], CLS_FULL);
         if (n.op == FS_REDUCE_MAX)
           e.line("  if (row_ok) UNROLL for (int k = 0; k < K; ++k) UNROLL for (int j = 0; j < W; ++j) ca%d[k][j] = fmax(ca%d[k][j], (double)%s);", n.id, n.id, x.c_str());
-        else
+        else      // (what a ragged row's last chunk sums up of its neighbour's columns is not stored)
           e.line("  if (row_ok) UNROLL for (int k = 0; k < K; ++k) UNROLL for (int j = 0; j < W; ++j) ca%d[k][j] += (double)%s;", n.id, x.c_str());
         continue;
       }
@@ -1501,7 +1565,7 @@ struct Gen {
         e.line("  float r%d = %s;", n.id, sum ? "0.0f" : "-__builtin_inff()");
         e.line("  UNROLL for (int k = 0; k < K; ++k) {");
         if (!exact) e.line("    if (!ok[k]) continue;");
-        e.line("    UNROLL for (int j = 0; j < W; ++j) r%d = %s;", n.id,
+        e.line("    UNROLL for (int j = 0; j < W; ++j) %sr%d = %s;", if_counts, n.id,
                sum ? ("r" + std::to_string(n.id) + " + " + x).c_str() : ("fmaxf(r" + std::to_string(n.id) + ", " + x + ")").c_str());
         e.line("  }");
         combine(n.id, sum);
@@ -1511,7 +1575,7 @@ struct Gen {
         e.line("  float r%d = 0.0f;", n.id);
         e.line("  UNROLL for (int k = 0; k < K; ++k) {");
         if (!exact) e.line("    if (!ok[k]) continue;");
-        e.line("    UNROLL for (int j = 0; j < W; ++j) r%d = fmaf(%s, v%d[k][j], r%d);", n.id, x.c_str(), n.dot_full[0], n.id);
+        e.line("    UNROLL for (int j = 0; j < W; ++j) %sr%d = fmaf(%s, v%d[k][j], r%d);", if_counts, n.id, x.c_str(), n.dot_full[0], n.id);
         e.line("  }");
         combine(n.id, true);
       } else if (n.op == ROP_DOT_MMA_IN) {
@@ -1557,45 +1621,78 @@ struct Gen {
         continue;
       }
       if (stage) {
+        // The tile holds the values as they are stored; a lane writes a chunk at once (element-wise writes of lanes
+        // W elements apart fall on the same banks).
+        const bool f32 = n.out_dtype == FS_F32;
+        const char* cv = n.out_dtype == FS_F16 ? "to_f16" : "to_bf16";
+        const char* ty = f32 ? "float" : "unsigned short";
+        const int V = f32 ? 4 : 8;                       // elements of a 16-byte store
+        const bool even = ((int64_t)(wg / L) * A.cols) % V == 0;      // every workgroup's run starts on 16 bytes
         e.line("  __syncthreads();                             // the tile's previous use is over");
+        e.line("  {");
+        e.line("  %s* const st = reinterpret_cast<%s*>(stage);", ty, ty);
         e.line("  UNROLL for (int k = 0; k < K; ++k) {");
         e.line("    if (!ok[k]) continue;");
-        e.line("    UNROLL for (int j = 0; j < W; ++j) stage[row_local * N + col[k] + j] = t%d[k][j];", n.id);
+        e.line("    %s* p = st + row_local * N + col[k];", ty);
+        auto by_element = [&](const char* ind, const char* cond) {
+          if (f32) e.line("%sUNROLL for (int j = 0; j < W; ++j) %sp[j] = t%d[k][j];", ind, cond, n.id);
+          else e.line("%sUNROLL for (int j = 0; j < W; ++j) %sp[j] = (unsigned short)%s(t%d[k][j]);", ind, cond, cv, n.id);
+        };
+        if (W == 1 || (W == 2 && f32)) {
+          by_element("    ", "");
+        } else {
+          if (ragged) {
+            e.line("    if (lo[k] > 0) {");
+            by_element("      ", "if (j >= lo[k]) ");
+            e.line("      continue;");
+            e.line("    }");
+          }
+          if (f32) {
+            e.line("    *reinterpret_cast<f32x4%s*>(p) = f32x4%s{t%d[k][0], t%d[k][1], t%d[k][2], t%d[k][3]};", al.c_str(), al.c_str(), n.id, n.id, n.id, n.id);
+          } else {
+            e.line("    unsigned w[W / 2];");
+            e.line("    UNROLL for (int j = 0; j < W / 2; ++j) w[j] = pack_%s(t%d[k][2 * j], t%d[k][2 * j + 1]);", cv, n.id, n.id);
+            if (W == 8) e.line("    *reinterpret_cast<u32x4%s*>(p) = u32x4%s{w[0], w[1], w[2], w[3]};", al.c_str(), al.c_str());
+            else if (W == 4) e.line("    *reinterpret_cast<u32x2%s*>(p) = u32x2%s{w[0], w[1]};", al.c_str(), al.c_str());
+            else e.line("    *reinterpret_cast<unsigned*>(p) = w[0];");
+          }
+        }
         e.line("  }");
         e.line("  __syncthreads();");
-        if (n.out_dtype == FS_F32) {
-          e.line("  {");
-          e.line("    float* o = static_cast<float*>(a.out[%d]) + wg_row0 * N;", n.out_ord);
-          e.line("    for (int i = threadIdx.x * 4; i + 4 <= wg_count; i += %d * 4)", wg);
-          e.line("      __builtin_nontemporal_store(f32x4{stage[i], stage[i + 1], stage[i + 2], stage[i + 3]}, reinterpret_cast<f32x4*>(o + i));");
-          e.line("    for (int i = (wg_count & ~3) + threadIdx.x; i < wg_count; i += %d) o[i] = stage[i];", wg);
-          e.line("  }");
+        e.line("  %s* o = static_cast<%s*>(a.out[%d]) + wg_row0 * N;", ty, ty, n.out_ord);
+        const char* vt = f32 ? "f32x4" : "u32x4";
+        if (even) {
+          e.line("  for (int i = threadIdx.x * %d; i + %d <= wg_count; i += %d * %d)", V, V, wg, V);
+          e.line("    __builtin_nontemporal_store(*reinterpret_cast<const %s*>(st + i), reinterpret_cast<%s*>(o + i));", vt, vt);
+          e.line("  for (int i = wg_count / %d * %d + threadIdx.x; i < wg_count; i += %d) o[i] = st[i];", V, V, wg);
         } else {
-          const char* cv = n.out_dtype == FS_F16 ? "to_f16" : "to_bf16";
-          // 8 values per 16-byte store where the workgroup's first element is 16-byte aligned, else 4
-          const int V = ((int64_t)(wg / L) * A.cols) % 8 == 0 ? 8 : 4;
-          e.line("  {");
-          e.line("    unsigned short* o = static_cast<unsigned short*>(a.out[%d]) + wg_row0 * N;", n.out_ord);
-          e.line("    for (int i = threadIdx.x * %d; i + %d <= wg_count; i += %d * %d) {", V, V, wg, V);
-          e.line("      unsigned w[%d];", V / 2);
-          e.line("      UNROLL for (int j = 0; j < %d; ++j) w[j] = pack_%s(stage[i + 2 * j], stage[i + 2 * j + 1]);", V / 2, cv);
-          if (V == 8) e.line("      __builtin_nontemporal_store(u32x4{w[0], w[1], w[2], w[3]}, reinterpret_cast<u32x4*>(o + i));");
-          else e.line("      __builtin_nontemporal_store(u32x2{w[0], w[1]}, reinterpret_cast<u32x2*>(o + i));");
-          e.line("    }");
-          e.line("    for (int i = wg_count / %d * %d + threadIdx.x; i < wg_count; i += %d) o[i] = (unsigned short)%s(stage[i]);", V, V, wg, cv);
-          e.line("  }");
+          // 16-bit values, a run that starts on 8 bytes
+          e.line("  for (int i = threadIdx.x * 4; i + 4 <= wg_count; i += %d * 4)", wg);
+          e.line("    __builtin_nontemporal_store(*reinterpret_cast<const u32x2*>(st + i), reinterpret_cast<u32x2*>(o + i));");
+          e.line("  for (int i = wg_count / 4 * 4 + threadIdx.x; i < wg_count; i += %d) o[i] = st[i];", wg);
         }
+        e.line("  }");
         continue;
       }
       e.line("  UNROLL for (int k = 0; k < K; ++k) {");
       e.line("    if (!(row_ok && ok[k])) continue;");
+      if (ragged) {
+        // the last chunk element by element: its first ones are stored by the lane that owns them
+        const char* ty = n.out_dtype == FS_F32 ? "float" : "unsigned short";
+        const char* cv = n.out_dtype == FS_F32 ? "" : n.out_dtype == FS_F16 ? "(unsigned short)to_f16" : "(unsigned short)to_bf16";
+        e.line("    if (lo[k] > 0) {");
+        e.line("      %s* p = static_cast<%s*>(a.out[%d]) + row * %lldll + col[k];", ty, ty, n.out_ord, (long long)A.cols);
+        e.line("      UNROLL for (int j = 0; j < W; ++j) if (j >= lo[k]) p[j] = %s(t%d[k][j]);", cv, n.id);
+        e.line("      continue;");
+        e.line("    }");
+      }
       if (n.out_dtype == FS_F32) {
         e.line("    float* p = static_cast<float*>(a.out[%d]) + row * %lldll + col[k];", n.out_ord, (long long)A.cols);
         if (W == 1) e.line("    p[0] = t%d[k][0];", n.id);
         else if (W == 2) e.line("    __builtin_nontemporal_store(f32x2{t%d[k][0], t%d[k][1]}, reinterpret_cast<f32x2*>(p));", n.id, n.id);
         else for (int h = 0; h < W / 4; ++h)
-          e.line("    __builtin_nontemporal_store(f32x4{t%d[k][%d], t%d[k][%d], t%d[k][%d], t%d[k][%d]}, reinterpret_cast<f32x4*>(p) + %d);",
-                 n.id, 4 * h, n.id, 4 * h + 1, n.id, 4 * h + 2, n.id, 4 * h + 3, h);
+          e.line("    __builtin_nontemporal_store(f32x4%s{t%d[k][%d], t%d[k][%d], t%d[k][%d], t%d[k][%d]}, reinterpret_cast<f32x4%s*>(p) + %d);",
+                 al.c_str(), n.id, 4 * h, n.id, 4 * h + 1, n.id, 4 * h + 2, n.id, 4 * h + 3, al.c_str(), h);
       } else {
         const char* cv = n.out_dtype == FS_F16 ? "to_f16" : "to_bf16";
         e.line("    unsigned short* p = static_cast<unsigned short*>(a.out[%d]) + row * %lldll + col[k];", n.out_ord, (long long)A.cols);
@@ -1603,8 +1700,8 @@ struct Gen {
         else {
           e.line("    unsigned w[W / 2];");
           e.line("    UNROLL for (int j = 0; j < W / 2; ++j) w[j] = pack_%s(t%d[k][2 * j], t%d[k][2 * j + 1]);", cv, n.id, n.id);
-          if (W == 8) e.line("    __builtin_nontemporal_store(u32x4{w[0], w[1], w[2], w[3]}, reinterpret_cast<u32x4*>(p));");
-          else if (W == 4) e.line("    __builtin_nontemporal_store(u32x2{w[0], w[1]}, reinterpret_cast<u32x2*>(p));");
+          if (W == 8) e.line("    __builtin_nontemporal_store(u32x4%s{w[0], w[1], w[2], w[3]}, reinterpret_cast<u32x4%s*>(p));", al.c_str(), al.c_str());
+          else if (W == 4) e.line("    __builtin_nontemporal_store(u32x2%s{w[0], w[1]}, reinterpret_cast<u32x2%s*>(p));", al.c_str(), al.c_str());
           else e.line("    __builtin_nontemporal_store(w[0], reinterpret_cast<unsigned*>(p));");
         }
       }
@@ -1645,8 +1742,8 @@ struct Gen {
         snprintf(val, sizeof val, "ca%d[k][j]", n.id);
         e.line("  UNROLL for (int k = 0; k < K; ++k) {");
         e.line("    if (!ok[k]) continue;");
-        if (direct) e.line("    UNROLL for (int j = 0; j < W; ++j) %s", direct_store(n, "col[k] + j", val).c_str());
-        else e.line("    UNROLL for (int j = 0; j < W; ++j) ws[((long long)%d * gridDim.x + blockIdx.x) * %lldll + col[k] + j] = ca%d[k][j];", ci, (long long)A.cols, n.id);
+        if (direct) e.line("    UNROLL for (int j = 0; j < W; ++j) %s%s", if_counts, direct_store(n, "col[k] + j", val).c_str());
+        else e.line("    UNROLL for (int j = 0; j < W; ++j) %sws[((long long)%d * gridDim.x + blockIdx.x) * %lldll + col[k] + j] = ca%d[k][j];", if_counts, ci, (long long)A.cols, n.id);
         e.line("  }");
         ++ci;
       }
@@ -1665,7 +1762,7 @@ struct Gen {
         snprintf(val, sizeof val, "ca%d[k][j]", n.id);
         e.line("    UNROLL for (int k = 0; k < K; ++k) {");
         e.line("      if (!ok[k]) continue;");
-        e.line("      UNROLL for (int j = 0; j < W; ++j) %s", direct_store(n, "col[k] + j", val).c_str());
+        e.line("      UNROLL for (int j = 0; j < W; ++j) %s%s", if_counts, direct_store(n, "col[k] + j", val).c_str());
         e.line("    }");
       }
       e.line("  }");
@@ -1696,8 +1793,8 @@ struct Gen {
       for (const RNode& n : A.nodes) if (n.cls == CLS_COL) {
         e.line("      UNROLL for (int k = 0; k < K; ++k) {");
         e.line("        if (!ok[k]) continue;");
-        if (n.op == FS_REDUCE_MAX) e.line("        UNROLL for (int j = 0; j < W; ++j) colacc[%d][col[k] + j] = fmax(colacc[%d][col[k] + j], ca%d[k][j]);", ci, ci, n.id);
-        else e.line("        UNROLL for (int j = 0; j < W; ++j) colacc[%d][col[k] + j] += ca%d[k][j];", ci, n.id);
+        if (n.op == FS_REDUCE_MAX) e.line("        UNROLL for (int j = 0; j < W; ++j) %scolacc[%d][col[k] + j] = fmax(colacc[%d][col[k] + j], ca%d[k][j]);", if_counts, ci, ci, n.id);
+        else e.line("        UNROLL for (int j = 0; j < W; ++j) %scolacc[%d][col[k] + j] += ca%d[k][j];", if_counts, ci, n.id);
         e.line("      }");
         ++ci;
       }

@@ -366,6 +366,34 @@ def test_elementwise_chain_with_a_column_sum_and_no_row_reduction(rows, cols, dt
     check_against_oracle(ops, ins, what=f"bias+GELU backward {rows}x{cols} grid 2", grid=2)
 
 
+# rows whose length no vector width divides: two chunks and a bit, the edges of the lanes-per-row templates, of a wavefront and of
+# a team; row counts that leave the last workgroup partly empty
+@pytest.mark.parametrize("rows,cols", [(70, 9), (131, 17), (67, 33), (1000, 65), (301, 197), (41, 511), (41, 513), (29, 999), (9, 1025), (37, 2047), (3, 2049), (33, 3001),
+                                       (5, 5001), (2, 32767)])
+def test_ragged_rows_generated(rows, cols):
+    announce(f"generated ragged rows {rows}x{cols}")
+    for dtype in ("f32", "bf16"):
+        check_against_oracle(graphs.log_softmax((rows, cols), dtype), inputs.normal_tensors([(rows, cols)], dtype, scale=3.0), what="log_softmax")
+        check_against_oracle(graphs.bias_gelu_residual_layernorm(rows, cols, dtype), inputs.bias_gelu_residual_layernorm(rows, cols, dtype), what="cfg4")
+        check_against_oracle(graphs.bias_gelu_bwd(rows, cols, dtype), inputs.normal_tensors([(rows, cols), (rows, cols), (cols,)], dtype), what="bias+GELU backward")
+        if cols <= 4096:
+            check_against_oracle(graphs.sequence_pool((3, rows, cols), dtype=dtype, pool="both"), inputs.normal_tensors([(3, rows, cols)], dtype), what="pooled")
+    if cols <= 5001:                      # (longer rows: their running sums fit no template)
+        check_against_oracle(graphs.layernorm_bwd(rows, cols), inputs.layernorm_bwd(rows, cols), "generated", what="LN backward")
+    if cols <= 1025:
+        check_against_oracle(graphs.sequence_pool((300, 7, cols), with_row_work=True), inputs.normal_tensors([(300, 7, cols)]), what="pooled rows")
+    # in the input's own buffer: a chunk that overlaps its neighbour must not read what the neighbour has already stored
+    for ops, ins in [(graphs.log_softmax((rows, cols)), inputs.normal_tensors([(rows, cols)], scale=3.0)),
+                     (graphs.gated_rows((rows, cols)), inputs.normal_tensors([(rows, cols), (rows,), (cols,)]))]:
+        bufs, outs = to_device(ops, ins), alloc_outputs(ops)
+        outs[0] = bufs[0]
+        with Plan(ops) as p:
+            p.launch(bufs, outs)
+            torch.cuda.synchronize()
+        for got, want in zip(outs, interp.run(ops, ins)):
+            assert_close(got.to(torch.float64).cpu().numpy(), want, 1e-5, "in place")
+
+
 def test_layernorm_backward_generated_at_full_size():
     announce("generated LN backward full size")
     ops, ins = BY_NAME["layernorm_bwd"].build("full")
