@@ -5,19 +5,20 @@
 namespace fs {
 namespace {
 
-constexpr int kKs[] = {1, 2, 3, 4, 6, 8};
-
-int pick_K(int nvec) {
-  const int need = (nvec + 63) / 64;
-  for (int k : kKs) if (k >= need) return k;
-  return -1;
-}
-
-int pick_L(int nvec) {
-  if (nvec >= 64) return 64;
-  int L = 8;
-  while (L < nvec) L *= 2;
-  return L;
+// Lanes per row and vectors per lane.  A lane holds 16 elements where the row has that many for 16 lanes: the
+// reductions then serve 64 / L rows at once.
+void pick_tile(int nvec, int V, int* K, int* L) {
+  const int one = V == 4 ? 32 : 16, most = 16 / V;       // up to `one` vectors: one per lane
+  if (nvec <= one) {
+    *L = 8;
+    while (*L < nvec) *L *= 2;
+    *K = 1;
+    return;
+  }
+  *L = 16;
+  while (*L < 64 && nvec > *L * most) *L *= 2;
+  const int need = (nvec + *L - 1) / *L;
+  *K = need <= 4 ? need : need <= 6 ? 6 : 8;
 }
 
 int max_U(int K, int V) { return K * V <= 8 ? 4 : K * V <= 16 ? 2 : 1; }
@@ -36,8 +37,7 @@ bool row_stitch_plan(const RowSpec& sp, const LaunchOpts& opt, RowLaunch* out, s
   // (launch options that only the block-composed form of a ragged row takes are left to it)
   if (rl.ragged && opt.wg_size && (opt.wg_size < 64 || opt.wg_size > 512 || opt.wg_size % 64)) { *err = "row schedule: a ragged row with a workgroup of the block form"; return false; }
   if (rl.ragged && opt.rows_per_wave > 8) { *err = "row schedule: a ragged row with an option of another form"; return false; }
-  rl.K = pick_K((int)nvec);
-  rl.L = pick_L((int)nvec);
+  pick_tile((int)nvec, V, &rl.K, &rl.L);
   rl.wg = opt.wg_size ? opt.wg_size : 256;
   if (rl.wg < 64 || rl.wg > 512 || rl.wg % 64) { *err = "row schedule: wg_size must be a multiple of 64 in [64,512]"; return false; }
   // default row groups in flight per wavefront: two while a lane holds at most 32 bytes of
@@ -58,6 +58,7 @@ bool row_stitch_plan(const RowSpec& sp, const LaunchOpts& opt, RowLaunch* out, s
   const bool mask_bcast = !(sp.mask_d1 == 1 && sp.mask_d2 == 1 && sp.mask_stride[0] == 1);
   rl.lds_bytes = rl.ragged ? (int64_t)waves * rl.U * G * sp.cols * dtype_size(sp.dtype) : 0;      // at most 8 rows of 8188 bytes
   rl.variant = sp.core == CORE_LAYERNORM ? (sp.gelu ? 1 : 0) : (sp.in_mask < 0 ? 2 : mask_bcast ? 4 : 3);
+  rl.stream = sp.rows * sp.cols * dtype_size(sp.dtype) * (2 + (sp.in_res >= 0) + (rl.variant == 3)) > kStreamBytes;
   *out = rl;
   return true;
 }

@@ -52,46 +52,65 @@ struct RowArgs {
 };
 
 // How a row fits the lane tile: exactly (cols == K*L*V: no masking), in whole vectors, or ragged (cols not a
-// multiple of V)
-enum RowFit : int { FIT_VECTORS = 0, FIT_EXACT = 1, FIT_RAGGED = 2 };
+// multiple of V); the first two with nontemporal loads or (CACHED) ordinary ones
+enum RowFit : int { FIT_VECTORS = 0, FIT_EXACT = 1, FIT_RAGGED = 2, FIT_VECTORS_CACHED = 3, FIT_EXACT_CACHED = 4 };
 
 constexpr float kLog2e = 1.4426950408889634f;
 
+// Bytes a group moves up to which its inputs are loaded through the caches.  What a kernel before has just written
+// is still in the L2s and the memory-side cache then, and a nontemporal load does not find it as well: a
+// chain of a producer, LayerNorm and a consumer over 24 rotating buffer sets takes 32.3 us with nontemporal loads
+// and 29.7 with ordinary ones at 43 MB of LayerNorm's own, 40.6 and 39.2 at 65 MB, 43.3 and 43.5 at 100 MB, 65.6
+// and 68.4 at 134 MB; alone and cold there is no difference up to 134 MB.
+constexpr int64_t kStreamBytes = 64ll << 20;
+
+// 1 / sqrt(x) as the hardware's estimate and one Newton step: a correctly rounded square root and division take
+// some thirty instructions per row
+__device__ __forceinline__ float rsqrt_newton(float x) {
+  const float r = __builtin_amdgcn_rsqf(x);
+  return fmaf(0.5f * r, fmaf(-x * r, r, 1.f), r);
+}
+
 // VARIANT: 0 LayerNorm, 1 prologue(bias,GELU,residual)+LayerNorm, 2 softmax, 3 softmax with a
 // mask of the scores' shape, 4 softmax with a mask broadcast over leading dims
-// What bounds a ragged row is HBM like any other: softmax with a key-padding mask over 75648 rows of 197 fp16 takes
-// 15.4 us (3.9 TB/s; 46 us with one element per access and the row in LDS), LayerNorm over 8192 rows of 999 fp32
-// 13.9 (21.2), over 32768 of 333 fp16 12.8 (48.7).
+// Bound by HBM, and for 16-bit rows nearly as much by instructions: a lane holds 16 elements and 64 / L rows share a
+// reduction's steps, only the last vector is masked, and gamma and beta come with the row.  Warm (three buffer
+// sets) LayerNorm over 16384 x 1024 bf16 takes 10.8 us (13.7 with a row per wavefront, every vector masked and a
+// correctly rounded 1 / sqrt), 16384 x 768 fp32 18.0 (19.1), 8192 x 999 fp32 11.3; softmax with a key-padding mask
+// over 75648 rows of 197 fp16 11.4 (46 with one element per access and the row in LDS).
 template <typename T, int VARIANT, int K, int L, int U, int FIT>
 __global__ __launch_bounds__(512) void row_stitch_kernel(const RowArgs a) {
   constexpr int V = Vec<T>::V;
   constexpr int G = 64 / L;
   constexpr bool kLN = VARIANT <= 1, kGelu = VARIANT == 1, kMask = VARIANT >= 3, kMaskBcast = VARIANT == 4;
-  constexpr bool EXACT = FIT == FIT_EXACT, RAGGED = FIT == FIT_RAGGED;
+  constexpr bool EXACT = FIT == FIT_EXACT || FIT == FIT_EXACT_CACHED, RAGGED = FIT == FIT_RAGGED;
+  constexpr bool STREAM = FIT == FIT_EXACT || FIT == FIT_VECTORS;
   const int lane = threadIdx.x & 63;
   const int sub = lane / L, l = lane % L;
   const int waves = blockDim.x >> 6;
   const T* __restrict__ x = static_cast<const T*>(a.x);
   T* __restrict__ y = static_cast<T*>(a.y);
 
+  // K is the least that covers the row, or with 6 and 8 at most one more: only the last vectors can be partial
+  constexpr int KFULL = EXACT ? K : K <= 4 ? K - 1 : K - 2;
   bool vld[K];
   int voff[K], dup[K];                 // dup: elements of the vector that the one before it holds too
 #pragma unroll
   for (int k = 0; k < K; ++k) {
     const int vi = k * L + l;
-    vld[k] = EXACT || vi < a.nvec;
+    vld[k] = k < KFULL || vi < a.nvec;
     voff[k] = (vld[k] ? vi : 0) * V;   // masked-off lanes re-read vector 0: always in bounds
     dup[k] = 0;
-    if (RAGGED && vi == a.nvec - 1) { dup[k] = a.nvec * V - a.cols; voff[k] = a.cols - V; }
+    if (RAGGED && k >= KFULL && vi == a.nvec - 1) { dup[k] = a.nvec * V - a.cols; voff[k] = a.cols - V; }
   }
-  auto counts = [&](int k, int j) { return EXACT || (vld[k] && (!RAGGED || j >= dup[k])); };
+  auto holds = [&](int k) { return k < KFULL || vld[k]; };
+  auto counts = [&](int k, int j) { return k < KFULL || (vld[k] && (!RAGGED || j >= dup[k])); };
 
   // per-column operands (cached loads, kept packed in their storage dtype); an absent
   // operand becomes its neutral element so the per-element code has no conditionals.
-  // The bias is needed first and is read up front; gamma and beta are read inside the
-  // loop right where the epilogue needs them, which keeps them out of the register budget
-  // while the row is being reduced (a one-shot grid visits one row group per wavefront, so
-  // nothing is read twice; a persistent grid re-reads them from L1).
+  // The bias is needed first and is read up front; gamma and beta are requested right behind the
+  // row (one memory latency for all of them: requested where the epilogue needs them, they cost
+  // a second one), a one-shot grid visits one row group per wavefront, so nothing is read twice.
   constexpr uint32_t kOne = sizeof(T) == 4 ? 0x3F800000u : (Vec<T>::kOneBits | (Vec<T>::kOneBits << 16));
   u32x4 bia[K];
   if constexpr (kGelu) {
@@ -113,6 +132,10 @@ __global__ __launch_bounds__(512) void row_stitch_kernel(const RowArgs a) {
   // all HBM reads of one iteration: the row groups of x and of the second streamed operand
   // (`aux`: the residual, or the mask)
   auto load_groups = [&](int64_t it, u32x4 (&raw)[U][K], u32x4 (&aux)[U][K], int64_t (&row)[U], bool (&rok)[U]) {
+    auto load = [&](const T* p) {
+      if constexpr (STREAM) return stream_load16(p);
+      else return cached_load<T, !RAGGED>(p);
+    };
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int64_t r = (it * U + u) * G + sub;
@@ -120,7 +143,7 @@ __global__ __launch_bounds__(512) void row_stitch_kernel(const RowArgs a) {
       row[u] = rok[u] ? r : a.rows - 1;
 #pragma unroll
       for (int k = 0; k < K; ++k) {
-        raw[u][k] = stream_load<T, !RAGGED>(x + row[u] * a.cols + voff[k]);
+        raw[u][k] = load(x + row[u] * a.cols + voff[k]);
         aux[u][k] = u32x4{0u, 0u, 0u, 0u};
       }
     }
@@ -130,7 +153,7 @@ __global__ __launch_bounds__(512) void row_stitch_kernel(const RowArgs a) {
         for (int u = 0; u < U; ++u)
 #pragma unroll
           for (int k = 0; k < K; ++k)
-            aux[u][k] = stream_load<T, !RAGGED>(static_cast<const T*>(a.res) + row[u] * a.cols + voff[k]);
+            aux[u][k] = load(static_cast<const T*>(a.res) + row[u] * a.cols + voff[k]);
       }
     }
     if constexpr (kMask) {
@@ -144,11 +167,10 @@ __global__ __launch_bounds__(512) void row_stitch_kernel(const RowArgs a) {
           const uint32_t i0 = a.mask_d1.div(t), i1 = t - i0 * a.mask_d1.d;
           mrow = i0 * a.ms0 + i1 * a.ms1 + i2 * a.ms2;
         }
-        // a broadcast mask row is shared by many score rows: cached load; a full mask is
-        // touched once: streaming load
+        // a broadcast mask row is shared by many score rows: cached load
 #pragma unroll
         for (int k = 0; k < K; ++k)
-          aux[u][k] = kMaskBcast ? cached_load<T, !RAGGED>(mk + mrow * a.cols + voff[k]) : stream_load<T, !RAGGED>(mk + mrow * a.cols + voff[k]);
+          aux[u][k] = kMaskBcast ? cached_load<T, !RAGGED>(mk + mrow * a.cols + voff[k]) : load(mk + mrow * a.cols + voff[k]);
       }
     }
   };
@@ -163,6 +185,16 @@ __global__ __launch_bounds__(512) void row_stitch_kernel(const RowArgs a) {
     bool rok[U];
     u32x4 raw[U][K], aux[U][K];
     load_groups(it, raw, aux, row, rok);
+    u32x4 gam[kLN ? K : 1], bet[kLN ? K : 1];
+    if constexpr (kLN) {
+#pragma unroll
+      for (int k = 0; k < K; ++k) {
+        gam[k] = u32x4{kOne, kOne, kOne, kOne};
+        bet[k] = u32x4{0u, 0u, 0u, 0u};
+        if (a.gamma) gam[k] = cached_load<T, !RAGGED>(static_cast<const T*>(a.gamma) + voff[k]);
+        if (a.beta) bet[k] = cached_load<T, !RAGGED>(static_cast<const T*>(a.beta) + voff[k]);
+      }
+    }
 
     // ---- thread-composed prologue ---------------------------------------------------
     if constexpr (kGelu) {
@@ -238,16 +270,8 @@ __global__ __launch_bounds__(512) void row_stitch_kernel(const RowArgs a) {
             v[u][k][j] -= mean;
             q += counts(k, j) ? v[u][k][j] * v[u][k][j] : 0.f;
           }
-        u32x4 gam[K], bet[K];
-#pragma unroll
-        for (int k = 0; k < K; ++k) {
-          gam[k] = u32x4{kOne, kOne, kOne, kOne};
-          bet[k] = u32x4{0u, 0u, 0u, 0u};
-          if (a.gamma) gam[k] = cached_load<T, !RAGGED>(static_cast<const T*>(a.gamma) + voff[k]);
-          if (a.beta) bet[k] = cached_load<T, !RAGGED>(static_cast<const T*>(a.beta) + voff[k]);
-        }
         const float var = group_allreduce<SumOp, L>(q) * a.inv_n;
-        const float rstd = 1.f / sqrtf(var + a.eps);
+        const float rstd = rsqrt_newton(var + a.eps);
 #pragma unroll
         for (int k = 0; k < K; ++k) {
           float o[V], gk[V], bk[V];
@@ -262,7 +286,7 @@ __global__ __launch_bounds__(512) void row_stitch_kernel(const RowArgs a) {
 #pragma unroll
         for (int k = 0; k < K; ++k)
 #pragma unroll
-          for (int j = 0; j < V; ++j) mx = fmaxf(mx, EXACT || vld[k] ? v[u][k][j] : -INFINITY);
+          for (int j = 0; j < V; ++j) mx = fmaxf(mx, holds(k) ? v[u][k][j] : -INFINITY);
         mx = group_allreduce<MaxOp, L>(mx);
         const float nmx = -mx * kLog2e;
         float s = 0.f;
@@ -271,7 +295,7 @@ __global__ __launch_bounds__(512) void row_stitch_kernel(const RowArgs a) {
 #pragma unroll
           for (int j = 0; j < V; ++j) {
             // exp(z - max) as one fma and one exp2
-            const float e = vld[k] ? __builtin_amdgcn_exp2f(fmaf(v[u][k][j], kLog2e, nmx)) : 0.f;
+            const float e = holds(k) ? __builtin_amdgcn_exp2f(fmaf(v[u][k][j], kLog2e, nmx)) : 0.f;
             v[u][k][j] = e;
             s += !RAGGED || counts(k, j) ? e : 0.f;
           }
@@ -306,10 +330,14 @@ template <int KV> constexpr int max_rows_in_flight() { return KV <= 8 ? 4 : KV <
 
 template <typename T, int VARIANT, int K, int L, int U>
 hipError_t row_launch_fit(const RowArgs& a, int fit, int grid, int wg, hipStream_t s) {
-  if (fit == FIT_EXACT) hipLaunchKernelGGL((row_stitch_kernel<T, VARIANT, K, L, U, FIT_EXACT>), dim3(grid), dim3(wg), 0, s, a);
-  else if (fit == FIT_VECTORS) hipLaunchKernelGGL((row_stitch_kernel<T, VARIANT, K, L, U, FIT_VECTORS>), dim3(grid), dim3(wg), 0, s, a);
-  else hipLaunchKernelGGL((row_stitch_kernel<T, VARIANT, K, L, U, FIT_RAGGED>), dim3(grid), dim3(wg),
-                          (unsigned)((wg / 64) * U * (64 / L) * a.cols * (int)sizeof(T)), s, a);
+  const unsigned lds = fit == FIT_RAGGED ? (unsigned)((wg / 64) * U * (64 / L) * a.cols * (int)sizeof(T)) : 0;
+  switch (fit) {
+    case FIT_EXACT: hipLaunchKernelGGL((row_stitch_kernel<T, VARIANT, K, L, U, FIT_EXACT>), dim3(grid), dim3(wg), lds, s, a); break;
+    case FIT_VECTORS: hipLaunchKernelGGL((row_stitch_kernel<T, VARIANT, K, L, U, FIT_VECTORS>), dim3(grid), dim3(wg), lds, s, a); break;
+    case FIT_EXACT_CACHED: hipLaunchKernelGGL((row_stitch_kernel<T, VARIANT, K, L, U, FIT_EXACT_CACHED>), dim3(grid), dim3(wg), lds, s, a); break;
+    case FIT_VECTORS_CACHED: hipLaunchKernelGGL((row_stitch_kernel<T, VARIANT, K, L, U, FIT_VECTORS_CACHED>), dim3(grid), dim3(wg), lds, s, a); break;
+    default: hipLaunchKernelGGL((row_stitch_kernel<T, VARIANT, K, L, U, FIT_RAGGED>), dim3(grid), dim3(wg), lds, s, a); break;
+  }
   return hipGetLastError();
 }
 
@@ -323,31 +351,39 @@ hipError_t row_launch_U(const RowArgs& a, int U, int fit, int grid, int wg, hipS
 
 template <typename T, int VARIANT>
 hipError_t row_launch_KL(const RowArgs& a, int K, int L, int U, int fit, int grid, int wg, hipStream_t s) {
-  if (K == 1) {
-    switch (L) {
-      case 8: return row_launch_U<T, VARIANT, 1, 8>(a, U, fit, grid, wg, s);
-      case 16: return row_launch_U<T, VARIANT, 1, 16>(a, U, fit, grid, wg, s);
-      case 32: return row_launch_U<T, VARIANT, 1, 32>(a, U, fit, grid, wg, s);
-      default: return row_launch_U<T, VARIANT, 1, 64>(a, U, fit, grid, wg, s);
-    }
-  }
-  switch (K) {
-    case 2: return row_launch_U<T, VARIANT, 2, 64>(a, U, fit, grid, wg, s);
-    case 3: return row_launch_U<T, VARIANT, 3, 64>(a, U, fit, grid, wg, s);
-    case 4: return row_launch_U<T, VARIANT, 4, 64>(a, U, fit, grid, wg, s);
+  switch (K * 100 + L) {
+    case 108: return row_launch_U<T, VARIANT, 1, 8>(a, U, fit, grid, wg, s);
+    case 116: return row_launch_U<T, VARIANT, 1, 16>(a, U, fit, grid, wg, s);
+    case 364: return row_launch_U<T, VARIANT, 3, 64>(a, U, fit, grid, wg, s);
+    case 464: return row_launch_U<T, VARIANT, 4, 64>(a, U, fit, grid, wg, s);
     default: break;
   }
-  // 6 or 8 vectors per lane fit the register file only for 4-byte elements
   if constexpr (Vec<T>::V == 4) {
-    if (K == 6) return row_launch_U<T, VARIANT, 6, 64>(a, U, fit, grid, wg, s);
-    if (K == 8) return row_launch_U<T, VARIANT, 8, 64>(a, U, fit, grid, wg, s);
+    switch (K * 100 + L) {
+      case 132: return row_launch_U<T, VARIANT, 1, 32>(a, U, fit, grid, wg, s);
+      case 316: return row_launch_U<T, VARIANT, 3, 16>(a, U, fit, grid, wg, s);
+      case 416: return row_launch_U<T, VARIANT, 4, 16>(a, U, fit, grid, wg, s);
+      case 332: return row_launch_U<T, VARIANT, 3, 32>(a, U, fit, grid, wg, s);
+      case 432: return row_launch_U<T, VARIANT, 4, 32>(a, U, fit, grid, wg, s);
+      case 664: return row_launch_U<T, VARIANT, 6, 64>(a, U, fit, grid, wg, s);
+      case 864: return row_launch_U<T, VARIANT, 8, 64>(a, U, fit, grid, wg, s);
+      default: break;
+    }
+  } else {
+    switch (K * 100 + L) {
+      case 216: return row_launch_U<T, VARIANT, 2, 16>(a, U, fit, grid, wg, s);
+      case 232: return row_launch_U<T, VARIANT, 2, 32>(a, U, fit, grid, wg, s);
+      case 264: return row_launch_U<T, VARIANT, 2, 64>(a, U, fit, grid, wg, s);
+      default: break;
+    }
   }
   return hipErrorInvalidValue;
 }
 
 template <typename T>
 hipError_t row_launch_dtype(const RowArgs& a, const RowLaunch& rl, hipStream_t s) {
-  const int fit = rl.ragged ? FIT_RAGGED : a.nvec == rl.K * rl.L ? FIT_EXACT : FIT_VECTORS;
+  const bool exact = a.nvec == rl.K * rl.L;
+  const int fit = rl.ragged ? FIT_RAGGED : rl.stream ? (exact ? FIT_EXACT : FIT_VECTORS) : exact ? FIT_EXACT_CACHED : FIT_VECTORS_CACHED;
   switch (rl.variant) {
     case 0: return row_launch_KL<T, 0>(a, rl.K, rl.L, rl.U, fit, rl.grid, rl.wg, s);
     case 1: return row_launch_KL<T, 1>(a, rl.K, rl.L, rl.U, fit, rl.grid, rl.wg, s);

@@ -112,7 +112,7 @@ __global__ __launch_bounds__(1024) void row_team_kernel(const RowArgs a) {
           q += counts(k, j) ? v[k][j] * v[k][j] : 0.f;
         }
       const float var = team_allreduce<SumOp>(q, exch[1], waves, 0.f) * a.inv_n;
-      const float rstd = 1.f / sqrtf(var + a.eps);
+      const float rstd = rsqrt_newton(var + a.eps);
 #pragma unroll
       for (int k = 0; k < K; ++k) {
         u32x4 graw = u32x4{kOne, kOne, kOne, kOne}, braw = u32x4{0u, 0u, 0u, 0u};
