@@ -32,6 +32,7 @@
 #include <algorithm>
 #include <functional>
 #include <map>
+#include <set>
 
 namespace fs {
 
@@ -770,6 +771,7 @@ struct Gen {
   int L = 64, K = 1, W = 4;
   bool ragged = false;        // chunks are aligned to the element only and the last one overlaps its neighbour
   bool allow_ragged = true;
+  bool long_row = false;      // more than 32 elements of a value per thread of a full workgroup
   bool exact = true;          // K*L chunks cover the row exactly
   bool fast = false;          // 16-bit group: short tanh
   std::vector<int> splat;     // per view: 1 if one scalar per row (last stride 0 or row view)
@@ -931,6 +933,56 @@ struct Gen {
     return width + 8;
   }
 
+  bool read_by_one_reduction(int id) const {
+    int readers = 0, reductions = 0;
+    for (const RNode& y : A.nodes) for (int j = 0; j < y.nop; ++j) if (y.o[j].kind == OP_NODE && y.o[j].index == id) {
+      ++readers;
+      if (y.cls == CLS_ROW && (y.op == FS_REDUCE_SUM || y.op == FS_REDUCE_MAX)) ++reductions;
+    }
+    return readers == 1 && reductions == 1;
+  }
+  // Full values alive at once: the operands loaded at the top until their last use, computed values from their op to
+  // their last use (one that only a reduction reads is consumed element by element).
+  int live_values() const {
+    std::vector<int> last_node(A.g.size(), -1), last_view(A.views.size(), -1);
+    const int n = (int)A.nodes.size();
+    for (int i = 0; i < n; ++i) {
+      const RNode& x = A.nodes[i];
+      for (int j = 0; j < x.nop; ++j) {
+        if (x.o[j].kind == OP_NODE) last_node[x.o[j].index] = i;
+        else if (x.o[j].kind == OP_VIEW) last_view[x.o[j].index] = i;
+      }
+    }
+    int live = 0;
+    std::set<int> counted;
+    for (size_t q = 0; q < A.views.size(); ++q) if (A.views[q].cls == CLS_FULL && A.views[q].stride[A.rank - 1] != 0) ++live;
+    int peak = live;
+    for (int i = 0; i < n; ++i) {
+      const RNode& x = A.nodes[i];
+      for (int j = 0; j < x.nop; ++j) {
+        if (j == 1 && x.o[0].kind == x.o[1].kind && x.o[0].index == x.o[1].index) continue;
+        if (x.o[j].kind == OP_VIEW && last_view[x.o[j].index] == i && A.views[x.o[j].index].cls == CLS_FULL && A.views[x.o[j].index].stride[A.rank - 1] != 0) --live;
+        if (x.o[j].kind == OP_NODE && last_node[x.o[j].index] == i && counted.count(x.o[j].index)) { --live; counted.erase(x.o[j].index); }
+      }
+      if (x.cls == CLS_FULL && last_node[x.id] >= 0 && !read_by_one_reduction(x.id)) { ++live; counted.insert(x.id); }
+      if (live > peak) peak = live;
+    }
+    return peak;
+  }
+  // A row of more than 32 elements per thread of a full workgroup still lives in its registers where no more than 88 of
+  // a thread's 128 hold values (chunk by chunk code without interleaving keeps the others few: no spills up to
+  // there).  One read and one write instead of a read per pass: log-softmax over 512 rows of 50257 fp32 47.6 us (streamed
+  // in three passes, element by element, 81.9), of 50257 bf16 21.6 (54.0), of 65536 fp32 59.5 (79.3), 64 rows of 50257
+  // fp32 11.4 (31.2), RMSNorm over 512 x 43000 fp32 34.7 (41.2).  16-bit rows with more than one live value stay
+  // streamed: their row fits the LDS buffers (RMSNorm over 512 x 36000 bf16 15.2 streamed, 16.1 here); so do launches of
+  // a few rows of whole chunks, which are one row's latency either way (2 x 40000 fp32 8.3 streamed, 7.7 here).
+  bool long_row_fits() const {
+    if (lanes_per_row > 0 || A.n_col > 0 || A.n_reduce == 0 || (A.rows < 4 && !ragged)) return false;
+    for (const RNode& n : A.nodes) if (n.op == ROP_DOT_OUTER || n.op == ROP_DOT_REDUCE) return false;
+    const int live = live_values();
+    return (int64_t)K * W * (live < 1 ? 1 : live) <= 88 && !(fast && live > 1);
+  }
+
   bool geometry(std::string* err) {
     if (A.mma_in >= 0) return geometry_mma(err);
     if (geometry_rows(err)) return true;
@@ -978,7 +1030,8 @@ struct Gen {
     // a row too long for one wavefront's registers goes to a team of wavefronts (one
     // workgroup per row)
     while (lanes_per_row == 0 && (int64_t)K * W > 32 && L < 1024) { L *= 2; K = (int)((nvec + L - 1) / L); }
-    if ((int64_t)K * W > 32) {
+    long_row = (int64_t)K * W > 32 && L == 1024 && long_row_fits();
+    if ((int64_t)K * W > 32 && !long_row) {
       *err = lanes_per_row > 0 ? "generated row schedule: too few lanes per row for this row length"
                                : "generated row schedule: row longer than 32768 elements";
       return false;
@@ -1525,6 +1578,7 @@ struct Gen {
     }
     // ---- ops in order
     std::vector<char> inv_done(A.g.size(), 0);
+    std::map<int, std::string> inline_expr;       // values of a long row that only one reduction reads: computed in its loop
     int red_index = 0;
     for (const RNode& n : A.nodes) {
       const bool reduce = n.op == FS_REDUCE_SUM || n.op == FS_REDUCE_MAX;
@@ -1561,9 +1615,11 @@ struct Gen {
         combine(n.id, sum);
       } else if (reduce) {
         const bool sum = n.op == FS_REDUCE_SUM;
-        const std::string x = opnd(n.o[0], CLS_FULL);
+        const bool inlined = n.o[0].kind == OP_NODE && inline_expr.count(n.o[0].index) > 0;
+        const std::string x = inlined ? "(" + inline_expr[n.o[0].index] + ")" : opnd(n.o[0], CLS_FULL);
         e.line("  float r%d = %s;", n.id, sum ? "0.0f" : "-__builtin_inff()");
         e.line("  UNROLL for (int k = 0; k < K; ++k) {");
+        if (long_row) e.line("    __builtin_amdgcn_sched_barrier(0);");
         if (!exact) e.line("    if (!ok[k]) continue;");
         e.line("    UNROLL for (int j = 0; j < W; ++j) %sr%d = %s;", if_counts, n.id,
                sum ? ("r" + std::to_string(n.id) + " + " + x).c_str() : ("fmaxf(r" + std::to_string(n.id) + ", " + x + ")").c_str());
@@ -1610,8 +1666,13 @@ struct Gen {
           e.line("  const float inv%d = 1.0f / r%d;", n.o[1].index, n.o[1].index);
           inv_done[n.o[1].index] = 1;
         }
+        if (long_row && n.out_ord < 0 && read_by_one_reduction(n.id)) {
+          inline_expr[n.id] = expr(n);
+          continue;
+        }
         e.line("  float t%d[K][W];", n.id);
-        e.line("  UNROLL for (int k = 0; k < K; ++k) UNROLL for (int j = 0; j < W; ++j) t%d[k][j] = %s;", n.id, expr(n).c_str());
+        e.line("  UNROLL for (int k = 0; k < K; ++k) %sUNROLL for (int j = 0; j < W; ++j) t%d[k][j] = %s;%s", long_row ? "{ __builtin_amdgcn_sched_barrier(0); " : "", n.id, expr(n).c_str(),
+               long_row ? " }" : "");
       }
       if (n.out_ord < 0) continue;
       if (n.cls == CLS_ROW) {
@@ -1840,6 +1901,8 @@ struct Gen {
 struct Stream {
   const Analysis& A;
   int W = 4, wg = 512;
+  bool ragged = false;                // chunks aligned to the element only, the last one moved back to end with the row (see Gen)
+  int64_t n_chunks() const { return (A.cols + W - 1) / W; }
   bool fast = false, cached = true, cache_views = true;
   std::vector<int> idx_of;            // node id -> index into A.nodes
   std::vector<int> ready;             // full value: first pass it can be computed in; per-row value: passes that must be over
@@ -1860,7 +1923,7 @@ struct Stream {
 
   static bool is_col(const RNode& n) { return n.cls == CLS_COL; }     // a reduction over the rows: running values per thread and column
   static bool is_red(const RNode& n) { return !is_col(n) && (n.op == FS_REDUCE_SUM || n.op == FS_REDUCE_MAX || n.op == ROP_DOT_REDUCE); }
-  int n_iter() const { return (int)((A.cols / W + wg - 1) / wg); }   // chunks of a row per thread
+  int n_iter() const { return (int)((n_chunks() + wg - 1) / wg); }   // chunks of a row per thread
 
   void schedule() {
     const int n = (int)A.nodes.size();
@@ -1976,10 +2039,13 @@ struct Stream {
     lds_floats = r.total_bytes / 4;
   }
 
-  bool geometry(int want_wg, std::string* err) {
+  bool geometry(int want_wg, std::string* err, bool allow_ragged = true) {
     W = chunk_elements(A, &fast);
     if (W == 0) { *err = "generated row schedule: an operand strided along the last dim"; return false; }
-    const int64_t nvec = A.cols / W;
+    const int rw = allow_ragged && W <= 2 ? ragged_chunk_elements(A) : 0;
+    ragged = rw > W;
+    if (ragged) W = rw;
+    const int64_t nvec = n_chunks();
     wg = want_wg ? want_wg : nvec <= 2048 ? 256 : nvec <= 8192 ? 512 : 1024;
     return true;
   }
@@ -2014,25 +2080,35 @@ struct Stream {
       e.line("          const f32x2 x = *reinterpret_cast<const f32x2*>(p); %s[0] = x[0]; %s[1] = x[1];", name.c_str(), name.c_str());
     } else if (v.dtype == FS_F32) {
       for (int h = 0; h < W / 4; ++h)
-        e.line("          { const f32x4 x = *(reinterpret_cast<const f32x4*>(p) + %d); UNROLL for (int j = 0; j < 4; ++j) %s[%d + j] = x[j]; }", h, name.c_str(), 4 * h);
+        e.line("          { const f32x4 x = *(reinterpret_cast<const f32x4%s*>(p) + %d); UNROLL for (int j = 0; j < 4; ++j) %s[%d + j] = x[j]; }", ragged ? "e" : "", h, name.c_str(), 4 * h);
     } else {
       const char* lo = v.dtype == FS_F16 ? "f16_lo" : "bf16_lo";
       const char* hi = v.dtype == FS_F16 ? "f16_hi" : "bf16_hi";
       if (W == 2) e.line("          const unsigned x[1] = {*reinterpret_cast<const unsigned*>(p)};");
-      else e.line("          const %s x = *reinterpret_cast<const %s*>(p);", W == 8 ? "u32x4" : "u32x2", W == 8 ? "u32x4" : "u32x2");
+      else e.line("          const %s x = *reinterpret_cast<const %s%s*>(p);", W == 8 ? "u32x4" : "u32x2", W == 8 ? "u32x4" : "u32x2", ragged ? "e" : "");
       e.line("          UNROLL for (int j = 0; j < W / 2; ++j) { %s[2 * j] = %s(x[j]); %s[2 * j + 1] = %s(x[j]); }", name.c_str(), lo, name.c_str(), hi);
     }
     e.line("        }");
   }
   void store_global(const RNode& n) {
-    e.line("        {");
+    const char* al = ragged ? "e" : "";
+    if (ragged) {
+      const char* ty = n.out_dtype == FS_F32 ? "float" : "unsigned short";
+      const char* cv = n.out_dtype == FS_F32 ? "" : n.out_dtype == FS_F16 ? "(unsigned short)to_f16" : "(unsigned short)to_bf16";
+      e.line("        if (lo > 0) {");
+      e.line("          %s* p = static_cast<%s*>(a.out[%d]) + row * %lldll + col;", ty, ty, n.out_ord, (long long)A.cols);
+      e.line("          UNROLL for (int j = 0; j < W; ++j) if (j >= lo) p[j] = %s(t%d[j]);", cv, n.id);
+      e.line("        } else {");
+    } else {
+      e.line("        {");
+    }
     if (n.out_dtype == FS_F32) {
       e.line("          float* p = static_cast<float*>(a.out[%d]) + row * %lldll + col;", n.out_ord, (long long)A.cols);
       if (W == 1) e.line("          p[0] = t%d[0];", n.id);
       else if (W == 2) e.line("          __builtin_nontemporal_store(f32x2{t%d[0], t%d[1]}, reinterpret_cast<f32x2*>(p));", n.id, n.id);
       else for (int h = 0; h < W / 4; ++h)
-        e.line("          __builtin_nontemporal_store(f32x4{t%d[%d], t%d[%d], t%d[%d], t%d[%d]}, reinterpret_cast<f32x4*>(p) + %d);",
-               n.id, 4 * h, n.id, 4 * h + 1, n.id, 4 * h + 2, n.id, 4 * h + 3, h);
+        e.line("          __builtin_nontemporal_store(f32x4%s{t%d[%d], t%d[%d], t%d[%d], t%d[%d]}, reinterpret_cast<f32x4%s*>(p) + %d);",
+               al, n.id, 4 * h, n.id, 4 * h + 1, n.id, 4 * h + 2, n.id, 4 * h + 3, al, h);
     } else {
       const char* cv = n.out_dtype == FS_F16 ? "to_f16" : "to_bf16";
       e.line("          unsigned short* p = static_cast<unsigned short*>(a.out[%d]) + row * %lldll + col;", n.out_ord, (long long)A.cols);
@@ -2040,8 +2116,8 @@ struct Stream {
       else {
         e.line("          unsigned w[W / 2];");
         e.line("          UNROLL for (int j = 0; j < W / 2; ++j) w[j] = pack_%s(t%d[2 * j], t%d[2 * j + 1]);", cv, n.id, n.id);
-        if (W == 8) e.line("          __builtin_nontemporal_store(u32x4{w[0], w[1], w[2], w[3]}, reinterpret_cast<u32x4*>(p));");
-        else if (W == 4) e.line("          __builtin_nontemporal_store(u32x2{w[0], w[1]}, reinterpret_cast<u32x2*>(p));");
+        if (W == 8) e.line("          __builtin_nontemporal_store(u32x4%s{w[0], w[1], w[2], w[3]}, reinterpret_cast<u32x4%s*>(p));", al, al);
+        else if (W == 4) e.line("          __builtin_nontemporal_store(u32x2%s{w[0], w[1]}, reinterpret_cast<u32x2%s*>(p));", al, al);
         else e.line("          __builtin_nontemporal_store(w[0], reinterpret_cast<unsigned*>(p));");
       }
     }
@@ -2064,8 +2140,10 @@ struct Stream {
 
     e.s = ew_preamble();
     e.s += kReducePreamble;
+    if (ragged) e.s += kRaggedPreamble;
+    const char* if_counts = ragged ? "if (j >= lo) " : "";
     e.line("extern \"C\" __global__ __launch_bounds__(%d) void FS_ROW_NAME(const Args a) {", wg);
-    e.line("  constexpr int W = %d, NVEC = %lld, WG = %d, T = %d;", W, (long long)(A.cols / W), wg, T);
+    e.line("  constexpr int W = %d, NVEC = %lld, WG = %d, T = %d;", W, (long long)n_chunks(), wg, T);
     if (lds_floats > 0) e.line("  __shared__ float rowbuf[%lld];", (long long)lds_floats);
     if (n_red > 0) e.line("  __shared__ float exch[%d][T];", n_red);
     const bool cols_red = A.n_col > 0;
@@ -2112,11 +2190,11 @@ struct Stream {
       if (cols_red) {
         e.line("    UNROLL for (int it = 0; it < NIT; ++it) {      // pass %d", p);
         e.line("      const int c = (int)threadIdx.x + it * WG;");
-        e.line("      const int col = c * W;");
+        emit_col();
         e.line("      if (c < NVEC) {");
       } else {
         e.line("    for (int c = threadIdx.x; c < NVEC; c += WG) {      // pass %d", p);
-        e.line("      const int col = c * W;");
+        emit_col();
         e.line("      {");
       }
       std::vector<char> have_node(n, 0), have_view(nv, 0);
@@ -2127,7 +2205,7 @@ struct Stream {
         snprintf(name, sizeof name, "v%d", q);
         if (cached && cut_view[q] && p > first_use[q]) {
           e.line("        float %s[W];", name);
-          e.line("        UNROLL for (int j = 0; j < W; ++j) %s[j] = rowbuf[%lld + col + j];", name, (long long)off_view[q]);
+          read_buffer(name, off_view[q]);
         } else {
           load_global(name, q);
         }
@@ -2138,7 +2216,7 @@ struct Stream {
         const RNode& x = A.nodes[k];
         if (cached && cut_node[k] && ready[k] < p) {
           e.line("        float t%d[W];", x.id);
-          e.line("        UNROLL for (int j = 0; j < W; ++j) t%d[j] = rowbuf[%lld + col + j];", x.id, (long long)off_node[k]);
+          read_buffer("t" + std::to_string(x.id), off_node[k]);
           return;
         }
         for (int j = 0; j < x.nop; ++j) {
@@ -2182,15 +2260,15 @@ struct Stream {
         const RNode& x = A.nodes[t];
         if (!is_red(x)) continue;
         const std::string v = opnd(x.o[0], CLS_FULL);
-        if (x.op == FS_REDUCE_SUM) e.line("        UNROLL for (int j = 0; j < W; ++j) r%d = r%d + %s;", x.id, x.id, v.c_str());
-        else if (x.op == FS_REDUCE_MAX) e.line("        UNROLL for (int j = 0; j < W; ++j) r%d = fmaxf(r%d, %s);", x.id, x.id, v.c_str());
-        else e.line("        UNROLL for (int j = 0; j < W; ++j) r%d = fmaf(%s, v%d[j], r%d);", x.id, v.c_str(), x.dot_full[0], x.id);
+        if (x.op == FS_REDUCE_SUM) e.line("        UNROLL for (int j = 0; j < W; ++j) %sr%d = r%d + %s;", if_counts, x.id, x.id, v.c_str());
+        else if (x.op == FS_REDUCE_MAX) e.line("        UNROLL for (int j = 0; j < W; ++j) %sr%d = fmaxf(r%d, %s);", if_counts, x.id, x.id, v.c_str());
+        else e.line("        UNROLL for (int j = 0; j < W; ++j) %sr%d = fmaf(%s, v%d[j], r%d);", if_counts, x.id, v.c_str(), x.dot_full[0], x.id);
       }
       if (cached) {
         for (int q = 0; q < nv; ++q) if (cut_view[q] && first_use[q] == p)
-          e.line("        UNROLL for (int j = 0; j < W; ++j) rowbuf[%lld + col + j] = v%d[j];", (long long)off_view[q], q);
+          write_buffer("v" + std::to_string(q), off_view[q]);
         for (int k = 0; k < n; ++k) if (cut_node[k] && ready[k] == p)
-          e.line("        UNROLL for (int j = 0; j < W; ++j) rowbuf[%lld + col + j] = t%d[j];", (long long)off_node[k], A.nodes[k].id);
+          write_buffer("t" + std::to_string(A.nodes[k].id), off_node[k]);
       }
       for (int t : targets[p]) {
         const RNode& x = A.nodes[t];
@@ -2233,7 +2311,8 @@ struct Stream {
       for (const RNode& x : A.nodes) if (is_col(x)) {
         e.line("  UNROLL for (int it = 0; it < NIT; ++it) {");
         e.line("    const int c = (int)threadIdx.x + it * WG;");
-        e.line("    if (c < NVEC) { UNROLL for (int j = 0; j < W; ++j) ws[((long long)%d * gridDim.x + blockIdx.x) * %lldll + c * W + j] = ca%d[it][j]; }", ci, (long long)A.cols, x.id);
+        emit_col();
+        e.line("    if (c < NVEC) { UNROLL for (int j = 0; j < W; ++j) %sws[((long long)%d * gridDim.x + blockIdx.x) * %lldll + col + j] = ca%d[it][j]; }", if_counts, ci, (long long)A.cols, x.id);
         e.line("  }");
         ++ci;
       }
@@ -2246,6 +2325,27 @@ struct Stream {
     *kernel_name = name;
     const std::string tag = "FS_ROW_NAME";
     e.s.replace(e.s.find(tag), tag.size(), name);
+  }
+  // a chunk from and to its row buffer (ragged: 16 bytes at a time at any address, and only the elements that are the
+  // chunk's own are written: its neighbour may still read, or have taken over, the others)
+  void read_buffer(const std::string& name, int64_t off) {
+    if (!ragged) { e.line("        UNROLL for (int j = 0; j < W; ++j) %s[j] = rowbuf[%lld + col + j];", name.c_str(), (long long)off); return; }
+    for (int h = 0; h < W / 4; ++h)
+      e.line("        { const f32x4 x = *reinterpret_cast<const f32x4e*>(rowbuf + %lld + col); UNROLL for (int j = 0; j < 4; ++j) %s[%d + j] = x[j]; }", (long long)off + 4 * h, name.c_str(), 4 * h);
+  }
+  void write_buffer(const std::string& name, int64_t off) {
+    const char* n = name.c_str();
+    if (!ragged) { e.line("        UNROLL for (int j = 0; j < W; ++j) rowbuf[%lld + col + j] = %s[j];", (long long)off, n); return; }
+    e.line("        if (lo > 0) { UNROLL for (int j = 0; j < W; ++j) if (j >= lo) rowbuf[%lld + col + j] = %s[j]; }", (long long)off, n);
+    e.line("        else {");
+    for (int h = 0; h < W / 4; ++h)
+      e.line("          *reinterpret_cast<f32x4e*>(rowbuf + %lld + col) = f32x4e{%s[%d], %s[%d], %s[%d], %s[%d]};", (long long)off + 4 * h, n, 4 * h, n, 4 * h + 1, n, 4 * h + 2, n, 4 * h + 3);
+    e.line("        }");
+  }
+  // the chunk's first element, and how many of its elements its neighbour holds too
+  void emit_col() {
+    if (!ragged) { e.line("      const int col = c * W;"); return; }
+    e.line("      const int col = c == NVEC - 1 ? %lld : c * W, lo = c == NVEC - 1 ? %lld : 0;", (long long)A.cols - W, (long long)(n_chunks() * W - A.cols));
   }
   void row_out(const RNode& x) {
     if (x.out_ord < 0) return;
@@ -2336,7 +2436,7 @@ bool row_gen_plan(const Graph& g, const LaunchOpts& opt, RowGenLaunch* out, int*
     std::string cerr;
     if (!ew_compile_source(gen.e.s, &l.code_object, &cerr)) { *err = "generated row schedule: " + cerr; return false; }
     l.L = gen.L; l.K = gen.K; l.W = gen.W;
-    l.rows_read_before_written = true;
+    l.rows_read_before_written = !gen.long_row;      // (rows of that length take no update in place in either form)
     for (const RNode& n : A.nodes) if (n.op == ROP_DOT_OUTER || n.op == ROP_DOT_REDUCE) l.rows_read_before_written = false;
     l.lds_bytes = gen.L > 64 ? (int64_t)A.n_reduce * (gen.L / 64) * 4 : gen.stage_bytes;
     l.wg = l.L > 64 ? l.L : gen.wg;     // a team is one workgroup per row
@@ -2399,9 +2499,9 @@ bool row_gen_plan(const Graph& g, const LaunchOpts& opt, RowGenLaunch* out, int*
     // workgroup whose threads can hold their share (rounded up to whole passes) is taken.
     const int sizes[3] = {1024, 512, 256};
     bool fits = false;
-    for (int k = 0; k < 3 && !fits; ++k) {
-      if (opt.wg_size && k > 0) break;
-      if (!st.geometry(opt.wg_size ? opt.wg_size : sizes[k], err)) return false;
+    for (int k = 0; k < 6 && !fits; ++k) {       // ... in chunks at element alignment if those fit, else in narrow ones
+      if (opt.wg_size && k % 3 > 0) continue;
+      if (!st.geometry(opt.wg_size ? opt.wg_size : sizes[k % 3], err, k < 3)) return false;
       const int64_t per_thread = (int64_t)st.n_iter() * st.W * A.n_col;
       fits = per_thread <= (st.wg > 512 ? 40 : st.wg > 256 ? 104 : 232);
     }

@@ -394,6 +394,29 @@ def test_ragged_rows_generated(rows, cols):
             assert_close(got.to(torch.float64).cpu().numpy(), want, 1e-5, "in place")
 
 
+# rows beyond the register templates: register-resident in a full workgroup (up to 88 live elements per thread), or streamed; of any length
+@pytest.mark.parametrize("rows,cols", [(5, 32769), (4, 36865), (9, 40001), (6, 45056), (5, 50257), (4, 65536), (7, 65537), (4, 90112), (4, 90113), (4, 100001),
+                                       (3, 40001), (2, 131071)])
+def test_long_rows_of_any_length(rows, cols):
+    announce(f"generated long rows {rows}x{cols}")
+    for dtype in ("f32", "bf16"):
+        check_against_oracle(graphs.log_softmax((rows, cols), dtype), inputs.normal_tensors([(rows, cols)], dtype, scale=3.0), what="log_softmax")
+        check_against_oracle(graphs.rmsnorm((rows, cols), dtype), inputs.normal_tensors([(rows, cols), (cols,)], dtype), what="rmsnorm")
+        check_against_oracle(graphs.layernorm_fwd_with_stats(rows, cols, dtype), inputs.layernorm_fwd(rows, cols, dtype), what="layernorm with stats")
+    check_against_oracle(graphs.softmax_with_lse((rows, cols)), inputs.normal_tensors([(rows, cols)], scale=2.0), what="softmax + lse")
+    if cols <= 50257:
+        check_against_oracle(graphs.bias_gelu_bwd(rows, cols), inputs.normal_tensors([(rows, cols), (rows, cols), (cols,)]), what="bias+GELU backward")
+    # masked entries at -inf, and a row that holds nothing else but one value
+    x = inputs.normal_tensors([(rows, cols)], scale=3.0)
+    x[0][0, ::3] = -np.inf
+    x[0][-1, 1:] = -np.inf
+    with np.errstate(divide="ignore", invalid="ignore"):
+        (want,) = interp.run(graphs.log_softmax((rows, cols)), x)
+    got = run_gpu(graphs.log_softmax((rows, cols)), x)[0]
+    assert np.array_equal(np.isfinite(got), np.isfinite(want))
+    assert_close(np.where(np.isfinite(got), got, 0.0), np.where(np.isfinite(want), want, 0.0), 1e-5, "log_softmax with -inf")
+
+
 def test_layernorm_backward_generated_at_full_size():
     announce("generated LN backward full size")
     ops, ins = BY_NAME["layernorm_bwd"].build("full")
