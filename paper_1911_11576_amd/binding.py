@@ -66,6 +66,8 @@ def lib():
         vp, i32, i64 = C.c_void_p, C.c_int32, C.c_int64
         L.fs_plan_create.argtypes = [C.POINTER(fs_op_desc), i32, C.POINTER(fs_plan_options), C.POINTER(vp)]
         L.fs_plan_create.restype = i32
+        L.fs_plan_create_packed.argtypes = [C.POINTER(C.POINTER(fs_op_desc)), C.POINTER(i32), i32, C.POINTER(C.c_uint8), C.POINTER(vp)]
+        L.fs_plan_create_packed.restype = i32
         L.fs_launch.argtypes = [vp, C.POINTER(vp), i32, C.POINTER(vp), i32, vp]
         L.fs_launch.restype = i32
         L.fs_launch_static.argtypes = [vp, C.POINTER(vp), i32, C.POINTER(vp), i32, vp]
@@ -159,6 +161,17 @@ def fs_plan_create(ops, mode=FS_MODE_STITCHED, wg_size=0, rows_per_wave=0, grid=
     out = C.c_void_p()
     _check(lib().fs_plan_create(arr, len(arr), C.byref(opt), C.byref(out)))
     return out.value
+
+
+def fs_plan_create_packed(groups):
+    """groups: marshalled op lists of independent groups -> (plan handle, indices of the groups it runs), or
+    FsError with FS_ERR_UNSUPPORTED if no two of them can share a launch."""
+    n = len(groups)
+    ptrs = (C.POINTER(fs_op_desc) * max(1, n))(*[C.cast(g, C.POINTER(fs_op_desc)) for g in groups])
+    sizes = (C.c_int32 * max(1, n))(*[len(g) for g in groups])
+    taken, out = (C.c_uint8 * max(1, n))(), C.c_void_p()
+    _check(lib().fs_plan_create_packed(ptrs, sizes, n, taken, C.byref(out)))
+    return out.value, [k for k in range(n) if taken[k]]
 
 
 def _pointers(tensors):
@@ -302,6 +315,12 @@ class Plan:
         self.tuned = None
 
     @classmethod
+    def packed(cls, groups):
+        """Independent groups as one launch (fs_plan_create_packed) -> (plan, indices of the groups it runs)."""
+        h, taken = fs_plan_create_packed(groups)
+        return cls(None, _handle=h), taken
+
+    @classmethod
     def tune(cls, ops, inputs, outputs, stream=None, trials=20):
         """The fastest of the schedule's launch templates for these buffers (fs_plan_tune)."""
         h, opts, us = fs_plan_tune(ops, inputs, outputs, stream, trials)
@@ -435,9 +454,9 @@ def describe_group_ops(arr):
 
 
 class FusedProgram:
-    """A whole computation graph run as the groups its fusion plan chose: one Plan per group,
-    intermediates between groups in device tensors.  Inputs: one tensor per parameter op of the
-    original list, in order; outputs: one per output op."""
+    """A whole computation graph run as the groups its fusion plan chose: one Plan per group, or one per
+    several small row groups that do not depend on each other, intermediates between groups in device
+    tensors.  Inputs: one tensor per parameter op of the original list, in order; outputs: one per output op."""
 
     def __init__(self, ops, fusion=None, **fusion_options):
         import torch
@@ -446,30 +465,68 @@ class FusedProgram:
         self.fusion = fusion if fusion is not None else FusionPlan(self.ops, **fusion_options)
         self.param_ops = [i for i, op in enumerate(self.ops) if op.kind == "parameter"]
         self.output_ops = [i for i, op in enumerate(self.ops) if op.kind == "output"]
-        self.plans = []
-        for g in self.fusion.groups:
-            try:
-                plan = Plan(g["ops"])
-            except FsError as e:
-                if e.status != FS_ERR_UNSUPPORTED:
-                    raise
-                plan = Plan(g["ops"], "per_op")       # an op left alone that no stitched schedule takes (a lone dot)
-            self.plans.append(plan)
-        self.n_kernels = sum(p.info()["n_kernels"] for p in self.plans)
+        self.plans = [None] * len(self.fusion.groups)       # per group; None: the group runs in a packed launch
+        self._units = self._pack()
+        for plan, members in self._units:
+            if plan is None:
+                self.plans[members[0]] = self._group_plan(members[0])
+        self._count_kernels()
 
-    def run(self, inputs, stream=None):
+    def _group_plan(self, k):
+        try:
+            return Plan(self.fusion.groups[k]["ops"])
+        except FsError as e:
+            if e.status != FS_ERR_UNSUPPORTED:
+                raise
+            return Plan(self.fusion.groups[k]["ops"], "per_op")   # an op left alone that no stitched schedule takes (a lone dot)
+
+    def _pack(self):
+        """The program's launches in order, as (packed plan or None, groups): groups sorted by the length of the
+        longest chain of groups they depend on, which leaves those of one level independent of each other;
+        of a level, what can share a launch does."""
+        groups = self.fusion.groups
+        made_by, level = {}, []
+        for k, g in enumerate(groups):
+            level.append(1 + max((level[made_by[i]] for i in g["input_of"] if i in made_by), default=-1))
+            for i in g["output_of"]:
+                made_by[i] = k
+        units = []
+        for lv in range(max(level, default=-1) + 1):
+            left = [k for k in range(len(groups)) if level[k] == lv]
+            while len(left) > 1:
+                try:
+                    plan, taken = Plan.packed([groups[k]["ops"] for k in left])
+                except FsError as e:
+                    if e.status != FS_ERR_UNSUPPORTED:
+                        raise
+                    break
+                units.append((plan, [left[t] for t in taken]))
+                left = [k for t, k in enumerate(left) if t not in taken]
+            units += [(None, [k]) for k in left]
+        return units
+
+    def _count_kernels(self):
+        self.n_kernels = sum((plan or self.plans[members[0]]).info()["n_kernels"] for plan, members in self._units)
+
+    def _unit_args(self, values, members, device):
+        """Inputs and freshly allocated outputs of a launch's groups, in order."""
         torch = self._torch
         dt = {"f32": torch.float32, "f16": torch.float16, "bf16": torch.bfloat16}
-        values = {i: t for i, t in zip(self.param_ops, inputs)}
-        for g, plan in zip(self.fusion.groups, self.plans):
-            gin = [values[i] for i in g["input_of"]]
-            gout = []
+        gin, gout = [], []
+        for k in members:
+            g = self.fusion.groups[k]
+            gin += [values[i] for i in g["input_of"]]
             for i in g["output_of"]:
                 op = self.ops[i]
-                t = torch.empty(op.shape, dtype=dt[op.dtype], device=gin[0].device if gin else "cuda:0")
-                values[i] = t
-                gout.append(t)
-            plan.launch(gin, gout, stream)
+                values[i] = torch.empty(op.shape, dtype=dt[op.dtype], device=device or (gin[0].device if gin else "cuda:0"))
+                gout.append(values[i])
+        return gin, gout
+
+    def run(self, inputs, stream=None):
+        values = {i: t for i, t in zip(self.param_ops, inputs)}
+        for plan, members in self._units:
+            gin, gout = self._unit_args(values, members, None)
+            (plan or self.plans[members[0]]).launch(gin, gout, stream)
         return [values[self.ops[i].operands[0]] for i in self.output_ops]
 
     @classmethod
@@ -543,8 +600,15 @@ class FusedProgram:
 
     def tune(self, inputs, trials=10):
         """Time every group's launch templates on the program's own data (fs_plan_tune, group by group in
-        execution order) and keep the winners.  -> the program's outputs, as run() would return them."""
+        execution order) and keep the winners; every group is then a launch of its own.  -> the program's
+        outputs, as run() would return them."""
         torch = self._torch
+        for plan, members in self._units:
+            if plan is not None:
+                for k in members:
+                    self.plans[k] = self._group_plan(k)
+                plan.close()
+        self._units = [(None, [k]) for k in range(len(self.plans))]
         dt = {"f32": torch.float32, "f16": torch.float16, "bf16": torch.bfloat16}
         values = {i: t for i, t in zip(self.param_ops, inputs)}
         for k, g in enumerate(self.fusion.groups):
@@ -560,26 +624,19 @@ class FusedProgram:
             tuned = Plan.tune(g["ops"], gin, gout, trials=trials)      # leaves the group's outputs written
             self.plans[k].close()
             self.plans[k] = tuned
-        self.n_kernels = sum(p.info()["n_kernels"] for p in self.plans)
+        self._count_kernels()
         return [values[self.ops[i].operands[0]] for i in self.output_ops]
 
     def bind(self, inputs):
         """Fix the program's buffers: the given input tensors, and one freshly allocated tensor per value
         that crosses a group boundary.  -> the output tensors; run_bound() then launches every group on
         those buffers without allocating, which is what a HIP graph capture needs."""
-        torch = self._torch
-        dt = {"f32": torch.float32, "f16": torch.float16, "bf16": torch.bfloat16}
         values = {i: t for i, t in zip(self.param_ops, inputs)}
         device = inputs[0].device if inputs else "cuda:0"
         self._bound = []
-        for g, plan in zip(self.fusion.groups, self.plans):
-            gin = [values[i] for i in g["input_of"]]
-            gout = []
-            for i in g["output_of"]:
-                op = self.ops[i]
-                values[i] = torch.empty(op.shape, dtype=dt[op.dtype], device=device)
-                gout.append(values[i])
-            self._bound.append((plan, BoundArgs(gin, gout)))
+        for plan, members in self._units:
+            gin, gout = self._unit_args(values, members, device)
+            self._bound.append((plan or self.plans[members[0]], BoundArgs(gin, gout)))
         self._bound_outputs = [values[self.ops[i].operands[0]] for i in self.output_ops]
         return self._bound_outputs
 
@@ -604,9 +661,10 @@ class FusedProgram:
         return graph, outs
 
     def close(self):
-        for p in self.plans:
-            p.close()
-        self.plans = []
+        for p in self.plans + [plan for plan, _ in self._units]:
+            if p is not None:
+                p.close()
+        self.plans, self._units = [], []
         self._bound = []
 
     def __enter__(self):

@@ -60,6 +60,7 @@ uint64_t group_key(const fs_op_desc* ops, int32_t n_ops) {
 }
 
 fs_status plan_create_impl(const fs_op_desc* ops, int32_t n_ops, const fs_plan_options* opt, fs_plan** out);
+void collapse_reductions(fs::Graph* g);
 
 }  // namespace
 
@@ -89,6 +90,53 @@ fs_status fs_plan_create(const fs_op_desc* ops, int32_t n_ops, const fs_plan_opt
     if (hit && plan_create_impl(ops, n_ops, &e.opt, out) == FS_OK) return FS_OK;
   }
   return plan_create_impl(ops, n_ops, opt, out);
+}
+
+fs_status fs_plan_create_packed(const fs_op_desc* const* groups, const int32_t* n_ops, int32_t n_groups, uint8_t* taken, fs_plan** out) {
+  if (!out) return set_error(FS_ERR_INVALID, "out is NULL");
+  *out = nullptr;
+  if (!groups || !n_ops || !taken || n_groups < 1 || n_groups > 4096) return set_error(FS_ERR_INVALID, "fs_plan_create_packed: NULL argument or n_groups out of range [1,4096]");
+  try {
+    std::vector<fs::Graph> graphs((size_t)n_groups);
+    for (int32_t k = 0; k < n_groups; ++k) {
+      taken[k] = 0;
+      std::string err;
+      if (!fs::build_graph(groups[k], n_ops[k], &graphs[k], &err)) return set_error(FS_ERR_INVALID, err);
+      collapse_reductions(&graphs[k]);
+    }
+    std::unique_ptr<fs_plan> p(new fs_plan);
+    std::vector<char> which;
+    int st = FS_OK;
+    std::string err;
+    if (!fs::row_gen_plan_packed(graphs, &which, &p->row_gen, &st, &err)) return set_error((fs_status)st, err);
+    // the launch's own list: the lists of the groups taken, one behind the other
+    std::vector<fs_op_desc> list;
+    for (int32_t k = 0; k < n_groups; ++k) {
+      if (!which[k]) continue;
+      const int base = (int)list.size();
+      for (int32_t i = 0; i < n_ops[k]; ++i) {
+        fs_op_desc d = groups[k][i];
+        for (int j = 0; j < 3; ++j) if (d.operand[j] >= 0) d.operand[j] += base;
+        list.push_back(d);
+      }
+    }
+    if (!fs::build_graph(list.data(), (int32_t)list.size(), &p->graph, &err)) return set_error(FS_ERR_UNSUPPORTED, err);
+    for (int32_t k = 0; k < n_groups; ++k) taken[k] = (uint8_t)which[k];
+    p->mode = FS_MODE_STITCHED;
+    p->match.kind = fs::MATCH_NONE;
+    p->schedule = FS_SCHED_ROW;
+    p->row_form = 3;
+    p->lds_bytes = p->row_gen.lds_bytes;
+    p->moved_bytes = p->graph.algorithmic_bytes();
+    p->n_kernels = 1;
+    p->description = fs::row_gen_describe(p->row_gen);
+    *out = p.release();
+  } catch (const std::bad_alloc&) {
+    return set_error(FS_ERR_NOMEM, "out of host memory");
+  } catch (...) {
+    return set_error(FS_ERR_INVALID, "internal error while planning");
+  }
+  return FS_OK;
 }
 
 fs_status fs_kernel_cache_dir(const char* dir) {
@@ -183,6 +231,23 @@ fs_status fs_tune_cache_load(const char* path) {
 
 namespace {
 
+// The graph of a group as the generator takes it: chained reductions over the trailing dims become one reduction over a
+// merged dim, reductions over the leading dim that keep the inner dims one over merged inner dims (same memory).
+void collapse_reductions(fs::Graph* g) {
+  std::vector<fs_op_desc> merged;
+  for (int step = 0; step < FS_MAX_RANK && fs::collapse_trailing_reductions(*g, &merged); ++step) {
+    fs::Graph g2;
+    std::string err;
+    if (!fs::build_graph(merged.data(), (int32_t)merged.size(), &g2, &err)) break;
+    *g = g2;
+  }
+  if (fs::collapse_kept_dims_of_leading_reductions(*g, &merged)) {
+    fs::Graph g2;
+    std::string err;
+    if (fs::build_graph(merged.data(), (int32_t)merged.size(), &g2, &err)) *g = g2;
+  }
+}
+
 fs_status plan_create_impl(const fs_op_desc* ops, int32_t n_ops, const fs_plan_options* opt, fs_plan** out) {
   if (!out) return set_error(FS_ERR_INVALID, "out is NULL");
   *out = nullptr;
@@ -206,20 +271,7 @@ fs_status plan_create_impl(const fs_op_desc* ops, int32_t n_ops, const fs_plan_o
       lo.wg_size = opt->wg_size; lo.rows_per_wave = opt->rows_per_wave; lo.grid = opt->grid;
     }
     if (p->mode != FS_MODE_PER_OP) {
-      // chained reductions over the trailing dims become one reduction over a merged dim (same memory)
-      std::vector<fs_op_desc> merged;
-      for (int step = 0; step < FS_MAX_RANK && fs::collapse_trailing_reductions(p->graph, &merged); ++step) {
-        fs::Graph g2;
-        std::string err2;
-        if (!fs::build_graph(merged.data(), (int32_t)merged.size(), &g2, &err2)) break;
-        p->graph = g2;
-      }
-      // reductions over the leading dim that keep the inner dims: the inner dims become one (same memory)
-      if (fs::collapse_kept_dims_of_leading_reductions(p->graph, &merged)) {
-        fs::Graph g2;
-        std::string err2;
-        if (fs::build_graph(merged.data(), (int32_t)merged.size(), &g2, &err2)) p->graph = g2;
-      }
+      collapse_reductions(&p->graph);
     }
     const int64_t algo = p->graph.algorithmic_bytes();
     if (p->mode == FS_MODE_PER_OP) {

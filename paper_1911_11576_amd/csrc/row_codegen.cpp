@@ -992,6 +992,20 @@ struct Gen {
     L = 64;
     return geometry_rows(err);
   }
+  // The geometry of a part of a packed launch: every part has workgroups of `threads`, a row at most one of them.
+  bool geometry_part(int threads, std::string* err) {
+    wg = threads;
+    if (!geometry(err)) return false;
+    if (mma || persistent || long_row || L > threads) { *err = "generated row schedule: not a part for a packed launch"; return false; }
+    if (L > 64 && L < threads) {
+      L = threads;
+      const int64_t nvec = (A.cols + W - 1) / W;
+      K = (int)((nvec + L - 1) / L);
+      exact = (int64_t)K * L == nvec && !ragged;
+    }
+    wg = threads;
+    return true;
+  }
   bool geometry_rows(std::string* err) {
     W = chunk_elements(A, &fast);
     if (W == 0) { *err = "generated row schedule: an operand strided along the last dim"; return false; }
@@ -2568,8 +2582,116 @@ bool row_gen_plan(const Graph& g, const LaunchOpts& opt, RowGenLaunch* out, int*
   return true;
 }
 
+// Independent row groups as one launch (kernel packing, Section 5.1): each is generated as for a launch of its own,
+// its kernel's body becomes a function of the workgroup's number within the part, and every part gets a run of
+// consecutive workgroups -- the parts with the fewest first, since a part of one workgroup is a chain of latencies
+// that the others hide.  What it saves is the launches: the sums of squares of eight gradient tensors of a layer,
+// 1.2 to 5 us of kernel and about as much of gap each.  Only groups up to kPackBytes: the registers of a launch are
+// those of its widest part, which a launch that lasts has no reason to share.
+constexpr int64_t kPackBytes = 64ll << 20;
+constexpr int kPackThreads = 256;
+
+bool row_gen_plan_packed(const std::vector<Graph>& graphs, std::vector<char>* taken, RowGenLaunch* out, int* status, std::string* err) {
+  *status = FS_ERR_UNSUPPORTED;
+  taken->assign(graphs.size(), 0);
+  struct Part { int64_t grid; std::string body; };
+  std::vector<Part> parts;
+  RowGenLaunch l;
+  bool any_ragged = false;
+  int64_t lds = 0;
+  int param_base = 0, out_base = 0;      // of the groups taken so far: their parameters and outputs follow each other
+  for (size_t gi = 0; gi < graphs.size(); ++gi) {
+    const Graph& g = graphs[gi];
+    const int n_par = (int)g.params.size(), n_out = (int)g.outputs.size();
+    std::string why;
+    Analysis A(g);
+    if (g.algorithmic_bytes() > kPackBytes || out_base + n_out > 16 || param_base + n_par > 64 || !A.run() || A.n_col > 0 || A.mma_in >= 0 || A.rows == 0 ||
+        A.cols == 0 || (int64_t)l.view_param.size() + (int64_t)A.views.size() > 64)
+      continue;
+    Gen gen(A);
+    if (!gen.geometry_part(kPackThreads, &why)) continue;
+    const int64_t part_lds = gen.L > 64 ? (int64_t)A.n_reduce * (gen.L / 64) * 4 : gen.stage_bytes;
+    const int64_t rows_per_wg = gen.L > 64 ? 1 : gen.wg / gen.L;
+    const int64_t grid = (A.rows + rows_per_wg - 1) / rows_per_wg;
+    if (lds + part_lds > 64 * 1024 || grid + l.grid > 0x3fffffffLL) continue;
+    std::string name;
+    gen.emit(&name);
+    // the body, its operands and outputs numbered within the launch, its workgroups within the part
+    const std::string head = "void " + name + "(const Args a) {\n";
+    const size_t at = gen.e.s.find(head);
+    if (at == std::string::npos) continue;
+    const std::string text = gen.e.s.substr(at + head.size());
+    std::string body;
+    for (size_t k = 0; k < text.size();) {
+      const bool in = text.compare(k, 5, "a.in[") == 0, ou = text.compare(k, 6, "a.out[") == 0;
+      if (in || ou) {
+        const size_t from = k + (in ? 5 : 6), to = text.find(']', from);
+        const int number = atoi(text.substr(from, to - from).c_str()) + (in ? (int)l.view_param.size() : out_base);
+        body += (in ? "a.in[" : "a.out[") + std::to_string(number) + "]";
+        k = to + 1;
+      } else if (text.compare(k, 10, "blockIdx.x") == 0) {
+        body += "bid";
+        k += 10;
+      } else {
+        body += text[k++];
+      }
+    }
+    for (const RView& v : A.views) { l.view_param.push_back(param_base + v.param); l.view_dense.push_back(0); }
+    l.n_ops += (int)A.nodes.size();
+    l.n_reduce += A.n_reduce;
+    any_ragged = any_ragged || gen.ragged;
+    lds += part_lds;
+    l.grid = (int)(parts.empty() ? grid : l.grid + grid);
+    parts.push_back(Part{grid, body});
+    param_base += n_par;
+    out_base += n_out;
+    (*taken)[gi] = 1;
+  }
+  if (parts.size() < 2) { *err = "packed row groups: fewer than two groups that can share a launch"; return false; }
+  Emitter e;
+  e.s = ew_preamble();
+  e.s += kReducePreamble;
+  if (any_ragged) e.s += kRaggedPreamble;
+  std::vector<size_t> order(parts.size());
+  for (size_t k = 0; k < parts.size(); ++k) order[k] = k;
+  std::stable_sort(order.begin(), order.end(), [&](size_t a, size_t b) { return parts[a].grid < parts[b].grid; });
+  for (size_t k = 0; k < parts.size(); ++k) {
+    e.line("static __device__ __forceinline__ void part_%zu(const Args& a, const unsigned bid) {", k);
+    e.s += parts[k].body;
+  }
+  e.line("extern \"C\" __global__ __launch_bounds__(%d) void FS_ROW_NAME(const Args a) {", kPackThreads);
+  int64_t first = 0;
+  for (size_t k : order) {
+    e.line("  if (blockIdx.x < %lldu) { part_%zu(a, blockIdx.x - %lldu); return; }", (long long)(first + parts[k].grid), k, (long long)first);
+    first += parts[k].grid;
+  }
+  e.line("}");
+  uint64_t h = 1469598103934665603ull;
+  for (unsigned char c : e.s) { h ^= c; h *= 1099511628211ull; }
+  char name[32];
+  snprintf(name, sizeof name, "fs_row_%08x", (unsigned)(h ^ (h >> 32)));
+  l.kernel_name = name;
+  const std::string tag = "FS_ROW_NAME";
+  e.s.replace(e.s.find(tag), tag.size(), name);
+  dump_source(e.s);
+  std::string cerr;
+  if (!ew_compile_source(e.s, &l.code_object, &cerr)) { *err = "packed row groups: " + cerr; return false; }
+  l.rows = l.cols = 1;                       // (none of the parts is empty)
+  l.parts = (int)parts.size();
+  l.wg = kPackThreads;
+  l.lds_bytes = lds;
+  *out = l;
+  *status = FS_OK;
+  return true;
+}
+
 std::string row_gen_describe(const RowGenLaunch& l) {
   char buf[720];
+  if (l.parts > 1) {
+    snprintf(buf, sizeof buf, "reduce x%d + elementwise x%d packed in %d independent row groups, a run of workgroups each (generated kernel %s, %zu bytes of code); cta_num=%d, cta_size=%d, lds=%lld",
+             l.n_reduce, l.n_ops - l.n_reduce, l.parts, l.kernel_name.c_str(), l.code_object.size(), l.grid, l.wg, (long long)l.lds_bytes);
+    return buf;
+  }
   if (l.streamed) {
     char cols[96] = "";
     if (l.n_col > 0) snprintf(cols, sizeof cols, " + column reduce x%d[GRID-THREAD,CTA] (%d partial rows, then a combine kernel)", l.n_col, l.grid);
@@ -2624,7 +2746,7 @@ int row_gen_launch(RowGenLaunch& l, const void* const* in, void* const* out, int
   }
   GenArgs args{};
   for (size_t k = 0; k < l.view_param.size(); ++k) args.in[k] = in[l.view_param[k]];
-  for (int k = 0; k < n_out && k < 8; ++k) args.out[k] = out[k];
+  for (int k = 0; k < n_out && k < 16; ++k) args.out[k] = out[k];
   args.ws = workspace;
   const int rc = ew_module_launch(&l.loaded, l.code_object, l.kernel_name, &args, sizeof args, l.grid, l.wg, stream, err);
   if (rc != 0 || l.n_col == 0 || l.n_kernels == 1) return rc;

@@ -30,6 +30,7 @@ struct RowGenLaunch {
   int64_t seg_count = 0;
   int seg_groups = 0;
   int n_kernels = 1;
+  int parts = 1;                      // independent row groups packed into the launch
   // block composition around dots on the matrix unit: one workgroup per batch element
   bool mma = false;
   int mma_dots = 0, mma_k = 0, mma_d = 0;   // dots on MFMA (1 or 2), contraction of the first, result width of the second
@@ -43,6 +44,9 @@ struct RowGenLaunch {
   EwModule loaded;                    // run-time state: the module once it is on a device
 };
 bool row_gen_plan(const Graph&, const LaunchOpts&, RowGenLaunch*, int* status, std::string* err);
+// Those of the graphs that can share one launch (taken[k] = 1), at least two of them; parameters and outputs of the
+// groups taken follow each other in order.
+bool row_gen_plan_packed(const std::vector<Graph>&, std::vector<char>* taken, RowGenLaunch*, int* status, std::string* err);
 std::string row_gen_describe(const RowGenLaunch&);
 int row_gen_launch(RowGenLaunch&, const void* const* in, void* const* out, int n_out, void* workspace,
                    void* stream, std::string* err);

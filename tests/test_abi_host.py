@@ -443,6 +443,31 @@ def test_generated_mode_and_prebuilt_mode_on_recognised_groups():
     _expect(binding.FS_ERR_INVALID, graphs.log_softmax((300, 64)), wg_size=512)    # register templates: up to 256
 
 
+def test_packed_row_groups_on_the_host():
+    small, cols, dot = graphs.log_softmax((30, 64)), graphs.layernorm_bwd(64, 128), graphs.sigmoid_attention(2, 16, 16, 32, 32)
+    big = graphs.log_softmax((65536, 1024))                   # beyond the size that shares a launch
+    lists = [binding.marshal_ops(o) for o in (small, cols, graphs.rmsnorm((5, 33)), dot, big, graphs.log_softmax((2, 300)))]
+    plan, taken = Plan.packed(lists)
+    with plan:
+        assert taken == [0, 2, 5] and plan.info()["schedule"] == "row" and plan.info()["n_kernels"] == 1
+        assert "packed in 3 independent row groups" in plan.describe()
+        assert plan.info()["algorithmic_bytes"] == 2 * 30 * 64 * 4 + (2 * 5 * 33 + 33) * 4 + 2 * 2 * 300 * 4
+    for few in ([lists[0]], [lists[0], lists[1]], [lists[1], lists[3]]):
+        with pytest.raises(FsError) as e:
+            Plan.packed(few)
+        assert e.value.status == binding.FS_ERR_UNSUPPORTED
+    broken = binding.marshal_ops(small)
+    broken[len(broken) - 1].operand[0] = 99
+    for bad in ([lists[0], broken], []):
+        with pytest.raises(FsError) as e:
+            Plan.packed(bad)
+        assert e.value.status == binding.FS_ERR_INVALID
+    # sixteen outputs at most: the rest is left out
+    plan, taken = Plan.packed([binding.marshal_ops(graphs.log_softmax((2, 512)))] * 20)
+    with plan:
+        assert taken == list(range(16))
+
+
 def test_motivating_pattern_plans_as_one_kernel():
     ops = graphs.multi_interest_pattern(16384)
     with Plan(ops) as p:

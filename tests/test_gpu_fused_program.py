@@ -7,10 +7,10 @@ import pytest
 import torch
 
 from oracle import interp
-from paper_1911_11576_amd import FusedProgram, Plan
+from paper_1911_11576_amd import FusedProgram, Plan, binding
 from workloads import TOLERANCE, graphs, inputs
 
-from gpu_util import assert_close, to_device
+from gpu_util import alloc_outputs, assert_close, group_dtype, to_device
 
 pytestmark = pytest.mark.gpu
 
@@ -283,3 +283,50 @@ def test_fine_grained_dots_are_fused_with_the_ops_around_them(name):
         torch.cuda.synchronize()
         for a, b in zip(outs, want):
             assert_close(a.to(torch.float64).cpu().numpy(), b, TOLERANCE[cfg.dtype], name + " (measured plan)")
+
+
+def test_independent_row_groups_in_one_launch():
+    """Groups of every register template (thread, lanes, wavefront, workgroup), staged and ragged rows, 16-bit storage, per-row and
+    full outputs, packed into one launch: each gives what it gives on its own."""
+    announce("packed row groups")
+    cases = [(graphs.log_softmax((37, 100)), inputs.normal_tensors([(37, 100)], scale=3.0)),            # staged rows
+             (graphs.log_softmax((300, 5)), inputs.normal_tensors([(300, 5)], scale=3.0)),              # a thread per row
+             (graphs.rmsnorm((203, 1024), "bf16"), inputs.normal_tensors([(203, 1024), (1024,)], "bf16")),
+             (graphs.softmax_with_lse((29, 999)), inputs.normal_tensors([(29, 999)], scale=2.0)),       # ragged rows
+             (graphs.row_sum_of_squares((11, 3001)), inputs.normal_tensors([(11, 3001)])),              # a ragged row per workgroup
+             (graphs.row_sum_of_squares((1, 8192)), inputs.normal_tensors([(1, 8192)])),
+             (graphs.layernorm_fwd_with_stats(33, 96, "f16"), inputs.layernorm_fwd(33, 96, "f16")),
+             (graphs.gated_rows((2, 3, 5, 32)), inputs.normal_tensors([(2, 3, 5, 32), (2, 3, 5), (32,)])),
+             (graphs.layernorm_bwd(64, 128), inputs.layernorm_bwd(64, 128))]                            # column sums: left out
+    plan, taken = Plan.packed([binding.marshal_ops(ops) for ops, _ in cases])
+    assert taken == list(range(8)) and plan.info()["n_kernels"] == 1 and plan.info()["workspace_bytes"] == 0
+    ins = [t for k in taken for t in to_device(*cases[k])]
+    outs = [alloc_outputs(cases[k][0]) for k in taken]
+    with plan:
+        for _ in range(2):
+            plan.launch(ins, [t for o in outs for t in o])
+        torch.cuda.synchronize()
+    for k, got in zip(taken, outs):
+        tol = TOLERANCE[group_dtype(cases[k][0])]
+        for a, b in zip(got, interp.run(*cases[k])):
+            assert_close(a.to(torch.float64).cpu().numpy(), b, tol, f"packed group {k}")
+
+
+@pytest.mark.parametrize("shapes", [[(64, 96), (96,), (96, 64), (64,)], [(300, 999), (999,), (5, 7), (1,)] * 3, [(33, 5000), (9000,)]])
+def test_clipping_takes_as_few_launches_whatever_the_number_of_tensors(shapes):
+    announce(f"packed clipping {shapes[:4]} x{len(shapes)}")
+    ops, ins = graphs.clip_by_global_norm(shapes, 1.0), inputs.normal_tensors(shapes, scale=0.1)
+    want = interp.run(ops, ins)
+    dev_in = to_device(ops, ins)
+    with FusedProgram(ops) as prog:
+        assert prog.n_kernels <= 4 + sum(sh[-1] > 8192 for sh in shapes)      # (a row of more than 8192 elements takes a launch of its own)
+        results = [prog.run(dev_in)]
+        prog.bind(dev_in)
+        results.append(prog.run_bound())
+        torch.cuda.synchronize()
+        results.append(prog.tune(dev_in, trials=2))            # a launch per group again
+        assert prog.n_kernels == len(prog.fusion.groups)
+        torch.cuda.synchronize()
+        for got in results:
+            for a, b in zip(got, want):
+                assert_close(a.to(torch.float64).cpu().numpy(), b, TOLERANCE["f32"], "clipped")
