@@ -9,6 +9,7 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+from array import array
 
 FS_MAX_RANK = 4
 LIB_PATH = os.environ.get("FS_LIB_PATH") or os.path.join(os.path.dirname(os.path.abspath(__file__)),
@@ -52,11 +53,13 @@ class FsError(RuntimeError):
 
 
 _lib = None
+_raw_launch = None          # fs_launch and fs_launch_static taking plain addresses, with lib()
+_raw_launch_static = None
 
 
 def lib():
     """The loaded shared library (loaded on first use)."""
-    global _lib
+    global _lib, _raw_launch, _raw_launch_static
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise ImportError(
@@ -123,6 +126,13 @@ def lib():
         L.fs_fusion_pattern_group_size.restype = i32
         L.fs_fusion_pattern_group.argtypes = [vp, i32, C.POINTER(fs_op_desc), C.POINTER(i32), C.POINTER(i32)]
         L.fs_fusion_pattern_group.restype = i32
+        # the two launch entry points once more, on a handle of their own: ints in place of typed pointers cost a
+        # call a microsecond less
+        raw = C.CDLL(LIB_PATH)
+        for f in (raw.fs_launch, raw.fs_launch_static):
+            f.argtypes = [vp, vp, i32, vp, i32, vp]
+            f.restype = i32
+        _raw_launch, _raw_launch_static = raw.fs_launch, raw.fs_launch_static
         _lib = L
     return _lib
 
@@ -181,21 +191,48 @@ def _pointers(tensors):
     return arr
 
 
+_torch_stream = None
+
+
+def _current_stream():
+    """The handle of torch's current stream (without the stream object that torch.cuda.current_stream() makes)."""
+    global _torch_stream
+    if _torch_stream is None:
+        import torch
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        if raw is None:
+            _torch_stream = lambda: torch.cuda.current_stream().cuda_stream
+        else:
+            device = torch.cuda.current_device
+            _torch_stream = lambda: raw(device())
+    return _torch_stream()
+
+
+def _addresses(tensors):
+    return array("Q", [t if isinstance(t, int) else t.data_ptr() for t in tensors] or [0])
+
+
 def fs_launch(plan, inputs, outputs, stream=None):
     """inputs/outputs: device tensors (anything with .data_ptr()) or raw addresses.
     stream: a hipStream_t address; None = torch's current stream."""
     if stream is None:
-        import torch
-        stream = torch.cuda.current_stream().cuda_stream
-    _check(lib().fs_launch(plan, _pointers(inputs), len(inputs), _pointers(outputs), len(outputs), stream))
+        stream = _current_stream()
+    if _raw_launch is None:
+        lib()
+    ins, outs = _addresses(inputs), _addresses(outputs)
+    status = _raw_launch(plan, ins.buffer_info()[0], len(inputs), outs.buffer_info()[0], len(outputs), stream)
+    if status != FS_OK:
+        raise FsError(status, fs_last_error())
 
 
 def fs_launch_static(plan, inputs, outputs, stream=None):
     """fs_launch without any allocation: the plan's scratch memory is the library's static device array."""
     if stream is None:
-        import torch
-        stream = torch.cuda.current_stream().cuda_stream
-    _check(lib().fs_launch_static(plan, _pointers(inputs), len(inputs), _pointers(outputs), len(outputs), stream))
+        stream = _current_stream()
+    if _raw_launch_static is None:
+        lib()
+    ins, outs = _addresses(inputs), _addresses(outputs)
+    _check(_raw_launch_static(plan, ins.buffer_info()[0], len(inputs), outs.buffer_info()[0], len(outputs), stream))
 
 
 def fs_plan_tune(ops, inputs, outputs, stream=None, trials=20):
@@ -301,6 +338,7 @@ class BoundArgs:
         self.keep = (list(inputs), list(outputs))
         self.n_in, self.n_out = len(inputs), len(outputs)
         self.in_ptrs, self.out_ptrs = _pointers(inputs), _pointers(outputs)
+        self.in_addr, self.out_addr = C.addressof(self.in_ptrs), C.addressof(self.out_ptrs)
 
 
 class Plan:
@@ -336,7 +374,7 @@ class Plan:
 
     def launch_bound(self, bound, stream):
         """Launch with pre-marshalled arguments (see BoundArgs) on an explicit stream handle."""
-        st = lib().fs_launch(self._h, bound.in_ptrs, bound.n_in, bound.out_ptrs, bound.n_out, stream)
+        st = _raw_launch(self._h, bound.in_addr, bound.n_in, bound.out_addr, bound.n_out, stream)
         if st != FS_OK:
             raise FsError(st, fs_last_error())
 
@@ -642,7 +680,7 @@ class FusedProgram:
 
     def run_bound(self, stream=None):
         if stream is None:
-            stream = self._torch.cuda.current_stream().cuda_stream
+            stream = _current_stream()
         for plan, args in self._bound:
             plan.launch_bound(args, stream)
         return self._bound_outputs
