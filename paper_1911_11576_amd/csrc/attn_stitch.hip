@@ -25,6 +25,18 @@ bool attn_stitch_plan(const AttnSpec& sp, const LaunchOpts& opt, AttnLaunch* out
   l.wg = 64 * l.nq;
   if (opt.wg_size && opt.wg_size != l.wg) { *err = "attention schedule: wg_size is fixed at 64 per 16 query rows"; *status = FS_ERR_INVALID; return false; }
   l.grid = (int)sp.batch;
+  if (sp.sq == 1 && !sp.causal) {
+    // one query: matrix-vector products, a wavefront per batch element (attn_decode.hip); up to four to a workgroup
+    // where that leaves four workgroups for every CU (512 elements of 128 keys of 64 fp16: 5.3 us with one each, 7.0
+    // with four on half of the CUs), and one if the caller names the workgroup of a single query tile
+    l.decode = true;
+    l.wg = opt.wg_size ? opt.wg_size : sp.batch >= 4096 ? 256 : sp.batch >= 2048 ? 128 : 64;
+    const int waves = l.wg / 64;
+    l.grid = (int)((sp.batch + waves - 1) / waves);
+    *out = l;
+    *status = FS_OK;
+    return true;
+  }
   l.lds_bytes = attn_lds_bytes(l.nk, (int)sp.dim);
   if (l.lds_bytes > kLdsBudget) {
     char buf[160];
@@ -41,6 +53,13 @@ bool attn_stitch_plan(const AttnSpec& sp, const LaunchOpts& opt, AttnLaunch* out
 
 std::string attn_stitch_describe(const AttnSpec& sp, const AttnLaunch& l) {
   char buf[640];
+  if (l.decode) {
+    snprintf(buf, sizeof buf,
+             "dot_1[GRID-WARP,WARP]; %ssoftmax[GRID-WARP,WARP]; %sdot_2[GRID-WARP,WARP]; %s%s(one query: matrix-vector products) cta_num=%d, cta_size=%d, lds=0",
+             sp.in_mask >= 0 ? "add_mask[GRID-WARP,WARP]; " : "", sp.out_lse >= 0 ? "logsumexp[GRID-WARP,WARP]; " : "",
+             sp.in_gate >= 0 ? "multiply_gate[GRID-WARP,WARP-THREAD_8]; " : "", sp.in_res >= 0 ? "add_residual[GRID-WARP,WARP-THREAD_8]; " : "", l.grid, l.wg);
+    return buf;
+  }
   snprintf(buf, sizeof buf,
            "dot_1[GRID,WARP_16,CTA]; %ssoftmax[GRID,WARP_16,WARP]; %sdot_2[GRID,WARP_16,CTA]S; %s%s"
            "cta_num=%d, cta_size=%d, lds=%lld",
@@ -67,7 +86,7 @@ int attn_stitch_launch(const AttnSpec& sp, const AttnLaunch& l, const void* cons
   a.scale = sp.scale; a.fill = sp.fill; a.causal = sp.causal ? 1 : 0;
   a.skip_masked_tiles = sp.causal && sp.fill == -INFINITY;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const hipError_t e = sp.dtype == DT_F16 ? attn_launch_f16(a, l.nq, l.nk, s) : attn_launch_bf16(a, l.nq, l.nk, s);
+  const hipError_t e = l.decode ? attn_decode_launch(a, sp.dtype == DT_F16, l.grid, l.wg, s) : sp.dtype == DT_F16 ? attn_launch_f16(a, l.nq, l.nk, s) : attn_launch_bf16(a, l.nq, l.nk, s);
   if (e != hipSuccess) { *err = std::string("attn_stitch launch: ") + hipGetErrorString(e); return -1; }
   return 0;
 }

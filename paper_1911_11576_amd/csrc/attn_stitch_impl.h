@@ -427,6 +427,7 @@ hipError_t attn_launch_dtype(const AttnArgs& a, int nq, int nk, hipStream_t s) {
   }
 }
 
+hipError_t attn_decode_launch(const AttnArgs& a, bool f16, int grid, int wg, hipStream_t s);      // one query per batch element
 hipError_t attn_launch_f16(const AttnArgs& a, int nq, int nk, hipStream_t s);
 hipError_t attn_launch_bf16(const AttnArgs& a, int nq, int nk, hipStream_t s);
 

@@ -347,6 +347,13 @@ ATTN_BLOCK_CASES = [
     (2, 128, 128, 128, "bf16", dict(causal=True, mask="full", gate=True, residual=True, lse=True)),   # maximum sizes
     (1, 1, 1, 32, "f16", dict(lse=True, gate=True)),                           # a single score
 ]
+# one query per batch element: every number of key tiles, whole and partial, every head dim; batches that leave a workgroup partly empty
+DECODE_CASES = [(b, 1, sk, d, dt, kw) for b, sk, d, dt, kw in [
+    (5, 1, 64, "f16", dict()), (3, 16, 32, "bf16", dict()), (6, 17, 128, "f16", dict()), (7, 31, 64, "bf16", dict(mask="key")), (9, 48, 128, "bf16", dict(mask="key", lse=True)),
+    (4, 50, 32, "f16", dict(mask="full", gate=True)), (1, 64, 64, "f16", dict(mask="shared", residual=True)), (130, 77, 64, "bf16", dict(mask="key")),
+    (5, 90, 128, "f16", dict(gate=True, residual=True, lse=True)), (6, 112, 32, "bf16", dict(mask="key", gate=True, residual=True, lse=True)),
+    (33, 127, 64, "f16", dict(mask="key")), (11, 128, 128, "f16", dict(mask="key")), (10, 128, 64, "bf16", dict()), (3, 127, 128, "bf16", dict(mask="full"))]]
+ATTN_BLOCK_CASES += DECODE_CASES
 
 
 @pytest.mark.parametrize("case", ATTN_BLOCK_CASES, ids=lambda c: f"{c[0]}x{c[1]}x{c[2]}x{c[3]}-{c[4]}-" + "+".join(sorted(c[5])))
