@@ -1469,7 +1469,10 @@ struct Gen {
         const char* rt = raw_type(v);
         const std::string pt_s = rt + al;
         const char* pt = pt_s.c_str();
-        const char* ld = ragged ? "*" : "__builtin_nontemporal_load";
+        // (a team of wavefronts per row: ordinary loads for groups of up to 128 MB.  LayerNorm backward over 2048 x 4096,
+        // 101 MB: 23.7 us against 31.5 nontemporal; over 8192 x 4096, 402 MB, 81.5 against 78.8; with 201 MB one or the
+        // other is 2 to 5 % ahead.  A row per wavefront: 16384 x 2048 82.1 against 76.8.)
+        const char* ld = ragged || (L > 64 && A.g.algorithmic_bytes() <= (128ll << 20)) ? "*" : "__builtin_nontemporal_load";
         bool dummy = false;
         const std::string offp = row_offset(v, &dummy, "rowp"), offn = row_offset(v, &dummy, "rown");
         if (rotating) {
@@ -2461,7 +2464,17 @@ bool row_gen_plan(const Graph& g, const LaunchOpts& opt, RowGenLaunch* out, int*
       // (teams: as many workgroups as keep 2048 threads on every CU, but at least sixteen rows each, so
       // that the partial rows stay small beside the rows themselves)
       int64_t want = opt.grid > 0 ? opt.grid : l.L > 64 ? 256 * (2048 / l.L) / 2 : 256;
-      if (l.L > 64 && opt.grid <= 0 && want > (A.rows + 15) / 16) want = (A.rows + 15) / 16;
+      if (l.L > 64 && opt.grid <= 0 && want > (A.rows + 15) / 16) {
+        // ... but from 256 rows on, where that leaves CUs idle, down to four rows each as long as the partial rows stay
+        // within 8 MiB (which also is what a launch without allocations has): LayerNorm backward over 512 x 4096 24.3 ->
+        // 14.3 us, over 1024 x 2304 23.1 -> 16.1, bias + GELU backward over 512 x 8192 bf16 34.1 -> 16.7 (all with the
+        // ordinary loads of small groups)
+        const int64_t few = (A.rows + 15) / 16, row_bytes = (int64_t)std::max(1, A.n_col) * A.cols * 8;
+        int64_t more = std::min<int64_t>(256, (A.rows + 3) / 4);
+        if (more > (8ll << 20) / row_bytes) more = (8ll << 20) / row_bytes;
+        if (A.rows < 256) more = few;
+        if (want > std::max(few, more)) want = std::max(few, more);
+      }
       if (want < grid) grid = want;
       if (n_seg > 0) grid = gen.seg_per_wave ? (n_seg + l.wg / 64 - 1) / (l.wg / 64) : n_seg * gen.seg_groups;      // the runs of rows fix the grid
       l.segmented = A.seg_rows > 0;
