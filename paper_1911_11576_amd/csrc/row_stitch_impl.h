@@ -65,10 +65,16 @@ constexpr float kLog2e = 1.4426950408889634f;
 constexpr int64_t kStreamBytes = 64ll << 20;
 
 // 1 / sqrt(x) as the hardware's estimate and one Newton step: a correctly rounded square root and division take
-// some thirty instructions per row
+// some thirty instructions per row.  The estimate takes a subnormal argument for zero, so one is scaled by 2^24 first
+// (eps = 0 and a spread below 1e-19); where the residual is not finite (x = inf, a variance that overflows; x = 0) the
+// estimate itself is the answer: 0 or inf.
 __device__ __forceinline__ float rsqrt_newton(float x) {
-  const float r = __builtin_amdgcn_rsqf(x);
-  return fmaf(0.5f * r, fmaf(-x * r, r, 1.f), r);
+  const bool tiny = x < 0x1p-126f;
+  const float s = tiny ? x * 0x1p24f : x;
+  const float r = __builtin_amdgcn_rsqf(s);
+  const float e = fmaf(-s * r, r, 1.f);
+  const float n = e == e ? fmaf(0.5f * r, e, r) : r;
+  return tiny ? n * 0x1p12f : n;
 }
 
 // VARIANT: 0 LayerNorm, 1 prologue(bias,GELU,residual)+LayerNorm, 2 softmax, 3 softmax with a

@@ -187,6 +187,21 @@ def test_layernorm_team_form_f32(rows, cols):
     check_against_oracle(graphs.layernorm_fwd(rows, cols), inputs.layernorm_fwd(rows, cols), what=f"ln team {rows}x{cols}")
 
 
+@pytest.mark.parametrize("dtype,cols", [("f32", 64), ("f32", 768), ("f32", 333), ("f32", 2048), ("f32", 4096), ("f32", 3001), ("bf16", 1024), ("bf16", 999), ("bf16", 5003)])
+def test_layernorm_variance_beyond_and_below_the_normal_range(dtype, cols):
+    """A variance that overflows fp32 gives 1 / sqrt(inf) = 0, that is beta; a subnormal one (eps = 0) still normalises."""
+    announce(f"layernorm variance limits {dtype} {cols}")
+    ops, ins = graphs.layernorm_fwd(7, cols, dtype, eps=0.0), inputs.layernorm_fwd(7, cols, dtype)
+    x = ins[0]
+    x[1::2] = np.where(np.arange(cols) % 2, 1.0, -1.0) * 2.0 ** 65             # squares of 2^130
+    x[2] *= 2.0 ** -65                                                          # squares around 2^-130, known to 2^-149: 1e-6 of the variance
+    (want,) = interp.run(ops, ins)
+    for mode in ("stitched", "generated"):
+        (got,) = run_gpu(ops, ins, mode)
+        assert np.array_equal(got[1::2], np.broadcast_to(ins[2], got[1::2].shape)), mode
+        assert_close(got[0::2], want[0::2], TOLERANCE[dtype], f"LN {mode}")
+
+
 @pytest.mark.parametrize("mode", GELU_LN_MODES)
 @pytest.mark.parametrize("dtype,rows,cols", [("bf16", 3, 2056), ("f16", 5, 4096), ("bf16", 2, 32768), ("f16", 3, 12288)])
 def test_gelu_layernorm_team_form_16bit(dtype, rows, cols, mode):
