@@ -59,6 +59,17 @@ uint64_t group_key(const fs_op_desc* ops, int32_t n_ops) {
   return h;
 }
 
+// The options recorded for a group, if it was tuned.
+bool tuned_options(const fs_op_desc* ops, int32_t n_ops, fs_plan_options* opt) {
+  if (g_tuning || !ops || n_ops < 1 || n_ops > 4096) return false;
+  std::lock_guard<std::mutex> lock(g_tune_mu);
+  if (g_tune.empty()) return false;
+  const auto it = g_tune.find(group_key(ops, n_ops));
+  if (it == g_tune.end()) return false;
+  *opt = it->second.opt;
+  return true;
+}
+
 fs_status plan_create_impl(const fs_op_desc* ops, int32_t n_ops, const fs_plan_options* opt, fs_plan** out);
 void collapse_reductions(fs::Graph* g);
 
@@ -76,19 +87,9 @@ const char* fs_last_error(void) { return g_error.c_str(); }
 fs_status fs_plan_create(const fs_op_desc* ops, int32_t n_ops, const fs_plan_options* opt, fs_plan** out) {
   if (!out) return set_error(FS_ERR_INVALID, "out is NULL");
   const bool defaults = !opt || (opt->mode == FS_MODE_STITCHED && opt->wg_size == 0 && opt->rows_per_wave == 0 && opt->grid == 0);
-  if (defaults && !g_tuning && ops && n_ops >= 1 && n_ops <= 4096) {
-    TuneEntry e;
-    bool hit = false;
-    {
-      std::lock_guard<std::mutex> lock(g_tune_mu);
-      if (!g_tune.empty()) {
-        const auto it = g_tune.find(group_key(ops, n_ops));
-        if (it != g_tune.end()) { e = it->second; hit = true; }
-      }
-    }
-    // recorded options that no longer build (another library version wrote the file): the defaults
-    if (hit && plan_create_impl(ops, n_ops, &e.opt, out) == FS_OK) return FS_OK;
-  }
+  fs_plan_options tuned{};
+  // recorded options that no longer build (another library version wrote the file): the defaults
+  if (defaults && tuned_options(ops, n_ops, &tuned) && plan_create_impl(ops, n_ops, &tuned, out) == FS_OK) return FS_OK;
   return plan_create_impl(ops, n_ops, opt, out);
 }
 
@@ -98,17 +99,21 @@ fs_status fs_plan_create_packed(const fs_op_desc* const* groups, const int32_t* 
   if (!groups || !n_ops || !taken || n_groups < 1 || n_groups > 4096) return set_error(FS_ERR_INVALID, "fs_plan_create_packed: NULL argument or n_groups out of range [1,4096]");
   try {
     std::vector<fs::Graph> graphs((size_t)n_groups);
+    std::vector<char> apart((size_t)n_groups, 0);
     for (int32_t k = 0; k < n_groups; ++k) {
       taken[k] = 0;
       std::string err;
       if (!fs::build_graph(groups[k], n_ops[k], &graphs[k], &err)) return set_error(FS_ERR_INVALID, err);
       collapse_reductions(&graphs[k]);
+      // a tuned group's own plan is the one that was timed
+      fs_plan_options tuned{};
+      apart[k] = tuned_options(groups[k], n_ops[k], &tuned);
     }
     std::unique_ptr<fs_plan> p(new fs_plan);
     std::vector<char> which;
     int st = FS_OK;
     std::string err;
-    if (!fs::row_gen_plan_packed(graphs, &which, &p->row_gen, &st, &err)) return set_error((fs_status)st, err);
+    if (!fs::row_gen_plan_packed(graphs, apart, &which, &p->row_gen, &st, &err)) return set_error((fs_status)st, err);
     // the launch's own list: the lists of the groups taken, one behind the other
     std::vector<fs_op_desc> list;
     for (int32_t k = 0; k < n_groups; ++k) {

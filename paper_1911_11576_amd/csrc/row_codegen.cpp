@@ -2604,7 +2604,7 @@ bool row_gen_plan(const Graph& g, const LaunchOpts& opt, RowGenLaunch* out, int*
 constexpr int64_t kPackBytes = 64ll << 20;
 constexpr int kPackThreads = 256;
 
-bool row_gen_plan_packed(const std::vector<Graph>& graphs, std::vector<char>* taken, RowGenLaunch* out, int* status, std::string* err) {
+bool row_gen_plan_packed(const std::vector<Graph>& graphs, const std::vector<char>& apart, std::vector<char>* taken, RowGenLaunch* out, int* status, std::string* err) {
   *status = FS_ERR_UNSUPPORTED;
   taken->assign(graphs.size(), 0);
   struct Part { int64_t grid; std::string body; };
@@ -2614,6 +2614,7 @@ bool row_gen_plan_packed(const std::vector<Graph>& graphs, std::vector<char>* ta
   int64_t lds = 0;
   int param_base = 0, out_base = 0;      // of the groups taken so far: their parameters and outputs follow each other
   for (size_t gi = 0; gi < graphs.size(); ++gi) {
+    if (apart[gi]) continue;
     const Graph& g = graphs[gi];
     const int n_par = (int)g.params.size(), n_out = (int)g.outputs.size();
     std::string why;

@@ -44,9 +44,9 @@ struct RowGenLaunch {
   EwModule loaded;                    // run-time state: the module once it is on a device
 };
 bool row_gen_plan(const Graph&, const LaunchOpts&, RowGenLaunch*, int* status, std::string* err);
-// Those of the graphs that can share one launch (taken[k] = 1), at least two of them; parameters and outputs of the
-// groups taken follow each other in order.
-bool row_gen_plan_packed(const std::vector<Graph>&, std::vector<char>* taken, RowGenLaunch*, int* status, std::string* err);
+// Those of the graphs that can share one launch (taken[k] = 1) and are not to stay apart[k], at least two of them;
+// parameters and outputs of the groups taken follow each other in order.
+bool row_gen_plan_packed(const std::vector<Graph>&, const std::vector<char>& apart, std::vector<char>* taken, RowGenLaunch*, int* status, std::string* err);
 std::string row_gen_describe(const RowGenLaunch&);
 int row_gen_launch(RowGenLaunch&, const void* const* in, void* const* out, int n_out, void* workspace,
                    void* stream, std::string* err);

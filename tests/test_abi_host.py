@@ -468,6 +468,27 @@ def test_packed_row_groups_on_the_host():
         assert taken == list(range(16))
 
 
+def test_tuned_groups_are_not_packed(tmp_path):
+    """Recorded options are those of the group's own plan: it keeps that plan, in a program built later too."""
+    from paper_1911_11576_amd import FusedProgram, fs_group_key, fs_tune_cache_clear, fs_tune_cache_load
+    shapes = [(30, 1024), (1024,), (7, 3, 50)]
+    ops = graphs.clip_by_global_norm(shapes, 1.0)
+    fs_tune_cache_clear()
+    try:
+        with FusedProgram(ops) as prog:
+            assert [members for plan, members in prog._units if plan is not None] == [[0, 2, 3], [1, 4]]
+            tuned = prog.fusion.groups[2]["ops"]
+            wanted = Plan(prog.fusion.groups[2]["ops"], wg_size=64).describe()
+        f = tmp_path / "tuned"
+        f.write_text(f"fs-tune-cache 1\n{fs_group_key(tuned):016x} {binding.FS_MODE_STITCHED} 64 0 0 3.0\n")
+        fs_tune_cache_load(f)
+        with FusedProgram(ops) as prog:
+            assert [members for plan, members in prog._units if plan is not None] == [[0, 3], [1, 4]]
+            assert prog.plans[2].describe() == wanted and "cta_size=64" in wanted
+    finally:
+        fs_tune_cache_clear()
+
+
 def test_motivating_pattern_plans_as_one_kernel():
     ops = graphs.multi_interest_pattern(16384)
     with Plan(ops) as p:
