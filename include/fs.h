@@ -169,10 +169,12 @@ typedef enum {
 fs_status fs_plan_create(const fs_op_desc* ops, int32_t n_ops,
                          const fs_plan_options* opt, fs_plan** out);
 
-/* Several independent groups as one launch (kernel packing, Section 5.1): of the given groups, those that are generated
- * register row kernels without column reductions or dots, of at most 64 MB each and without recorded tuning options,
- * as one kernel in which each has a run of workgroups.  The plan's inputs and outputs are those of the groups taken, in the order given; no output may be
- * another's input (the caller packs groups that do not depend on each other), none may share a buffer with an input.
+/* Several independent groups as one launch (kernel packing, Section 5.1): of the given groups, those that a generated
+ * register row kernel without column reductions or dots takes (also where fs_plan_create has a hand-written or an
+ * elementwise kernel for them), that move at most 64 MB each and have no recorded tuning options, as one kernel in which
+ * each has a run of workgroups.  The plan's inputs and outputs are those of the groups taken, in the order given; no
+ * output may be another's input (the caller packs groups that do not depend on each other), none may share a buffer
+ * with an input.
  *   groups, n_ops  host arrays of n_groups op lists and their lengths (borrowed for the call only)
  *   taken          host, n_groups entries out: 1 for a group the plan runs, 0 for one it leaves out
  * Errors: FS_ERR_INVALID (malformed list or argument), FS_ERR_UNSUPPORTED (fewer than two groups can share a launch),

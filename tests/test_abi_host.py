@@ -462,6 +462,12 @@ def test_packed_row_groups_on_the_host():
         with pytest.raises(FsError) as e:
             Plan.packed(bad)
         assert e.value.status == binding.FS_ERR_INVALID
+    # groups that have a hand-written or an elementwise kernel of their own are taken, those with a dot of any kind are not
+    lists = [binding.marshal_ops(o) for o in (graphs.layernorm_fwd(30, 768), graphs.scaled_masked_softmax((1, 2, 30, 30)), graphs.bias_gelu_residual(8, 64, "f32"),
+                                              graphs.multi_interest_pattern(5), graphs.attention_block(3, 16, 16, 32))]
+    plan, taken = Plan.packed(lists)
+    with plan:
+        assert taken == [0, 1, 2]
     # sixteen outputs at most: the rest is left out
     plan, taken = Plan.packed([binding.marshal_ops(graphs.log_softmax((2, 512)))] * 20)
     with plan:

@@ -312,6 +312,28 @@ def test_independent_row_groups_in_one_launch():
             assert_close(a.to(torch.float64).cpu().numpy(), b, tol, f"packed group {k}")
 
 
+def test_packed_parts_that_have_kernels_of_their_own():
+    """Groups that fs_plan_create gives a hand-written or an elementwise kernel, as parts of one launch of generated code."""
+    announce("packed groups with hand-written and elementwise kernels of their own")
+    cases = [(graphs.layernorm_fwd(203, 768), inputs.layernorm_fwd(203, 768)),
+             (graphs.layernorm_fwd(37, 333, "f16"), inputs.layernorm_fwd(37, 333, "f16")),
+             (graphs.layernorm_fwd(5, 4096, "bf16"), inputs.layernorm_fwd(5, 4096, "bf16")),              # a row per team
+             (graphs.scaled_masked_softmax((2, 3, 40, 40), 0.125, "key_padding"), inputs.scaled_masked_softmax((2, 3, 40, 40), "key_padding")),
+             (graphs.scaled_masked_softmax((130, 197), 0.125, "full", "f16"), inputs.scaled_masked_softmax((130, 197), "full", "f16")),
+             (graphs.bias_gelu_residual_layernorm(65, 999), inputs.bias_gelu_residual_layernorm(65, 999)),
+             (graphs.bias_gelu_residual(33, 520, "f32"), inputs.normal_tensors([(33, 520), (520,), (33, 520)]))]
+    plan, taken = Plan.packed([binding.marshal_ops(ops) for ops, _ in cases])
+    assert taken == list(range(len(cases))) and plan.info()["n_kernels"] == 1
+    ins = [t for ops, x in cases for t in to_device(ops, x)]
+    outs = [alloc_outputs(ops) for ops, _ in cases]
+    with plan:
+        plan.launch(ins, [t for o in outs for t in o])
+        torch.cuda.synchronize()
+    for k, got in enumerate(outs):
+        for a, b in zip(got, interp.run(*cases[k])):
+            assert_close(a.to(torch.float64).cpu().numpy(), b, TOLERANCE[group_dtype(cases[k][0])], f"packed group {k}")
+
+
 @pytest.mark.parametrize("shapes", [[(64, 96), (96,), (96, 64), (64,)], [(300, 999), (999,), (5, 7), (1,)] * 3, [(33, 5000), (9000,)]])
 def test_clipping_takes_as_few_launches_whatever_the_number_of_tensors(shapes):
     announce(f"packed clipping {shapes[:4]} x{len(shapes)}")
