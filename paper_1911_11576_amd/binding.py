@@ -503,12 +503,20 @@ class FusedProgram:
         self.fusion = fusion if fusion is not None else FusionPlan(self.ops, **fusion_options)
         self.param_ops = [i for i, op in enumerate(self.ops) if op.kind == "parameter"]
         self.output_ops = [i for i, op in enumerate(self.ops) if op.kind == "output"]
-        self.plans = [None] * len(self.fusion.groups)       # per group; None: the group runs in a packed launch
+        self._plans = [None] * len(self.fusion.groups)      # per group; None: not built, the group runs in a packed launch
         self._units = self._pack()
         for plan, members in self._units:
             if plan is None:
-                self.plans[members[0]] = self._group_plan(members[0])
+                self._plans[members[0]] = self._group_plan(members[0])
         self._count_kernels()
+
+    @property
+    def plans(self):
+        """Every group's own plan, in execution order.  That of a group that runs in a packed launch is built when it is asked for."""
+        for k, plan in enumerate(self._plans):
+            if plan is None:
+                self._plans[k] = self._group_plan(k)
+        return self._plans
 
     def _group_plan(self, k):
         try:
@@ -544,7 +552,7 @@ class FusedProgram:
         return units
 
     def _count_kernels(self):
-        self.n_kernels = sum((plan or self.plans[members[0]]).info()["n_kernels"] for plan, members in self._units)
+        self.n_kernels = sum((plan or self._plans[members[0]]).info()["n_kernels"] for plan, members in self._units)
 
     def _unit_args(self, values, members, device):
         """Inputs and freshly allocated outputs of a launch's groups, in order."""
@@ -564,7 +572,7 @@ class FusedProgram:
         values = {i: t for i, t in zip(self.param_ops, inputs)}
         for plan, members in self._units:
             gin, gout = self._unit_args(values, members, None)
-            (plan or self.plans[members[0]]).launch(gin, gout, stream)
+            (plan or self._plans[members[0]]).launch(gin, gout, stream)
         return [values[self.ops[i].operands[0]] for i in self.output_ops]
 
     @classmethod
@@ -646,12 +654,11 @@ class FusedProgram:
         execution order) and keep the winners; every group is then a launch of its own.  -> the program's
         outputs, as run() would return them."""
         torch = self._torch
+        plans = self.plans
         for plan, members in self._units:
             if plan is not None:
-                for k in members:
-                    self.plans[k] = self._group_plan(k)
                 plan.close()
-        self._units = [(None, [k]) for k in range(len(self.plans))]
+        self._units = [(None, [k]) for k in range(len(plans))]
         dt = {"f32": torch.float32, "f16": torch.float16, "bf16": torch.bfloat16}
         values = {i: t for i, t in zip(self.param_ops, inputs)}
         for k, g in enumerate(self.fusion.groups):
@@ -661,12 +668,12 @@ class FusedProgram:
                 op = self.ops[i]
                 values[i] = torch.empty(op.shape, dtype=dt[op.dtype], device=gin[0].device if gin else "cuda:0")
                 gout.append(values[i])
-            if self.plans[k].info()["schedule"] == "per_op":
-                self.plans[k].launch(gin, gout)
+            if plans[k].info()["schedule"] == "per_op":
+                plans[k].launch(gin, gout)
                 continue
             tuned = Plan.tune(g["ops"], gin, gout, trials=trials)      # leaves the group's outputs written
-            self.plans[k].close()
-            self.plans[k] = tuned
+            plans[k].close()
+            plans[k] = tuned
         self._count_kernels()
         return [values[self.ops[i].operands[0]] for i in self.output_ops]
 
@@ -679,7 +686,7 @@ class FusedProgram:
         self._bound = []
         for plan, members in self._units:
             gin, gout = self._unit_args(values, members, device)
-            self._bound.append((plan or self.plans[members[0]], BoundArgs(gin, gout)))
+            self._bound.append((plan or self._plans[members[0]], BoundArgs(gin, gout)))
         self._bound_outputs = [values[self.ops[i].operands[0]] for i in self.output_ops]
         return self._bound_outputs
 
@@ -704,10 +711,10 @@ class FusedProgram:
         return graph, outs
 
     def close(self):
-        for p in self.plans + [plan for plan, _ in self._units]:
+        for p in self._plans + [plan for plan, _ in self._units]:
             if p is not None:
                 p.close()
-        self.plans, self._units = [], []
+        self._plans, self._units = [], []
         self._bound = []
 
     def __enter__(self):

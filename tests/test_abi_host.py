@@ -474,6 +474,18 @@ def test_packed_row_groups_on_the_host():
         assert taken == list(range(16))
 
 
+def test_a_program_has_a_plan_for_every_group():
+    from paper_1911_11576_amd import FusedProgram
+    with FusedProgram(graphs.clip_by_global_norm([(30, 1024), (1024,), (7, 3, 50)], 1.0)) as prog:
+        n = prog.n_kernels
+        assert n < len(prog.fusion.groups) == len(prog.plans)
+        for plan, group in zip(prog.plans, prog.fusion.groups):
+            with Plan(group["ops"]) as alone:
+                assert plan.describe() == alone.describe()
+        assert prog.n_kernels == n and prog.plans[0] is prog.plans[0]
+    assert prog.plans == []
+
+
 def test_tuned_groups_are_not_packed(tmp_path):
     """Recorded options are those of the group's own plan: it keeps that plan, in a program built later too."""
     from paper_1911_11576_amd import FusedProgram, fs_group_key, fs_tune_cache_clear, fs_tune_cache_load
