@@ -608,8 +608,10 @@ class FusedProgram:
     def measured(cls, ops, top=12, trials=20, device="cuda:0", **fusion_options):
         """The hybrid scoring policy of Section 4.3.  Plan with the model's scores; build the plan's
         patterns and the `top` best other candidates, time each stitched and as one kernel per op on
-        buffers of the right shapes, and plan again with the measured savings in place of the model's
-        for those patterns.  -> (program, list of (pattern ops, model score, measured score))."""
+        buffers of the right shapes (`trials` launches recorded and replayed, the medians of seven replays), and
+        plan again with the measured savings in place of the model's for those patterns.  Groups are timed one by one: what
+        sharing launches saves beyond that is not in the scores.
+        -> (program, list of (pattern ops, model score, measured score))."""
         import torch
         ops = list(ops)
         dt = {"f32": torch.float32, "f16": torch.float16, "bf16": torch.bfloat16}
@@ -619,21 +621,33 @@ class FusedProgram:
         n_chosen = sum(1 for p in ranked if p["chosen"])
         picked = ranked[:n_chosen + top]
 
-        def launch(plan, gin, gout):
-            # arguments typed and marshalled anew for every launch: a launch's cost on the host is part of what a pattern is
-            # measured to save, and one launch less has to outweigh the scatter of the kernel times
-            _check(lib().fs_launch(plan._h, _pointers(gin), len(gin), _pointers(gout), len(gout), torch.cuda.current_stream().cuda_stream))
+        def replayed(plan, bound):
+            """`trials` launches of the plan, recorded after an ordinary one (kernel loaded, workspace allocated)."""
+            plan.launch_bound(bound, _current_stream())
+            torch.cuda.synchronize()
+            graph = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(graph, stream=torch.cuda.Stream()):
+                for _ in range(trials):
+                    plan.launch_bound(bound, _current_stream())
+            return graph
 
-        def timed(plan, gin, gout):
-            for _ in range(2):
-                launch(plan, gin, gout)
+        def timed(graph):
             e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
             e0.record()
-            for _ in range(trials):
-                launch(plan, gin, gout)
+            graph.replay()
             e1.record()
             torch.cuda.synchronize()
             return e0.elapsed_time(e1) * 1e3 / trials
+
+        def saving(apart, fused, bound):
+            # Kernels and the gaps between them, as the device runs them: a replayed graph, since the host's share of a launch (4 to
+            # 10 us on one machine within a minute, for one kernel or seventeen) would drown what patterns differ by.  Both in turn, medians.
+            graphs = [replayed(apart, bound), replayed(fused, bound)]
+            us = [[], []]
+            for _ in range(7):
+                for k, graph in enumerate(graphs):
+                    us[k].append(timed(graph))
+            return sorted(us[0])[3] - sorted(us[1])[3]
 
         report = []
         for p in picked:
@@ -641,7 +655,7 @@ class FusedProgram:
             gin = [torch.randn(sh, dtype=torch.float32, device=device).to(dt[d]) for sh, d in shapes]
             gout = [torch.empty(ops[i].shape, dtype=dt[ops[i].dtype], device=device) for i in p["output_of"]]
             with Plan(p["group_ops"]) as fused, Plan(p["group_ops"], "per_op") as apart:
-                saved = timed(apart, gin, gout) - timed(fused, gin, gout)
+                saved = saving(apart, fused, BoundArgs(gin, gout))
             report.append((p["ops"], p["score_us"], saved))
         kw = dict(fusion_options)
         extra = list(kw.pop("extra_patterns", None) or [])

@@ -156,6 +156,30 @@ def test_planning_with_measured_scores(name):
             assert_close(a.to(torch.float64).cpu().numpy(), b, TOLERANCE["f32"], f"measured planning {name}")
 
 
+def test_measured_savings_are_those_of_the_device(monkeypatch):
+    """What a pattern is measured to save does not depend on how long the host takes to launch."""
+    announce("measured planning, slow host")
+    import time
+    ops = graphs.encoder_tail(300, 1024, 6, 128)
+
+    def slow(f):
+        def call(*args):
+            end = time.perf_counter() + 3e-4
+            while time.perf_counter() < end:
+                pass
+            return f(*args)
+        return call
+
+    prog, report = FusedProgram.measured(ops, top=3)
+    prog.close()
+    monkeypatch.setattr(binding, "_pointers", slow(binding._pointers))
+    monkeypatch.setattr(Plan, "launch_bound", slow(Plan.launch_bound))
+    prog, slow_report = FusedProgram.measured(ops, top=3)
+    prog.close()
+    for (pat, _, saved), (slow_pat, _, slow_saved) in zip(report, slow_report):
+        assert pat == slow_pat and saved > 0 and 0.5 * saved < slow_saved < 2 * saved, (len(pat), saved, slow_saved)
+
+
 def test_fused_program_as_a_captured_graph():
     """The groups of a planned graph recorded into one HIP graph: replayed with new input values and
     eager work in between, every replay against the oracle; and timed against launching group by group."""
