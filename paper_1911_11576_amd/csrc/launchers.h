@@ -8,7 +8,7 @@
 
 namespace fs {
 
-struct RowLaunch { int variant = 0, K = 1, L = 64, U = 1, wg = 256, grid = 1; bool ragged = false, stream = true; int64_t lds_bytes = 0; };
+struct RowLaunch { int variant = 0, K = 1, L = 64, U = 1, wg = 256, grid = 1; bool ragged = false, late = false; int64_t lds_bytes = 0; };
 bool row_stitch_plan(const RowSpec&, const LaunchOpts&, RowLaunch*, std::string* err);
 std::string row_stitch_describe(const RowSpec&, const RowLaunch&);
 int row_stitch_launch(const RowSpec&, const RowLaunch&, const void* const* in, void* const* out,

@@ -58,7 +58,9 @@ bool row_stitch_plan(const RowSpec& sp, const LaunchOpts& opt, RowLaunch* out, s
   const bool mask_bcast = !(sp.mask_d1 == 1 && sp.mask_d2 == 1 && sp.mask_stride[0] == 1);
   rl.lds_bytes = rl.ragged ? (int64_t)waves * rl.U * G * sp.cols * dtype_size(sp.dtype) : 0;      // at most 8 rows of 8188 bytes
   rl.variant = sp.core == CORE_LAYERNORM ? (sp.gelu ? 1 : 0) : (sp.in_mask < 0 ? 2 : mask_bcast ? 4 : 3);
-  rl.stream = sp.rows * sp.cols * dtype_size(sp.dtype) * (2 + (sp.in_res >= 0) + (rl.variant == 3)) > kStreamBytes;
+  // up to sixteen wavefronts per CU start at once (measured: 4096 of them, both sides beside the kernel; 8192 are level for
+  // 32768 x 256 bf16, 7.7 us and 7.4, and ahead with the early request for 16384 x 512 fp32, 13.0 and 13.9)
+  rl.late = n_iters <= 16 * 256;
   *out = rl;
   return true;
 }

@@ -52,17 +52,10 @@ struct RowArgs {
 };
 
 // How a row fits the lane tile: exactly (cols == K*L*V: no masking), in whole vectors, or ragged (cols not a
-// multiple of V); the first two with nontemporal loads or (CACHED) ordinary ones
-enum RowFit : int { FIT_VECTORS = 0, FIT_EXACT = 1, FIT_RAGGED = 2, FIT_VECTORS_CACHED = 3, FIT_EXACT_CACHED = 4 };
+// multiple of V).  The first two of LayerNorm also with gamma and beta requested late (see row_stitch_kernel).
+enum RowFit : int { FIT_VECTORS = 0, FIT_EXACT = 1, FIT_RAGGED = 2, FIT_VECTORS_LATE = 3, FIT_EXACT_LATE = 4 };
 
 constexpr float kLog2e = 1.4426950408889634f;
-
-// Bytes a group moves up to which its inputs are loaded through the caches.  What a kernel before has just written
-// is still in the L2s and the memory-side cache then, and a nontemporal load does not find it as well: a
-// chain of a producer, LayerNorm and a consumer over 24 rotating buffer sets takes 32.3 us with nontemporal loads
-// and 29.7 with ordinary ones at 43 MB of LayerNorm's own, 40.6 and 39.2 at 65 MB, 43.3 and 43.5 at 100 MB, 65.6
-// and 68.4 at 134 MB; alone and cold there is no difference up to 134 MB.
-constexpr int64_t kStreamBytes = 64ll << 20;
 
 // 1 / sqrt(x) as the hardware's estimate and one Newton step: a correctly rounded square root and division take
 // some thirty instructions per row.  The estimate takes a subnormal argument for zero, so one is scaled by 2^24 first
@@ -80,17 +73,21 @@ __device__ __forceinline__ float rsqrt_newton(float x) {
 // VARIANT: 0 LayerNorm, 1 prologue(bias,GELU,residual)+LayerNorm, 2 softmax, 3 softmax with a
 // mask of the scores' shape, 4 softmax with a mask broadcast over leading dims
 // Bound by HBM, and for 16-bit rows nearly as much by instructions: a lane holds 16 elements and 64 / L rows share a
-// reduction's steps, only the last vector is masked, and gamma and beta come with the row.  Warm (three buffer
-// sets) LayerNorm over 16384 x 1024 bf16 takes 10.8 us (13.7 with a row per wavefront, every vector masked and a
-// correctly rounded 1 / sqrt), 16384 x 768 fp32 18.0 (19.1), 8192 x 999 fp32 11.3; softmax with a key-padding mask
-// over 75648 rows of 197 fp16 11.4 (46 with one element per access and the row in LDS).
+// reduction's steps, and only the last vector is masked.  From warm buffers (three sets) LayerNorm over 16384 x 1024 bf16 takes
+// 13.0 us (13.8 with a row per wavefront, every vector masked and a correctly rounded 1 / sqrt), 16384 x 768 fp32 18.2
+// (19.1), 4096 x 512 bf16 3.3 (3.9), but 16384 x 512 bf16 7.8 (7.4); softmax with a key-padding mask over 75648 rows of 197
+// fp16 11.4 (46 with one element per access and the row in LDS).
+// Whole vectors of the rows are loaded nontemporally at every size.  Ordinary loads are the faster ones only where the same
+// buffers were read a pass before (16384 x 1024 bf16 from three sets 11.2 us against 13.0); on buffers new to the pass they
+// are slower (13.8 against 13.0; 4096 x 1024 5.3 against 4.3), and behind a kernel that has just written x as well: producer, this kernel
+// and a consumer as a graph over new buffers 38.8 us against 36.7, 4096 x 1500 fp32 31.3 against 31.8, 512 x 1024 bf16 8.0 against 7.3.
 template <typename T, int VARIANT, int K, int L, int U, int FIT>
 __global__ __launch_bounds__(512) void row_stitch_kernel(const RowArgs a) {
   constexpr int V = Vec<T>::V;
   constexpr int G = 64 / L;
   constexpr bool kLN = VARIANT <= 1, kGelu = VARIANT == 1, kMask = VARIANT >= 3, kMaskBcast = VARIANT == 4;
-  constexpr bool EXACT = FIT == FIT_EXACT || FIT == FIT_EXACT_CACHED, RAGGED = FIT == FIT_RAGGED;
-  constexpr bool STREAM = FIT == FIT_EXACT || FIT == FIT_VECTORS;
+  constexpr bool EXACT = FIT == FIT_EXACT || FIT == FIT_EXACT_LATE, RAGGED = FIT == FIT_RAGGED;
+  constexpr bool LATE = kLN && (FIT == FIT_EXACT_LATE || FIT == FIT_VECTORS_LATE);
   const int lane = threadIdx.x & 63;
   const int sub = lane / L, l = lane % L;
   const int waves = blockDim.x >> 6;
@@ -114,9 +111,11 @@ __global__ __launch_bounds__(512) void row_stitch_kernel(const RowArgs a) {
 
   // per-column operands (cached loads, kept packed in their storage dtype); an absent
   // operand becomes its neutral element so the per-element code has no conditionals.
-  // The bias is needed first and is read up front; gamma and beta are requested right behind the
-  // row (one memory latency for all of them: requested where the epilogue needs them, they cost
-  // a second one), a one-shot grid visits one row group per wavefront, so nothing is read twice.
+  // The bias is needed first and is read up front.  gamma and beta are requested right behind the row, one memory
+  // latency for all of them, where wavefronts follow each other on a CU: LayerNorm over 16384 x 1024 fp32 24.6 -> 23.5 us
+  // against a request where the epilogue needs them, 16384 x 768 bf16 11.7 -> 10.7.  Where all wavefronts of a launch start at once (LATE), those
+  // requests of the first stand before the rows of the last: 4096 x 768 fp32 4.9 us requested late, 5.7 with the row,
+  // 4096 x 1024 bf16 4.4 and 5.0.  Nothing is read twice: a one-shot grid visits one row group per wavefront.
   constexpr uint32_t kOne = sizeof(T) == 4 ? 0x3F800000u : (Vec<T>::kOneBits | (Vec<T>::kOneBits << 16));
   u32x4 bia[K];
   if constexpr (kGelu) {
@@ -138,10 +137,6 @@ __global__ __launch_bounds__(512) void row_stitch_kernel(const RowArgs a) {
   // all HBM reads of one iteration: the row groups of x and of the second streamed operand
   // (`aux`: the residual, or the mask)
   auto load_groups = [&](int64_t it, u32x4 (&raw)[U][K], u32x4 (&aux)[U][K], int64_t (&row)[U], bool (&rok)[U]) {
-    auto load = [&](const T* p) {
-      if constexpr (STREAM) return stream_load16(p);
-      else return cached_load<T, !RAGGED>(p);
-    };
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int64_t r = (it * U + u) * G + sub;
@@ -149,7 +144,7 @@ __global__ __launch_bounds__(512) void row_stitch_kernel(const RowArgs a) {
       row[u] = rok[u] ? r : a.rows - 1;
 #pragma unroll
       for (int k = 0; k < K; ++k) {
-        raw[u][k] = load(x + row[u] * a.cols + voff[k]);
+        raw[u][k] = stream_load<T, !RAGGED>(x + row[u] * a.cols + voff[k]);
         aux[u][k] = u32x4{0u, 0u, 0u, 0u};
       }
     }
@@ -159,7 +154,7 @@ __global__ __launch_bounds__(512) void row_stitch_kernel(const RowArgs a) {
         for (int u = 0; u < U; ++u)
 #pragma unroll
           for (int k = 0; k < K; ++k)
-            aux[u][k] = load(static_cast<const T*>(a.res) + row[u] * a.cols + voff[k]);
+            aux[u][k] = stream_load<T, !RAGGED>(static_cast<const T*>(a.res) + row[u] * a.cols + voff[k]);
       }
     }
     if constexpr (kMask) {
@@ -173,10 +168,10 @@ __global__ __launch_bounds__(512) void row_stitch_kernel(const RowArgs a) {
           const uint32_t i0 = a.mask_d1.div(t), i1 = t - i0 * a.mask_d1.d;
           mrow = i0 * a.ms0 + i1 * a.ms1 + i2 * a.ms2;
         }
-        // a broadcast mask row is shared by many score rows: cached load
+        // a broadcast mask row is shared by many score rows: cached load; a full mask is touched once: streaming load
 #pragma unroll
         for (int k = 0; k < K; ++k)
-          aux[u][k] = kMaskBcast ? cached_load<T, !RAGGED>(mk + mrow * a.cols + voff[k]) : load(mk + mrow * a.cols + voff[k]);
+          aux[u][k] = kMaskBcast ? cached_load<T, !RAGGED>(mk + mrow * a.cols + voff[k]) : stream_load<T, !RAGGED>(mk + mrow * a.cols + voff[k]);
       }
     }
   };
@@ -192,7 +187,7 @@ __global__ __launch_bounds__(512) void row_stitch_kernel(const RowArgs a) {
     u32x4 raw[U][K], aux[U][K];
     load_groups(it, raw, aux, row, rok);
     u32x4 gam[kLN ? K : 1], bet[kLN ? K : 1];
-    if constexpr (kLN) {
+    auto load_gamma_beta = [&]() {
 #pragma unroll
       for (int k = 0; k < K; ++k) {
         gam[k] = u32x4{kOne, kOne, kOne, kOne};
@@ -200,7 +195,8 @@ __global__ __launch_bounds__(512) void row_stitch_kernel(const RowArgs a) {
         if (a.gamma) gam[k] = cached_load<T, !RAGGED>(static_cast<const T*>(a.gamma) + voff[k]);
         if (a.beta) bet[k] = cached_load<T, !RAGGED>(static_cast<const T*>(a.beta) + voff[k]);
       }
-    }
+    };
+    if constexpr (kLN && !LATE) load_gamma_beta();
 
     // ---- thread-composed prologue ---------------------------------------------------
     if constexpr (kGelu) {
@@ -276,6 +272,7 @@ __global__ __launch_bounds__(512) void row_stitch_kernel(const RowArgs a) {
             v[u][k][j] -= mean;
             q += counts(k, j) ? v[u][k][j] * v[u][k][j] : 0.f;
           }
+        if constexpr (LATE) load_gamma_beta();
         const float var = group_allreduce<SumOp, L>(q) * a.inv_n;
         const float rstd = rsqrt_newton(var + a.eps);
 #pragma unroll
@@ -340,8 +337,12 @@ hipError_t row_launch_fit(const RowArgs& a, int fit, int grid, int wg, hipStream
   switch (fit) {
     case FIT_EXACT: hipLaunchKernelGGL((row_stitch_kernel<T, VARIANT, K, L, U, FIT_EXACT>), dim3(grid), dim3(wg), lds, s, a); break;
     case FIT_VECTORS: hipLaunchKernelGGL((row_stitch_kernel<T, VARIANT, K, L, U, FIT_VECTORS>), dim3(grid), dim3(wg), lds, s, a); break;
-    case FIT_EXACT_CACHED: hipLaunchKernelGGL((row_stitch_kernel<T, VARIANT, K, L, U, FIT_EXACT_CACHED>), dim3(grid), dim3(wg), lds, s, a); break;
-    case FIT_VECTORS_CACHED: hipLaunchKernelGGL((row_stitch_kernel<T, VARIANT, K, L, U, FIT_VECTORS_CACHED>), dim3(grid), dim3(wg), lds, s, a); break;
+    case FIT_EXACT_LATE:
+      if constexpr (VARIANT <= 1) hipLaunchKernelGGL((row_stitch_kernel<T, VARIANT, K, L, U, FIT_EXACT_LATE>), dim3(grid), dim3(wg), lds, s, a);
+      break;
+    case FIT_VECTORS_LATE:
+      if constexpr (VARIANT <= 1) hipLaunchKernelGGL((row_stitch_kernel<T, VARIANT, K, L, U, FIT_VECTORS_LATE>), dim3(grid), dim3(wg), lds, s, a);
+      break;
     default: hipLaunchKernelGGL((row_stitch_kernel<T, VARIANT, K, L, U, FIT_RAGGED>), dim3(grid), dim3(wg), lds, s, a); break;
   }
   return hipGetLastError();
@@ -389,7 +390,7 @@ hipError_t row_launch_KL(const RowArgs& a, int K, int L, int U, int fit, int gri
 template <typename T>
 hipError_t row_launch_dtype(const RowArgs& a, const RowLaunch& rl, hipStream_t s) {
   const bool exact = a.nvec == rl.K * rl.L;
-  const int fit = rl.ragged ? FIT_RAGGED : rl.stream ? (exact ? FIT_EXACT : FIT_VECTORS) : exact ? FIT_EXACT_CACHED : FIT_VECTORS_CACHED;
+  const int fit = rl.ragged ? FIT_RAGGED : rl.late && rl.variant <= 1 ? (exact ? FIT_EXACT_LATE : FIT_VECTORS_LATE) : exact ? FIT_EXACT : FIT_VECTORS;
   switch (rl.variant) {
     case 0: return row_launch_KL<T, 0>(a, rl.K, rl.L, rl.U, fit, rl.grid, rl.wg, s);
     case 1: return row_launch_KL<T, 1>(a, rl.K, rl.L, rl.U, fit, rl.grid, rl.wg, s);

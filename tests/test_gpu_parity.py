@@ -181,6 +181,15 @@ def test_ragged_rows(dtype, rows, cols):
         assert np.array_equal(run_gpu(ops, ins, **opts)[0], ref[0]) or cols > 2048
 
 
+# more wavefronts than start at once (16 per CU): gamma and beta requested with the row, not late
+@pytest.mark.parametrize("dtype,rows,cols", [("f32", 4099, 1024), ("f32", 4097, 1000), ("f32", 16391, 200), ("bf16", 4099, 1024), ("f16", 4097, 1000), ("bf16", 33000, 136)])
+def test_layernorm_of_many_wavefronts(dtype, rows, cols):
+    announce(f"layernorm of many wavefronts {dtype} {rows}x{cols}")
+    check_against_oracle(graphs.layernorm_fwd(rows, cols, dtype), inputs.layernorm_fwd(rows, cols, dtype), what=f"ln {rows}x{cols}")
+    check_against_oracle(graphs.bias_gelu_residual_layernorm(rows, cols, dtype), inputs.bias_gelu_residual_layernorm(rows, cols, dtype), "prebuilt",
+                         what=f"cfg4 {rows}x{cols}")
+
+
 @pytest.mark.parametrize("rows,cols", [(3, 2052), (5, 5000), (4, 8192), (2, 32768), (3, 20480)])
 def test_layernorm_team_form_f32(rows, cols):
     announce(f"layernorm team form f32 {rows}x{cols}")
