@@ -134,8 +134,9 @@ typedef enum {
                             ([B, S, H] -> [B, H]: sequence pooling) */
   FS_SCHED_BDOT_SOFTMAX = 3, /* batched dot -> softmax -> batched dot on MFMA; the probabilities stay in
                                 registers (accumulators of the first dot = operands of the second), K and V
-                                go through LDS.  With one query per batch element and no causal mask: two
-                                matrix-vector products in a wavefront's registers */
+                                go through LDS.  With one query per batch element and no causal mask (but
+                                for 9 to 32 keys of head dim 32): two matrix-vector products in a wavefront's
+                                registers */
   FS_SCHED_ELEMENTWISE = 4,  /* any all-elementwise group: thread composition + packing, as
                                 a kernel generated for the group (or interpreted, see
                                 FS_MODE_STITCHED_PREBUILT).  The ops share one shape, or fall into

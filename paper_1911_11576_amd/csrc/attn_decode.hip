@@ -7,7 +7,11 @@
 // its share of the dot products is summed over the CH lanes of a key, after which those lanes hold the scores
 // of just the keys whose V chunks they read: the weights need no exchange either, only the D sums at the end do.
 // All K requests of the element are in flight before the first use, V's behind them (or, where the registers do not
-// hold both, each in the place of a K chunk that has been used).
+// hold both, each in the place of a K chunk that has been used).  The compiler sinks requests towards their uses to
+// save registers, which costs a second and a third memory latency: scheduling barriers hold them (HOLD).  From cold buffers,
+// bf16: 512 elements x 64 keys x 64 4.9 -> 4.1 us, 128 x 77 x 128 5.5 -> 4.8, 4096 x 33 x 64 8.6 -> 8.0.  Not in launches of more than 32
+// MB of whole tiles and 32 requests or more per wavefront, where other wavefronts hide what the registers cost: 4096 x 128 x 64
+// 22.3 us, 23.2 held.
 // Measured, 4096 elements x 128 keys x 64 fp16: 21.5 us, 6.3 TB/s (26.0 on a matrix-unit tile with K and V in LDS);
 // 8192 x 128 x 32: 20.5 (38.8); 2048 x 77 x 128 bf16 with a key mask: 14.4 (30.5).
 #include "attn_stitch_impl.h"
@@ -32,6 +36,7 @@ template <typename T, int D, int NT, bool X, bool E, bool STREAM>
 __global__ __launch_bounds__(256) void attn_decode_kernel(const AttnArgs a) {
   constexpr int CH = D / 8, KPR = 64 / CH, NR = NT * 16 / KPR;      // chunks per key, keys per round of the wavefront, rounds
   constexpr bool BOTH = NR <= 16;                                   // K and V in registers at once
+  constexpr bool HOLD = !(STREAM && E && !X && NR >= 16);
   const int lane = threadIdx.x & 63;
   const int b = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)));
   if (b >= a.batch) return;
@@ -66,6 +71,7 @@ __global__ __launch_bounds__(256) void attn_decode_kernel(const AttnArgs a) {
     if (a.res) rs = *reinterpret_cast<const u32x4*>(static_cast<const uint16_t*>(a.res) + row);
   }
   asm volatile("" ::: "memory");     // the requests above stay above
+  if constexpr (HOLD) __builtin_amdgcn_sched_barrier(0);
 
   // ---- scores, in units of log 2, of the keys the lane reads
   constexpr float kLog2e = 1.4426950408889634f, kLn2 = 0.6931471805599453f;
@@ -78,7 +84,10 @@ __global__ __launch_bounds__(256) void attn_decode_kernel(const AttnArgs a) {
     Vec<T>::unpack(kr[r], k);
 #pragma unroll
     for (int j = 0; j < 8; ++j) t = fmaf(q[j], k[j], t);
-    if constexpr (!BOTH) vr[r] = read(vb, r);
+    if constexpr (!BOTH) {
+      vr[r] = read(vb, r);
+      if constexpr (HOLD) __builtin_amdgcn_sched_barrier(0);
+    }
     float z = group_allreduce<SumOp, CH>(t) * sc2;
     if constexpr (X) if (a.mask) z = fmaf(mk[r], kLog2e, z);
     if (!E && key_of(r) >= sk) z = -INFINITY;
@@ -147,7 +156,9 @@ template <typename T, int D>
 hipError_t decode_launch_keys(const AttnArgs& a, int grid, int wg, hipStream_t s) {
   switch ((a.sk + 15) / 16) {
     case 1: return decode_launch_one<T, D, 1>(a, grid, wg, s);
-    case 2: return decode_launch_one<T, D, 2>(a, grid, wg, s);
+    case 2:
+      if constexpr (D > 32) return decode_launch_one<T, D, 2>(a, grid, wg, s);      // (of 32: the matrix-unit tile)
+      return hipErrorInvalidValue;
     case 3: return decode_launch_one<T, D, 3>(a, grid, wg, s);
     case 4: return decode_launch_one<T, D, 4>(a, grid, wg, s);
     case 5: return decode_launch_one<T, D, 5>(a, grid, wg, s);

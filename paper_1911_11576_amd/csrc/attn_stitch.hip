@@ -25,8 +25,10 @@ bool attn_stitch_plan(const AttnSpec& sp, const LaunchOpts& opt, AttnLaunch* out
   l.wg = 64 * l.nq;
   if (opt.wg_size && opt.wg_size != l.wg) { *err = "attention schedule: wg_size is fixed at 64 per 16 query rows"; *status = FS_ERR_INVALID; return false; }
   l.grid = (int)sp.batch;
-  if (sp.sq == 1 && !sp.causal) {
-    // one query: matrix-vector products, a wavefront per batch element (attn_decode.hip); up to four to a workgroup
+  if (sp.sq == 1 && !sp.causal && !(sp.dim == 32 && sp.sk > 8 && sp.sk <= 32)) {
+    // one query: matrix-vector products, a wavefront per batch element (attn_decode.hip).  9 to 32 keys of 32 stay on the
+    // matrix-unit tile: level from warm buffers, 4 to 10 % ahead from cold ones (4096 x 20 x 32 bf16 4.4 us against 4.8,
+    // 8192 x 16 x 32 5.5 against 6.0).  Up to four wavefronts to a workgroup
     // where that leaves four workgroups for every CU (512 elements of 128 keys of 64 fp16: 5.3 us with one each, 7.0
     // with four on half of the CUs), and one if the caller names the workgroup of a single query tile
     l.decode = true;

@@ -157,27 +157,28 @@ def test_planning_with_measured_scores(name):
 
 
 def test_measured_savings_are_those_of_the_device(monkeypatch):
-    """What a pattern is measured to save does not depend on how long the host takes to launch."""
-    announce("measured planning, slow host")
+    """What a pattern is measured to save does not depend on how steadily the host launches."""
+    announce("measured planning, unsteady host")
     import time
     ops = graphs.encoder_tail(300, 1024, 6, 128)
+    calls = [0]
 
-    def slow(f):
+    def unsteady(f):                       # every 13th call takes 5 ms more: up to 250 us per launch of a block of 20
         def call(*args):
-            end = time.perf_counter() + 3e-4
-            while time.perf_counter() < end:
-                pass
+            calls[0] += 1
+            if calls[0] % 13 == 0:
+                time.sleep(5e-3)
             return f(*args)
         return call
 
     prog, report = FusedProgram.measured(ops, top=3)
     prog.close()
-    monkeypatch.setattr(binding, "_pointers", slow(binding._pointers))
-    monkeypatch.setattr(Plan, "launch_bound", slow(Plan.launch_bound))
-    prog, slow_report = FusedProgram.measured(ops, top=3)
+    monkeypatch.setattr(binding, "_pointers", unsteady(binding._pointers))
+    monkeypatch.setattr(Plan, "launch_bound", unsteady(Plan.launch_bound))
+    prog, again = FusedProgram.measured(ops, top=3)
     prog.close()
-    for (pat, _, saved), (slow_pat, _, slow_saved) in zip(report, slow_report):
-        assert pat == slow_pat and saved > 0 and 0.5 * saved < slow_saved < 2 * saved, (len(pat), saved, slow_saved)
+    for (pat, _, saved), (same, _, saved_again) in zip(report, again):
+        assert pat == same and saved > 0 and 0.5 * saved < saved_again < 2 * saved, (len(pat), saved, saved_again)
 
 
 def test_fused_program_as_a_captured_graph():
