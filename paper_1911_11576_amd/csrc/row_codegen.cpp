@@ -742,10 +742,17 @@ int chunk_elements(const Analysis& A, bool* fast) {
 // Measured, single elements against ragged chunks: LayerNorm over 32768 rows of 333 fp16 8.3 against 8.9 us, 94 fp32
 // columns (the motivating pattern) 47 against 52; 8192 x 999 fp32 12.1 against 11.0, 8192 x 2047 bf16 14.1 against
 // 12.4, 4096 x 3001 fp32 22.2 against 16.3, LayerNorm backward over 4096 x 3001 40.8 against 35.1.  So from 512 on.
-// Neighbouring rows share lines: ragged chunks are loaded through the caches (that last figure is 40.4 with
+// With column reductions a row of up to 2048 elements takes them from 2048 rows on: LayerNorm backward over 1024 x 999 12.7 us
+// with ragged chunks, 12.3 with single elements, 256 x 639 8.6 and 7.8, 256 x 1999 14.5 and 13.5; 2048 x 999 14.4 and 14.4 (15.1
+// and 15.8 from cold buffers), 8192 x 999 23.4 and 26.0.  Sums per run of rows the other way round, up to 8192 rows: pooling of 64
+// runs of 32 x 1023 11.2 with ragged chunks, 11.9 with single elements, 16 of 50 x 1023 9.2 and 9.4 (10.4 and 13.1 from cold
+// buffers); 300 of 37 x 1023 27.3 and 26.2, 1024 of 20 x 513 12.1 and 11.0.  Longer rows are a team's: LayerNorm backward over
+// 256 x 3001 12.6 and 24.0.
+// Neighbouring rows share lines: ragged chunks are loaded through the caches (4096 x 3001 35.1, 40.4 with
 // nontemporal loads).
-constexpr int64_t kRaggedCols = 512;
+constexpr int64_t kRaggedCols = 512, kRaggedColumnRows = 2048, kRaggedRunRows = 8192;
 int ragged_chunk_elements(const Analysis& A) {
+  if (A.n_col > 0 && A.cols <= 2048 && (A.seg_rows > 0 ? A.rows >= kRaggedRunRows : A.rows < kRaggedColumnRows)) return 0;
   bool any32 = false;
   for (const RView& v : A.views) {
     if (v.cls != CLS_FULL) continue;

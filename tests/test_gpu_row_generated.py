@@ -9,7 +9,7 @@ import torch
 
 from oracle import interp
 from paper_1911_11576_amd import FsError, Plan, binding
-from workloads import BY_NAME, graphs, inputs
+from workloads import BY_NAME, TOLERANCE, graphs, inputs
 
 from gpu_util import alloc_outputs, assert_close, check_against_oracle, run_gpu, to_device
 
@@ -392,6 +392,21 @@ def test_ragged_rows_generated(rows, cols):
             torch.cuda.synchronize()
         for got, want in zip(outs, interp.run(ops, ins)):
             assert_close(got.to(torch.float64).cpu().numpy(), want, 1e-5, "in place")
+
+
+@pytest.mark.parametrize("rows,cols", [(2047, 999), (2048, 999), (2050, 513), (2049, 2047), (2300, 1025)])
+def test_column_reductions_over_many_ragged_rows(rows, cols):
+    """Both sides of the line from which rows of no vector width take 16-byte chunks beside column sums, and the edges of the lane tiles beyond it."""
+    announce(f"column reductions over ragged rows {rows}x{cols}")
+    check_against_oracle(graphs.layernorm_bwd(rows, cols), inputs.layernorm_bwd(rows, cols), "generated", what="LN backward")
+    for dtype in ("f32", "bf16"):
+        ops, ins = graphs.bias_gelu_bwd(rows, cols, dtype), inputs.normal_tensors([(rows, cols), (rows, cols), (cols,)], dtype)
+        got, want = run_gpu(ops, ins), interp.run(ops, ins)
+        assert_close(got[0], want[0], TOLERANCE[dtype], f"bias+GELU backward {dtype}, full output")
+        # a term of a column's sum is an fp32 chain of some ten roundings beside dy, 2^-22 of |dy| on average at most
+        assert_close(got[1], want[1], TOLERANCE[dtype], f"bias+GELU backward {dtype}, column sums", slack=2.0 ** -22 * np.abs(ins[0]).sum(axis=0))
+    for shape in ((23, rows // 23, cols), (91, 91, 513)):                                    # ... and per run of rows, both sides of its line
+        check_against_oracle(graphs.sequence_pool(shape, pool="both"), inputs.normal_tensors([shape]), what="pooled")
 
 
 # rows beyond the register templates: register-resident in a full workgroup (up to 88 live elements per thread), or streamed; of any length
