@@ -222,8 +222,9 @@ bool row_team_plan(const RowSpec& sp, const LaunchOpts& opt, RowTeamLaunch* out,
       if (nvec <= (int64_t)wv * 64 * (16 / V)) waves = wv;
     // ... of any size where that power of two would leave more than three lanes in ten without work:
     // LayerNorm over 4096 rows of 5003 bf16 21.8 -> 16.8 us, of 5000 18.9 -> 17.7, softmax over 4096 of 4099 fp16 16.2 -> 14.2
-    // (where it does not, the power of two is the faster one by 1 to 2 %: 2048 x 5120 fp32, 4096 x 6000 bf16)
-    if (waves) {
+    // (where it does not, the power of two is the faster one by 1 to 2 %: 2048 x 5120 fp32, 4096 x 6000 bf16; and where whole
+    // vectors leave a CU no third team the wider one is: 256 x 5000 bf16 4.0 against 4.2, 600 x 5000 5.1 against 5.0)
+    if (waves && (l.ragged || sp.rows > 512)) {
       const int64_t chunks = (nvec + waves * 64 - 1) / (waves * 64);
       if (nvec * 10 < chunks * waves * 64 * 7)
         for (int wv = waves / 2 + 1; wv < waves; ++wv)

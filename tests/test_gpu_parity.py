@@ -226,6 +226,17 @@ def test_softmax_team_form(shape, mask):
                          inputs.scaled_masked_softmax(shape, mask), what=f"softmax team {shape} {mask}")
 
 
+@pytest.mark.parametrize("rows", [512, 513])
+def test_team_of_any_number_of_wavefronts(rows):
+    """Whole vectors: teams of a power of two up to 512 rows, beyond it of as many wavefronts as the row keeps busy."""
+    announce(f"team form, odd teams {rows}")
+    ops, ins = graphs.layernorm_fwd(rows, 5000, "bf16"), inputs.layernorm_fwd(rows, 5000, "bf16")
+    with Plan(ops) as plan:
+        assert ("cta_size=512" if rows == 512 else "cta_size=320") in plan.describe()
+    check_against_oracle(ops, ins, what=f"ln team {rows}x5000")
+    check_against_oracle(graphs.scaled_masked_softmax((rows, 4104), 0.125, "full", "f16"), inputs.scaled_masked_softmax((rows, 4104), "full", "f16"), what=f"softmax team {rows}x4104")
+
+
 def test_team_form_launch_options():
     announce("row team form options")
     ops, ins = graphs.layernorm_fwd(77, 8192), inputs.layernorm_fwd(77, 8192)
