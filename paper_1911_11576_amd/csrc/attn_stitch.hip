@@ -87,6 +87,13 @@ int attn_stitch_launch(const AttnSpec& sp, const AttnLaunch& l, const void* cons
   a.batch = (int)sp.batch; a.sq = (int)sp.sq; a.sk = (int)sp.sk; a.dim = (int)sp.dim;
   a.scale = sp.scale; a.fill = sp.fill; a.causal = sp.causal ? 1 : 0;
   a.skip_masked_tiles = sp.causal && sp.fill == -INFINITY;
+  // Nontemporal stores of O in groups of less than 128 MB, but not in the bare exact form (4096 x 64 x 64 x 64 fp16 from cold
+  // buffers 24.5 us with ordinary stores, 25.5 without).  From warm / cold buffers against ordinary stores, 64 wide, bf16: with every
+  // operand 512 x 100 x 100 10.3 / 11.3 (10.8 / 12.4), 1536 x 100 x 100 26.1 / 27.1 (27.6 / 27.7); with a key mask only 512 x 100 x 100
+  // 7.7 / 8.0 (8.2 / 9.0), 1536 x 128 x 128 24.3 / 27.5 (26.9 / 27.6), 4096 x 128 x 128 66.0 / 66.0 (65.0 / 64.9).  A kernel that reads O at once
+  // finds less of it in the caches: with a consumer 512 x 100 x 100 16.0 (16.3), 1536 x 100 x 100 37.8 (36.8), 4096 x 64 x 64
+  // with a key mask 41.5 (39.5).
+  a.stream_out = sp.batch * sp.dim * 2 * (sp.sq * (2 + (a.gate != nullptr) + (a.res != nullptr)) + 2 * sp.sk) < (128ll << 20);
   hipStream_t s = static_cast<hipStream_t>(stream);
   const hipError_t e = l.decode ? attn_decode_launch(a, sp.dtype == DT_F16, l.grid, l.wg, s) : sp.dtype == DT_F16 ? attn_launch_f16(a, l.nq, l.nk, s) : attn_launch_bf16(a, l.nq, l.nk, s);
   if (e != hipSuccess) { *err = std::string("attn_stitch launch: ") + hipGetErrorString(e); return -1; }

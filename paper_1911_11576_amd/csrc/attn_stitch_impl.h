@@ -46,6 +46,7 @@ struct AttnArgs {
   int batch, sq, sk, dim;
   float scale, fill;
   int causal, skip_masked_tiles, mask_vec;   // mask_vec: four mask values of a lane are one aligned 16-byte load
+  int stream_out;               // O leaves with nontemporal stores (not in the bare exact form, which has ordinary ones)
 };
 
 template <typename T> struct Mfma;
@@ -344,11 +345,17 @@ __global__ __launch_bounds__(64 * NQ) void attn_stitch_kernel(const AttnArgs a) 
       // odd rows of the first operand trade places with even rows of the second
       const auto r0 = __builtin_amdgcn_permlane16_swap(a0, b0, false, false);
       const auto r1 = __builtin_amdgcn_permlane16_swap(a1, b1, false, false);
-      // (nontemporal except in the bare exact form: 1536 x 100 x 100 x 64 bf16 with every operand 27.1 -> 25.3 us, and
-      // 27.5 -> 26.9 from cold buffers; 4096 x 64 x 64 x 64 fp16 from cold buffers 24.5 with ordinary stores, 25.5 so)
       const u32x4 w4 = {r0[0], r1[0], r0[1], r1[1]};
       if constexpr (E && !X) *reinterpret_cast<u32x4*>(orow + dp * 32) = w4;
-      else if (E || qi < sq) stream_store16(orow + dp * 32, w4);
+      else if (E || qi < sq) {
+        if (a.stream_out) {
+          stream_store16(orow + dp * 32, w4);
+        } else {
+          asm volatile("" ::: "memory");      // (these keep the two stores apart: merged, they lose the hint)
+          *reinterpret_cast<u32x4*>(orow + dp * 32) = w4;
+          asm volatile("" ::: "memory");
+        }
+      }
     }
   };
   if (active) {

@@ -382,6 +382,8 @@ ATTN_BLOCK_CASES = [
     (2, 128, 128, 128, "bf16", dict(causal=True, mask="full", gate=True, residual=True, lse=True)),   # maximum sizes
     (1, 1, 1, 32, "f16", dict(lse=True, gate=True)),                           # a single score
 ]
+# 128 MB and more: ordinary stores of the result
+ATTN_BLOCK_CASES += [(1320, 100, 100, 128, "bf16", dict(causal=True, mask="key")), (1030, 128, 128, 128, "f16", dict(gate=True))]
 # one query per batch element: every number of key tiles, whole and partial, every head dim, one wavefront to a workgroup
 DECODE_CASES = [(b, 1, sk, d, dt, kw) for b, sk, d, dt, kw in [
     (5, 1, 64, "f16", dict()), (3, 16, 32, "bf16", dict()), (6, 17, 128, "f16", dict()), (7, 31, 64, "bf16", dict(mask="key")), (9, 48, 128, "bf16", dict(mask="key", lse=True)),
