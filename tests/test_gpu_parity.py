@@ -178,7 +178,8 @@ def test_ragged_rows(dtype, rows, cols):
     ops, ins = graphs.scaled_masked_softmax(shape, 0.125, "key_padding", dtype), inputs.scaled_masked_softmax(shape, "key_padding", dtype)
     ref, _ = check_against_oracle(ops, ins, what=f"softmax ragged {shape}")
     for opts in (dict(grid=3), dict(wg_size=128), dict(rows_per_wave=4, grid=2)):       # several trips of the row loop, other tiles
-        assert np.array_equal(run_gpu(ops, ins, **opts)[0], ref[0]) or cols > 2048
+        got, _ = check_against_oracle(ops, ins, what=f"softmax ragged {shape} {opts}", **opts)
+        assert cols > 2048 or np.array_equal(got[0], ref[0])                             # (a team's size decides the order of its sums)
 
 
 # more wavefronts than start at once (16 per CU): gamma and beta requested with the row, not late

@@ -409,6 +409,19 @@ def test_column_reductions_over_many_ragged_rows(rows, cols):
         check_against_oracle(graphs.sequence_pool(shape, pool="both"), inputs.normal_tensors([shape]), what="pooled")
 
 
+# a team per row: sixteen rows to a workgroup below 256, down to four from there on within the bound on partial rows, sixteen
+# again where there are rows enough; ordinary loads, and nontemporal ones beyond 128 MB (3 x 2300 x 5000 fp32)
+@pytest.mark.parametrize("rows,cols,grid", [(255, 4096, 16), (256, 4096, 64), (257, 3001, 65), (300, 4096, 75), (1024, 2304, 227), (1030, 4096, 128), (2300, 5000, 144)])
+def test_column_reductions_over_team_rows(rows, cols, grid):
+    announce(f"column reductions over team rows {rows}x{cols}")
+    ops, ins = graphs.layernorm_bwd(rows, cols), inputs.layernorm_bwd(rows, cols)
+    with Plan(ops, "generated") as p:
+        assert p.info()["workspace_bytes"] == 2 * grid * cols * 8, p.describe()
+    check_against_oracle(ops, ins, "generated", what="LN backward")
+    if rows <= 300:
+        check_against_oracle(graphs.bias_gelu_bwd(rows, cols, "bf16"), inputs.normal_tensors([(rows, cols), (rows, cols), (cols,)], "bf16"), what="bias+GELU backward")
+
+
 # rows beyond the register templates: register-resident in a full workgroup (up to 88 live elements per thread), or streamed; of any length
 @pytest.mark.parametrize("rows,cols", [(5, 32769), (4, 36865), (9, 40001), (6, 45056), (5, 50257), (4, 65536), (7, 65537), (4, 90112), (4, 90113), (4, 100001),
                                        (3, 40001), (2, 131071)])
