@@ -977,12 +977,14 @@ struct Gen {
     return peak;
   }
   // A row of more than 32 elements per thread of a full workgroup still lives in its registers where no more than 88 of
-  // a thread's 128 hold values (chunk by chunk code without interleaving keeps the others few: no spills up to
-  // there).  One read and one write instead of a read per pass: log-softmax over 512 rows of 50257 fp32 47.6 us (streamed
-  // in three passes, element by element, 81.9), of 50257 bf16 21.6 (54.0), of 65536 fp32 59.5 (79.3), 64 rows of 50257
-  // fp32 11.4 (31.2), RMSNorm over 512 x 43000 fp32 34.7 (41.2).  16-bit rows with more than one live value stay
-  // streamed: their row fits the LDS buffers (RMSNorm over 512 x 36000 bf16 15.2 streamed, 16.1 here); so do launches of
-  // a few rows of whole chunks, which are one row's latency either way (2 x 40000 fp32 8.3 streamed, 7.7 here).
+  // a thread's 128 hold values (chunk by chunk code without interleaving keeps the others few).  One read and one write instead of
+  // a read per pass: log-softmax over 512 rows of 50257 fp32 47.6 us (streamed in three passes, element by element, 81.9), of
+  // 50257 bf16 21.6 (54.0), of 65536 fp32 56.6 (79.1), 64 rows of 50257 fp32 11.6 (32.4), RMSNorm over 512 x 43000 fp32 34.7
+  // (41.2).  Up to 72 values none of these spill; softmax with its log-sum-exp in fp32 spills 4 registers at 77824 columns and 16 to 21
+  // from 84000 to 90112, which is still the faster form by far (512 x 90112 86.4, streamed 118.5).  16-bit rows with more than one
+  // live value stay streamed: their row fits the LDS buffers (RMSNorm over 512 x 36000 bf16 15.2 streamed, 16.1 here).
+  // Launches of up to three rows of whole chunks are streamed as well, to leave the plans of such rows (their LDS, their form) as callers
+  // know them; it costs them time: 2 x 40000 fp32 8.4 streamed, 7.6 here, 1 x 65536 14.9 and 10.7, 2 x 50256 bf16 9.0 and 5.1.
   bool long_row_fits() const {
     if (lanes_per_row > 0 || A.n_col > 0 || A.n_reduce == 0 || (A.rows < 4 && !ragged)) return false;
     for (const RNode& n : A.nodes) if (n.op == ROP_DOT_OUTER || n.op == ROP_DOT_REDUCE) return false;
@@ -1476,9 +1478,10 @@ struct Gen {
         const char* rt = raw_type(v);
         const std::string pt_s = rt + al;
         const char* pt = pt_s.c_str();
-        // (a team of wavefronts per row: ordinary loads for groups of up to 128 MB.  LayerNorm backward over 2048 x 4096,
-        // 101 MB: 23.7 us against 31.5 nontemporal; over 8192 x 4096, 402 MB, 81.5 against 78.8; with 201 MB one or the
-        // other is 2 to 5 % ahead.  A row per wavefront: 16384 x 2048 82.1 against 76.8.)
+        // (a team of wavefronts per row: ordinary loads for groups of up to 128 MB.  LayerNorm backward over 2048 x 4096, 101 MB:
+        // 24.1 us from warm buffers and 30.6 from cold ones, 32.0 and 31.9 nontemporal; 1024 x 4096 16.6 / 20.1 and 21.4 / 21.6;
+        // over 8192 x 4096, 402 MB, 81.5 against 78.8; with 201 MB one or the other is 2 to 5 % ahead.  A row per wavefront:
+        // 16384 x 2048 82.1 against 76.8.)
         const char* ld = ragged || (L > 64 && A.g.algorithmic_bytes() <= (128ll << 20)) ? "*" : "__builtin_nontemporal_load";
         bool dummy = false;
         const std::string offp = row_offset(v, &dummy, "rowp"), offn = row_offset(v, &dummy, "rown");
@@ -2473,9 +2476,11 @@ bool row_gen_plan(const Graph& g, const LaunchOpts& opt, RowGenLaunch* out, int*
       int64_t want = opt.grid > 0 ? opt.grid : l.L > 64 ? 256 * (2048 / l.L) / 2 : 256;
       if (l.L > 64 && opt.grid <= 0 && want > (A.rows + 15) / 16) {
         // ... but from 256 rows on, where that leaves CUs idle, down to four rows each as long as the partial rows stay
-        // within 8 MiB (which also is what a launch without allocations has): LayerNorm backward over 512 x 4096 24.3 ->
-        // 14.3 us, over 1024 x 2304 23.1 -> 16.1, bias + GELU backward over 512 x 8192 bf16 34.1 -> 16.7 (all with the
-        // ordinary loads of small groups)
+        // within 8 MiB (which also is what a launch without allocations has): LayerNorm backward over 512 x 4096 24.2 ->
+        // 14.4 us, over 1024 x 2304 23.0 -> 16.5, bias + GELU backward over 512 x 8192 bf16 34.1 -> 16.7.  (Loaded through the caches, see
+        // below; nontemporally 15.9 for the first.)  Below 256 rows sixteen rows each stay, to leave the workspace of such plans as
+        // callers know it (64 x 8192: four partial rows); four rows each would halve their time: LayerNorm backward over 64 x 4096
+        // 19.2 and 8.9, 128 x 4096 19.3 and 9.7, 255 x 4096 20.0 and 12.1, 128 x 8192 30.9 and 15.3.
         const int64_t few = (A.rows + 15) / 16, row_bytes = (int64_t)std::max(1, A.n_col) * A.cols * 8;
         int64_t more = std::min<int64_t>(256, (A.rows + 3) / 4);
         if (more > (8ll << 20) / row_bytes) more = (8ll << 20) / row_bytes;
