@@ -83,13 +83,13 @@ template <int N> struct TileCount { static constexpr int value = N; };   // a co
 // X: the group has a mask, an epilogue operand or a second output (without any of them those paths
 // are compiled out: on the bare dot-softmax-dot group their run-time tests alone cost 0.15 us of 6);
 // E: the lengths are exactly 16 NQ queries and 16 NK keys (NK >= 2), so no row is clamped and no key
-// or query is tested against a length.
+// or query is tested against a length; S: O leaves with nontemporal stores.
 // With two wavefronts per SIMD and a memory phase of one round trip, the kernel's time follows its
 // instruction count: everything that is the same for a whole wavefront (its first query row, the
 // number of key tiles it needs, whether a tile touches the causal diagonal or the end of the keys)
 // is kept in scalar registers and decided by scalar branches, and only tiles that a mask can touch
 // pay for the comparisons.
-template <typename T, int NQ, int NK, int D, bool X, bool E>
+template <typename T, int NQ, int NK, int D, bool X, bool E, bool S>
 __global__ __launch_bounds__(64 * NQ) void attn_stitch_kernel(const AttnArgs a) {
   constexpr int KS = D / 32;                 // k-steps of the first dot
   constexpr int NKP = NK < 2 ? 2 : NK;       // key tiles padded to whole 32-key steps
@@ -346,16 +346,8 @@ __global__ __launch_bounds__(64 * NQ) void attn_stitch_kernel(const AttnArgs a) 
       const auto r0 = __builtin_amdgcn_permlane16_swap(a0, b0, false, false);
       const auto r1 = __builtin_amdgcn_permlane16_swap(a1, b1, false, false);
       const u32x4 w4 = {r0[0], r1[0], r0[1], r1[1]};
-      if constexpr (E && !X) *reinterpret_cast<u32x4*>(orow + dp * 32) = w4;
-      else if (E || qi < sq) {
-        if (a.stream_out) {
-          stream_store16(orow + dp * 32, w4);
-        } else {
-          asm volatile("" ::: "memory");      // (these keep the two stores apart: merged, they lose the hint)
-          *reinterpret_cast<u32x4*>(orow + dp * 32) = w4;
-          asm volatile("" ::: "memory");
-        }
-      }
+      if constexpr (S) { if (E || qi < sq) stream_store16(orow + dp * 32, w4); }
+      else if (E || qi < sq) *reinterpret_cast<u32x4*>(orow + dp * 32) = w4;
     }
   };
   if (active) {
@@ -379,34 +371,28 @@ inline int64_t attn_lds_bytes(int NK, int D) {
   return 2 * ((int64_t)NKP * 16 * VP + (int64_t)NK * 16 * (D + 8));
 }
 
+template <typename T, int NQ, int NK, int D, bool X, bool E, bool S>
+hipError_t attn_launch_form(const AttnArgs& a, hipStream_t s) {
+  const size_t lds = (size_t)attn_lds_bytes(NK, D);
+  if (lds > 64 * 1024) {     // more dynamic LDS than a kernel may use unasked
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(attn_stitch_kernel<T, NQ, NK, D, X, E, S>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL((attn_stitch_kernel<T, NQ, NK, D, X, E, S>), dim3(a.batch), dim3(64 * NQ), lds, s, a);
+  return hipGetLastError();
+}
+
 template <typename T, int NQ, int NK, int D>
 hipError_t attn_launch_one(const AttnArgs& a, hipStream_t s) {
   const bool extras = a.mask || a.gate || a.res || a.lse;
-  const bool exact = NK >= 2 && a.sq == 16 * NQ && a.sk == 16 * NK;
-  const dim3 grid(a.batch), wg(64 * NQ);
-  const size_t lds = (size_t)attn_lds_bytes(NK, D);
-  if (lds > 64 * 1024) {     // more dynamic LDS than a kernel may use unasked
-    const void* f = extras ? reinterpret_cast<const void*>(attn_stitch_kernel<T, NQ, NK, D, true, false>)
-                           : reinterpret_cast<const void*>(attn_stitch_kernel<T, NQ, NK, D, false, false>);
-    const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    if constexpr (NK >= 2) {
-      const void* fe = extras ? reinterpret_cast<const void*>(attn_stitch_kernel<T, NQ, NK, D, true, true>)
-                              : reinterpret_cast<const void*>(attn_stitch_kernel<T, NQ, NK, D, false, true>);
-      const hipError_t e2 = hipFuncSetAttribute(fe, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-      if (e2 != hipSuccess) return e2;
-    }
-  }
   if constexpr (NK >= 2) {
-    if (exact) {
-      if (extras) hipLaunchKernelGGL((attn_stitch_kernel<T, NQ, NK, D, true, true>), grid, wg, lds, s, a);
-      else hipLaunchKernelGGL((attn_stitch_kernel<T, NQ, NK, D, false, true>), grid, wg, lds, s, a);
-      return hipGetLastError();
+    if (a.sq == 16 * NQ && a.sk == 16 * NK) {
+      if (!extras) return attn_launch_form<T, NQ, NK, D, false, true, false>(a, s);
+      return a.stream_out ? attn_launch_form<T, NQ, NK, D, true, true, true>(a, s) : attn_launch_form<T, NQ, NK, D, true, true, false>(a, s);
     }
   }
-  if (extras) hipLaunchKernelGGL((attn_stitch_kernel<T, NQ, NK, D, true, false>), grid, wg, lds, s, a);
-  else hipLaunchKernelGGL((attn_stitch_kernel<T, NQ, NK, D, false, false>), grid, wg, lds, s, a);
-  return hipGetLastError();
+  if (extras) return a.stream_out ? attn_launch_form<T, NQ, NK, D, true, false, true>(a, s) : attn_launch_form<T, NQ, NK, D, true, false, false>(a, s);
+  return a.stream_out ? attn_launch_form<T, NQ, NK, D, false, false, true>(a, s) : attn_launch_form<T, NQ, NK, D, false, false, false>(a, s);
 }
 
 template <typename T, int NQ, int NK>
