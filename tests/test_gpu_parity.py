@@ -182,6 +182,15 @@ def test_ragged_rows(dtype, rows, cols):
         assert cols > 2048 or np.array_equal(got[0], ref[0])                             # (a team's size decides the order of its sums)
 
 
+@pytest.mark.parametrize("opts", [dict(wg_size=1024), dict(wg_size=576), dict(rows_per_wave=16), dict(wg_size=128, grid=2)], ids=str)
+@pytest.mark.parametrize("rows,cols", [(37, 11), (70, 333), (9, 2047)])
+def test_ragged_rows_under_options_of_other_forms(rows, cols, opts):
+    """Launch options that the wavefront form does not take (recorded for the block form, say): a team, most of it idle, or a row block."""
+    announce(f"ragged rows {rows}x{cols} {opts}")
+    check_against_oracle(graphs.layernorm_fwd(rows, cols, "f16"), inputs.layernorm_fwd(rows, cols, "f16"), what="ln", **opts)
+    check_against_oracle(graphs.scaled_masked_softmax((rows, cols), 0.125, "full"), inputs.scaled_masked_softmax((rows, cols), "full"), what="softmax", **opts)
+
+
 # more wavefronts than start at once (16 per CU): gamma and beta requested with the row, not late
 @pytest.mark.parametrize("dtype,rows,cols", [("f32", 4099, 1024), ("f32", 4097, 1000), ("f32", 16391, 200), ("bf16", 4099, 1024), ("f16", 4097, 1000), ("bf16", 33000, 136)])
 def test_layernorm_of_many_wavefronts(dtype, rows, cols):
