@@ -9,9 +9,9 @@
 // All K requests of the element are in flight before the first use, V's behind them (or, where the registers do not
 // hold both, each in the place of a K chunk that has been used).  The compiler sinks requests towards their uses to
 // save registers, which costs a second and a third memory latency: scheduling barriers hold them (HOLD).  From cold buffers,
-// bf16: 512 elements x 64 keys x 64 4.9 -> 4.1 us, 128 x 77 x 128 5.5 -> 4.8, 4096 x 33 x 64 8.6 -> 8.0.  Not in launches of more than 32
-// MB of whole tiles and 32 requests or more per wavefront, where other wavefronts hide what the registers cost: 4096 x 128 x 64
-// 22.3 us, 23.2 held.
+// bf16: 512 elements x 64 keys x 64 4.9 -> 4.1 us, 128 x 77 x 128 5.5 -> 4.8, 4096 x 33 x 64 8.6 -> 8.0.  Not in the nontemporal form of
+// whole tiles without operands and with 32 requests or more per wavefront, where other wavefronts hide what the registers
+// cost: 4096 x 128 x 64 22.3 us, 23.2 held.
 // Measured, 4096 elements x 128 keys x 64 fp16: 21.5 us, 6.3 TB/s (26.0 on a matrix-unit tile with K and V in LDS);
 // 8192 x 128 x 32: 20.5 (38.8); 2048 x 77 x 128 bf16 with a key mask: 14.4 (30.5).
 #include "attn_stitch_impl.h"
@@ -144,11 +144,12 @@ hipError_t decode_launch_form(const AttnArgs& a, int grid, int wg, hipStream_t s
   return hipGetLastError();
 }
 
-// K and V of up to 32 MB are loaded through the caches, where a step's own writes and the step before leave them: 512
-// elements of 128 keys of 64 fp16 5.3 us, 6.5 with nontemporal loads; 4096 of them 24.2, 21.5 with nontemporal loads.
+// K and V of up to 12 MB are loaded through the caches.  From warm / cold buffers, ordinary loads against nontemporal ones, bf16: 512
+// elements x 64 keys x 64 (8 MB) 2.8 / 4.1 us and 3.6 / 3.6, 512 x 77 x 64 (10 MB) 3.4 / 4.5 and 3.8 / 4.0; 512 x 128 x 64 (17 MB) 4.8 / 5.4
+// and 4.7 / 5.0, 1536 x 64 x 64 (25 MB) 6.1 / 6.8 and 5.5 / 6.1.
 template <typename T, int D, int NT>
 hipError_t decode_launch_one(const AttnArgs& a, int grid, int wg, hipStream_t s) {
-  if ((int64_t)a.batch * a.sk * D * 4 > (32ll << 20)) return decode_launch_form<T, D, NT, true>(a, grid, wg, s);
+  if ((int64_t)a.batch * a.sk * D * 4 > (12ll << 20)) return decode_launch_form<T, D, NT, true>(a, grid, wg, s);
   return decode_launch_form<T, D, NT, false>(a, grid, wg, s);
 }
 

@@ -401,12 +401,13 @@ DECODE_CASES = [(b, 1, sk, d, dt, kw) for b, sk, d, dt, kw in [
     (5, 90, 128, "f16", dict(gate=True, residual=True, lse=True)), (6, 112, 32, "bf16", dict(mask="key", gate=True, residual=True, lse=True)),
     (33, 127, 64, "f16", dict(mask="key")), (11, 128, 128, "f16", dict(mask="key")), (10, 128, 64, "bf16", dict()), (3, 127, 128, "bf16", dict(mask="full"))]]
 # ... both sides of the lines of the rule that picks the kernel; two and four wavefronts to a workgroup (from 2048 and 4096 elements on),
-# the last workgroup partly empty; K and V of more than 32 MB (nontemporal loads), whole and partial tiles, bare and with operands
+# the last workgroup partly empty; K and V of more than 12 MB (nontemporal loads), whole and partial tiles, bare and with operands
 DECODE_CASES += [(b, 1, sk, d, dt, kw) for b, sk, d, dt, kw in [
     (7, 8, 32, "f16", dict()), (7, 9, 32, "bf16", dict(mask="key")), (6, 32, 32, "f16", dict(mask="key", lse=True)), (6, 33, 32, "f16", dict(mask="key", lse=True)),
     (2047, 17, 64, "bf16", dict()), (2049, 40, 32, "bf16", dict(mask="key")), (4095, 5, 32, "f16", dict(gate=True)), (4099, 33, 32, "f16", dict()),
     (4099, 9, 128, "bf16", dict(mask="full", residual=True)), (4098, 16, 64, "f16", dict(lse=True)),
     (2049, 128, 64, "f16", dict()), (2050, 128, 64, "bf16", dict(mask="key")), (4099, 77, 64, "bf16", dict()), (4097, 77, 64, "f16", dict(mask="key", gate=True, residual=True, lse=True)),
+    (767, 64, 64, "f16", dict()), (769, 64, 64, "f16", dict()),                          # (12 MB lie between them)
     (1031, 128, 128, "bf16", dict()), (1030, 100, 128, "f16", dict(mask="shared", lse=True)), (1033, 70, 128, "bf16", dict()), (4100, 100, 32, "f16", dict(mask="key"))]]
 ATTN_BLOCK_CASES += DECODE_CASES
 
