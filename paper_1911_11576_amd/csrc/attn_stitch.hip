@@ -95,7 +95,10 @@ int attn_stitch_launch(const AttnSpec& sp, const AttnLaunch& l, const void* cons
   // with a key mask 41.5 (39.5).
   a.stream_out = sp.batch * sp.dim * 2 * (sp.sq * (2 + (a.gate != nullptr) + (a.res != nullptr)) + 2 * sp.sk) < (128ll << 20);
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const hipError_t e = l.decode ? attn_decode_launch(a, sp.dtype == DT_F16, l.grid, l.wg, s) : sp.dtype == DT_F16 ? attn_launch_f16(a, l.nq, l.nk, s) : attn_launch_bf16(a, l.nq, l.nk, s);
+  const bool f16 = sp.dtype == DT_F16;
+  const hipError_t e = l.decode ? attn_decode_launch(a, f16, l.grid, l.wg, s)
+                     : l.nq <= 2 ? (f16 ? attn_launch_f16 : attn_launch_bf16)(a, l.nq, l.nk, s)
+                                 : (f16 ? attn_launch_f16_wide : attn_launch_bf16_wide)(a, l.nq, l.nk, s);
   if (e != hipSuccess) { *err = std::string("attn_stitch launch: ") + hipGetErrorString(e); return -1; }
   return 0;
 }

@@ -414,18 +414,16 @@ hipError_t attn_launch_NK(const AttnArgs& a, int nk, hipStream_t s) {
   }
 }
 
-template <typename T>
-hipError_t attn_launch_dtype(const AttnArgs& a, int nq, int nk, hipStream_t s) {
-  switch (nq) {
-    case 1: return attn_launch_NK<T, 1>(a, nk, s);
-    case 2: return attn_launch_NK<T, 2>(a, nk, s);
-    case 4: return attn_launch_NK<T, 4>(a, nk, s);
-    default: return attn_launch_NK<T, 8>(a, nk, s);
-  }
+// one translation unit per dtype and pair of query tile counts
+template <typename T, int NQ0, int NQ1>
+hipError_t attn_launch_tiles(const AttnArgs& a, int nq, int nk, hipStream_t s) {
+  return nq == NQ0 ? attn_launch_NK<T, NQ0>(a, nk, s) : attn_launch_NK<T, NQ1>(a, nk, s);
 }
 
 hipError_t attn_decode_launch(const AttnArgs& a, bool f16, int grid, int wg, hipStream_t s);      // one query per batch element
-hipError_t attn_launch_f16(const AttnArgs& a, int nq, int nk, hipStream_t s);
+hipError_t attn_launch_f16(const AttnArgs& a, int nq, int nk, hipStream_t s);             // 1 or 2 query tiles
+hipError_t attn_launch_f16_wide(const AttnArgs& a, int nq, int nk, hipStream_t s);        // 4 or 8
 hipError_t attn_launch_bf16(const AttnArgs& a, int nq, int nk, hipStream_t s);
+hipError_t attn_launch_bf16_wide(const AttnArgs& a, int nq, int nk, hipStream_t s);
 
 }  // namespace fs
