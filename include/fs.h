@@ -142,13 +142,15 @@ typedef enum {
                                 FS_MODE_STITCHED_PREBUILT).  The ops share one shape, or fall into
                                 up to 16 parts that share no computed value, each of one shape
                                 (generated form only): one kernel, a run of workgroups per part */
-  FS_SCHED_BLOCK_DOT = 5     /* generated block composition around batched dots on MFMA (Sections 5.1, 5.3):
+  FS_SCHED_BLOCK_DOT = 5,    /* generated block composition around batched dots on MFMA (Sections 5.1, 5.3):
                                 a[B,M,K] . b, b stored [B,N,K] or [B,K,N] (16-bit, K 16..128, tile up to 128 x 128) -> any
                                 elementwise ops and row reductions on the tile -> optionally a second dot
                                 with v[B,N,D], its operand handed over through LDS -> optionally
                                 elementwise ops and row reductions on the [B,M,D] result (operands: such
                                 values, per-row values, constants, inputs seen as [B,M,D]);
                                 what the hand-written FS_SCHED_BDOT_SOFTMAX kernel does not match */
+  FS_SCHED_TWO_STEP = 6      /* two generated kernels (fs_plan_create_two_step): reductions over whole tensors, then the
+                                ops that read their results */
 } fs_schedule;
 
 /* Build a plan from a fusion group.
@@ -182,6 +184,18 @@ fs_status fs_plan_create(const fs_op_desc* ops, int32_t n_ops,
  * FS_ERR_NOMEM. */
 fs_status fs_plan_create_packed(const fs_op_desc* const* groups, const int32_t* n_ops, int32_t n_groups, uint8_t* taken,
                                 fs_plan** out);
+
+/* A group in which values reduced over whole tensors feed ops on whole tensors (clipping by a global norm), as two
+ * kernels: chains of reductions of one kind from elementwise ops on inputs down to rank 0, elementwise ops on those
+ * scalars, and elementwise ops on tensors of any number of shapes (up to 16 independent parts) that read the scalars
+ * through broadcasts; tensor operands of the tensors' own shapes, scalars in f32.  fs_plan_create takes no such group,
+ * and the planner cuts it.
+ *   partial_bytes  host, receives the size of the partial results that the first kernel hands to the second.  The
+ *                  caller gives fs_launch a device buffer of that size as ONE MORE OUTPUT, behind the group's own; nothing in
+ *                  it has to start at zero, and launches with buffers of their own may overlap in time.
+ * No output may share a buffer with an input.
+ * Errors: FS_ERR_INVALID, FS_ERR_UNSUPPORTED (not such a group), FS_ERR_NOMEM. */
+fs_status fs_plan_create_two_step(const fs_op_desc* ops, int32_t n_ops, int64_t* partial_bytes, fs_plan** out);
 
 /* Run the plan's kernel (Section 5.5: the generated kernel is handed to the run time, which launches it):
  * enqueue the group on `hip_stream` (a hipStream_t passed as void*, NULL = the default stream) and return
@@ -251,12 +265,14 @@ fs_status fs_plan_tune(const fs_op_desc* ops, int32_t n_ops,
  * after a header line.  All of it is host work and thread-safe.
  *   fs_group_key         key of a group (host out-pointer); FS_ERR_INVALID on a NULL or empty list
  *   fs_tune_cache_size   number of recorded groups
+ *   fs_tune_cache_has    1 if the group of that key is recorded
  *   fs_tune_cache_clear  forget them all
  *   fs_tune_cache_save   write the file (overwrites); FS_ERR_INVALID if it cannot be written
  *   fs_tune_cache_load   merge a file, later entries winning; FS_ERR_INVALID if it cannot be
  *                        read or a line is malformed (nothing is merged then) */
 fs_status fs_group_key(const fs_op_desc* ops, int32_t n_ops, uint64_t* key);
 int32_t fs_tune_cache_size(void);
+int32_t fs_tune_cache_has(uint64_t key);
 fs_status fs_tune_cache_clear(void);
 fs_status fs_tune_cache_save(const char* path);
 fs_status fs_tune_cache_load(const char* path);

@@ -10,6 +10,7 @@ from __future__ import annotations
 import ctypes as C
 import os
 from array import array
+from collections import namedtuple
 
 FS_MAX_RANK = 4
 LIB_PATH = os.environ.get("FS_LIB_PATH") or os.path.join(os.path.dirname(os.path.abspath(__file__)),
@@ -18,7 +19,7 @@ LIB_PATH = os.environ.get("FS_LIB_PATH") or os.path.join(os.path.dirname(os.path
 FS_OK, FS_ERR_INVALID, FS_ERR_UNSUPPORTED, FS_ERR_LDS, FS_ERR_HIP, FS_ERR_NOMEM = range(6)
 STATUS_NAMES = ["FS_OK", "FS_ERR_INVALID", "FS_ERR_UNSUPPORTED", "FS_ERR_LDS", "FS_ERR_HIP", "FS_ERR_NOMEM"]
 FS_MODE_STITCHED, FS_MODE_PER_OP, FS_MODE_STITCHED_PREBUILT, FS_MODE_STITCHED_GENERATED = 0, 1, 2, 3
-SCHEDULE_NAMES = ["per_op", "row", "row_col", "bdot_softmax", "elementwise", "block_dot"]
+SCHEDULE_NAMES = ["per_op", "row", "row_col", "bdot_softmax", "elementwise", "block_dot", "two_step"]
 
 DTYPES = {"f32": 0, "f16": 1, "bf16": 2}
 OPKINDS = {name: i for i, name in enumerate((
@@ -71,6 +72,8 @@ def lib():
         L.fs_plan_create.restype = i32
         L.fs_plan_create_packed.argtypes = [C.POINTER(C.POINTER(fs_op_desc)), C.POINTER(i32), i32, C.POINTER(C.c_uint8), C.POINTER(vp)]
         L.fs_plan_create_packed.restype = i32
+        L.fs_plan_create_two_step.argtypes = [C.POINTER(fs_op_desc), i32, C.POINTER(i64), C.POINTER(vp)]
+        L.fs_plan_create_two_step.restype = i32
         L.fs_launch.argtypes = [vp, C.POINTER(vp), i32, C.POINTER(vp), i32, vp]
         L.fs_launch.restype = i32
         L.fs_launch_static.argtypes = [vp, C.POINTER(vp), i32, C.POINTER(vp), i32, vp]
@@ -97,6 +100,8 @@ def lib():
         L.fs_kernel_cache_drop_memory.restype = i32
         L.fs_group_key.argtypes = [C.POINTER(fs_op_desc), i32, C.POINTER(C.c_uint64)]
         L.fs_group_key.restype = i32
+        L.fs_tune_cache_has.argtypes = [C.c_uint64]
+        L.fs_tune_cache_has.restype = i32
         L.fs_tune_cache_size.argtypes = []
         L.fs_tune_cache_size.restype = i32
         L.fs_tune_cache_clear.argtypes = []
@@ -182,6 +187,15 @@ def fs_plan_create_packed(groups):
     taken, out = (C.c_uint8 * max(1, n))(), C.c_void_p()
     _check(lib().fs_plan_create_packed(ptrs, sizes, n, taken, C.byref(out)))
     return out.value, [k for k in range(n) if taken[k]]
+
+
+def fs_plan_create_two_step(ops):
+    """A group in which values reduced over whole tensors feed ops on whole tensors -> (plan handle, bytes of the partial
+    results, for which the plan takes a buffer as one more output), or FsError with FS_ERR_UNSUPPORTED."""
+    arr = ops if isinstance(ops, C.Array) else marshal_ops(ops)
+    nbytes, out = C.c_int64(), C.c_void_p()
+    _check(lib().fs_plan_create_two_step(arr, len(arr), C.byref(nbytes), C.byref(out)))
+    return out.value, nbytes.value
 
 
 def _pointers(tensors):
@@ -306,6 +320,10 @@ def fs_group_key(ops):
     return key.value
 
 
+def fs_tune_cache_has(key):
+    return bool(lib().fs_tune_cache_has(key))
+
+
 def fs_tune_cache_size():
     return lib().fs_tune_cache_size()
 
@@ -357,6 +375,12 @@ class Plan:
         """Independent groups as one launch (fs_plan_create_packed) -> (plan, indices of the groups it runs)."""
         h, taken = fs_plan_create_packed(groups)
         return cls(None, _handle=h), taken
+
+    @classmethod
+    def two_step(cls, ops):
+        """fs_plan_create_two_step -> (plan, bytes of the buffer it takes as its last output)."""
+        h, nbytes = fs_plan_create_two_step(ops)
+        return cls(None, _handle=h), nbytes
 
     @classmethod
     def tune(cls, ops, inputs, outputs, stream=None, trials=20):
@@ -491,9 +515,16 @@ def describe_group_ops(arr):
     return out
 
 
+# A launch of a program: its plan (None: its one group's own), its groups, the values it reads and writes, the bytes of the buffer
+# that it takes as one more output (0: none)
+_Launch = namedtuple("_Launch", "plan members inputs outputs extra")
+_OpRecord = namedtuple("_OpRecord", "kind dtype shape operands axis attr")
+
+
 class FusedProgram:
-    """A whole computation graph run as the groups its fusion plan chose: one Plan per group, or one per
-    several small row groups that do not depend on each other, intermediates between groups in device
+    """A whole computation graph run as the groups its fusion plan chose: one Plan per group, one per
+    several small row groups that do not depend on each other, or one of two kernels for groups that pass scalars reduced
+    over whole tensors on to ops on whole tensors; intermediates between launches in device
     tensors.  Inputs: one tensor per parameter op of the original list, in order; outputs: one per output op."""
 
     def __init__(self, ops, fusion=None, **fusion_options):
@@ -503,20 +534,43 @@ class FusedProgram:
         self.fusion = fusion if fusion is not None else FusionPlan(self.ops, **fusion_options)
         self.param_ops = [i for i, op in enumerate(self.ops) if op.kind == "parameter"]
         self.output_ops = [i for i, op in enumerate(self.ops) if op.kind == "output"]
-        self._plans = [None] * len(self.fusion.groups)      # per group; None: not built, the group runs in a packed launch
-        self._units = self._pack()
-        for plan, members in self._units:
-            if plan is None:
-                self._plans[members[0]] = self._group_plan(members[0])
+        self._plans = [None] * len(self.fusion.groups)      # per group; None: not built, the group runs in a launch with others
+        self._packed_units = None
+        self._levels()
+        self._launches = self._pack(self._two_steps())
+        self._build_single_plans()
+
+    def _levels(self):
+        """made_by: the group that makes a value; level: the length of the longest chain of groups a group depends on."""
+        self._made_by, self._level = {}, []
+        for k, g in enumerate(self.fusion.groups):
+            self._level.append(1 + max((self._level[self._made_by[i]] for i in g["input_of"] if i in self._made_by), default=-1))
+            for i in g["output_of"]:
+                self._made_by[i] = k
+
+    def _build_single_plans(self):
+        for u in self._launches:
+            if u.plan is None and self._plans[u.members[0]] is None:
+                self._plans[u.members[0]] = self._group_plan(u.members[0])
         self._count_kernels()
 
     @property
     def plans(self):
-        """Every group's own plan, in execution order.  That of a group that runs in a packed launch is built when it is asked for."""
+        """Every group's own plan, in execution order.  That of a group that runs in a launch with others is built when it is asked for."""
         for k, plan in enumerate(self._plans):
             if plan is None:
                 self._plans[k] = self._group_plan(k)
         return self._plans
+
+    @property
+    def _units(self):
+        """The program as launches of groups and of packed groups: (packed plan or None, groups).  Where it has two-step plans instead,
+        built when it is asked for."""
+        if not any(u.extra for u in self._launches):
+            return [(u.plan, u.members) for u in self._launches]
+        if self._packed_units is None:
+            self._packed_units = [(u.plan, u.members) for u in self._pack([])]
+        return self._packed_units
 
     def _group_plan(self, k):
         try:
@@ -526,19 +580,75 @@ class FusedProgram:
                 raise
             return Plan(self.fusion.groups[k]["ops"], "per_op")   # an op left alone that no stitched schedule takes (a lone dot)
 
-    def _pack(self):
-        """The program's launches in order, as (packed plan or None, groups): groups sorted by the length of the
-        longest chain of groups they depend on, which leaves those of one level independent of each other;
-        of a level, what can share a launch does."""
-        groups = self.fusion.groups
-        made_by, level = {}, []
+    def _two_steps(self):
+        """Launches of two-step plans: a group that reads scalars other groups make, with all that makes them, where nothing else
+        reads what is made on the way.  A group with recorded tuning options keeps its own plan."""
+        groups, ops = self.fusion.groups, self.ops
+        used_by = {}
         for k, g in enumerate(groups):
-            level.append(1 + max((level[made_by[i]] for i in g["input_of"] if i in made_by), default=-1))
-            for i in g["output_of"]:
-                made_by[i] = k
-        units = []
-        for lv in range(max(level, default=-1) + 1):
-            left = [k for k in range(len(groups)) if level[k] == lv]
+            for i in g["input_of"]:
+                used_by.setdefault(i, set()).add(k)
+        returned = {ops[i].operands[0] for i in self.output_ops}
+        taken, launches = set(), []
+        for last, g in enumerate(groups):
+            made = [i for i in g["input_of"] if ops[i].shape == () and i in self._made_by]
+            members, stack = {last}, [self._made_by[i] for i in made]
+            while stack:
+                k = stack.pop()
+                if k not in members:
+                    members.add(k)
+                    stack += [self._made_by[i] for i in groups[k]["input_of"] if i in self._made_by]
+            if len(members) < 2 or members & taken:
+                continue
+            if any(used_by.get(i, set()) - members or i in returned for k in members - {last} for i in groups[k]["output_of"]):
+                continue
+            if any(fs_tune_cache_has(fs_group_key(groups[k]["ops"])) for k in members):
+                continue
+            outputs = list(g["output_of"])
+            inside, leaves, stack = set(), set(), list(outputs)
+            while stack:
+                i = stack.pop()
+                if i in inside or i in leaves:
+                    continue
+                if ops[i].kind == "parameter" or (i in self._made_by and self._made_by[i] not in members):
+                    leaves.add(i)
+                else:
+                    inside.add(i)
+                    stack += ops[i].operands
+            inputs = sorted(leaves)
+            number, listed = {}, []
+            for i in inputs + sorted(inside):
+                op = ops[i]
+                number[i] = len(listed)
+                if i in leaves:
+                    listed.append(_OpRecord("parameter", op.dtype, op.shape, (), -1, 0.0))
+                else:
+                    listed.append(_OpRecord(op.kind, op.dtype, op.shape, tuple(number[o] for o in op.operands), op.axis, op.attr))
+            for i in outputs:
+                listed.append(_OpRecord("output", ops[i].dtype, ops[i].shape, (number[i],), -1, 0.0))
+            try:
+                plan, extra = Plan.two_step(listed)
+            except FsError as e:
+                if e.status not in (FS_ERR_UNSUPPORTED, FS_ERR_INVALID):      # (invalid: more inputs, outputs or ops than a list may have)
+                    raise
+                continue
+            taken |= members
+            launches.append(_Launch(plan, sorted(members), inputs, outputs, extra))
+        return launches
+
+    def _pack(self, two_steps):
+        """The program's launches in order: groups sorted by their level, which leaves those of one level independent of each
+        other; of a level, what can share a launch does.  A two-step plan runs at the level of its last group."""
+        groups = self.fusion.groups
+        inside = {k for u in two_steps for k in u.members}
+        launches = []
+
+        def add(plan, members):
+            launches.append(_Launch(plan, members, [i for k in members for i in groups[k]["input_of"]],
+                                    [i for k in members for i in groups[k]["output_of"]], 0))
+
+        for lv in range(max(self._level, default=-1) + 1):
+            left = [k for k in range(len(groups)) if self._level[k] == lv and k not in inside]
             while len(left) > 1:
                 try:
                     plan, taken = Plan.packed([groups[k]["ops"] for k in left])
@@ -546,33 +656,35 @@ class FusedProgram:
                     if e.status != FS_ERR_UNSUPPORTED:
                         raise
                     break
-                units.append((plan, [left[t] for t in taken]))
+                add(plan, [left[t] for t in taken])
                 left = [k for t, k in enumerate(left) if t not in taken]
-            units += [(None, [k]) for k in left]
-        return units
+            for k in left:
+                add(None, [k])
+            launches += [u for u in two_steps if max(self._level[k] for k in u.members) == lv]
+        return launches
 
     def _count_kernels(self):
-        self.n_kernels = sum((plan or self._plans[members[0]]).info()["n_kernels"] for plan, members in self._units)
+        self.n_kernels = sum((u.plan or self._plans[u.members[0]]).info()["n_kernels"] for u in self._launches)
 
-    def _unit_args(self, values, members, device):
-        """Inputs and freshly allocated outputs of a launch's groups, in order."""
+    def _launch_args(self, values, launch, device):
+        """Inputs and freshly allocated outputs of a launch, in order."""
         torch = self._torch
         dt = {"f32": torch.float32, "f16": torch.float16, "bf16": torch.bfloat16}
-        gin, gout = [], []
-        for k in members:
-            g = self.fusion.groups[k]
-            gin += [values[i] for i in g["input_of"]]
-            for i in g["output_of"]:
-                op = self.ops[i]
-                values[i] = torch.empty(op.shape, dtype=dt[op.dtype], device=device or (gin[0].device if gin else "cuda:0"))
-                gout.append(values[i])
+        gin, gout = [values[i] for i in launch.inputs], []
+        device = device or (gin[0].device if gin else "cuda:0")
+        for i in launch.outputs:
+            op = self.ops[i]
+            values[i] = torch.empty(op.shape, dtype=dt[op.dtype], device=device)
+            gout.append(values[i])
+        if launch.extra:
+            gout.append(torch.empty(launch.extra, dtype=torch.uint8, device=device))
         return gin, gout
 
     def run(self, inputs, stream=None):
         values = {i: t for i, t in zip(self.param_ops, inputs)}
-        for plan, members in self._units:
-            gin, gout = self._unit_args(values, members, None)
-            (plan or self._plans[members[0]]).launch(gin, gout, stream)
+        for u in self._launches:
+            gin, gout = self._launch_args(values, u, None)
+            (u.plan or self._plans[u.members[0]]).launch(gin, gout, stream)
         return [values[self.ops[i].operands[0]] for i in self.output_ops]
 
     @classmethod
@@ -669,10 +781,8 @@ class FusedProgram:
         outputs, as run() would return them."""
         torch = self._torch
         plans = self.plans
-        for plan, members in self._units:
-            if plan is not None:
-                plan.close()
-        self._units = [(None, [k]) for k in range(len(plans))]
+        self._close_shared()
+        self._launches = [_Launch(None, [k], g["input_of"], g["output_of"], 0) for k, g in enumerate(self.fusion.groups)]
         dt = {"f32": torch.float32, "f16": torch.float16, "bf16": torch.bfloat16}
         values = {i: t for i, t in zip(self.param_ops, inputs)}
         for k, g in enumerate(self.fusion.groups):
@@ -698,9 +808,9 @@ class FusedProgram:
         values = {i: t for i, t in zip(self.param_ops, inputs)}
         device = inputs[0].device if inputs else "cuda:0"
         self._bound = []
-        for plan, members in self._units:
-            gin, gout = self._unit_args(values, members, device)
-            self._bound.append((plan or self._plans[members[0]], BoundArgs(gin, gout)))
+        for u in self._launches:
+            gin, gout = self._launch_args(values, u, device)
+            self._bound.append((u.plan or self._plans[u.members[0]], BoundArgs(gin, gout)))
         self._bound_outputs = [values[self.ops[i].operands[0]] for i in self.output_ops]
         return self._bound_outputs
 
@@ -724,11 +834,19 @@ class FusedProgram:
             self.run_bound()
         return graph, outs
 
-    def close(self):
-        for p in self._plans + [plan for plan, _ in self._units]:
+    def _close_shared(self):
+        """The plans that run more than one group."""
+        for p in [u.plan for u in self._launches] + [plan for plan, _ in self._packed_units or []]:
             if p is not None:
                 p.close()
-        self._plans, self._units = [], []
+        self._launches, self._packed_units = [], None
+
+    def close(self):
+        for p in self._plans:
+            if p is not None:
+                p.close()
+        self._close_shared()
+        self._plans = []
         self._bound = []
 
     def __enter__(self):

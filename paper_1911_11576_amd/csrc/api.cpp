@@ -144,6 +144,36 @@ fs_status fs_plan_create_packed(const fs_op_desc* const* groups, const int32_t* 
   return FS_OK;
 }
 
+fs_status fs_plan_create_two_step(const fs_op_desc* ops, int32_t n_ops, int64_t* partial_bytes, fs_plan** out) {
+  if (!out) return set_error(FS_ERR_INVALID, "out is NULL");
+  *out = nullptr;
+  if (!partial_bytes) return set_error(FS_ERR_INVALID, "fs_plan_create_two_step: partial_bytes is NULL");
+  try {
+    std::unique_ptr<fs_plan> p(new fs_plan);
+    std::string err;
+    if (!fs::build_graph(ops, n_ops, &p->graph, &err)) return set_error(FS_ERR_INVALID, err);
+    if (!fs::two_step_plan(p->graph, &p->two_step, &err)) return set_error(FS_ERR_UNSUPPORTED, err);
+    p->mode = FS_MODE_STITCHED;
+    p->match.kind = fs::MATCH_NONE;
+    p->schedule = FS_SCHED_TWO_STEP;
+    p->lds_bytes = p->two_step.lds_bytes;
+    p->n_kernels = 2;
+    *partial_bytes = p->two_step.n_partials * 8;
+    p->moved_bytes = p->graph.algorithmic_bytes() + 2 * *partial_bytes;
+    for (int v : p->two_step.view_param[0]) {         // (what the first kernel reads is read once more)
+      const fs::Node& x = p->graph[p->graph.params[v]];
+      p->moved_bytes += x.numel() * (x.dtype == FS_F32 ? 4 : 2);
+    }
+    p->description = fs::two_step_describe(p->two_step);
+    *out = p.release();
+  } catch (const std::bad_alloc&) {
+    return set_error(FS_ERR_NOMEM, "out of host memory");
+  } catch (...) {
+    return set_error(FS_ERR_INVALID, "internal error while planning");
+  }
+  return FS_OK;
+}
+
 fs_status fs_kernel_cache_dir(const char* dir) {
   try {
     fs::codegen_cache_dir(dir);
@@ -167,6 +197,11 @@ fs_status fs_group_key(const fs_op_desc* ops, int32_t n_ops, uint64_t* key) {
   if (!ops || !key || n_ops < 1 || n_ops > 4096) return set_error(FS_ERR_INVALID, "fs_group_key: NULL argument or n_ops out of range [1,4096]");
   *key = group_key(ops, n_ops);
   return FS_OK;
+}
+
+int32_t fs_tune_cache_has(uint64_t key) {
+  std::lock_guard<std::mutex> lock(g_tune_mu);
+  return g_tune.count(key) ? 1 : 0;
 }
 
 int32_t fs_tune_cache_size(void) {
@@ -424,11 +459,19 @@ fs_status fs::check_launch_args(fs_plan* p, const void* const* inputs, int32_t n
   if (!p) return set_error(FS_ERR_INVALID, "plan is NULL");
   const fs::Graph& g = p->graph;
   if (n_in != (int32_t)g.params.size()) return set_error(FS_ERR_INVALID, "n_in differs from the number of parameters");
-  if (n_out != (int32_t)g.outputs.size()) return set_error(FS_ERR_INVALID, "n_out differs from the number of outputs");
+  const bool two_step = p->schedule == FS_SCHED_TWO_STEP;
+  if (n_out != (int32_t)g.outputs.size() + (two_step ? 1 : 0)) return set_error(FS_ERR_INVALID, "n_out differs from the number of outputs");
   if (!inputs || !outputs) return set_error(FS_ERR_INVALID, "inputs/outputs is NULL");
   for (int i = 0; i < n_in; ++i) {
     if (g[g.params[i]].numel() == 0) continue;
     if (!inputs[i] || (reinterpret_cast<uintptr_t>(inputs[i]) & 15)) return set_error(FS_ERR_INVALID, "input pointer is NULL or not 16-byte aligned");
+  }
+  if (two_step) {
+    // the partial results: one more output, of no op
+    const void* partials = outputs[--n_out];
+    if (!partials || (reinterpret_cast<uintptr_t>(partials) & 15)) return set_error(FS_ERR_INVALID, "output pointer is NULL or not 16-byte aligned");
+    for (int k = 0; k < n_out; ++k) if (outputs[k] == partials) return set_error(FS_ERR_INVALID, "two outputs share one buffer");
+    for (int k = 0; k < n_in; ++k) if (inputs[k] == partials) return set_error(FS_ERR_INVALID, "an output shares its buffer with an input");
   }
   for (int i = 0; i < n_out; ++i) {
     if (g[g.outputs[i]].numel() == 0) continue;
@@ -478,6 +521,7 @@ fs_status fs::enqueue_plan(fs_plan* p, const void* const* inputs, void* const* o
       case FS_SCHED_BLOCK_DOT: rc = fs::row_gen_launch(p->row_gen, inputs, outputs, n_out, workspace, hip_stream, &err); break;
       case FS_SCHED_BDOT_SOFTMAX: rc = fs::attn_stitch_launch(p->match.attn, p->attn, inputs, outputs, hip_stream, &err); break;
       case FS_SCHED_ELEMENTWISE: rc = fs::ew_stitch_launch(p->ew, inputs, outputs, n_out, hip_stream, &err); break;
+      case FS_SCHED_TWO_STEP: rc = fs::two_step_launch(p->two_step, inputs, outputs, n_out - 1, outputs[n_out - 1], hip_stream, &err); break;
       default: rc = fs::per_op_launch(p->graph, p->per_op, inputs, outputs, workspace, hip_stream, &err); break;
     }
     if (rc != 0) return set_error(FS_ERR_HIP, err);
@@ -634,6 +678,7 @@ fs_status fs_destroy(fs_plan* p) {
   }
   fs::ew_stitch_release(p->ew);
   fs::row_gen_release(p->row_gen);
+  fs::two_step_release(p->two_step);
   delete p;
   return st;
 }

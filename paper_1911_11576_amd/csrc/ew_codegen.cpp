@@ -154,6 +154,7 @@ std::string op_text(const EwIrNode& n, bool fast) {
 }  // namespace
 
 const char* ew_preamble() { return kPreamble; }
+std::string ew_op_text(const EwIrNode& n, bool fast) { return op_text(n, fast); }
 
 // Chunk width of a group: as many consecutive elements as one 16-byte access of the narrowest
 // tensor holds, provided every row start stays aligned; otherwise one element.
@@ -492,17 +493,19 @@ bool ew_compile_source(const std::string& source, std::vector<char>* code_object
 }
 
 int ew_module_launch(EwModule* m, const std::vector<char>& code_object, const std::string& kernel_name,
-                     const void* args, size_t args_bytes, int grid, int block, void* stream, std::string* err) {
+                     const void* args, size_t args_bytes, int grid, int block, void* stream, std::string* err, const EwModule* holder) {
   int dev = -1;
   if (hipGetDevice(&dev) != hipSuccess) { *err = "hipGetDevice failed"; return -1; }
   if (!m->function) {
     hipModule_t mod = nullptr;
-    hipError_t e = hipModuleLoadData(&mod, code_object.data());
+    hipError_t e = hipSuccess;
+    if (holder) mod = static_cast<hipModule_t>(holder->module);
+    else e = hipModuleLoadData(&mod, code_object.data());
     if (e != hipSuccess) { *err = std::string("hipModuleLoadData: ") + hipGetErrorString(e); return -1; }
     hipFunction_t fn = nullptr;
     e = hipModuleGetFunction(&fn, mod, kernel_name.c_str());
-    if (e != hipSuccess) { (void)hipModuleUnload(mod); *err = std::string("hipModuleGetFunction: ") + hipGetErrorString(e); return -1; }
-    m->module = mod; m->function = fn; m->device = dev;
+    if (e != hipSuccess) { if (!holder) (void)hipModuleUnload(mod); *err = std::string("hipModuleGetFunction: ") + hipGetErrorString(e); return -1; }
+    m->module = holder ? nullptr : mod; m->function = fn; m->device = dev;
   } else if (dev != m->device) {
     *err = "plan is bound to the device of its first launch";
     return -1;

@@ -640,8 +640,7 @@ static_assert(kEwMaxViews <= 64 && kEwMaxOuts <= 16, "EwGenArgs mirrors the Args
 // that share no computed value -- typically the same update applied to tensors of different
 // shapes -- and each part is an elementwise group of its own shape.  One generated kernel runs
 // them all, each part on its own run of workgroups.
-static bool ew_plan_packed(const Graph& g, const LaunchOpts& opt, EwLaunch* out, int* status, std::string* err) {
-  *status = FS_ERR_UNSUPPORTED;
+static bool ew_split(const Graph& g, size_t least, std::vector<std::vector<char>>* parts, std::string* err) {
   const int n = g.size();
   EwCompiler probe(g);
   // parts = connected components of the compute ops under "reads the value of"
@@ -663,25 +662,52 @@ static bool ew_plan_packed(const Graph& g, const LaunchOpts& opt, EwLaunch* out,
   }
   std::vector<int> roots;
   for (int i = 0; i < n; ++i) if (part[i] >= 0 && find(i) == i && reaches_output[i]) roots.push_back(i);
-  if (roots.size() < 2) { *err = "elementwise schedule: ops of different shapes in one group"; return false; }
+  if (roots.size() < least) { *err = "elementwise schedule: ops of different shapes in one group"; return false; }
   if (roots.size() > 16) { *err = "elementwise schedule: more than 16 independent parts in one group"; return false; }
   if (g.outputs.size() > 16) { *err = "elementwise schedule: more than 16 outputs"; return false; }
+  for (int r : roots) {
+    parts->emplace_back(n, 0);
+    for (int i = 0; i < n; ++i) if (part[i] >= 0 && find(i) == r) parts->back()[i] = 1;
+  }
+  return true;
+}
+
+static bool ew_analyse_split(const Graph& g, const std::vector<std::vector<char>>& parts, std::vector<std::unique_ptr<EwCompiler>>* cs, std::string* err) {
+  for (const std::vector<char>& active : parts) {
+    cs->emplace_back(new EwCompiler(g));
+    EwCompiler& cc = *cs->back();
+    cc.active = active;
+    if (!cc.analyse()) { *err = cc.err; return false; }
+    if (cc.ir.n_outputs > kEwMaxOuts) { *err = "elementwise schedule: more than 8 outputs in one part"; return false; }
+  }
+  return true;
+}
+
+// The parts of an all-elementwise group, one or more, as resolved ops.
+bool ew_analyse_parts(const Graph& g, std::vector<EwIr>* parts, std::string* err) {
+  std::vector<std::vector<char>> split;
+  std::vector<std::unique_ptr<EwCompiler>> cs;
+  if (!ew_split(g, 1, &split, err) || !ew_analyse_split(g, split, &cs, err)) return false;
+  for (const auto& c : cs) parts->push_back(c->ir);
+  return true;
+}
+
+static bool ew_plan_packed(const Graph& g, const LaunchOpts& opt, EwLaunch* out, int* status, std::string* err) {
+  *status = FS_ERR_UNSUPPORTED;
+  std::vector<std::vector<char>> split;
+  std::vector<std::unique_ptr<EwCompiler>> cs;
+  if (!ew_split(g, 2, &split, err)) return false;
   if (opt.wg_size && (opt.wg_size < 64 || opt.wg_size > 256 || opt.wg_size % 64)) {
     *status = FS_ERR_INVALID;
     *err = "elementwise schedule: wg_size must be 64, 128, 192 or 256";
     return false;
   }
-  std::vector<std::unique_ptr<EwCompiler>> cs;
+  if (!ew_analyse_split(g, split, &cs, err)) return false;
   std::vector<const EwIr*> irs;
   EwLaunch l;
   int n_views = 0;
-  for (int r : roots) {
-    cs.emplace_back(new EwCompiler(g));
-    EwCompiler& cc = *cs.back();
-    cc.active.assign(n, 0);
-    for (int i = 0; i < n; ++i) if (part[i] >= 0 && find(i) == r) cc.active[i] = 1;
-    if (!cc.analyse()) { *err = cc.err; return false; }
-    if (cc.ir.n_outputs > kEwMaxOuts) { *err = "elementwise schedule: more than 8 outputs in one part"; return false; }
+  for (const auto& c : cs) {
+    const EwCompiler& cc = *c;
     irs.push_back(&cc.ir);
     l.n_ops += (int)cc.ir.nodes.size();
     for (int k = 0; k < cc.c.n_views; ++k) { l.view_param.push_back(cc.c.view_param[k]); l.view_full.push_back(cc.ir.views[k].full ? 1 : 0); }
@@ -698,7 +724,7 @@ static bool ew_plan_packed(const Graph& g, const LaunchOpts& opt, EwLaunch* out,
   std::string gen_err;
   if (!ew_compile_source(src, &l.code_object, &gen_err)) { *err = "elementwise schedule: " + gen_err; return false; }
   l.generated = true;
-  l.parts = (int)roots.size();
+  l.parts = (int)cs.size();
   l.width = *std::max_element(widths.begin(), widths.end());
   int64_t grid = 0;
   for (int b : blocks) grid += b;

@@ -53,8 +53,9 @@ extern "C" fs_status fs_launch_static(fs_plan* p, const void* const* inputs, int
   }
   // a generated kernel is put on the device by the plan's first fs_launch; loading a code object allocates
   const bool elementwise = p->schedule == FS_SCHED_ELEMENTWISE;
-  const bool generated = elementwise ? p->ew.generated : (p->schedule != FS_SCHED_PER_OP && p->row_form == 3);
-  const fs::EwModule& mod = elementwise ? p->ew.loaded : p->row_gen.loaded;
+  const bool two_step = p->schedule == FS_SCHED_TWO_STEP;
+  const bool generated = elementwise ? p->ew.generated : two_step || (p->schedule != FS_SCHED_PER_OP && p->row_form == 3);
+  const fs::EwModule& mod = elementwise ? p->ew.loaded : two_step ? p->two_step.loaded[1] : p->row_gen.loaded;
   int dev = -1;
   if (generated && (hipGetDevice(&dev) != hipSuccess || !mod.function || mod.device != dev))
     return fs::set_error(FS_ERR_INVALID, "fs_launch_static: this plan runs a generated kernel that is not on this device yet; "

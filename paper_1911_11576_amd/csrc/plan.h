@@ -4,6 +4,7 @@
 
 #include "../../include/fs.h"
 #include "graph.h"
+#include "grid_codegen.h"
 #include "launchers.h"
 #include "match.h"
 #include "per_op.h"
@@ -22,6 +23,7 @@ struct fs_plan {
   fs::LnBwdLaunch lnbwd;
   fs::AttnLaunch attn;
   fs::EwLaunch ew;
+  fs::TwoStepLaunch two_step;   // schedule FS_SCHED_TWO_STEP: takes one more output, the doubles between its two kernels
   fs::PerOpPlan per_op;
   int n_kernels = 1;
   int64_t lds_bytes = 0, workspace_bytes = 0, moved_bytes = 0;

@@ -2386,6 +2386,8 @@ struct GenArgs { const void* in[64]; void* out[16]; void* ws; };   // mirrors Ar
 
 }  // namespace
 
+const char* row_reduce_preamble() { return kReducePreamble; }
+
 static void dump_source(const std::string& src) {
   if (const char* dump = getenv("FS_DUMP_SOURCE")) {        // debugging aid: append what was generated
     if (FILE* f = fopen(dump, "a")) { fputs(src.c_str(), f); fputs("\n// ----\n", f); fclose(f); }

@@ -759,3 +759,80 @@ def test_block_dot_groups_are_generated_or_refused_with_a_reason():
     _expect(binding.FS_ERR_INVALID, g.ops)        # the op list itself is malformed: operand shapes differ
     assert "32, 64 or 128" in _expect(binding.FS_ERR_UNSUPPORTED, _dot_group(d=48))
     assert "multiple of 8" in _expect(binding.FS_ERR_UNSUPPORTED, _dot_group(kc=20))
+
+
+def _clip(shapes, wrong=None):
+    g = graphs.Graph()
+    params = [g.parameter(f"g{k}", "f32", s) for k, s in enumerate(shapes)]
+    total = None
+    for x in params:
+        s = g.multiply(x, x)
+        while len(g.shape(s)) > 0:
+            s = g.reduce_sum(s, len(g.shape(s)) - 1)
+        total = s if total is None else g.add(total, s)
+    if wrong == "twice":                  # a reduction of what depends on a reduction
+        y = g.multiply(params[0], g.broadcast(total, shapes[0], 0))
+        while len(g.shape(y)) > 0:
+            y = g.reduce_sum(y, len(g.shape(y)) - 1)
+        total = g.add(total, y)
+    if wrong == "kinds":                  # a chain of two kinds
+        total = g.add(total, g.reduce_max(g.reduce_sum(params[0], 1), 0))
+    if wrong == "rows":                   # a reduction that ends in a row
+        g.output(g.reduce_sum(params[0], 1), "rows")
+    if wrong == "operand":                # a tensor operand of another shape
+        params[0] = g.add(params[0], g.broadcast(g.parameter("bias", "f32", (shapes[0][1],)), shapes[0], 1))
+    for k, x in enumerate(params):
+        g.output(x if wrong == "copy" else g.multiply(x, g.broadcast(total, g.shape(x), 0)), f"y{k}")
+    return g.ops
+
+
+def test_two_step_groups_on_the_host():
+    """What fs_plan_create_two_step takes and refuses; fs_plan_create refuses such groups as before."""
+    shapes = [(30, 64), (64,), (7, 3, 50)]
+    plan, extra = Plan.two_step(_clip(shapes))
+    with plan:
+        info = plan.info()
+        assert info["schedule"] == "two_step" and info["n_kernels"] == 2 and info["workspace_bytes"] == 0 and extra % 8 == 0
+        n = 4 * (30 * 64 + 64 + 7 * 3 * 50)
+        assert info["algorithmic_bytes"] == 2 * n and info["moved_bytes"] == 3 * n + 2 * extra
+    _expect(binding.FS_ERR_UNSUPPORTED, _clip(shapes))
+    for wrong in ("twice", "kinds", "rows", "operand", "copy"):
+        with pytest.raises(FsError) as e:
+            Plan.two_step(_clip(shapes, wrong))
+        assert e.value.status == binding.FS_ERR_UNSUPPORTED, wrong
+    for ops in (graphs.layernorm_fwd(8, 64), graphs.bias_gelu_residual(8, 64, "f32"), graphs.sigmoid_attention(2, 16, 16, 32, 32), _clip([(0, 4)])):
+        with pytest.raises(FsError) as e:
+            Plan.two_step(ops)
+        assert e.value.status == binding.FS_ERR_UNSUPPORTED
+    broken = binding.marshal_ops(_clip(shapes))
+    broken[len(broken) - 1].operand[0] = 99
+    with pytest.raises(FsError) as e:
+        Plan.two_step(broken)
+    assert e.value.status == binding.FS_ERR_INVALID
+
+
+def test_programs_with_two_step_plans(tmp_path):
+    """A program takes one where a group reads scalars that are made for it alone; recorded options of any of its groups keep the groups apart."""
+    from paper_1911_11576_amd import FusedProgram
+    for shapes in ([(30, 64), (64,)] * 8, [(30, 64), (64,)]):
+        ops = graphs.clip_by_global_norm(shapes, 1.0)
+        with FusedProgram(ops) as prog:
+            assert [u.extra > 0 for u in prog._launches] == [True] and prog.n_kernels == 2
+            key = binding.fs_group_key(prog.fusion.groups[0]["ops"])
+            assert sorted(k for _, members in prog._units for k in members) == list(range(len(prog.fusion.groups)))
+    f = tmp_path / "tuned"
+    f.write_text(f"fs-tune-cache 1\n{key:016x} {binding.FS_MODE_STITCHED} 64 0 0 3.0\n")
+    try:
+        assert not binding.fs_tune_cache_has(key)
+        binding.fs_tune_cache_load(f)
+        assert binding.fs_tune_cache_has(key)
+        with FusedProgram(ops) as prog:
+            assert all(u.extra == 0 for u in prog._launches)
+    finally:
+        binding.fs_tune_cache_clear()
+    # the norm is asked for as well: groups apart
+    ops = list(ops)
+    norm = next(i for i, op in enumerate(ops) if op.kind == "sqrt")
+    ops.append(Op("output", "f32", (), (norm,), -1, 0.0, "norm"))
+    with FusedProgram(ops) as prog:
+        assert all(u.extra == 0 for u in prog._launches)

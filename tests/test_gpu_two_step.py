@@ -1,0 +1,183 @@
+"""Groups in which values reduced over whole tensors feed ops on whole tensors, as two kernels (fs_plan_create_two_step),
+against the oracle: tensor sizes at the edges of a chunk, of a workgroup's run and of the whole grid, several dtypes and
+ops, sums and maxima, scalars as inputs and outputs; and which groups are refused."""
+import sys
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import interp
+from paper_1911_11576_amd import FsError, FusedProgram, Plan, binding
+from workloads import TOLERANCE, graphs, inputs
+
+from gpu_util import alloc_outputs, assert_close, to_device
+
+pytestmark = pytest.mark.gpu
+
+
+def announce(msg):
+    sys.__stderr__.write(f"[gpu-case] {msg}\n")
+    sys.__stderr__.flush()
+
+
+@pytest.fixture(autouse=True)
+def _need_gpu(device):
+    yield
+
+
+def clip(shapes, dtypes, kind="sum", limit_input=False, returns_norm=False):
+    """Every tensor scaled by limit / max(limit, norm), the norm over all of them a root of a sum of squares or a largest square."""
+    g = graphs.Graph()
+    params = [g.parameter(f"g{k}", d, s) for k, (s, d) in enumerate(zip(shapes, dtypes))]
+    limit = g.parameter("limit", "f32", ()) if limit_input else g.constant(1.0)
+    total = None
+    for x in params:
+        v = x if g.dtype(x) == "f32" else g.convert(x, "f32")
+        s = g.multiply(v, v)
+        while len(g.shape(s)) > 0:
+            s = (g.reduce_sum if kind == "sum" else g.reduce_max)(s, len(g.shape(s)) - 1)
+        total = s if total is None else (g.add if kind == "sum" else g.maximum)(total, s)
+    norm = g.sqrt(total)
+    factor = g.divide(limit, g.maximum(norm, limit))
+    for k, x in enumerate(params):
+        v = x if g.dtype(x) == "f32" else g.convert(x, "f32")
+        y = g.multiply(v, g.broadcast(factor, g.shape(x), 0))
+        g.output(y if g.dtype(x) == "f32" else g.convert(y, g.dtype(x)), f"g{k}")
+    if returns_norm:
+        g.output(norm, "norm")
+    return g.ops
+
+
+def run(ops, dev_in, repeats=1):
+    plan, extra = Plan.two_step(ops)
+    with plan:
+        assert plan.info()["schedule"] == "two_step" and plan.info()["n_kernels"] == 2 and plan.info()["workspace_bytes"] == 0
+        for _ in range(repeats):
+            outs = [o.fill_(float("nan")) for o in alloc_outputs(ops)]
+            partials = torch.full((extra,), 0xff, dtype=torch.uint8, device="cuda:0")
+            plan.launch(dev_in, outs + [partials])
+            torch.cuda.synchronize()
+    return outs
+
+
+CASES = [
+    # (a chunk is 4 or 8 elements, a workgroup's run in the first kernel 1024 chunks or more)
+    ([(1,), (2,), (3,), (4,), (5,)], "f32"),
+    ([(7,), (8,), (9,), (15, 17)], "bf16"),
+    ([(4096,), (4095,), (4097,)], "f32"),
+    ([(8191,), (8193,), (2, 3, 5, 7)], "f16"),
+    ([(33, 5000), (9000,), (1, 1, 1)], "f32"),
+    ([(1024, 1024), (1024, 1030), (1021, 1021)], "f32"),      # beyond 1024 runs of 1024 chunks together with the next
+    ([(2300, 2049)], "f32"),
+    ([(1000, 4099)], "bf16"),
+]
+
+
+@pytest.mark.parametrize("shapes,dtype", CASES)
+@pytest.mark.parametrize("kind", ["sum", "max"])
+def test_clipping_in_two_kernels(shapes, dtype, kind):
+    announce(f"two-step {shapes} {dtype} {kind}")
+    ops = clip(shapes, [dtype] * len(shapes), kind)
+    ins = [inputs.round_to(a, dtype) for a in inputs.normal_tensors(shapes, scale=0.3)]
+    for got, want in zip(run(ops, to_device(ops, ins), repeats=2), interp.run(ops, ins)):
+        assert_close(got.to(torch.float64).cpu().numpy(), want, TOLERANCE[dtype], f"two-step {shapes} {dtype} {kind}")
+
+
+def test_dtypes_mixed_scalar_inputs_and_outputs():
+    announce("two-step, mixed dtypes, scalar input and output")
+    shapes, dtypes = [(300, 1001), (77,), (64, 64), (5,)], ["f32", "bf16", "f16", "f32"]
+    ops = clip(shapes, dtypes, limit_input=True, returns_norm=True)
+    ins = [inputs.round_to(a, d) for a, d in zip(inputs.normal_tensors(shapes), dtypes)] + [np.float64(7.5)]
+    for got, want, d in zip(run(ops, to_device(ops, ins)), interp.run(ops, ins), dtypes + ["f32"]):
+        assert_close(got.to(torch.float64).cpu().numpy(), want, TOLERANCE[d], "two-step, mixed")
+
+
+def test_several_operands_and_several_scalars():
+    """A trust-ratio update: w - lr * |w| / |u| * u with u = m + decay * w, and a sum and a maximum of one tensor beside it."""
+    announce("two-step, several operands")
+    shape = (513, 771)
+    g = graphs.Graph()
+    w, m, lr = g.parameter("w", "f32", shape), g.parameter("m", "f32", shape), g.parameter("lr", "f32", ())
+    u = g.add(m, g.multiply(g.constant(0.01), w))
+
+    def total(v, reduce=g.reduce_sum):
+        return reduce(reduce(v, 1), 0)
+    ratio = g.divide(g.sqrt(total(g.multiply(w, w))), g.sqrt(total(g.multiply(u, u))))
+    step = g.multiply(u, g.broadcast(g.multiply(lr, ratio), shape, 0))
+    g.output(g.subtract(w, step), "w")
+    g.output(g.subtract(m, g.broadcast(total(w, g.reduce_max), shape, 0)), "shifted")
+    g.output(total(m), "sum")
+    ins = inputs.normal_tensors([shape, shape]) + [np.float64(0.125)]
+    for got, want in zip(run(g.ops, to_device(g.ops, ins)), interp.run(g.ops, ins)):
+        want = np.asarray(want)
+        # (the sum of 395523 values of either sign in f32: their own rounding leaves |error| <= 2^-24 sum |m|)
+        tol = 1e-5 if want.ndim else 2.0 ** -24 * np.abs(ins[1]).sum()
+        assert_close(got.to(torch.float64).cpu().numpy(), want, tol, "two-step, several operands")
+
+
+def test_infinities_and_nan_go_through():
+    announce("two-step, infinities")
+    ops = clip([(700,), (33,)], ["f32", "f32"])
+    for value in (float("inf"), float("nan")):
+        x, y = torch.randn(700, device="cuda:0"), torch.randn(33, device="cuda:0")
+        x[123] = value
+        got = run(ops, [x, y])
+        factor = 1.0 / torch.clamp(torch.sqrt((x * x).sum() + (y * y).sum()), min=1.0)
+        if value == float("inf"):      # everything finite is scaled to 0; inf * 0 is NaN
+            assert torch.isnan(got[0][123]) and int(torch.isnan(got[0]).sum()) == 1 and float(got[1].abs().max()) == 0.0 == float(factor)
+        else:                          # maximum(NaN, 1) is 1 in the kernels, as in every other schedule
+            assert torch.isnan(got[0][123]) and torch.equal(got[1], y)
+
+
+def test_replayed_and_concurrent_launches():
+    """One plan, launches with buffers of their own on two streams and in a replayed graph."""
+    announce("two-step, streams and graphs")
+    shapes = [(400, 1024), (1024,), (3000,)]
+    ops = graphs.clip_by_global_norm(shapes, 1.0)
+    sets = []
+    for seed in (1, 2):
+        ins = inputs.normal_tensors(shapes, seed_offset=seed)
+        sets.append((ins, to_device(ops, ins), interp.run(ops, ins)))
+    with FusedProgram(ops) as prog:
+        assert prog.n_kernels == 2
+        streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+        torch.cuda.synchronize()
+        got = []
+        for _ in range(20):
+            for st, (_, dev_in, _) in zip(streams, sets):
+                with torch.cuda.stream(st):
+                    got.append(prog.run(dev_in))
+        torch.cuda.synchronize()
+        for k, outs in enumerate(got):
+            for a, b in zip(outs, sets[k % 2][2]):
+                assert_close(a.double().cpu().numpy(), b, 1e-5, "two streams")
+        dev_in = sets[0][1]
+        graph, outs = prog.capture(dev_in)
+        for rep in range(3):
+            ins = [a * (rep + 0.5) for a in sets[0][0]]
+            ins = [inputs.round_to(a, "f32") for a in ins]
+            for t, s in zip(dev_in, to_device(ops, ins)):
+                t.copy_(s)
+            prog.run(sets[1][1])
+            graph.replay()
+            torch.cuda.synchronize()
+            for a, b in zip(outs, interp.run(ops, ins)):
+                assert_close(a.double().cpu().numpy(), b, 1e-5, f"replay {rep}")
+
+
+def test_arguments_are_checked():
+    ops = graphs.clip_by_global_norm([(64,)], 1.0)
+    plan, extra = Plan.two_step(ops)
+    x, y, p = torch.randn(64, device="cuda:0"), torch.empty(64, device="cuda:0"), torch.empty(extra, dtype=torch.uint8, device="cuda:0")
+    with plan:
+        for ins, outs in (([x], [y]), ([x], [x, p]), ([x], [y, y]), ([x], [y, x]), ([x], [y, p, p])):
+            with pytest.raises(FsError) as e:
+                plan.launch(ins, outs)
+            assert e.value.status == binding.FS_ERR_INVALID
+        with pytest.raises(FsError):
+            plan.launch_static([x], [y, p])              # not on the device yet
+        plan.launch([x], [y, p])
+        first = y.clone()
+        plan.launch_static([x], [y, p])
+        assert torch.equal(first, y)
