@@ -750,6 +750,8 @@ int chunk_elements(const Analysis& A, bool* fast) {
 // 256 x 3001 12.6 and 24.0.
 // Neighbouring rows share lines: ragged chunks are loaded through the caches (4096 x 3001 35.1, 40.4 with
 // nontemporal loads).
+constexpr int64_t kSpreadRows = 256;
+constexpr int64_t kTeamBytes = 128ll << 20;      // groups up to here: teams with column sums load through the caches
 constexpr int64_t kRaggedCols = 512, kRaggedColumnRows = 2048, kRaggedRunRows = 8192;
 int ragged_chunk_elements(const Analysis& A) {
   if (A.n_col > 0 && A.cols <= 2048 && (A.seg_rows > 0 ? A.rows >= kRaggedRunRows : A.rows < kRaggedColumnRows)) return 0;
@@ -850,17 +852,16 @@ struct Gen {
   bool seg_per_wave = false;  // ... or every wavefront has a run of its own (many short runs): no LDS, no barrier
   bool stage = false;         // full outputs leave through an LDS staging tile (see emit)
   int64_t stage_bytes = 0;
+  int exchange_sets = 1;      // of a team's exchange slots
+  bool default_shape = false; // the caller fixes no launch shape
+  bool spread = false;        // a row that a wavefront could hold, given to a team
 
   // Row steps requested ahead in the persistent form: one, or two (FS_ROW_PREFETCH=2): two row buffers per
   // streamed operand, the row loop unrolled twice so that each keeps its registers, and a buffer requested
   // again - for two steps ahead - as soon as its row has been taken out of it.  (Shifting the buffers down at
   // the end of an iteration instead makes the iteration wait for the request it has just issued.)
   int force_prefetch = 0;     // 1 or 2: the caller's choice
-  int prefetch_depth(int n_prefetched) const {
-    (void)n_prefetched;
-    if (force_prefetch == 2 && A.seg_rows == 0 && L <= 64) return 2;
-    return 1;
-  }
+  int prefetch_depth() const { return force_prefetch == 2 && A.seg_rows == 0 && L <= 64 ? 2 : 1; }
 
   // ---- block composition around dots on the matrix unit (Section 5.1; DotGen of Section 5.3): one
   // workgroup per batch element, one wavefront per 16 rows of the tile.  The producing dot is computed
@@ -1064,9 +1065,21 @@ struct Gen {
     // memory, so its full outputs are first laid out in LDS and then stored as one dense run
     // of 16-byte accesses (stores of separate row pieces straddle lines and measured 2x slower).
     if (A.n_col > 0) {
+      // More than twenty elements of a row in a lane, with their running sums: a team, where the sums are three or more (they and
+      // the rows no longer fit a lane's registers: backward tail of 4096 x 2048 62.6 us with a wavefront per row, 40.3 with a team,
+      // 8192 x 1500 70.2 and 56.2, 32768 x 1400 221 and 180), and with two in groups of up to 128 MB, up to 24 elements 64 MB (LayerNorm backward over
+      // 600 x 2048 13.3 and 11.0, 6000 x 1700 32.2 and 29.1, 2304 x 1510 17.0 and 16.6, from cold buffers 19.5 and 18.2; 7000 x 1400, 118 MB, 30.8 and
+      // 29.5, cold 30.9 and 33.5; 8000 x 1999, 192 MB, 44.9 and 46.5; 16384 x 2048 75.3 and 82).  Up to twenty elements:
+      // 10624 x 658 20.0 and 25.3, 8192 x 1280 28.5 and 29.2, the tail of 16384 x 1024 63.0 and 74.  Below 256 rows a team has sixteen rows to a
+      // workgroup (see the grid): 130 x 1500 10.4 and 15.3.
+      if (L == 64 && default_shape && A.seg_rows == 0 && A.rows >= kSpreadRows && K * W > 20 && (A.n_col > 2 || (A.n_col == 2 && A.g.algorithmic_bytes() <= (K * W > 24 ? kTeamBytes : kTeamBytes / 2)))) {
+        L = 128;
+        spread = true;
+      }
       if (L > 64) {
         // a team of wavefronts per row: every lane's columns are its own in the workgroup, so the
         // running sums (two registers per column and reduction) stay few by spreading the row wider
+        K = (int)((nvec + L - 1) / L);
         while ((int64_t)K * W * A.n_col > 16 && L < 1024) { L *= 2; K = (int)((nvec + L - 1) / L); }
         if ((int64_t)K * W * A.n_col > 16) { *err = "generated row schedule: column reductions over rows too long for their running sums to stay in registers"; return false; }
         exact = (int64_t)K * L == nvec && !ragged;
@@ -1365,7 +1378,10 @@ struct Gen {
       } else {
         e.line("  const int rl = threadIdx.x / L;");
         e.line("  const long long first_row = (long long)blockIdx.x * RPW, row_step = (long long)gridDim.x * RPW;");
-        if (L <= 64) {
+        // (Teams too, where the chunks cover the row and a thread has registers for it: no copies of the requests, a barrier a row for all
+        // reductions.  LayerNorm backward over 4096 x 4096 46.8 -> 45.2 us, 2048 x 4096 24.2 -> 22.9, the backward tail of 1024 x 4096 34.3 -> 30.0;
+        // the other way round 8192 x 4096, 403 MB, 79.7 -> 80.2, 8192 x 3001 68.1 -> 69.3, 4096 x 6000 65.6 -> 84.0.  Two and three rows ahead are no faster: 46.2, 46.6.)
+        if (L <= 64 || (exact && (L < 1024 || K == 1) && A.g.algorithmic_bytes() <= 2 * kTeamBytes)) {
           // One step of the row loop as a function of the row buffer it works on (ph) and of whether every row
           // of the step exists (ALL): the loop below is unrolled over the buffers, which take turns without
           // ever being copied, and has a branch-free main part.
@@ -1442,9 +1458,7 @@ struct Gen {
       // handed to raw<q> at the end of the iteration.
       std::string pro, nxt, adv;
       char buf[640];
-      int n_pref = 0;
-      for (size_t q = 0; q < A.views.size(); ++q) n_pref += prefetched[q] ? 1 : 0;
-      const int depth = rotating ? prefetch_depth(n_pref) : 1;
+      const int depth = rotating ? prefetch_depth() : 1;
       const int nb = depth + 1;
       rot_buffers = nb;
       // A per-row scalar loaded where it is used would make every iteration wait for all requests issued
@@ -1482,7 +1496,7 @@ struct Gen {
         // 24.1 us from warm buffers and 30.6 from cold ones, 32.0 and 31.9 nontemporal; 1024 x 4096 16.6 / 20.1 and 21.4 / 21.6;
         // over 8192 x 4096, 402 MB, 81.5 against 78.8; with 201 MB one or the other is 2 to 5 % ahead.  A row per wavefront:
         // 16384 x 2048 82.1 against 76.8.)
-        const char* ld = ragged || (L > 64 && A.g.algorithmic_bytes() <= (128ll << 20)) ? "*" : "__builtin_nontemporal_load";
+        const char* ld = ragged || (L > 64 && A.g.algorithmic_bytes() <= kTeamBytes) ? "*" : "__builtin_nontemporal_load";
         bool dummy = false;
         const std::string offp = row_offset(v, &dummy, "rowp"), offn = row_offset(v, &dummy, "rown");
         if (rotating) {
@@ -1607,18 +1621,35 @@ struct Gen {
     std::vector<char> inv_done(A.g.size(), 0);
     std::map<int, std::string> inline_expr;       // values of a long row that only one reduction reads: computed in its loop
     int red_index = 0;
+    const char* turn = rotating ? "[ph]" : "";      // row steps take turns with the exchange slots as with the row buffers
+    // A team's reductions whose results nothing has read yet share a barrier.
+    struct Pending { int id; bool sum; };
+    std::vector<Pending> pending;
+    auto flush = [&]() {
+      if (pending.empty()) return;
+      const int first_slot = red_index;
+      for (const Pending& q : pending) {
+        e.line("  r%d = lanes_allreduce<%s, 64>(r%d);", q.id, q.sum ? "SumOp" : "MaxOp", q.id);
+        e.line("  if ((threadIdx.x & 63) == 0) exch%s[%d][threadIdx.x >> 6] = r%d;", turn, red_index++, q.id);
+      }
+      e.line("  __syncthreads();");
+      for (size_t k = 0; k < pending.size(); ++k) {
+        const int id = pending[k].id, slot = first_slot + (int)k;
+        e.line("  r%d = exch%s[%d][0];", id, turn, slot);
+        e.line("  UNROLL for (int w = 1; w < T; ++w) r%d = %s::apply(r%d, exch%s[%d][w]);", id, pending[k].sum ? "SumOp" : "MaxOp", id, turn, slot);
+      }
+      pending.clear();
+    };
     for (const RNode& n : A.nodes) {
       const bool reduce = n.op == FS_REDUCE_SUM || n.op == FS_REDUCE_MAX;
+      for (int j = 0; j < n.nop; ++j)
+        for (const Pending& q : pending) if ((n.o[j].kind == OP_NODE || n.o[j].kind == OP_ROWB) && n.o[j].index == q.id) { flush(); break; }
       // combine the lanes' partial results of reduction r<id> (wavefront steps, then LDS across wavefronts)
       auto combine = [&](int id, bool sum) {
         const char* op = sum ? "SumOp" : "MaxOp";
         if (T > 1) {
-          e.line("  r%d = lanes_allreduce<%s, 64>(r%d);", id, op, id);
-          e.line("  if ((threadIdx.x & 63) == 0) exch[%d][threadIdx.x >> 6] = r%d;", red_index, id);
-          e.line("  __syncthreads();");
-          e.line("  r%d = exch[%d][0];", id, red_index);
-          e.line("  UNROLL for (int w = 1; w < T; ++w) r%d = %s::apply(r%d, exch[%d][w]);", id, op, id, red_index);
-          ++red_index;
+          pending.push_back(Pending{id, sum});
+          if (n.out_ord >= 0) flush();
         } else if (mma) {
           e.line("  r%d = rows_allreduce<%s>(r%d);", id, op, id);
         } else if (L > 1) {
@@ -1795,7 +1826,14 @@ struct Gen {
       }
       e.line("  }");
     }
+    flush();
     if (persistent && rotating) {
+      if (T > 1 && A.n_reduce > 0) {
+        exchange_sets = rot_buffers;
+        // (with as many sets of slots as row buffers, two or more, a set is written again behind the next step's barrier: none is needed here)
+        const std::string one = "  __shared__ float exch[", decl = one + std::to_string(A.n_reduce) + "][T];";
+        e.s.replace(e.s.find(decl), decl.size(), one + std::to_string(rot_buffers) + "][" + std::to_string(A.n_reduce) + "][T];");
+      }
       e.line("  };");
       e.s.insert(e.s.rfind(loop_anchor), deferred_head);
       // whole trips over the buffers without a branch inside (one path through the loop: the waits on the
@@ -1855,51 +1893,55 @@ struct Gen {
       }
       e.line("  }");
     } else if (persistent && A.n_col > 0) {
-      e.line("  __shared__ double colacc[%d][%lld];", A.n_col, (long long)A.cols);
-      {
-        unsigned max_mask = 0;      // a maximum starts from -inf (one loop: each element is initialised by one thread)
-        int r = 0;
-        for (const RNode& n : A.nodes) if (n.cls == CLS_COL) { if (n.op == FS_REDUCE_MAX) max_mask |= 1u << r; ++r; }
-        if (max_mask == 0)
-          e.line("  for (int i = threadIdx.x; i < %lld; i += blockDim.x) (&colacc[0][0])[i] = 0.0;", (long long)A.n_col * A.cols);
-        else
-          e.line("  for (int i = threadIdx.x; i < %lld; i += blockDim.x) (&colacc[0][0])[i] = ((0x%xu >> (i / %lld)) & 1u) ? -__builtin_inf() : 0.0;",
-                 (long long)A.n_col * A.cols, max_mask, (long long)A.cols);
-      }
-      e.line("  __syncthreads();");
-      // fixed summation order (results are bit-reproducible): first the row groups of a wavefront
-      // (lanes that hold the same columns) by an xor butterfly, then the wavefronts one after the other
+      // The sums of a workgroup meet in LDS.  Slot layout: element j of chunk k of lane l at (k * W + j) * L + (l ^ j * L / 4), so that
+      // the lanes of an access touch different banks, when they add their sums (same j, all l) and when the columns are read in
+      // order (all j, few l).  The wavefronts take turns with the W * K rows of slots, all of them at work on a share of their own at a
+      // time: four steps of a quarter each for four wavefronts.  The order of the additions is fixed (results are
+      // bit-reproducible): first the row groups of a wavefront (lanes that hold the same columns) by an xor butterfly, then
+      // the wavefronts, from the one whose turn is first.  Measured against
+      // wavefronts one after the other and lanes W columns apart, LayerNorm backward: 300 x 1600 12.3 -> 10.6 us, 4407 x 138 9.2 -> 8.5, 2304 x 1510 18.7
+      // -> 17.0, 10624 x 658 20.9 -> 19.9, 16384 x 2048 76.7 -> 75.2; pooling of 512 runs of 50 x 256 8.6 -> 8.1; the backward tail of 16384 x 1024 64.7 -> 63.0.
+      e.line("  __shared__ double colacc[%d][K * W * L];", A.n_col);
       if (L < 64) {
         for (const RNode& n : A.nodes) if (n.cls == CLS_COL)
           e.line(n.op == FS_REDUCE_MAX
                      ? "  for (int m = L; m < 64; m <<= 1) UNROLL for (int k = 0; k < K; ++k) UNROLL for (int j = 0; j < W; ++j) ca%d[k][j] = fmax(ca%d[k][j], shfl_xor_f64(ca%d[k][j], m));"
                      : "  for (int m = L; m < 64; m <<= 1) UNROLL for (int k = 0; k < K; ++k) UNROLL for (int j = 0; j < W; ++j) ca%d[k][j] += shfl_xor_f64(ca%d[k][j], m);", n.id, n.id, n.id);
       }
-      e.line("  for (int w = 0; w < (int)blockDim.x / 64; ++w) {");
-      e.line("    if ((int)(threadIdx.x >> 6) == w && (int)(threadIdx.x & 63) < L) {");
+      // (a sum that is added to for the first time is stored: no zeros first)
+      e.line("  constexpr int NWAVE = %d, TURNS = NWAVE < K * W ? NWAVE : K * W;      // shares of the rows of slots", wg / 64);
+      e.line("  for (int turn = 0; turn < NWAVE; ++turn) {");
+      e.line("    const int share = __builtin_amdgcn_readfirstlane(((int)(threadIdx.x >> 6) + turn) %% NWAVE);      // of this wavefront, this turn");
+      e.line("    if ((int)(threadIdx.x & 63) < L) UNROLL for (int s = 0; s < TURNS; ++s) if (share == s) UNROLL for (int q = s; q < K * W; q += TURNS) {");
+      e.line("      const int k = q / W, j = q %% W, at = q * L + (lane ^ (j * L / 4 & (L - 1)));");
       int ci = 0;
       for (const RNode& n : A.nodes) if (n.cls == CLS_COL) {
-        e.line("      UNROLL for (int k = 0; k < K; ++k) {");
-        e.line("        if (!ok[k]) continue;");
-        if (n.op == FS_REDUCE_MAX) e.line("        UNROLL for (int j = 0; j < W; ++j) %scolacc[%d][col[k] + j] = fmax(colacc[%d][col[k] + j], ca%d[k][j]);", if_counts, ci, ci, n.id);
-        else e.line("        UNROLL for (int j = 0; j < W; ++j) %scolacc[%d][col[k] + j] += ca%d[k][j];", if_counts, ci, n.id);
-        e.line("      }");
+        if (n.op == FS_REDUCE_MAX) e.line("      colacc[%d][at] = turn == 0 ? ca%d[k][j] : fmax(colacc[%d][at], ca%d[k][j]);", ci, n.id, ci, n.id);
+        else e.line("      colacc[%d][at] = turn == 0 ? ca%d[k][j] : colacc[%d][at] + ca%d[k][j];", ci, n.id, ci, n.id);
         ++ci;
       }
       e.line("    }");
       e.line("    __syncthreads();");
       e.line("  }");
+      // column -> slot
+      if (ragged) {
+        const int64_t nvec = (A.cols + W - 1) / W;
+        e.line("  auto slot = [&](int i) { const bool end = i >= %lld; const int c = end ? %lld : i / W, j = end ? i - %lld : i %% W, l = c %% L; return (c / L * W + j) * L + (l ^ (j * L / 4 & (L - 1))); };",
+               (long long)((nvec - 1) * W), (long long)nvec - 1, (long long)(A.cols - W));
+      } else {
+        e.line("  auto slot = [&](int i) { const int c = i / W, j = i %% W, l = c %% L; return (c / L * W + j) * L + (l ^ (j * L / 4 & (L - 1))); };");
+      }
       if (direct) {
         int r = 0;
         for (const RNode& n : A.nodes) if (n.cls == CLS_COL) {
           char val[32];
-          snprintf(val, sizeof val, "colacc[%d][i]", r++);
+          snprintf(val, sizeof val, "colacc[%d][slot(i)]", r++);
           e.line("  for (int i = threadIdx.x; i < %lld; i += blockDim.x) %s", (long long)A.cols, direct_store(n, "i", val).c_str());
         }
       } else {
         e.line("  double* ws = static_cast<double*>(a.ws);");
         e.line("  for (int r = 0; r < %d; ++r)", A.n_col);
-        e.line("    for (int i = threadIdx.x; i < %lld; i += blockDim.x) ws[((long long)r * gridDim.x + blockIdx.x) * %lldll + i] = colacc[r][i];",
+        e.line("    for (int i = threadIdx.x; i < %lld; i += blockDim.x) ws[((long long)r * gridDim.x + blockIdx.x) * %lldll + i] = colacc[r][slot(i)];",
                (long long)A.cols, (long long)A.cols);
       }
     }
@@ -2431,6 +2473,7 @@ bool row_gen_plan(const Graph& g, const LaunchOpts& opt, RowGenLaunch* out, int*
     l.view_dense.push_back(dense ? 1 : 0);
   }
   gen.want_persistent = want_persistent;
+  gen.default_shape = opt.wg_size == 0 && opt.rows_per_wave == 0 && opt.grid == 0;
   if (const char* pf = getenv("FS_ROW_PREFETCH")) gen.force_prefetch = atoi(pf);   // measurement aid: 1 or 2 row steps requested ahead
   gen.wg = opt.wg_size && (opt.wg_size <= 256 || A.n_col > 0) ? opt.wg_size : 256;
   if (gen.wg & (gen.wg - 1)) gen.wg = gen.wg > 512 ? 512 : gen.wg > 256 ? 256 : 128;   // lanes per row divide the workgroup
@@ -2467,7 +2510,7 @@ bool row_gen_plan(const Graph& g, const LaunchOpts& opt, RowGenLaunch* out, int*
     l.L = gen.L; l.K = gen.K; l.W = gen.W;
     l.rows_read_before_written = !gen.long_row;      // (rows of that length take no update in place in either form)
     for (const RNode& n : A.nodes) if (n.op == ROP_DOT_OUTER || n.op == ROP_DOT_REDUCE) l.rows_read_before_written = false;
-    l.lds_bytes = gen.L > 64 ? (int64_t)A.n_reduce * (gen.L / 64) * 4 : gen.stage_bytes;
+    l.lds_bytes = gen.L > 64 ? (int64_t)A.n_reduce * (gen.L / 64) * 4 * gen.exchange_sets : gen.stage_bytes;
     l.wg = l.L > 64 ? l.L : gen.wg;     // a team is one workgroup per row
     const int64_t rows_per_wg = l.L > 64 ? 1 : l.wg / l.L;
     int64_t grid = (A.rows + rows_per_wg - 1) / rows_per_wg;
@@ -2489,6 +2532,7 @@ bool row_gen_plan(const Graph& g, const LaunchOpts& opt, RowGenLaunch* out, int*
         if (A.rows < 256) more = few;
         if (want > std::max(few, more)) want = std::max(few, more);
       }
+      if (gen.spread && want > 256) want = 256;      // (the partial rows that a wavefront per row would leave)
       if (want < grid) grid = want;
       if (n_seg > 0) grid = gen.seg_per_wave ? (n_seg + l.wg / 64 - 1) / (l.wg / 64) : n_seg * gen.seg_groups;      // the runs of rows fix the grid
       l.segmented = A.seg_rows > 0;
@@ -2501,7 +2545,7 @@ bool row_gen_plan(const Graph& g, const LaunchOpts& opt, RowGenLaunch* out, int*
         l.col_is_max[l.n_col] = n.op == FS_REDUCE_MAX ? 1 : 0;
         ++l.n_col;
       }
-      if (A.n_col > 0 && l.L <= 64 && !gen.seg_per_wave) l.lds_bytes = (int64_t)A.n_col * A.cols * 8;
+      if (A.n_col > 0 && l.L <= 64 && !gen.seg_per_wave) l.lds_bytes = (int64_t)A.n_col * gen.K * gen.W * gen.L * 8;
       l.seg_per_wave = gen.seg_per_wave;
       l.workspace_bytes = (n_seg > 0 && gen.seg_groups == 1) ? 0 : (int64_t)A.n_col * grid * A.cols * 8;
       l.n_kernels = A.n_col > 0 && l.workspace_bytes > 0 ? 2 : 1;

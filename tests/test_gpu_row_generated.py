@@ -658,3 +658,19 @@ def test_reduction_over_the_leading_dim_keeping_the_inner_dims(shape, dtype):
     with Plan(g.ops) as plan:
         assert plan.info()["schedule"] == "row_col"
     check_against_oracle(g.ops, ins, what=f"leading-dim reduction {shape}")
+
+
+@pytest.mark.parametrize("rows,cols", [(256, 1284), (300, 1801), (257, 2048), (1030, 1535), (259, 30), (1025, 139), (260, 1023)])
+@pytest.mark.parametrize("group", ["layernorm_bwd", "encoder_tail_bwd"])
+def test_column_sums_meet_in_lds_and_in_teams(rows, cols, group):
+    """The hand-over of running sums between the wavefronts of a workgroup (lanes per row of every width, whole and ragged chunks), and rows
+    of more than twenty elements a lane: a team from 256 rows on; both against the oracle, and the same twice."""
+    announce(f"column sums {group} {rows}x{cols}")
+    ops, ins = getattr(graphs, group)(rows, cols), getattr(inputs, group)(rows, cols)
+    with Plan(ops, "generated") as p:
+        assert ("CTA-S" in p.describe()) == (cols > 1280)
+    got, _ = check_against_oracle(ops, ins, "generated", what=f"{group} {rows}x{cols}")
+    for a, b in zip(got, run_gpu(ops, ins, "generated", launches=2)):
+        assert np.array_equal(a, b)
+    for opts in (dict(wg_size=512), dict(wg_size=128, grid=5), dict(wg_size=64, grid=300)):      # a wavefront per row with other numbers of wavefronts
+        check_against_oracle(ops, ins, "generated", what=f"{group} {rows}x{cols} {opts}", **opts)
