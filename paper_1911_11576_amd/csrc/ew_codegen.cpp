@@ -492,24 +492,28 @@ bool ew_compile_source(const std::string& source, std::vector<char>* code_object
   return true;
 }
 
-int ew_module_launch(EwModule* m, const std::vector<char>& code_object, const std::string& kernel_name,
-                     const void* args, size_t args_bytes, int grid, int block, void* stream, std::string* err, const EwModule* holder) {
+int ew_module_load(EwModule* m, const std::vector<char>& code_object, const std::string& kernel_name, std::string* err, const EwModule* holder) {
   int dev = -1;
   if (hipGetDevice(&dev) != hipSuccess) { *err = "hipGetDevice failed"; return -1; }
-  if (!m->function) {
-    hipModule_t mod = nullptr;
-    hipError_t e = hipSuccess;
-    if (holder) mod = static_cast<hipModule_t>(holder->module);
-    else e = hipModuleLoadData(&mod, code_object.data());
-    if (e != hipSuccess) { *err = std::string("hipModuleLoadData: ") + hipGetErrorString(e); return -1; }
-    hipFunction_t fn = nullptr;
-    e = hipModuleGetFunction(&fn, mod, kernel_name.c_str());
-    if (e != hipSuccess) { if (!holder) (void)hipModuleUnload(mod); *err = std::string("hipModuleGetFunction: ") + hipGetErrorString(e); return -1; }
-    m->module = holder ? nullptr : mod; m->function = fn; m->device = dev;
-  } else if (dev != m->device) {
-    *err = "plan is bound to the device of its first launch";
-    return -1;
+  if (m->function) {
+    if (dev != m->device) { *err = "plan is bound to the device of its first launch"; return -1; }
+    return 0;
   }
+  hipModule_t mod = nullptr;
+  hipError_t e = hipSuccess;
+  if (holder) mod = static_cast<hipModule_t>(holder->module);
+  else e = hipModuleLoadData(&mod, code_object.data());
+  if (e != hipSuccess) { *err = std::string("hipModuleLoadData: ") + hipGetErrorString(e); return -1; }
+  hipFunction_t fn = nullptr;
+  e = hipModuleGetFunction(&fn, mod, kernel_name.c_str());
+  if (e != hipSuccess) { if (!holder) (void)hipModuleUnload(mod); *err = std::string("hipModuleGetFunction: ") + hipGetErrorString(e); return -1; }
+  m->module = holder ? nullptr : mod; m->function = fn; m->device = dev;
+  return 0;
+}
+
+int ew_module_launch(EwModule* m, const std::vector<char>& code_object, const std::string& kernel_name,
+                     const void* args, size_t args_bytes, int grid, int block, void* stream, std::string* err, const EwModule* holder) {
+  if (ew_module_load(m, code_object, kernel_name, err, holder) != 0) return -1;
   size_t sz = args_bytes;
   void* config[] = {HIP_LAUNCH_PARAM_BUFFER_POINTER, const_cast<void*>(args), HIP_LAUNCH_PARAM_BUFFER_SIZE, &sz, HIP_LAUNCH_PARAM_END};
   const hipError_t e = hipModuleLaunchKernel(static_cast<hipFunction_t>(m->function), (unsigned)grid, 1, 1, (unsigned)block, 1, 1, 0,

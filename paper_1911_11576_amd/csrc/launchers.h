@@ -30,11 +30,16 @@ int row_block_launch(const RowSpec&, const RowBlockLaunch&, const void* const* i
                      void* stream, std::string* err);
 
 // LayerNorm backward: row path for dx packed with the column path for dgamma/dbeta.
-struct LnBwdLaunch { int K = 1, wg = 256, grid = 1, n_kernels = 1; int64_t lds_bytes = 0, workspace_bytes = 0; };
+struct LnBwdLaunch { int K = 1, wg = 256, grid = 1, n_kernels = 1; int64_t lds_bytes = 0, workspace_bytes = 0; bool packed = false; int T = 1, strip = 32; };   // packed: one launch; T wavefronts to a row, strips of columns
 bool lnbwd_stitch_plan(const LnBwdSpec&, const LaunchOpts&, LnBwdLaunch*, std::string* err);
 std::string lnbwd_stitch_describe(const LnBwdSpec&, const LnBwdLaunch&);
 int lnbwd_stitch_launch(const LnBwdSpec&, const LnBwdLaunch&, const void* const* in, void* const* out,
                         void* workspace, void* stream, std::string* err);
+
+// The same over few rows as one launch: row path and column path as workgroups of their own.
+bool lnbwd_packed_plan(const LnBwdSpec&, const LaunchOpts&, LnBwdLaunch*);
+std::string lnbwd_packed_describe(const LnBwdLaunch&);
+int lnbwd_packed_launch(const LnBwdSpec&, const LnBwdLaunch&, const void* const* in, void* const* out, void* stream, std::string* err);
 
 // Batched dot -> softmax -> batched dot on MFMA.
 struct AttnLaunch { int wg = 256, grid = 1, nq = 4, nk = 4; bool decode = false; int64_t lds_bytes = 0; };   // nq, nk: 16-row tiles of queries (= wavefronts) and of keys

@@ -296,6 +296,32 @@ def test_layernorm_bwd_shapes(rows, cols, mode):
     check_against_oracle(graphs.layernorm_bwd(rows, cols), inputs.layernorm_bwd(rows, cols), mode, what=f"lnbwd {rows}x{cols}")
 
 
+@pytest.mark.parametrize("rows,cols", [(256, 4), (257, 5), (300, 31), (1024, 33), (401, 255), (400, 257), (999, 511), (1024, 1024), (513, 1025), (301, 1027), (260, 2048), (450, 2049), (258, 4095), (256, 4096)])
+def test_layernorm_bwd_in_one_launch(rows, cols):
+    """Few rows: the row path and strips of columns as workgroups of one launch; edges of vectors, strips, wavefronts and teams, the rule's
+    corners; bit-reproducible.  Where the generated kernel is the only other form, an update in place takes that form."""
+    announce(f"layernorm_bwd in one launch {rows}x{cols}")
+    ops, ins = graphs.layernorm_bwd(rows, cols), inputs.layernorm_bwd(rows, cols)
+    with Plan(ops) as p:
+        assert p.info()["n_kernels"] == 1 and p.info()["workspace_bytes"] == 0 and "strip of" in p.describe()
+    got, want = check_against_oracle(ops, ins, what=f"lnbwd {rows}x{cols}")
+    for a, b in zip(got, run_gpu(ops, ins, launches=2)):
+        assert np.array_equal(a, b)
+    dev_in, outs = to_device(ops, ins), alloc_outputs(ops)
+    with Plan(ops) as p:
+        if cols % 4 == 0 and cols <= 1024:
+            with pytest.raises(FsError):
+                p.launch(dev_in, [dev_in[0]] + outs[1:])
+            return
+        p.launch(dev_in, outs)
+        for launch in (p.launch_static, p.launch):
+            dev_in = to_device(ops, ins)
+            launch(dev_in, [dev_in[0]] + outs[1:])
+            torch.cuda.synchronize()
+            for a, b in zip([dev_in[0]] + outs[1:], want):
+                assert_close(a.double().cpu().numpy(), b, 1e-5, f"lnbwd in place {rows}x{cols}")
+
+
 @pytest.mark.parametrize("mode", LNBWD_MODES)
 @pytest.mark.parametrize("opts", [dict(grid=1), dict(grid=3, wg_size=64), dict(grid=100, wg_size=256), dict(grid=1024)])
 def test_layernorm_bwd_launch_options(opts, mode):
