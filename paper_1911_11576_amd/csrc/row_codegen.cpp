@@ -611,6 +611,12 @@ static __device__ __forceinline__ double shfl_xor_f64(double v, int mask) {
 template <int CTRL> static __device__ __forceinline__ float dpp_move(float v) {
   return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, false));
 }
+// e^x for x <= 0 (or NaN): exp2 of the rounded product, times what the product's rounding and log2(e)'s left out; below -104 e^x is 0 in fp32
+static __device__ __forceinline__ float exp_nonpositive(float x) {
+  x = x < -104.0f ? -104.0f : x;
+  const float p = x * 1.44269502f, r = fmaf(x, 1.925963033500e-08f, fmaf(x, 1.44269502f, -p)), y = __builtin_amdgcn_exp2f(p);
+  return fmaf(y, r * 0.69314718f, y);
+}
 struct std_true { static constexpr bool value = true; };      // compile-time switches handed to generic lambdas
 struct std_false { static constexpr bool value = false; };
 struct SumOp { static __device__ __forceinline__ float apply(float a, float b) { return a + b; } };
@@ -949,6 +955,30 @@ struct Gen {
     }
     return readers == 1 && reductions == 1;
   }
+  // A maximum m of x and the sum of exp(x - m), where nothing else reads the exponentials (log-softmax, log-sum-exp): both in one
+  // go over the row as it arrives.  Found by the maximum's node; -1 where there is none.
+  struct Online { int max_id = -1, exp_id = -1, sum_id = -1, sub_id = -1; bool sub_read = false; };
+  Online find_online() const {
+    for (const RNode& m : A.nodes) {
+      if (m.op != FS_REDUCE_MAX || m.cls != CLS_ROW || m.over_dot_out) continue;
+      for (const RNode& d : A.nodes) {
+        if (d.op != FS_SUBTRACT || d.cls != CLS_FULL || d.o[1].kind != OP_ROWB || d.o[1].index != m.id || d.o[0].kind != m.o[0].kind || d.o[0].index != m.o[0].index) continue;
+        if (d.o[0].kind != OP_NODE && d.o[0].kind != OP_VIEW) continue;
+        for (const RNode& x : A.nodes) {
+          if (x.op != FS_EXP || x.out_ord >= 0 || x.o[0].kind != OP_NODE || x.o[0].index != d.id || !read_by_one_reduction(x.id)) continue;
+          for (const RNode& q : A.nodes) {
+            if (q.op != FS_REDUCE_SUM || q.cls != CLS_ROW || q.over_dot_out || q.o[0].kind != OP_NODE || q.o[0].index != x.id) continue;
+            Online o;
+            o.max_id = m.id; o.sub_id = d.id; o.exp_id = x.id; o.sum_id = q.id;
+            o.sub_read = d.out_ord >= 0;
+            for (const RNode& y : A.nodes) if (y.id != x.id) for (int j = 0; j < y.nop; ++j) if (y.o[j].kind == OP_NODE && y.o[j].index == d.id) o.sub_read = true;
+            return o;
+          }
+        }
+      }
+    }
+    return Online();
+  }
   // Full values alive at once: the operands loaded at the top until their last use, computed values from their op to
   // their last use (one that only a reduction reads is consumed element by element).
   int live_values() const {
@@ -979,8 +1009,8 @@ struct Gen {
   }
   // A row of more than 32 elements per thread of a full workgroup still lives in its registers where no more than 88 of
   // a thread's 128 hold values (chunk by chunk code without interleaving keeps the others few).  One read and one write instead of
-  // a read per pass: log-softmax over 512 rows of 50257 fp32 47.6 us (streamed in three passes, element by element, 81.9), of
-  // 50257 bf16 21.6 (54.0), of 65536 fp32 56.6 (79.1), 64 rows of 50257 fp32 11.6 (32.4), RMSNorm over 512 x 43000 fp32 34.7
+  // a read per pass: log-softmax over 512 rows of 50257 fp32 47.6 us before its maximum and sum went in one go, 39.4 now (streamed in three passes, element by
+  // element, 81.9), of 50257 bf16 20.1 (54.0), of 65536 fp32 53.1 (79.1), RMSNorm over 512 x 43000 fp32 34.7
   // (41.2).  Up to 72 values none of these spill; softmax with its log-sum-exp in fp32 spills 4 registers at 77824 columns and 16 to 21
   // from 84000 to 90112, which is still the faster form by far (512 x 90112 86.4, streamed 118.5).  16-bit rows with more than one
   // live value stay streamed: their row fits the LDS buffers (RMSNorm over 512 x 36000 bf16 15.2 streamed, 16.1 here).
@@ -1429,6 +1459,13 @@ struct Gen {
       }
       if (A.has_causal) e.line("  const long long irow = i%d;      // the row's index in the second-to-last dim", nrow - 1);
     }
+    // Maximum and sum of exponentials in one go.  Measured on log-softmax, apart and in one go (these rows are bound by memory, but a
+    // workgroup of 1024 threads that holds a row is alone on its CU unless 64 registers are enough, and then loads, works and stores in turn):
+    // 512 x 50257 fp32 48.2 and 39.4 us, 300 x 45001 30.1 and 21.4, 64 x 64300 15.4 and 11.4, 1024 x 32768 55.3 and 44.9, 3000 x 9001 40.6 and 40.0;
+    // 1856 x 33152 bf16 49.5 and 43.7, 586 x 17994 8.8 and 8.8, 844 x 10176 bf16 6.3 and 6.6: there an exponential is two instructions, and the running
+    // maximum costs more than it saves up to 16384 columns.
+    const Online online = T > 1 && !persistent && (!fast || A.cols > 16384) ? find_online() : Online();
+    const bool scalar_starts = long_row && online.max_id >= 0;      // a chunk's start in scalar registers: one lane offset serves all chunks but the last
     // ---- loads
     // In the persistent form the next row's vectors are requested before the current row is
     // worked on (raw, still packed) and unpacked one iteration later: with few wavefronts per
@@ -1593,7 +1630,13 @@ struct Gen {
       const char* ld = dense && !ragged ? "__builtin_nontemporal_load" : "*";
       e.line("  float v%zu[K][W];", q);
       e.line("  UNROLL for (int k = 0; k < K; ++k) {");
-      e.line("    const %s* p = static_cast<const %s*>(a.in[%zu]) + (%s) + col[k];", ty, ty, q, roff[q].c_str());
+      if (scalar_starts) {
+        e.line("    long long at = (%s) + (k + 1 < K ? k * L * W : 0);", roff[q].c_str());
+        e.line("    asm(\"\" : \"+s\"(at));");
+        e.line("    const %s* p = static_cast<const %s*>(a.in[%zu]) + at + (k + 1 < K ? lane * W : col[k]);", ty, ty, q);
+      } else {
+        e.line("    const %s* p = static_cast<const %s*>(a.in[%zu]) + (%s) + col[k];", ty, ty, q, roff[q].c_str());
+      }
       if (W == 1) {
         e.line("    v%zu[k][0] = %s;", q, one);
       } else if (v.dtype == FS_F32 && W == 2) {
@@ -1642,6 +1685,41 @@ struct Gen {
     };
     for (const RNode& n : A.nodes) {
       const bool reduce = n.op == FS_REDUCE_SUM || n.op == FS_REDUCE_MAX;
+      if (online.max_id >= 0 && (n.id == online.exp_id || (n.id == online.sub_id && !online.sub_read))) continue;
+      if (online.max_id >= 0 && n.id == online.max_id) {
+        flush();
+        // A thread's running maximum and sum, chunk by chunk while the later ones are on their way: the exponentials cost no time of their
+        // own.  (Maxima of -inf stand for the least finite value in exponents, so that chunks of -inf add nothing to rows that have more.)
+        const std::string x = opnd(n.o[0], CLS_FULL), ex = fast ? "exp_fast" : "exp_nonpositive";
+        const int m = n.id, q = online.sum_id;
+        e.line("  float r%d = -__builtin_inff(), r%d = 0.0f;", m, q);
+        e.line("  UNROLL for (int k = 0; k < K; ++k) {");
+        e.line("    __builtin_amdgcn_sched_barrier(0);");
+        if (!exact) e.line("    if (!ok[k]) continue;");
+        // (a branch the compiler cannot see through, as a partial last chunk has: without one it interleaves what is behind the loop with it and takes
+        // up to 21 registers more: 85 instead of 64 at 53248 columns)
+        else if (long_row) e.line("    if (k + 1 == K) { int go = 1; asm(\"\" : \"+s\"(go)); if (!go) continue; }");
+        e.line("    float m = r%d;", m);
+        e.line("    UNROLL for (int j = 0; j < W; ++j) %sm = fmaxf(m, %s);", if_counts, x.c_str());
+        e.line("    const float mf = fmaxf(m, -3.402823466e38f);");
+        e.line("    if (k > 0) r%d = r%d * %s(r%d - mf);", q, q, ex.c_str(), m);
+        e.line("    UNROLL for (int j = 0; j < W; ++j) %sr%d = r%d + %s(%s - mf);", if_counts, q, q, ex.c_str(), x.c_str());
+        e.line("    r%d = m;", m);
+        e.line("  }");
+        e.line("  {");
+        e.line("    const float own = fmaxf(r%d, -3.402823466e38f);", m);
+        e.line("    r%d = lanes_allreduce<MaxOp, 64>(r%d);", m, m);
+        e.line("    r%d = lanes_allreduce<SumOp, 64>(r%d * %s(own - fmaxf(r%d, -3.402823466e38f)));", q, q, ex.c_str(), m);
+        e.line("    if ((threadIdx.x & 63) == 0) { exch[%d][threadIdx.x >> 6] = r%d; exch[%d][threadIdx.x >> 6] = r%d; }", red_index, m, red_index + 1, q);
+        e.line("    __syncthreads();");
+        // (a lane to a wavefront's results: sixteen of each in every lane's registers are what the row's values leave no room for)
+        e.line("    const float wm = exch[%d][threadIdx.x & (T - 1)];", red_index);
+        e.line("    r%d = lanes_allreduce<MaxOp, T>(wm);", m);
+        e.line("    r%d = lanes_allreduce<SumOp, T>(exch[%d][threadIdx.x & (T - 1)] * %s(fmaxf(wm, -3.402823466e38f) - fmaxf(r%d, -3.402823466e38f)));", q, red_index + 1, ex.c_str(), m);
+        e.line("  }");
+        red_index += 2;
+      }
+      const bool made = online.max_id >= 0 && (n.id == online.max_id || n.id == online.sum_id);      // its value is there
       for (int j = 0; j < n.nop; ++j)
         for (const Pending& q : pending) if ((n.o[j].kind == OP_NODE || n.o[j].kind == OP_ROWB) && n.o[j].index == q.id) { flush(); break; }
       // combine the lanes' partial results of reduction r<id> (wavefront steps, then LDS across wavefronts)
@@ -1671,6 +1749,7 @@ struct Gen {
         e.line("  UNROLL for (int dt = 0; dt < D2 / 16; ++dt) UNROLL for (int i = 0; i < 4; ++i) r%d = %s;", n.id,
                sum ? ("r" + std::to_string(n.id) + " + " + x).c_str() : ("fmaxf(r" + std::to_string(n.id) + ", " + x + ")").c_str());
         combine(n.id, sum);
+      } else if (made) {
       } else if (reduce) {
         const bool sum = n.op == FS_REDUCE_SUM;
         const bool inlined = n.o[0].kind == OP_NODE && inline_expr.count(n.o[0].index) > 0;
@@ -1805,8 +1884,17 @@ struct Gen {
         e.line("      continue;");
         e.line("    }");
       }
+      auto store_at = [&](const char* ty) {
+        if (scalar_starts) {
+          e.line("    long long at = row * %lldll + (k + 1 < K ? k * L * W : 0);", (long long)A.cols);
+          e.line("    asm(\"\" : \"+s\"(at));");
+          e.line("    %s* p = static_cast<%s*>(a.out[%d]) + at + (k + 1 < K ? lane * W : col[k]);", ty, ty, n.out_ord);
+        } else {
+          e.line("    %s* p = static_cast<%s*>(a.out[%d]) + row * %lldll + col[k];", ty, ty, n.out_ord, (long long)A.cols);
+        }
+      };
       if (n.out_dtype == FS_F32) {
-        e.line("    float* p = static_cast<float*>(a.out[%d]) + row * %lldll + col[k];", n.out_ord, (long long)A.cols);
+        store_at("float");
         if (W == 1) e.line("    p[0] = t%d[k][0];", n.id);
         else if (W == 2) e.line("    __builtin_nontemporal_store(f32x2{t%d[k][0], t%d[k][1]}, reinterpret_cast<f32x2*>(p));", n.id, n.id);
         else for (int h = 0; h < W / 4; ++h)
@@ -1814,7 +1902,7 @@ struct Gen {
                  al.c_str(), n.id, 4 * h, n.id, 4 * h + 1, n.id, 4 * h + 2, n.id, 4 * h + 3, al.c_str(), h);
       } else {
         const char* cv = n.out_dtype == FS_F16 ? "to_f16" : "to_bf16";
-        e.line("    unsigned short* p = static_cast<unsigned short*>(a.out[%d]) + row * %lldll + col[k];", n.out_ord, (long long)A.cols);
+        store_at("unsigned short");
         if (W == 1) e.line("    p[0] = (unsigned short)%s(t%d[k][0]);", cv, n.id);
         else {
           e.line("    unsigned w[W / 2];");

@@ -674,3 +674,54 @@ def test_column_sums_meet_in_lds_and_in_teams(rows, cols, group):
         assert np.array_equal(a, b)
     for opts in (dict(wg_size=512), dict(wg_size=128, grid=5), dict(wg_size=64, grid=300)):      # a wavefront per row with other numbers of wavefronts
         check_against_oracle(ops, ins, "generated", what=f"{group} {rows}x{cols} {opts}", **opts)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
+@pytest.mark.parametrize("cols", [2052, 4099, 9001, 16385, 32768, 32769, 45056, 50257, 53248, 57001, 90000])
+def test_maximum_and_sum_of_exponentials_in_one_go(cols, dtype):
+    """Log-softmax of rows for a team: rows of ordinary values, of values far apart in rising and falling order (every chunk has a new maximum, or
+    none), with elements of -inf, of the type's lowest value, and with what makes the row NaN."""
+    announce(f"log-softmax in one go {cols} {dtype}")
+    rows = 9
+    ops = graphs.log_softmax((rows, cols), dtype)
+    x = inputs.normal_tensors([(rows, cols)], dtype, scale=3.0)[0]
+    lowest = {"f32": -3.4028234663852886e38, "bf16": -3.3895313892515355e38, "f16": -65504.0}[dtype]
+    x[1] = np.linspace(-200.0, 90.0, cols)
+    x[2] = x[1][::-1]
+    x[3, : cols // 2] = -np.inf                      # whole chunks of nothing
+    x[4, ::3] = lowest
+    x[5] = lowest                                    # a row of equal values: -log(cols)
+    x[6, cols - 1] = 80.0                            # the maximum in the last, moved chunk
+    x = inputs.round_to(x, dtype)
+    with np.errstate(invalid="ignore"):
+        want = interp.run(ops, [x])[0]
+    got = run_gpu(ops, [x])[0]
+    same = np.isinf(want)
+    assert np.array_equal(same, np.isinf(got)) and np.array_equal(np.sign(want[same]), np.sign(got[same]))
+    assert_close(np.where(same, 0.0, got), np.where(same, 0.0, want), TOLERANCE[dtype], f"log-softmax {cols} {dtype}")
+    for bad in (np.full(cols, -np.inf), np.where(np.arange(cols) == cols // 3, np.inf, 0.0), np.where(np.arange(cols) == 5, np.nan, 0.0)):
+        x[7] = bad
+        out = run_gpu(ops, [inputs.round_to(x, dtype)])[0]
+        assert np.isnan(out[7]).all() and np.array_equal(out[:7], got[:7])
+
+
+@pytest.mark.parametrize("cols", [2052, 40001, 45056])
+def test_maximum_and_sum_in_one_go_beside_other_outputs(cols):
+    """The maximum, the sum and the difference as outputs too, an elementwise prologue, and a group that also reads the exponentials (apart)."""
+    announce(f"log-sum-exp forms {cols}")
+    for reads_exponentials in (False, True):
+        g = graphs.Graph()
+        x = g.parameter("x", "f32", (6, cols))
+        b = g.parameter("b", "f32", (cols,))
+        z = g.add(g.multiply(x, g.constant(0.5)), g.col_broadcast(b, x))
+        m = g.reduce_max(z, 1)
+        d = g.subtract(z, g.row_broadcast(m, z))
+        e = g.exp(d)
+        s = g.reduce_sum(e, 1)
+        g.output(g.add(m, g.log(s)), "lse")
+        g.output(m, "max")
+        g.output(s, "sum")
+        if reads_exponentials:
+            g.output(g.divide(e, g.row_broadcast(s, e)), "softmax")
+        ins = inputs.normal_tensors([(6, cols), (cols,)], scale=2.0)
+        check_against_oracle(g.ops, ins, what=f"log-sum-exp {cols} {reads_exponentials}")
