@@ -590,7 +590,10 @@ class FusedProgram:
                 used_by.setdefault(i, set()).add(k)
         returned = {ops[i].operands[0] for i in self.output_ops}
         taken, launches = set(), []
+        tuned = fs_tune_cache_size() > 0
         for last, g in enumerate(groups):
+            if all(ops[i].shape == () for i in g["output_of"]):
+                continue                                   # (makes scalars itself)
             made = [i for i in g["input_of"] if ops[i].shape == () and i in self._made_by]
             members, stack = {last}, [self._made_by[i] for i in made]
             while stack:
@@ -602,7 +605,7 @@ class FusedProgram:
                 continue
             if any(used_by.get(i, set()) - members or i in returned for k in members - {last} for i in groups[k]["output_of"]):
                 continue
-            if any(fs_tune_cache_has(fs_group_key(groups[k]["ops"])) for k in members):
+            if tuned and any(fs_tune_cache_has(fs_group_key(groups[k]["ops"])) for k in members):
                 continue
             outputs = list(g["output_of"])
             inside, leaves, stack = set(), set(), list(outputs)
