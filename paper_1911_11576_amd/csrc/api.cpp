@@ -428,6 +428,10 @@ fs_status plan_create_impl(const fs_op_desc* ops, int32_t n_ops, const fs_plan_o
             delete p;
             return set_error(bad_opt ? FS_ERR_INVALID : FS_ERR_UNSUPPORTED, err);
           }
+          if (fs::lnbwd_takes_ragged(p->match.lnbwd, lo)) {
+            int st2 = FS_OK;
+            p->in_place_form = fs::row_gen_plan(p->graph, lo, &p->row_gen, &st2, &gen_err);
+          }
           p->schedule = FS_SCHED_ROW_COL;
           p->lds_bytes = p->lnbwd.lds_bytes;
           p->workspace_bytes = p->lnbwd.workspace_bytes;
@@ -569,7 +573,9 @@ fs_status fs_launch(fs_plan* p, const void* const* inputs, int32_t n_in, void* c
     int dev = -1;
     if (hipGetDevice(&dev) != hipSuccess) return set_error(FS_ERR_HIP, "hipGetDevice failed");
     if (!p->workspace) {
-      const hipError_t e = hipMalloc(&p->workspace, (size_t)bytes);
+      // (of a plan with two forms, enough for either)
+      const int64_t most = p->in_place_form && p->row_gen.workspace_bytes > p->workspace_bytes ? p->row_gen.workspace_bytes : p->workspace_bytes;
+      const hipError_t e = hipMalloc(&p->workspace, (size_t)most);
       if (e != hipSuccess) { p->workspace = nullptr; return set_error(FS_ERR_NOMEM, std::string("workspace hipMalloc: ") + hipGetErrorString(e)); }
       p->device = dev;
     } else if (dev != p->device) {

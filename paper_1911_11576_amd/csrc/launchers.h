@@ -31,6 +31,7 @@ int row_block_launch(const RowSpec&, const RowBlockLaunch&, const void* const* i
 
 // LayerNorm backward: row path for dx packed with the column path for dgamma/dbeta.
 struct LnBwdLaunch { int K = 1, wg = 256, grid = 1, n_kernels = 1; int64_t lds_bytes = 0, workspace_bytes = 0; bool packed = false; int T = 1, strip = 32; };   // packed: one launch; T wavefronts to a row, strips of columns
+bool lnbwd_takes_ragged(const LnBwdSpec&, const LaunchOpts&);      // rows of no whole number of vectors that the hand-written kernel takes
 bool lnbwd_stitch_plan(const LnBwdSpec&, const LaunchOpts&, LnBwdLaunch*, std::string* err);
 std::string lnbwd_stitch_describe(const LnBwdSpec&, const LnBwdLaunch&);
 int lnbwd_stitch_launch(const LnBwdSpec&, const LnBwdLaunch&, const void* const* in, void* const* out,

@@ -37,7 +37,7 @@ static constexpr int64_t kLdsMax = 160 * 1024 - 1024;
 struct LnBwdArgs {
   const float* dy; const float* x; const float* gamma; const float* mean; const float* rstd;
   float* dx; float* dgamma; float* dbeta;
-  int64_t rows; int cols; int nvec; float inv_n;
+  int64_t rows; int cols; int nvec; float inv_n;      // nvec: vectors of a row, the last one moved back to end with the row where four do not divide it
   double* part;       // [grid][2*K*256]   one partial row (slot layout) per workgroup
 };
 
@@ -46,7 +46,9 @@ struct LnBwdArgs {
 // PF: row steps requested ahead of the one being worked on
 // MAXWG: largest workgroup the instance is launched with (256: one wavefront per SIMD may use the
 // whole register file; 512: two share it)
-template <int K, bool WANT_DX, int COL, bool EXACT, int PF, int MAXWG>
+// WHOLE: rows of whole vectors.  Otherwise vectors are read and written at element alignment, through the caches (neighbouring rows share
+// lines), and the first elements of a row's last vector, its neighbour's too, count in nothing.
+template <int K, bool WANT_DX, int COL, bool EXACT, int PF, int MAXWG, bool WHOLE = true>
 __global__ __launch_bounds__(MAXWG)
 void lnbwd_rows_kernel(const LnBwdArgs a) {
   extern __shared__ double lds[];   // [waves][2*K*256] slots
@@ -60,12 +62,16 @@ void lnbwd_rows_kernel(const LnBwdArgs a) {
     const int vi = k * 64 + lane;
     vld[k] = EXACT || vi < a.nvec;
     voff[k] = (vld[k] ? vi : 0) * 4;
+    if (!WHOLE && vi == a.nvec - 1) voff[k] = a.cols - 4;
   }
+  // elements of the lane's last vector that its neighbour holds too (the row's last vector is in the last set)
+  const int skip = !WHOLE && (K - 1) * 64 + lane == a.nvec - 1 ? a.nvec * 4 - a.cols : 0;
+  auto counts = [&](int k, int j) { return WHOLE || k < K - 1 ? vld[k] : vld[k] && j >= skip; };
   float gam[K][4];
   double dg[K][4], db[K][4];
 #pragma unroll
   for (int k = 0; k < K; ++k) {
-    if constexpr (WANT_DX) Vec<float>::load(a.gamma + voff[k], gam[k]);
+    if constexpr (WANT_DX) Vec<float>::unpack(cached_load<float, WHOLE>(a.gamma + voff[k]), gam[k]);
 #pragma unroll
     for (int j = 0; j < 4; ++j) { dg[k][j] = 0.0; db[k][j] = 0.0; }
   }
@@ -91,8 +97,8 @@ void lnbwd_rows_kernel(const LnBwdArgs a) {
     if constexpr (NEED_X) { rmu[b] = a.mean[r]; rrs[b] = a.rstd[r]; }
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-      rdy[b][k] = stream_load16(a.dy + r * a.cols + voff[k]);
-      if constexpr (NEED_X) rx[b][k] = stream_load16(a.x + r * a.cols + voff[k]);
+      rdy[b][k] = stream_load<float, WHOLE>(a.dy + r * a.cols + voff[k]);
+      if constexpr (NEED_X) rx[b][k] = stream_load<float, WHOLE>(a.x + r * a.cols + voff[k]);
     }
   };
 #pragma unroll
@@ -122,7 +128,7 @@ void lnbwd_rows_kernel(const LnBwdArgs a) {
     for (int k = 0; k < K; ++k) {
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        const float d = vld[k] ? dy[k][j] : 0.f;
+        const float d = counts(k, j) ? dy[k][j] : 0.f;
         if constexpr (NEED_X) xv[k][j] = fmaf(xv[k][j], rs, nmurs);      // xhat = (x - mu) * rs
         if constexpr (WANT_COL) db[k][j] += (double)d;
         if constexpr (COL == 2) dg[k][j] += (double)(d * xv[k][j]);
@@ -145,10 +151,15 @@ void lnbwd_rows_kernel(const LnBwdArgs a) {
         for (int j = 0; j < 4; ++j) {
           // (with four vectors per lane dy * gamma is multiplied out again rather than kept: sixteen registers
           // fewer is what keeps three row buffers, the fp64 sums and gamma inside the 256 vector registers)
-          const float gj = KEEP_G ? g[k][j] : (vld[k] ? dy[k][j] : 0.f) * gam[k][j];
+          const float gj = KEEP_G ? g[k][j] : (counts(k, j) ? dy[k][j] : 0.f) * gam[k][j];
           o[j] = fmaf(xv[k][j], nc2, fmaf(gj, rs, nc1));
         }
-        if (vld[k]) stream_store16(a.dx + r * a.cols + voff[k], pack16<float>(o));
+        if (!WHOLE && k == K - 1 && skip > 0) {
+#pragma unroll
+          for (int j = 0; j < 4; ++j) if (j >= skip) a.dx[r * a.cols + voff[k] + j] = o[j];
+        } else if (vld[k]) {
+          stream_store<float, WHOLE>(a.dx + r * a.cols + voff[k], pack16<float>(o));
+        }
       }
     }
   };
@@ -190,7 +201,7 @@ void lnbwd_rows_kernel(const LnBwdArgs a) {
 // with 16 the 16 lanes of a slice read one whole 128-byte line of a partial row.
 template <int SL, int NT = 256, int NL = 8>
 __global__ __launch_bounds__(NT)
-void lnbwd_combine_kernel(const double* __restrict__ part, int groups, int K, int nvec, float* dgamma, float* dbeta) {
+void lnbwd_combine_kernel(const double* __restrict__ part, int groups, int K, int nvec, int cols, float* dgamma, float* dbeta) {
   constexpr int NS = NT / SL;           // slices
   __shared__ double stage[NS][SL + 1];
   const int n2 = 2 * K * 256;
@@ -217,9 +228,9 @@ void lnbwd_combine_kernel(const double* __restrict__ part, int groups, int K, in
     // slot -> column
     const int slots = K * 256;
     const int r = s >= slots ? 1 : 0, q = (s - r * slots) >> 6, vi = (q >> 2) * 64 + (s & 63);
-    const int col = vi * 4 + (q & 3);
+    const int col = vi < nvec - 1 ? vi * 4 + (q & 3) : cols - 4 + (q & 3);
     float* o = r ? dgamma : dbeta;
-    if (vi < nvec && o) o[col] = (float)t;
+    if (vi < nvec && col >= vi * 4 && o) o[col] = (float)t;
   }
 }
 constexpr int kCombineSlots = 16;
@@ -261,6 +272,7 @@ hipError_t launch_KEW(const LnBwdArgs& a, bool want_dx, bool want_col, int grid,
 template <int K>
 hipError_t launch_K(const LnBwdArgs& a, bool want_dx, bool want_col, int grid, int wg, size_t lds,
                     hipStream_t s) {
+  if (a.cols % 4 != 0) return launch_with_lds(lnbwd_rows_kernel<K, true, 2, false, kPrefetch, 256, false>, a, grid, wg, lds, s);
   const bool exact = a.nvec == K * 64;
   if (wg <= 256) return exact ? launch_KEW<K, true, 256>(a, want_dx, want_col, grid, wg, lds, s)
                               : launch_KEW<K, false, 256>(a, want_dx, want_col, grid, wg, lds, s);
@@ -270,12 +282,21 @@ hipError_t launch_K(const LnBwdArgs& a, bool want_dx, bool want_col, int grid, i
 
 }  // namespace
 
+// Rows of no whole number of vectors: with all three outputs, from 1025 rows of 128 elements on.  The generated kernel, which is what such rows had (single
+// elements or vectors at element alignment, one row ahead), against this one: LayerNorm backward over 2000 x 255 11.5 and 6.4 us, 4407 x 138 8.3 and 7.4, 2000 x
+// 1023 13.9 and 11.1, 20000 x 511 32.3 and 23.9, 10624 x 658 20.0 and 18.9, 32768 x 1023 78.8 and 77.8, 32768 x 159 18.7 and 17.9; the other way round 32768 x
+// 131 16.1 and 17.9, where 33 of a wavefront's lanes hold a vector.  Fewer rows have a launch of their own kind (lnbwd_packed.hip), the fewest the generated kernel.
+bool lnbwd_takes_ragged(const LnBwdSpec& sp, const LaunchOpts& opt) {
+  return opt.codegen && opt.wg_size == 0 && opt.rows_per_wave == 0 && opt.grid == 0 && sp.cols % 4 != 0 && sp.cols >= 128 && sp.cols <= 1024 && sp.rows > 1024 && (sp.cols >= 160 || sp.rows <= 16384) &&
+         sp.out_dx >= 0 && sp.out_dgamma >= 0 && sp.out_dbeta >= 0;
+}
+
 bool lnbwd_stitch_plan(const LnBwdSpec& sp, const LaunchOpts& opt, LnBwdLaunch* out, std::string* err) {
-  if (sp.cols % 4 != 0) { *err = "LayerNorm-backward schedule: cols must be a multiple of 4"; return false; }
+  if (sp.cols % 4 != 0 && !lnbwd_takes_ragged(sp, opt)) { *err = "LayerNorm-backward schedule: cols must be a multiple of 4"; return false; }
   // a lane holds its columns' fp64 running sums: 4 vectors of 4 columns is what fits
   if (sp.cols > 1024) { *err = "LayerNorm-backward schedule: cols > 1024 exceed one wavefront's register tile"; return false; }
   LnBwdLaunch l;
-  const int need = (int)((sp.cols / 4 + 63) / 64);
+  const int need = (int)(((sp.cols + 3) / 4 + 63) / 64);
   l.K = 4;
   for (int k : kKs) if (k >= need) { l.K = k; break; }
   // 4 wavefronts per workgroup and one workgroup per CU: one wavefront per SIMD has the whole
@@ -326,7 +347,7 @@ int lnbwd_stitch_launch(const LnBwdSpec& sp, const LnBwdLaunch& l, const void* c
   a.dx = want_dx ? static_cast<float*>(out[sp.out_dx]) : nullptr;
   a.dgamma = sp.out_dgamma >= 0 ? static_cast<float*>(out[sp.out_dgamma]) : nullptr;
   a.dbeta = sp.out_dbeta >= 0 ? static_cast<float*>(out[sp.out_dbeta]) : nullptr;
-  a.rows = sp.rows; a.cols = (int)sp.cols; a.nvec = (int)(sp.cols / 4);
+  a.rows = sp.rows; a.cols = (int)sp.cols; a.nvec = (int)((sp.cols + 3) / 4);
   a.inv_n = (float)(1.0 / (double)sp.cols);
   a.part = static_cast<double*>(workspace);
   hipStream_t s = static_cast<hipStream_t>(stream);
@@ -346,7 +367,7 @@ int lnbwd_stitch_launch(const LnBwdSpec& sp, const LnBwdLaunch& l, const void* c
   }
   if (want_col) {
     // sums over zero rows are zero: the combine kernel over zero partial rows writes them
-    hipLaunchKernelGGL(lnbwd_combine_kernel<kCombineSlots>, dim3(2 * l.K * 256 / kCombineSlots), dim3(256), 0, s, a.part, groups, l.K, a.nvec, a.dgamma, a.dbeta);
+    hipLaunchKernelGGL(lnbwd_combine_kernel<kCombineSlots>, dim3(2 * l.K * 256 / kCombineSlots), dim3(256), 0, s, a.part, groups, l.K, a.nvec, a.cols, a.dgamma, a.dbeta);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) { *err = std::string("lnbwd_combine launch: ") + hipGetErrorString(e); return -1; }
   }

@@ -322,6 +322,30 @@ def test_layernorm_bwd_in_one_launch(rows, cols):
                 assert_close(a.double().cpu().numpy(), b, 1e-5, f"lnbwd in place {rows}x{cols}")
 
 
+@pytest.mark.parametrize("rows,cols", [(1025, 129), (1100, 255), (2051, 257), (1030, 513), (4099, 767), (1500, 769), (1033, 1021), (1040, 1022), (1027, 1023)])
+def test_layernorm_bwd_rows_of_no_whole_vectors(rows, cols):
+    """The hand-written rows kernel at element alignment: one to three elements over, one vector over a set of 64, trips of every length;
+    bit-reproducible, updates in place through the generated form, the prebuilt mode as before."""
+    announce(f"layernorm_bwd ragged {rows}x{cols}")
+    ops, ins = graphs.layernorm_bwd(rows, cols), inputs.layernorm_bwd(rows, cols)
+    with Plan(ops) as p:
+        assert "hand-written" in p.describe() and p.info()["n_kernels"] == 2
+    with pytest.raises(FsError):
+        Plan(ops, "prebuilt")
+    got, want = check_against_oracle(ops, ins, what=f"lnbwd {rows}x{cols}")
+    for a, b in zip(got, run_gpu(ops, ins, launches=2)):
+        assert np.array_equal(a, b)
+    dev_in, outs = to_device(ops, ins), alloc_outputs(ops)
+    with Plan(ops) as p:
+        p.launch(dev_in, outs)
+        for launch in (p.launch_static, p.launch, p.launch_static):
+            dev_in = to_device(ops, ins)
+            launch(dev_in, [dev_in[0]] + outs[1:])
+            torch.cuda.synchronize()
+            for a, b in zip([dev_in[0]] + outs[1:], want):
+                assert_close(a.double().cpu().numpy(), b, 1e-5, f"lnbwd in place {rows}x{cols}")
+
+
 @pytest.mark.parametrize("mode", LNBWD_MODES)
 @pytest.mark.parametrize("opts", [dict(grid=1), dict(grid=3, wg_size=64), dict(grid=100, wg_size=256), dict(grid=1024)])
 def test_layernorm_bwd_launch_options(opts, mode):
