@@ -188,7 +188,7 @@ fs_status fs_plan_create_packed(const fs_op_desc* const* groups, const int32_t* 
 /* A group in which values reduced over whole tensors feed ops on whole tensors (clipping by a global norm), as two
  * kernels: chains of reductions of one kind from elementwise ops on inputs down to rank 0, elementwise ops on those
  * scalars, and elementwise ops on tensors of any number of shapes (up to 16 independent parts) that read the scalars
- * through broadcasts; tensor operands of the tensors' own shapes, scalars in f32.  fs_plan_create takes no such group,
+ * through broadcasts; tensor operands of the tensors' own shapes, scalars in f32, up to 400 MB of tensors.  fs_plan_create takes no such group,
  * and the planner cuts it.
  *   partial_bytes  host, receives the size of the partial results that the first kernel hands to the second.  The
  *                  caller gives fs_launch a device buffer of that size as ONE MORE OUTPUT, behind the group's own; nothing in

@@ -42,7 +42,7 @@ struct Emitter {
 
 constexpr int kThreads = 256;
 // Partial results in all: one per workgroup of the first kernel, and a workgroup of the second reads every one of them.
-constexpr int64_t kPartials = 8192;
+constexpr int64_t kPartials = 4096;
 
 struct Reduction { int node = -1; bool is_max = false; int part = -1; int64_t first = 0, count = 0; };
 
@@ -93,9 +93,9 @@ bool is_fast(const EwIr& ir) {      // as in the elementwise kernels: 16-bit gro
 const char* raw_type(int dtype, int W) { return dtype == FS_F32 ? (W == 4 ? "f32x4" : "float") : W == 8 ? "u32x4" : W == 4 ? "u32x2" : "unsigned short"; }
 
 // requests of U chunks: raw<k>[u], addresses clamped to the tensor (`last` is the last valid chunk of the workgroup's run)
-void emit_requests(Emitter& e, const Part& p, const char* last, bool nontemporal) {
+void emit_requests(Emitter& e, const Part& p, const char* last, bool nontemporal, bool declare = true) {
   for (size_t k = 0; k < p.ir.views.size(); ++k)
-    if (p.scalar_of_view[k] < 0) e.line("    %s raw%zu[U];", raw_type(p.ir.views[k].dtype, p.W), k);
+    if (declare && p.scalar_of_view[k] < 0) e.line("    %s raw%zu[U];", raw_type(p.ir.views[k].dtype, p.W), k);
   e.line("    UNROLL for (int u = 0; u < U; ++u) {");
   e.line("      long long c = c0 + u * %d + (int)threadIdx.x;", kThreads);
   e.line("      c = c > %s ? %s : c;", last, last);
@@ -393,17 +393,22 @@ bool two_step_plan(const Graph& g, TwoStepLaunch* out, std::string* err) {
   // thread in the first and eight in the second 22.2; as four launches of packed groups 26.3.  Sixteen of width 1600, 164 MB: 76, four launches
   // and twelve single scalars 104; 2.6 MB: 6.1 with a workgroup on every CU, 6.8 with two, 8.3 as four launches.  Ordinary loads in the
   // second kernel: 22.3 and 84; nontemporal ones in the first: 23.3 and 84; the second kernel's workgroups in reverse
-  // order: no gain (19.4 and 76).  Up to 8192 partial results 76.0, up to 4096 79.3, up to 16384 75.9.
+  // order: no gain (19.4 and 76).  Up to 4096 partial results, a workgroup going on to its next run behind the first: 210 MB in two
+  // tensors 95.5 us, up to 8192 109, up to 1024 95.1, as launches of their own 105.8; 335 MB in sixteen 153, 155 and 160.
   int64_t total = 0, total2 = 0;
   int widest = 1;
   for (const Part& p : first) { total += p.n_chunks; widest = std::max(widest, p.n_full); }
   for (const Part& p : second) { total2 += p.n_chunks; widest = std::max(widest, p.n_full); }
+  // (beyond that the launches of their own are ahead: one tensor of 537 MB 249 us, 260 so)
+  int64_t read = 0;
+  for (const Part& p : first) for (const EwIrView& v : p.ir.views) read += p.ir.n * (v.dtype == FS_F32 ? 4 : 2);
+  if (read > (400ll << 20)) return fail("tensors of more than 400 MB");
   int U = std::max(1, 8 / widest);
   while (U > 1 && std::max(total, total2) < (int64_t)U * kThreads * 256) U /= 2;
   const int64_t run = (int64_t)U * kThreads;
   const int64_t per = ((total + kPartials - 1) / kPartials + run - 1) / run * run;      // chunks of a workgroup of the first kernel
   for (Part& p : first) p.blocks = (p.n_chunks + per - 1) / per;
-  for (Part& p : second) p.blocks = (p.n_chunks + run - 1) / run;
+  for (Part& p : second) p.blocks = (p.n_chunks + per - 1) / per;
 
   // ---- first kernel's text
   Emitter e;
@@ -475,16 +480,26 @@ static __device__ __forceinline__ double wave_max(double v) { UNROLL for (int m 
   for (size_t k = 0; k < scalar_param.size(); ++k) if (scalar_param[k] >= 1000) { input_slot[k] = (int)l.view_param[1].size(); l.view_param[1].push_back(scalar_param[k] - 1000); }
   if (l.view_param[1].size() > 64) return fail("more than 64 operand views");
   // Every workgroup adds the partial results: a wavefront takes its share of the reductions whole, so that each is one
-  // straight line of loads and one butterfly.
-  std::vector<size_t> by_count(reds.size());
-  for (size_t r = 0; r < reds.size(); ++r) by_count[r] = r;
-  std::stable_sort(by_count.begin(), by_count.end(), [&](size_t x, size_t y) { return reds[x].count > reds[y].count; });
+  // straight line of loads and one butterfly; one of more than 1024 partial results (a single large tensor) is cut into four.
+  struct Piece { size_t red; int64_t first, count; };
+  std::vector<Piece> pieces;
+  std::vector<std::vector<size_t>> pieces_of(reds.size());
+  for (size_t r = 0; r < reds.size(); ++r) {
+    const int64_t cuts = reds[r].count > 1024 ? 4 : 1, each = (reds[r].count + cuts - 1) / cuts;
+    for (int64_t from = 0; from < reds[r].count; from += each) {
+      pieces_of[r].push_back(pieces.size());
+      pieces.push_back(Piece{r, reds[r].first + from, std::min(each, reds[r].count - from)});
+    }
+  }
+  std::vector<size_t> by_count(pieces.size());
+  for (size_t r = 0; r < pieces.size(); ++r) by_count[r] = r;
+  std::stable_sort(by_count.begin(), by_count.end(), [&](size_t x, size_t y) { return pieces[x].count > pieces[y].count; });
   std::vector<std::vector<size_t>> share(kThreads / 64);
   std::vector<int64_t> load(kThreads / 64, 0);
   for (size_t r : by_count) {
     const size_t w = std::min_element(load.begin(), load.end()) - load.begin();
     share[w].push_back(r);
-    load[w] += (reds[r].count + 63) / 64 + 2;
+    load[w] += (pieces[r].count + 63) / 64 + 2;
   }
   Emitter pro;
   pro.line("    {");
@@ -494,11 +509,15 @@ static __device__ __forceinline__ double wave_max(double v) { UNROLL for (int m 
     if (share[w].empty()) continue;
     pro.line("      if (wave == %zu) {", w);
     for (size_t r : share[w]) {
-      pro.line("        double q%zu = %s;", r, reds[r].is_max ? "-__builtin_inf()" : "0.0");
-      pro.line("        UNROLL for (int i = 0; i < %lld; ++i) { const int at = i * 64 + lane; if (at < %lld) q%zu = %s; }", (long long)((reds[r].count + 63) / 64), (long long)reds[r].count, r,
-               ((reds[r].is_max ? "fmax(q" + std::to_string(r) + ", ps[" : "q" + std::to_string(r) + " + (ps[") + std::to_string(reds[r].first) + " + at])").c_str());
+      const Piece& q = pieces[r];
+      const bool mx = reds[q.red].is_max;
+      pro.line("        double q%zu = %s;", r, mx ? "-__builtin_inf()" : "0.0");
+      // (sixteen loads in flight at most: all of a large one's at once would take registers from the tensors)
+      pro.line("        %s for (int i = 0; i < %lld; ++i) { const int at = i * 64 + lane; if (at < %lld) q%zu = %s; }", q.count > 1024 ? "_Pragma(\"unroll 8\")" : "UNROLL",
+               (long long)((q.count + 63) / 64), (long long)q.count, r,
+               ((mx ? "fmax(q" + std::to_string(r) + ", ps[" : "q" + std::to_string(r) + " + (ps[") + std::to_string(q.first) + " + at])").c_str());
     }
-    for (size_t r : share[w]) pro.line("        q%zu = %s(q%zu);", r, reds[r].is_max ? "wave_max" : "wave_sum", r);
+    for (size_t r : share[w]) pro.line("        q%zu = %s(q%zu);", r, reds[pieces[r].red].is_max ? "wave_max" : "wave_sum", r);
     pro.line("        if (lane == 0) {");
     for (size_t r : share[w]) pro.line("          red[%zu] = q%zu;", r, r);
     pro.line("        }");
@@ -510,10 +529,13 @@ static __device__ __forceinline__ double wave_max(double v) { UNROLL for (int m 
   pro.line("    {");
   pro.line("      constexpr int j = 0;");
   auto param_text = [&](int k) {
-    char buf[96];
-    if (scalar_param[k] >= 1000) snprintf(buf, sizeof buf, "static_cast<const float*>(a.in[%d])[0]", input_slot[k]);
-    else snprintf(buf, sizeof buf, "(float)red[%d]", scalar_param[k]);
-    return std::string(buf);
+    if (scalar_param[k] >= 1000) return "static_cast<const float*>(a.in[" + std::to_string(input_slot[k]) + "])[0]";
+    std::string t;
+    for (size_t q : pieces_of[scalar_param[k]]) {
+      const std::string one = "red[" + std::to_string(q) + "]";
+      t = t.empty() ? one : reds[scalar_param[k]].is_max ? "fmax(" + t + ", " + one + ")" : t + " + " + one;
+    }
+    return "(float)(" + t + ")";
   };
   for (size_t k = 0; k < scalar_param.size(); ++k) pro.line("      const float v%zu[1] = {%s};", k, param_text((int)k).c_str());
   for (const EwIrNode& x : scalars) pro.line("      const float t%d[1] = {%s};", x.id, ew_op_text(x, false).c_str());
@@ -528,21 +550,27 @@ static __device__ __forceinline__ double wave_max(double v) { UNROLL for (int m 
   for (size_t q = 0; q < second.size(); ++q) {
     const Part& p = second[q];
     Emitter b;
-    b.line("    constexpr int W = %d, U = %d;", p.W, U);
-    b.line("    const long long c0 = (long long)(blockIdx.x - first) * (U * %d);", kThreads);
-    // the tensors' requests go out before the partial results are asked for
-    emit_requests(b, p, "(NV - 1)", true);
+    b.line("    constexpr int W = %d, U = %d; constexpr long long per = %lld;", p.W, U, (long long)per);
+    b.line("    const long long lo = (long long)(blockIdx.x - first) * per, hi = lo + per < NV ? lo + per : NV;");
+    b.line("    long long c0 = lo;");
+    // the tensors' first requests go out before the partial results are asked for
+    emit_requests(b, p, "(hi - 1)", true);
     b.s += pro.s;
+    b.line("    for (;;) {");
     b.line("    UNROLL for (int u = 0; u < U; ++u) {");
     b.line("      const long long c = c0 + u * %d + (int)threadIdx.x;", kThreads);
     b.line("      const long long e0 = c == NV - 1 ? N - W : c * W;");
-    b.line("      const int own = c >= NV ? 0 : c == NV - 1 ? (int)(N - (NV - 1) * W) : W;      // elements of the chunk that are not its neighbour's");
+    b.line("      const int own = c >= hi ? 0 : c == NV - 1 ? (int)(N - (NV - 1) * W) : W;      // elements of the chunk that are not its neighbour's");
     emit_ops(b, p, true);
+    b.line("    }");
+    b.line("    c0 += U * %d;", kThreads);
+    b.line("    if (c0 >= hi) break;");
+    emit_requests(b, p, "(hi - 1)", true, false);
     b.line("    }");
     cls2.add((int)q, b.s);
   }
   e.line("extern \"C\" __global__ __launch_bounds__(%d) void FS_GRID_APPLY(const Args a) {", kThreads);
-  e.line("  __shared__ double red[%zu];", reds.size());
+  e.line("  __shared__ double red[%zu];", pieces.size());
   at = 0;
   for (size_t k = 0; k < cls2.text.size(); ++k) {
     int64_t blocks = 0;
@@ -578,7 +606,7 @@ static __device__ __forceinline__ double wave_max(double v) { UNROLL for (int m 
   l.n_scalar_ops = (int)scalars.size();
   l.parts = (int)second.size();
   l.wg = kThreads;
-  l.lds_bytes = std::max<int64_t>(32, (int64_t)reds.size() * 8);
+  l.lds_bytes = std::max<int64_t>(32, (int64_t)pieces.size() * 8);
   *out = l;
   return true;
 }

@@ -611,12 +611,6 @@ static __device__ __forceinline__ double shfl_xor_f64(double v, int mask) {
 template <int CTRL> static __device__ __forceinline__ float dpp_move(float v) {
   return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, false));
 }
-// e^x for x <= 0 (or NaN): exp2 of the rounded product, times what the product's rounding and log2(e)'s left out; below -104 e^x is 0 in fp32
-static __device__ __forceinline__ float exp_nonpositive(float x) {
-  x = x < -104.0f ? -104.0f : x;
-  const float p = x * 1.44269502f, r = fmaf(x, 1.925963033500e-08f, fmaf(x, 1.44269502f, -p)), y = __builtin_amdgcn_exp2f(p);
-  return fmaf(y, r * 0.69314718f, y);
-}
 struct std_true { static constexpr bool value = true; };      // compile-time switches handed to generic lambdas
 struct std_false { static constexpr bool value = false; };
 struct SumOp { static __device__ __forceinline__ float apply(float a, float b) { return a + b; } };
@@ -639,6 +633,16 @@ template <class Op, int L> static __device__ __forceinline__ float lanes_allredu
     v = Op::apply(bits_f32(lo), bits_f32(hi));
   }
   return v;
+}
+)SRC";
+
+// what a maximum and a sum of exponentials in one go add in fp32 groups
+const char* kOnlinePreamble = R"SRC(
+// e^x for x <= 0 (or NaN): exp2 of the rounded product, times what the product's rounding and log2(e)'s left out; below -104 e^x is 0 in fp32
+static __device__ __forceinline__ float exp_nonpositive(float x) {
+  x = x < -104.0f ? -104.0f : x;
+  const float p = x * 1.44269502f, r = fmaf(x, 1.925963033500e-08f, fmaf(x, 1.44269502f, -p)), y = __builtin_amdgcn_exp2f(p);
+  return fmaf(y, r * 0.69314718f, y);
 }
 )SRC";
 
@@ -860,6 +864,7 @@ struct Gen {
   int64_t stage_bytes = 0;
   int exchange_sets = 1;      // of a team's exchange slots
   bool default_shape = false; // the caller fixes no launch shape
+  bool in_one_go = false;     // the kernel needs kOnlinePreamble
   bool spread = false;        // a row that a wavefront could hold, given to a team
 
   // Row steps requested ahead in the persistent form: one, or two (FS_ROW_PREFETCH=2): two row buffers per
@@ -1329,6 +1334,14 @@ struct Gen {
     e.s += kReducePreamble;
     if (mma) e.s += kMmaPreamble;
     if (ragged) e.s += kRaggedPreamble;
+    // Maximum and sum of exponentials in one go.  Measured on log-softmax, apart and in one go (these rows are bound by memory, but a
+    // workgroup of 1024 threads that holds a row is alone on its CU unless 64 registers are enough, and then loads, works and stores in turn):
+    // 512 x 50257 fp32 48.2 and 39.4 us, 300 x 45001 30.1 and 21.4, 64 x 64300 15.4 and 11.4, 1024 x 32768 55.3 and 44.9, 3000 x 9001 40.6 and 40.0;
+    // 1856 x 33152 bf16 49.5 and 43.7, 586 x 17994 8.8 and 8.8, 844 x 10176 bf16 6.3 and 6.6: there an exponential is two instructions, and the running
+    // maximum costs more than it saves up to 16384 columns.
+    const Online online = L > 64 && !persistent && !mma && (!fast || A.cols > 16384) ? find_online() : Online();
+    in_one_go = online.max_id >= 0 && !fast;
+    if (in_one_go) e.s += kOnlinePreamble;
     const std::string al = ragged ? "e" : "";       // the vector types' suffix
     const char* if_counts = ragged ? "if (j >= lo[k]) " : "";   // an element of a chunk that is its own
     const int T = L > 64 ? L / 64 : 1;      // wavefronts per row
@@ -1459,12 +1472,6 @@ struct Gen {
       }
       if (A.has_causal) e.line("  const long long irow = i%d;      // the row's index in the second-to-last dim", nrow - 1);
     }
-    // Maximum and sum of exponentials in one go.  Measured on log-softmax, apart and in one go (these rows are bound by memory, but a
-    // workgroup of 1024 threads that holds a row is alone on its CU unless 64 registers are enough, and then loads, works and stores in turn):
-    // 512 x 50257 fp32 48.2 and 39.4 us, 300 x 45001 30.1 and 21.4, 64 x 64300 15.4 and 11.4, 1024 x 32768 55.3 and 44.9, 3000 x 9001 40.6 and 40.0;
-    // 1856 x 33152 bf16 49.5 and 43.7, 586 x 17994 8.8 and 8.8, 844 x 10176 bf16 6.3 and 6.6: there an exponential is two instructions, and the running
-    // maximum costs more than it saves up to 16384 columns.
-    const Online online = T > 1 && !persistent && (!fast || A.cols > 16384) ? find_online() : Online();
     const bool scalar_starts = long_row && online.max_id >= 0;      // a chunk's start in scalar registers: one lane offset serves all chunks but the last
     // ---- loads
     // In the persistent form the next row's vectors are requested before the current row is
@@ -2760,7 +2767,7 @@ bool row_gen_plan_packed(const std::vector<Graph>& graphs, const std::vector<cha
   struct Part { int64_t grid; std::string body; };
   std::vector<Part> parts;
   RowGenLaunch l;
-  bool any_ragged = false;
+  bool any_ragged = false, any_in_one_go = false;
   int64_t lds = 0;
   int param_base = 0, out_base = 0;      // of the groups taken so far: their parameters and outputs follow each other
   for (size_t gi = 0; gi < graphs.size(); ++gi) {
@@ -2807,6 +2814,7 @@ bool row_gen_plan_packed(const std::vector<Graph>& graphs, const std::vector<cha
     l.n_ops += (int)A.nodes.size();
     l.n_reduce += A.n_reduce;
     any_ragged = any_ragged || gen.ragged;
+    any_in_one_go = any_in_one_go || gen.in_one_go;
     lds += part_lds;
     l.grid = (int)(parts.empty() ? grid : l.grid + grid);
     parts.push_back(Part{grid, body});
@@ -2819,6 +2827,7 @@ bool row_gen_plan_packed(const std::vector<Graph>& graphs, const std::vector<cha
   e.s = ew_preamble();
   e.s += kReducePreamble;
   if (any_ragged) e.s += kRaggedPreamble;
+  if (any_in_one_go) e.s += kOnlinePreamble;
   std::vector<size_t> order(parts.size());
   for (size_t k = 0; k < parts.size(); ++k) order[k] = k;
   std::stable_sort(order.begin(), order.end(), [&](size_t a, size_t b) { return parts[a].grid < parts[b].grid; });

@@ -725,3 +725,18 @@ def test_maximum_and_sum_in_one_go_beside_other_outputs(cols):
             g.output(g.divide(e, g.row_broadcast(s, e)), "softmax")
         ins = inputs.normal_tensors([(6, cols), (cols,)], scale=2.0)
         check_against_oracle(g.ops, ins, what=f"log-sum-exp {cols} {reads_exponentials}")
+
+
+def test_maximum_and_sum_in_one_go_in_a_packed_launch():
+    announce("log-softmax teams in a packed launch")
+    shapes = [((30, 5000), "f32"), ((20, 3001), "f32"), ((7, 4099), "bf16")]
+    lists = [graphs.log_softmax(s, d) for s, d in shapes]
+    ins = [inputs.normal_tensors([s], d, scale=3.0) for s, d in shapes]
+    plan, taken = Plan.packed([binding.marshal_ops(ops) for ops in lists])
+    outs = [o for ops in lists for o in alloc_outputs(ops)]
+    with plan:
+        assert taken == [0, 1, 2]
+        plan.launch([t for ops, x in zip(lists, ins) for t in to_device(ops, x)], outs)
+        torch.cuda.synchronize()
+    for got, ops, x, (_, d) in zip(outs, lists, ins, shapes):
+        assert_close(got.double().cpu().numpy(), interp.run(ops, x)[0], TOLERANCE[d], "packed log-softmax")

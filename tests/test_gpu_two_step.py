@@ -71,6 +71,7 @@ CASES = [
     ([(1024, 1024), (1024, 1030), (1021, 1021)], "f32"),      # beyond 1024 runs of 1024 chunks together with the next
     ([(2300, 2049)], "f32"),
     ([(1000, 4099)], "bf16"),
+    ([(2048, 8197), (5,)], "f32"),                             # more than 1024 partial results of one tensor
 ]
 
 
