@@ -800,7 +800,7 @@ def test_two_step_groups_on_the_host():
         with pytest.raises(FsError) as e:
             Plan.two_step(_clip(shapes, wrong))
         assert e.value.status == binding.FS_ERR_UNSUPPORTED, wrong
-    for ops in (graphs.layernorm_fwd(8, 64), graphs.bias_gelu_residual(8, 64, "f32"), graphs.sigmoid_attention(2, 16, 16, 32, 32), _clip([(0, 4)])):
+    for ops in (graphs.layernorm_fwd(8, 64), graphs.bias_gelu_residual(8, 64, "f32"), graphs.sigmoid_attention(2, 16, 16, 32, 32), _clip([(0, 4)]), _clip([(16384, 8192)])):
         with pytest.raises(FsError) as e:
             Plan.two_step(ops)
         assert e.value.status == binding.FS_ERR_UNSUPPORTED
