@@ -208,7 +208,9 @@ fs_status fs_plan_create_two_step(const fs_op_desc* ops, int32_t n_ops, int64_t*
  * given the very pointer of a parameter of its own shape and dtype where the plan runs a
  * generated elementwise kernel or a generated register row kernel (fs_plan_describe says so)
  * and reads that parameter only in the group's own layout (not through a broadcast); such
- * kernels read every element in the thread, or the row's lanes, that later writes it.  Any
+ * kernels read every element in the thread, or the row's lanes, that later writes it.  A hand-written
+ * LayerNorm backward plan whose description says "in place of dy or x" takes dx in either's buffer
+ * too, in the same workspace (or none), by two launches instead of one where the description says that.  Any
  * other identical pointer is refused with FS_ERR_INVALID; partial overlaps are not detected.  A plan that owns a workspace (fs_plan_info) must
  * not have two launches in flight at once; the workspace is allocated on the first
  * launch on the then-current device and the plan stays bound to that device.

@@ -410,11 +410,8 @@ fs_status plan_create_impl(const fs_op_desc* ops, int32_t n_ops, const fs_plan_o
           // takes the shape (fp32, up to 1024 columns); the generated kernel serves the other shapes and
           // FS_MODE_STITCHED_GENERATED.
           if (want_generated && fall_back_to_generated()) break;
-          // Few rows: one launch.  Shapes that only the generated kernel takes otherwise keep it for updates in place, in which the
-          // workgroups of one launch would write what others still read.
-          if (const bool taken = p->match.lnbwd.cols % 4 == 0 && p->match.lnbwd.cols <= 1024; !want_generated && (taken || lo.codegen) && fs::lnbwd_packed_plan(p->match.lnbwd, lo, &p->lnbwd)) {
-            int st2 = FS_OK;
-            if (!taken) p->in_place_form = fs::row_gen_plan(p->graph, lo, &p->row_gen, &st2, &gen_err);
+          // Few rows: one launch.
+          if (!want_generated && (lo.codegen || (p->match.lnbwd.cols % 4 == 0 && p->match.lnbwd.cols <= 1024)) && fs::lnbwd_packed_plan(p->match.lnbwd, lo, &p->lnbwd)) {
             p->schedule = FS_SCHED_ROW_COL;
             p->lds_bytes = p->lnbwd.lds_bytes;
             p->n_kernels = 1;
@@ -427,10 +424,6 @@ fs_status plan_create_impl(const fs_op_desc* ops, int32_t n_ops, const fs_plan_o
             if (!bad_opt && !gen_err.empty()) err += "; " + gen_err;
             delete p;
             return set_error(bad_opt ? FS_ERR_INVALID : FS_ERR_UNSUPPORTED, err);
-          }
-          if (fs::lnbwd_takes_ragged(p->match.lnbwd, lo)) {
-            int st2 = FS_OK;
-            p->in_place_form = fs::row_gen_plan(p->graph, lo, &p->row_gen, &st2, &gen_err);
           }
           p->schedule = FS_SCHED_ROW_COL;
           p->lds_bytes = p->lnbwd.lds_bytes;
@@ -496,7 +489,8 @@ fs_status fs::check_launch_args(fs_plan* p, const void* const* inputs, int32_t n
     // An output in the very buffer of a parameter (an update in place): fine where the kernel reads
     // every element of that parameter once, in the thread (or the row's lanes) that writes the same
     // element, before it writes -- the generated elementwise kernels and the generated register
-    // row kernels, for parameters of the output's own shape and dtype that are read in no other way.
+    // row kernels, for parameters of the output's own shape and dtype that are read in no other way, and the
+    // hand-written LayerNorm backward where its plan says so, for dx.
     for (int k = 0; k < n_in; ++k) {
       if (inputs[k] != outputs[i] || g[g.params[k]].numel() == 0) continue;
       const fs::Node& pn = g[g.params[k]];
@@ -505,27 +499,21 @@ fs_status fs::check_launch_args(fs_plan* p, const void* const* inputs, int32_t n
       const std::vector<int>* vp = nullptr;
       const std::vector<char>* vf = nullptr;
       if (ok && p->schedule == FS_SCHED_ELEMENTWISE && p->ew.generated) { vp = &p->ew.view_param; vf = &p->ew.view_full; }
-      else if (ok && (p->row_form == 3 || p->in_place_form) && !p->row_gen.streamed && p->row_gen.rows_read_before_written &&
+      else if (ok && p->schedule == FS_SCHED_ROW_COL && p->row_form != 3 && p->lnbwd.in_place) ok = !fs::lnbwd_broadcasts(p->match.lnbwd, pn.ordinal);      // (dy and x have dx's shape alone)
+      else if (ok && p->row_form == 3 && !p->row_gen.streamed && p->row_gen.rows_read_before_written &&
                (p->schedule == FS_SCHED_ROW || p->schedule == FS_SCHED_ROW_COL)) { vp = &p->row_gen.view_param; vf = &p->row_gen.view_dense; }
       else ok = false;
-      for (size_t q = 0; ok && q < vp->size(); ++q) if ((*vp)[q] == pn.ordinal && !(*vf)[q]) ok = false;
+      for (size_t q = 0; ok && vp && q < vp->size(); ++q) if ((*vp)[q] == pn.ordinal && !(*vf)[q]) ok = false;
       if (!ok) return set_error(FS_ERR_INVALID, "an output shares its buffer with an input that this plan may still read after writing it "
-                                                "(in-place updates: generated elementwise and register row kernels, same shape and dtype, parameter read only as the group's own layout)");
+                                                "(in-place updates: generated elementwise and register row kernels, LayerNorm backward plans that say so; same shape and dtype, parameter read only as the group's own layout)");
     }
   }
   return FS_OK;
 }
 
-int64_t fs::launch_workspace(const fs_plan* p, const void* const* inputs, int32_t n_in, void* const* outputs, int32_t n_out, bool* in_place) {
-  *in_place = false;
-  if (p->in_place_form)
-    for (int i = 0; i < n_out; ++i) for (int k = 0; k < n_in; ++k) if (inputs[k] == outputs[i] && p->graph[p->graph.outputs[i]].numel() != 0) *in_place = true;
-  return *in_place ? p->row_gen.workspace_bytes : p->workspace_bytes;
-}
-
 // The plan's kernels enqueued with `workspace` as their scratch memory (the plan's own, or the static array).
 fs_status fs::enqueue_plan(fs_plan* p, const void* const* inputs, void* const* outputs, int32_t n_out, void* workspace,
-                              void* hip_stream, bool in_place) {
+                              void* hip_stream) {
   std::string err;
   try {
     int rc = 0;
@@ -537,9 +525,9 @@ fs_status fs::enqueue_plan(fs_plan* p, const void* const* inputs, void* const* o
                                 : fs::row_stitch_launch(p->match.row, p->row, inputs, outputs, hip_stream, &err);
         break;
       case FS_SCHED_ROW_COL:
-        rc = p->row_form == 3 || in_place ? fs::row_gen_launch(p->row_gen, inputs, outputs, n_out, workspace, hip_stream, &err)
-             : p->lnbwd.packed            ? fs::lnbwd_packed_launch(p->match.lnbwd, p->lnbwd, inputs, outputs, hip_stream, &err)
-                                          : fs::lnbwd_stitch_launch(p->match.lnbwd, p->lnbwd, inputs, outputs, workspace, hip_stream, &err);
+        rc = p->row_form == 3  ? fs::row_gen_launch(p->row_gen, inputs, outputs, n_out, workspace, hip_stream, &err)
+             : p->lnbwd.packed ? fs::lnbwd_packed_launch(p->match.lnbwd, p->lnbwd, inputs, outputs, hip_stream, &err)
+                               : fs::lnbwd_stitch_launch(p->match.lnbwd, p->lnbwd, inputs, outputs, workspace, hip_stream, &err);
         break;
       case FS_SCHED_BLOCK_DOT: rc = fs::row_gen_launch(p->row_gen, inputs, outputs, n_out, workspace, hip_stream, &err); break;
       case FS_SCHED_BDOT_SOFTMAX: rc = fs::attn_stitch_launch(p->match.attn, p->attn, inputs, outputs, hip_stream, &err); break;
@@ -560,29 +548,20 @@ fs_status fs_launch(fs_plan* p, const void* const* inputs, int32_t n_in, void* c
                     void* hip_stream) {
   const fs_status st = fs::check_launch_args(p, inputs, n_in, outputs, n_out);
   if (st != FS_OK) return st;
-  bool in_place = false;
-  const int64_t bytes = fs::launch_workspace(p, inputs, n_in, outputs, n_out, &in_place);
-  if (p->in_place_form && !p->row_gen.loaded.function) {
-    // both forms are on the device after the first launch, as fs_launch_static asks for
-    std::string err;
-    if (fs::ew_module_load(&p->row_gen.loaded, p->row_gen.code_object, p->row_gen.kernel_name, &err) != 0) return set_error(FS_ERR_HIP, err);
-  }
-  if (bytes > 0) {
+  if (p->workspace_bytes > 0) {
     // Nothing in the workspace needs an initial value: every kernel that reads it reads only what an
     // earlier kernel of the same launch wrote there.
     int dev = -1;
     if (hipGetDevice(&dev) != hipSuccess) return set_error(FS_ERR_HIP, "hipGetDevice failed");
     if (!p->workspace) {
-      // (of a plan with two forms, enough for either)
-      const int64_t most = p->in_place_form && p->row_gen.workspace_bytes > p->workspace_bytes ? p->row_gen.workspace_bytes : p->workspace_bytes;
-      const hipError_t e = hipMalloc(&p->workspace, (size_t)most);
+      const hipError_t e = hipMalloc(&p->workspace, (size_t)p->workspace_bytes);
       if (e != hipSuccess) { p->workspace = nullptr; return set_error(FS_ERR_NOMEM, std::string("workspace hipMalloc: ") + hipGetErrorString(e)); }
       p->device = dev;
     } else if (dev != p->device) {
       return set_error(FS_ERR_INVALID, "plan is bound to the device of its first launch");
     }
   }
-  return fs::enqueue_plan(p, inputs, outputs, n_out, p->workspace, hip_stream, in_place);
+  return fs::enqueue_plan(p, inputs, outputs, n_out, p->workspace, hip_stream);
 }
 
 fs_status fs_plan_tune(const fs_op_desc* ops, int32_t n_ops, const void* const* inputs, int32_t n_in,

@@ -492,7 +492,8 @@ bool ew_compile_source(const std::string& source, std::vector<char>* code_object
   return true;
 }
 
-int ew_module_load(EwModule* m, const std::vector<char>& code_object, const std::string& kernel_name, std::string* err, const EwModule* holder) {
+// Put on the current device, if it is not yet.
+static int ew_module_load(EwModule* m, const std::vector<char>& code_object, const std::string& kernel_name, std::string* err, const EwModule* holder) {
   int dev = -1;
   if (hipGetDevice(&dev) != hipSuccess) { *err = "hipGetDevice failed"; return -1; }
   if (m->function) {

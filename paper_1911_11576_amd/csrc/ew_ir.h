@@ -76,8 +76,6 @@ struct EwModule {
 int ew_module_launch(EwModule* m, const std::vector<char>& code_object, const std::string& kernel_name,
                      const void* args, size_t args_bytes, int grid, int block, void* stream, std::string* err,
                      const EwModule* holder = nullptr);   // holder: a loaded module that has this kernel too (it keeps the module)
-// Put on the current device, if it is not yet.
-int ew_module_load(EwModule* m, const std::vector<char>& code_object, const std::string& kernel_name, std::string* err, const EwModule* holder = nullptr);
 void ew_module_release(EwModule* m);
 
 }  // namespace fs

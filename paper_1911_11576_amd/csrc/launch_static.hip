@@ -45,29 +45,27 @@ extern "C" fs_status fs_launch_static(fs_plan* p, const void* const* inputs, int
                                       int32_t n_out, void* hip_stream) {
   const fs_status st = fs::check_launch_args(p, inputs, n_in, outputs, n_out);
   if (st != FS_OK) return st;
-  bool in_place = false;
-  const int64_t bytes = fs::launch_workspace(p, inputs, n_in, outputs, n_out, &in_place);
-  if (bytes > (int64_t)FS_STATIC_SCRATCH_BYTES) {
+  if (p->workspace_bytes > (int64_t)FS_STATIC_SCRATCH_BYTES) {
     char buf[160];
     snprintf(buf, sizeof buf, "fs_launch_static: the plan needs %lld bytes of scratch memory, the static array holds %lld",
-             (long long)bytes, (long long)FS_STATIC_SCRATCH_BYTES);
+             (long long)p->workspace_bytes, (long long)FS_STATIC_SCRATCH_BYTES);
     return fs::set_error(FS_ERR_UNSUPPORTED, buf);
   }
   // a generated kernel is put on the device by the plan's first fs_launch; loading a code object allocates
   const bool elementwise = p->schedule == FS_SCHED_ELEMENTWISE;
   const bool two_step = p->schedule == FS_SCHED_TWO_STEP;
-  const bool generated = elementwise ? p->ew.generated : two_step || (p->schedule != FS_SCHED_PER_OP && p->row_form == 3) || in_place;
+  const bool generated = elementwise ? p->ew.generated : two_step || (p->schedule != FS_SCHED_PER_OP && p->row_form == 3);
   const fs::EwModule& mod = elementwise ? p->ew.loaded : two_step ? p->two_step.loaded[1] : p->row_gen.loaded;
   int dev = -1;
   if (generated && (hipGetDevice(&dev) != hipSuccess || !mod.function || mod.device != dev))
     return fs::set_error(FS_ERR_INVALID, "fs_launch_static: this plan runs a generated kernel that is not on this device yet; "
                                          "launch it once with fs_launch (or build the plan with FS_MODE_STITCHED_PREBUILT)");
   void* ws = nullptr;
-  if (bytes > 0) {
+  if (p->workspace_bytes > 0) {
     // Nothing in the array has to start at zero: every kernel that reads scratch memory reads only what
     // an earlier kernel of the same call wrote there.
     const fs_status s2 = static_scratch(&ws);
     if (s2 != FS_OK) return s2;
   }
-  return fs::enqueue_plan(p, inputs, outputs, n_out, ws, hip_stream, in_place);
+  return fs::enqueue_plan(p, inputs, outputs, n_out, ws, hip_stream);
 }

@@ -30,7 +30,8 @@ int row_block_launch(const RowSpec&, const RowBlockLaunch&, const void* const* i
                      void* stream, std::string* err);
 
 // LayerNorm backward: row path for dx packed with the column path for dgamma/dbeta.
-struct LnBwdLaunch { int K = 1, wg = 256, grid = 1, n_kernels = 1; int64_t lds_bytes = 0, workspace_bytes = 0; bool packed = false; int T = 1, strip = 32; };   // packed: one launch; T wavefronts to a row, strips of columns
+struct LnBwdLaunch { int K = 1, wg = 256, grid = 1, n_kernels = 1; int64_t lds_bytes = 0, workspace_bytes = 0; bool packed = false, in_place = false; int T = 1, strip = 32; };   // packed: one launch; T wavefronts to a row, strips of columns; in_place: dx may take the buffer of dy or x
+inline bool lnbwd_broadcasts(const LnBwdSpec& sp, int param) { return param == sp.in_gamma || param == sp.in_mean || param == sp.in_rstd; }
 bool lnbwd_takes_ragged(const LnBwdSpec&, const LaunchOpts&);      // rows of no whole number of vectors that the hand-written kernel takes
 bool lnbwd_stitch_plan(const LnBwdSpec&, const LaunchOpts&, LnBwdLaunch*, std::string* err);
 std::string lnbwd_stitch_describe(const LnBwdSpec&, const LnBwdLaunch&);

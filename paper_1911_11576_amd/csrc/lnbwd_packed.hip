@@ -5,6 +5,9 @@
 // second launch: what the form over many rows (lnbwd_stitch.hip and the generated one) spends on those is most of the time of
 // a small group.
 //
+// An update in place (dx in the buffer of dy or x) is two launches of the same kernel, the strips and behind them the rows, since
+// workgroups of one launch would write what others still read.  A row is written by the wavefronts that have all of it in registers.
+//
 // Any row length: vectors of four elements at element alignment, the last one of a row moved back to end with the row.
 #include <cstdio>
 
@@ -161,7 +164,7 @@ __global__ __launch_bounds__(kThreads) void lnbwd_packed_kernel(const Args a) {
 
 namespace {
 template <int T, int K>
-void launch(const Args& a, int grid, int cb, bool aligned, hipStream_t s) {
+void launch_blocks(const Args& a, int grid, int cb, bool aligned, hipStream_t s) {
   if (cb == 32) {
     if (aligned) hipLaunchKernelGGL((lnbwd_packed_kernel<T, K, 32, true>), dim3(grid), dim3(kThreads), 0, s, a);
     else hipLaunchKernelGGL((lnbwd_packed_kernel<T, K, 32, false>), dim3(grid), dim3(kThreads), 0, s, a);
@@ -169,6 +172,16 @@ void launch(const Args& a, int grid, int cb, bool aligned, hipStream_t s) {
     if (aligned) hipLaunchKernelGGL((lnbwd_packed_kernel<T, K, 16, true>), dim3(grid), dim3(kThreads), 0, s, a);
     else hipLaunchKernelGGL((lnbwd_packed_kernel<T, K, 16, false>), dim3(grid), dim3(kThreads), 0, s, a);
   }
+}
+
+template <int T, int K>
+void launch(Args a, int grid, int cb, bool aligned, hipStream_t s) {
+  if (a.dx == a.dy || a.dx == a.x) {
+    launch_blocks<T, K>(a, a.col_blocks, cb, aligned, s);
+    grid -= a.col_blocks;
+    a.col_blocks = 0;
+  }
+  launch_blocks<T, K>(a, grid, cb, aligned, s);
 }
 }  // namespace
 
@@ -184,6 +197,7 @@ bool lnbwd_packed_plan(const LnBwdSpec& sp, const LaunchOpts& opt, LnBwdLaunch* 
   LnBwdLaunch l;
   l.packed = true;
   const int nvec = (int)((sp.cols + 3) / 4);
+  l.in_place = sp.cols % 4 != 0 || sp.cols > 1024;      // (as of the other form for these rows, the generated one; the hand-written one takes none)
   l.T = nvec <= 256 ? 1 : nvec <= 512 ? 4 : 8;
   l.K = (nvec + 64 * l.T - 1) / (64 * l.T);
   l.strip = sp.cols % 32 == 0 || sp.cols >= 2048 || sp.rows <= 400 ? 32 : 16;
@@ -197,11 +211,11 @@ bool lnbwd_packed_plan(const LnBwdSpec& sp, const LaunchOpts& opt, LnBwdLaunch* 
 }
 
 std::string lnbwd_packed_describe(const LnBwdLaunch& l) {
-  char buf[400];
+  char buf[512];
   snprintf(buf, sizeof buf,
            "reduce_s1[GRID,%s]; reduce_s2[GRID,%s]; dx[GRID,%s-THREAD_%d] packed with reduce_dgamma[GRID-CTA,THREAD_4]S; reduce_dbeta[GRID-CTA,THREAD_4]S "
-           "(hand-written kernel; a workgroup to a strip of %d columns, the others to rows); cta_num=%d, cta_size=%d",
-           l.T == 1 ? "WARP" : "CTA", l.T == 1 ? "WARP" : "CTA", l.T == 1 ? "WARP" : "CTA", l.K * 4, l.strip, l.grid, l.wg);
+           "(hand-written kernel; a workgroup to a strip of %d columns, the others to rows%s); cta_num=%d, cta_size=%d",
+           l.T == 1 ? "WARP" : "CTA", l.T == 1 ? "WARP" : "CTA", l.T == 1 ? "WARP" : "CTA", l.K * 4, l.strip, l.in_place ? "; dx in place of dy or x: the strips first, the rows in a second launch" : "", l.grid, l.wg);
   return buf;
 }
 

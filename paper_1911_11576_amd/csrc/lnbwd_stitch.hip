@@ -91,7 +91,8 @@ void lnbwd_rows_kernel(const LnBwdArgs a) {
   u32x4 rdy[NB][K], rx[NB][K];
   float rmu[NB], rrs[NB];
   auto request = [&](int b, int64_t want) {
-    // past the end: row 0, which is in cache by then (no extra HBM traffic); its values are never used
+    // past the end: row 0, which is in cache by then (no extra HBM traffic); its values are never used (nor, in an
+    // update in place, is what its wavefront may be writing there)
     const int64_t r = want < row_end ? want : 0;
     // (loads complete in the order they are issued: the row's mean and rstd, needed first, go first)
     if constexpr (NEED_X) { rmu[b] = a.mean[r]; rrs[b] = a.rstd[r]; }
@@ -312,6 +313,8 @@ bool lnbwd_stitch_plan(const LnBwdSpec& sp, const LaunchOpts& opt, LnBwdLaunch* 
   l.grid = (int)grid;
   const bool want_col = sp.out_dgamma >= 0 || sp.out_dbeta >= 0;
   l.n_kernels = want_col ? 2 : 1;
+  // (a row is read by the one wavefront that writes it, before it does; whole vectors have never taken updates in place)
+  l.in_place = sp.cols % 4 != 0;
   l.lds_bytes = want_col ? (int64_t)waves * 2 * l.K * 256 * 8 : 0;
   if (l.lds_bytes > kLdsMax) {
     *err = "LayerNorm-backward schedule: wg_size needs more LDS for the column sums than a CU has";
@@ -327,8 +330,8 @@ std::string lnbwd_stitch_describe(const LnBwdSpec& sp, const LnBwdLaunch& l) {
   snprintf(buf, sizeof buf,
            "reduce_s1[GRID-WARP,WARP]; reduce_s2[GRID-WARP,WARP]; dx[GRID-WARP,WARP-THREAD_%d]; "
            "reduce_dgamma[GRID-CTA-THREAD,WARP-THREAD_%d]S; reduce_dbeta[GRID-CTA-THREAD,WARP-THREAD_%d]S "
-           "(hand-written kernel; %d partial rows, then a combine kernel); cta_num=%d, cta_size=%d",
-           l.K * 4, l.K * 4, l.K * 4, l.grid, l.grid, l.wg);
+           "(hand-written kernel; %d partial rows, then a combine kernel%s); cta_num=%d, cta_size=%d",
+           l.K * 4, l.K * 4, l.K * 4, l.grid, l.in_place ? "; takes dx in place of dy or x" : "", l.grid, l.wg);
   (void)sp;
   return buf;
 }

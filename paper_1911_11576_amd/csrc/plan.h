@@ -21,7 +21,6 @@ struct fs_plan {
   fs::RowGenLaunch row_gen;
   int row_form = 0;   // 0 one wavefront per row group, 1 wavefront team, 2 row cached in LDS, 3 generated kernel
   fs::LnBwdLaunch lnbwd;
-  bool in_place_form = false;   // row_gen is the form that takes updates in place (and is used for nothing else)
   fs::AttnLaunch attn;
   fs::EwLaunch ew;
   fs::TwoStepLaunch two_step;   // schedule FS_SCHED_TWO_STEP: takes one more output, the doubles between its two kernels
@@ -39,10 +38,8 @@ namespace fs {
 fs_status set_error(fs_status st, const std::string& msg);
 // Arguments of a launch checked against the plan: counts, NULL and alignment, identical pointers.
 fs_status check_launch_args(fs_plan* p, const void* const* inputs, int32_t n_in, void* const* outputs, int32_t n_out);
-// The scratch memory a launch with these buffers needs (that of the plan's in-place form where buffers are shared).
-int64_t launch_workspace(const fs_plan* p, const void* const* inputs, int32_t n_in, void* const* outputs, int32_t n_out, bool* in_place);
 // The plan's kernels enqueued with `workspace` as their scratch memory.
 fs_status enqueue_plan(fs_plan* p, const void* const* inputs, void* const* outputs, int32_t n_out, void* workspace,
-                       void* hip_stream, bool in_place);
+                       void* hip_stream);
 
 }  // namespace fs

@@ -836,3 +836,12 @@ def test_programs_with_two_step_plans(tmp_path):
     ops.append(Op("output", "f32", (), (norm,), -1, 0.0, "norm"))
     with FusedProgram(ops) as prog:
         assert all(u.extra == 0 for u in prog._launches)
+
+
+def test_layernorm_bwd_plans_name_the_update_in_place_and_hide_no_workspace():
+    """Rows that only the generated kernel takes otherwise accept dx in place; the hand-written plans say so, in what workspace they report."""
+    for rows, cols, takes, free in ((300, 1600, True, True), (512, 31, True, True), (1024, 4096, True, True), (300, 1024, False, True), (256, 32, False, True),
+                                    (2000, 1023, True, False), (2000, 1024, False, False)):
+        with Plan(graphs.layernorm_bwd(rows, cols)) as p:
+            assert "hand-written" in p.describe() and ("in place of dy or x" in p.describe()) == takes, (rows, cols)
+            assert (p.info()["workspace_bytes"] == 0) == free

@@ -299,7 +299,7 @@ def test_layernorm_bwd_shapes(rows, cols, mode):
 @pytest.mark.parametrize("rows,cols", [(256, 4), (257, 5), (300, 31), (1024, 33), (401, 255), (400, 257), (999, 511), (1024, 1024), (513, 1025), (301, 1027), (260, 2048), (450, 2049), (258, 4095), (256, 4096)])
 def test_layernorm_bwd_in_one_launch(rows, cols):
     """Few rows: the row path and strips of columns as workgroups of one launch; edges of vectors, strips, wavefronts and teams, the rule's
-    corners; bit-reproducible.  Where the generated kernel is the only other form, an update in place takes that form."""
+    corners; bit-reproducible.  Where the generated kernel is the only other form, an update in place is taken as by that one."""
     announce(f"layernorm_bwd in one launch {rows}x{cols}")
     ops, ins = graphs.layernorm_bwd(rows, cols), inputs.layernorm_bwd(rows, cols)
     with Plan(ops) as p:
@@ -325,7 +325,7 @@ def test_layernorm_bwd_in_one_launch(rows, cols):
 @pytest.mark.parametrize("rows,cols", [(1025, 129), (1100, 255), (2051, 257), (1030, 513), (4099, 767), (1500, 769), (1033, 1021), (1040, 1022), (1027, 1023)])
 def test_layernorm_bwd_rows_of_no_whole_vectors(rows, cols):
     """The hand-written rows kernel at element alignment: one to three elements over, one vector over a set of 64, trips of every length;
-    bit-reproducible, updates in place through the generated form, the prebuilt mode as before."""
+    bit-reproducible, updates in place as by the generated form, the prebuilt mode as before."""
     announce(f"layernorm_bwd ragged {rows}x{cols}")
     ops, ins = graphs.layernorm_bwd(rows, cols), inputs.layernorm_bwd(rows, cols)
     with Plan(ops) as p:
@@ -344,6 +344,46 @@ def test_layernorm_bwd_rows_of_no_whole_vectors(rows, cols):
             torch.cuda.synchronize()
             for a, b in zip([dev_in[0]] + outs[1:], want):
                 assert_close(a.double().cpu().numpy(), b, 1e-5, f"lnbwd in place {rows}x{cols}")
+
+
+@pytest.mark.parametrize("rows,cols", [(300, 31), (700, 1600), (301, 1027), (256, 4095), (1027, 1023)])
+def test_layernorm_bwd_in_place_beside_other_launches(rows, cols):
+    """Updates in place need no more than the plan reports: bit for bit what a launch with buffers of its own gives, in dy's buffer and in x's, captured after
+    one plain launch, and, where the plan owns no workspace, several at once on two streams."""
+    announce(f"layernorm_bwd in place, captured and overlapping {rows}x{cols}")
+    ops, ins = graphs.layernorm_bwd(rows, cols), inputs.layernorm_bwd(rows, cols)
+    names = [op.name for op in ops if op.kind == "parameter"]
+    dx = [op.shape for op in ops if op.kind == "output"].index((rows, cols))
+    with Plan(ops) as p:
+        free = p.info()["workspace_bytes"] == 0
+        assert free == (rows <= 1024) and "in place of dy or x" in p.describe()
+        want = alloc_outputs(ops)
+        p.launch(to_device(ops, ins), want)
+
+        def buffers(name):
+            dev_in, outs = to_device(ops, ins), alloc_outputs(ops)
+            outs[dx] = dev_in[names.index(name)]
+            return dev_in, outs
+        for name in ("dy", "x"):
+            dev_in, outs = buffers(name)
+            torch.cuda.synchronize()
+            graph = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(graph, stream=torch.cuda.Stream()):
+                p.launch(dev_in, outs)
+            for _ in range(2):
+                for t, s in zip(dev_in, to_device(ops, ins)):
+                    t.copy_(s)
+                graph.replay()
+                torch.cuda.synchronize()
+                assert all(torch.equal(a, b) for a, b in zip(outs, want)), name
+        sets = [buffers(("dy", "x")[k % 2]) for k in range(8)]
+        streams = [torch.cuda.Stream() for _ in range(2 if free else 1)]
+        torch.cuda.synchronize()
+        for k, (dev_in, outs) in enumerate(sets):
+            p.launch(dev_in, outs, streams[k % len(streams)].cuda_stream)
+        torch.cuda.synchronize()
+        for _, outs in sets:
+            assert all(torch.equal(a, b) for a, b in zip(outs, want))
 
 
 @pytest.mark.parametrize("mode", LNBWD_MODES)
