@@ -760,8 +760,6 @@ int chunk_elements(const Analysis& A, bool* fast) {
 // 256 x 3001 12.6 and 24.0.
 // Neighbouring rows share lines: ragged chunks are loaded through the caches (4096 x 3001 35.1, 40.4 with
 // nontemporal loads).
-constexpr int64_t kSpreadRows = 256;
-constexpr int64_t kTeamBytes = 128ll << 20;      // groups up to here: teams with column sums load through the caches
 constexpr int64_t kRaggedCols = 512, kRaggedColumnRows = 2048, kRaggedRunRows = 8192;
 int ragged_chunk_elements(const Analysis& A) {
   if (A.n_col > 0 && A.cols <= 2048 && (A.seg_rows > 0 ? A.rows >= kRaggedRunRows : A.rows < kRaggedColumnRows)) return 0;
@@ -784,6 +782,9 @@ typedef float f32x4e __attribute__((ext_vector_type(4), aligned(4)));
 typedef unsigned u32x2e __attribute__((ext_vector_type(2), aligned(2)));
 typedef unsigned u32x4e __attribute__((ext_vector_type(4), aligned(2)));
 )SRC";
+
+constexpr int64_t kSpreadRows = 256;
+constexpr int64_t kTeamBytes = 128ll << 20;      // groups up to here: teams with column sums load through the caches
 
 struct Gen {
   const Analysis& A;
@@ -1051,6 +1052,37 @@ struct Gen {
     wg = threads;
     return true;
   }
+  // Lanes of a team that holds the running sums of a row that one wavefront could hold too; 0 where none does.
+  int team_lanes(int64_t nvec) const {
+    auto sums = [&](int lanes) { return (nvec + lanes - 1) / lanes * W * A.n_col; };
+    for (int lanes = 128; lanes <= 1024; lanes *= 2) if (sums(lanes) <= 16) return lanes;
+    // more of them: with one chunk to a lane, or 512 lanes (a thread of up to 512 has 256 registers)
+    for (int lanes = 128; lanes <= 512; lanes *= 2) if ((lanes >= nvec || lanes == 512) && sums(lanes) <= 64) return lanes;
+    return 0;
+  }
+  // Whether a row of more than twenty elements a lane, with two or more column sums, is a team's rather than a wavefront's.  Two things
+  // decide.  What a wavefront's lane would hold: from about 345 of its 512 registers on (16-bit rows: 420) it is slower at every size.  Below, the
+  // bytes: a team's loads are spread thinner (a chunk a lane, through the caches up to kTeamBytes), which large groups notice, the more so
+  // the narrower their rows and the fewer their sums.  A wavefront's time and a team's in us, a product with its row sum, output and n column sums:
+  //   held       f32 n 3, 264: 8192 x 1300 36.0, 29.4; 8192 x 1536 37.4, 37.9; 16384 x 1536 60.1, 66.0.  352: 16384 x 2048 80.1, 77.0.  n 4, 336: 16384 x
+  //              1536 63.3, 67.6.  n 5, 408: 71.8, 69.0; 544: 16384 x 2048 395, 81.  Backward tail, n 3, 384: 16384 x 1400 121, 95; 8192 x 1300 69.2, 53.3
+  //   16-bit     n 3, 352: 8192 x 2048 34.5, 27.2; 16384 x 2048 48.7, 53.0.  n 5, 408: 16384 x 1536 52.1, 57.5.  n 4, 448: 16384 x 2048 61.8, 57.7
+  //   two sums   (from cold buffers) f32 4096 x 1300 22.7, 22.0; LayerNorm backward over 7000 x 1400 30.9, 33.5.  bf16 1000 x 1500 16.1, 14.5; 2000 x 1300
+  //              14.2, 15.2; 4096 x 1300 17.5, 21.2; 8192 x 1300 22.3, 32.2; up to 32 elements a lane 8192 x 2048 29.1, 28.4
+  //   16-bit     (cold) n 3 4096 x 1300 21.6, 21.9; 8192 x 1300 26.7, 31.6.  n 4 8192 x 1300 31.6, 32.7; 16384 x 1536 42.0, 55.8.  n 5 8192 x 1536 40.7, 34.2
+  bool team_is_faster() const {
+    if (A.n_col < 2) return false;
+    int halves = 2 * (2 * A.n_col + live_values());      // of registers, for each of a lane's elements: sums, values, rows on their way
+    for (const RView& v : A.views) {
+      bool per_row = false;
+      for (int d = 0; d + 1 < A.rank; ++d) if (v.stride[d] != 0) per_row = true;
+      if (v.cls == CLS_FULL && per_row) halves += v.dtype == FS_F32 ? 2 : 1;
+    }
+    if (A.n_col > 2 && K * W * halves > 2 * (fast ? 420 : 345)) return true;
+    int64_t most = kTeamBytes;
+    if (K * W <= 24) most = std::min<int64_t>(most, ((fast ? 16ll : 64ll) << 20) << (A.n_col - 2));
+    return A.g.algorithmic_bytes() <= most;
+  }
   bool geometry_rows(std::string* err) {
     W = chunk_elements(A, &fast);
     if (W == 0) { *err = "generated row schedule: an operand strided along the last dim"; return false; }
@@ -1100,18 +1132,15 @@ struct Gen {
     // memory, so its full outputs are first laid out in LDS and then stored as one dense run
     // of 16-byte accesses (stores of separate row pieces straddle lines and measured 2x slower).
     if (A.n_col > 0) {
-      // More than twenty elements of a row in a lane, with their running sums: a team, where the sums are three or more (they and
-      // the rows no longer fit a lane's registers: backward tail of 4096 x 2048 62.6 us with a wavefront per row, 40.3 with a team,
-      // 8192 x 1500 70.2 and 56.2, 32768 x 1400 221 and 180), and with two in groups of up to 128 MB, up to 24 elements 64 MB (LayerNorm backward over
-      // 600 x 2048 13.3 and 11.0, 6000 x 1700 32.2 and 29.1, 2304 x 1510 17.0 and 16.6, from cold buffers 19.5 and 18.2; 7000 x 1400, 118 MB, 30.8 and
-      // 29.5, cold 30.9 and 33.5; 8000 x 1999, 192 MB, 44.9 and 46.5; 16384 x 2048 75.3 and 82).  Up to twenty elements:
-      // 10624 x 658 20.0 and 25.3, 8192 x 1280 28.5 and 29.2, the tail of 16384 x 1024 63.0 and 74.  Below 256 rows a team has sixteen rows to a
-      // workgroup (see the grid): 130 x 1500 10.4 and 15.3.
-      if (L == 64 && default_shape && A.seg_rows == 0 && A.rows >= kSpreadRows && K * W > 20 && (A.n_col > 2 || (A.n_col == 2 && A.g.algorithmic_bytes() <= (K * W > 24 ? kTeamBytes : kTeamBytes / 2)))) {
-        L = 128;
+      // (Below kSpreadRows a team has sixteen rows to a workgroup, see the grid: 130 x 1500 10.4 us with a wavefront per row, 15.3 with a team.  Up to
+      // twenty elements a lane: LayerNorm backward over 10624 x 658 20.0 and 25.3, 8192 x 1280 28.5 and 29.2, the backward tail of 16384 x 1024 63.0 and 74.)
+      const int team = team_lanes(nvec);
+      if (L == 64 && default_shape && A.seg_rows == 0 && A.rows >= kSpreadRows && K * W > 20 && team > 0 && team_is_faster()) {
+        L = team;
         spread = true;
-      }
-      if (L > 64) {
+        K = (int)((nvec + L - 1) / L);
+        exact = (int64_t)K * L == nvec && !ragged;
+      } else if (L > 64) {
         // a team of wavefronts per row: every lane's columns are its own in the workgroup, so the
         // running sums (two registers per column and reduction) stay few by spreading the row wider
         K = (int)((nvec + L - 1) / L);

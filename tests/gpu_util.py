@@ -4,7 +4,7 @@ import numpy as np
 import torch
 
 from paper_1911_11576_amd import Plan
-from workloads import TOLERANCE, inputs as wl_inputs
+from workloads import TOLERANCE, graphs, inputs as wl_inputs
 
 _TORCH = {"f32": torch.float32, "f16": torch.float16, "bf16": torch.bfloat16}
 
@@ -73,3 +73,16 @@ def check_against_oracle(ops, ins, mode="stitched", tol=None, what="", **opts):
     for i, (a, b) in enumerate(zip(got, want)):
         assert_close(a, b, tol, f"{what} output {i} ({mode})")
     return got, want
+
+
+def product_with_column_sums(rows, cols, dtype, n):
+    """x * y scaled by its row sums, of x's dtype, and n column sums in f32 (of x, y, their product, sum, difference and squares)."""
+    g = graphs.Graph()
+    x, y = g.parameter("x", dtype, (rows, cols)), g.parameter("y", dtype, (rows, cols))
+    a, b = (v if dtype == "f32" else g.convert(v, "f32") for v in (x, y))
+    p = g.multiply(a, b)
+    o = g.multiply(p, g.row_broadcast(g.reduce_sum(p, 1), p))
+    g.output(o if dtype == "f32" else g.convert(o, dtype), "o")
+    for k, v in enumerate([p, a, b, g.multiply(a, a), g.multiply(b, b), g.add(a, b), g.subtract(a, b)][:n]):
+        g.output(g.reduce_sum(v, 0), f"sum{k}")
+    return g.ops

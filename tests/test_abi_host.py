@@ -11,6 +11,8 @@ from paper_1911_11576_amd import FsError, Plan, binding
 from workloads import BY_NAME, CONFIGS, algorithmic_bytes, graphs
 from workloads.graphs import Graph, Op
 
+from gpu_util import product_with_column_sums
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
@@ -845,3 +847,26 @@ def test_layernorm_bwd_plans_name_the_update_in_place_and_hide_no_workspace():
         with Plan(graphs.layernorm_bwd(rows, cols)) as p:
             assert "hand-written" in p.describe() and ("in place of dy or x" in p.describe()) == takes, (rows, cols)
             assert (p.info()["workspace_bytes"] == 0) == free
+
+
+def _in_place_status(ops):
+    """Status of a launch with the first output in the first parameter's buffer, by its arguments alone: FS_ERR_HIP where they pass, as there is no GPU."""
+    with Plan(ops) as p:
+        n_in, n_out = (sum(op.kind == k for op in ops) for k in ("parameter", "output"))
+        ins = (ctypes.c_void_p * n_in)(*[4096 * (k + 1) for k in range(n_in)])
+        outs = (ctypes.c_void_p * n_out)(*[4096 * (n_in + k + 1) for k in range(n_out)])
+        outs[0] = ins[0]
+        return binding.lib().fs_launch(p._h, ins, n_in, outs, n_out, None)
+
+
+@pytest.mark.parametrize("dtype,n", [("f32", 3), ("f32", 4), ("f32", 5), ("f32", 7), ("bf16", 2), ("bf16", 3), ("bf16", 4), ("f16", 7)])
+@pytest.mark.parametrize("rows,cols", [(256, 1284), (300, 1801), (4096, 1536), (4096, 2048), (16384, 1536), (16384, 1032)])
+def test_rows_with_several_column_sums_stay_in_registers(rows, cols, dtype, n):
+    """Rows that one wavefront holds with their column sums, whatever their number: never streamed, no more partial rows than 256, updates in place taken."""
+    import torch
+    ops = product_with_column_sums(rows, cols, dtype, n)
+    with Plan(ops) as p:
+        assert "streamed" not in p.describe(), p.describe()
+        assert p.info()["workspace_bytes"] <= 256 * n * cols * 8 and p.info()["lds_bytes"] <= 160 * 1024
+    if not torch.cuda.is_available():      # (the buffers are made up)
+        assert _in_place_status(ops) == binding.FS_ERR_HIP

@@ -11,7 +11,7 @@ from oracle import interp
 from paper_1911_11576_amd import FsError, Plan, binding
 from workloads import BY_NAME, TOLERANCE, graphs, inputs
 
-from gpu_util import alloc_outputs, assert_close, check_against_oracle, run_gpu, to_device
+from gpu_util import alloc_outputs, assert_close, check_against_oracle, product_with_column_sums, run_gpu, to_device
 
 pytestmark = pytest.mark.gpu
 
@@ -674,6 +674,27 @@ def test_column_sums_meet_in_lds_and_in_teams(rows, cols, group):
         assert np.array_equal(a, b)
     for opts in (dict(wg_size=512), dict(wg_size=128, grid=5), dict(wg_size=64, grid=300)):      # a wavefront per row with other numbers of wavefronts
         check_against_oracle(ops, ins, "generated", what=f"{group} {rows}x{cols} {opts}", **opts)
+
+
+@pytest.mark.parametrize("dtype,n", [("f32", 3), ("f32", 5), ("f32", 7), ("bf16", 2), ("bf16", 3), ("bf16", 4), ("f16", 7)])
+@pytest.mark.parametrize("rows,cols", [(255, 1536), (256, 1284), (300, 1801), (259, 2048), (1030, 1540), (2051, 1035)])
+def test_many_column_sums_over_rows_of_registers(rows, cols, dtype, n):
+    """Two to seven sums beside a row reduction and a full output, as a wavefront's rows and as a team's: against the oracle, the same twice, and the same in
+    place of the first input and from the static scratch memory."""
+    announce(f"{n} column sums {rows}x{cols} {dtype}")
+    ops, ins = product_with_column_sums(rows, cols, dtype, n), inputs.normal_tensors([(rows, cols)] * 2, dtype, scale=0.5)
+    got, _ = check_against_oracle(ops, ins, what=f"{n} column sums {rows}x{cols} {dtype}")
+    dev_in, outs = to_device(ops, ins), alloc_outputs(ops)
+    with Plan(ops) as p:
+        p.launch(dev_in, outs)
+        launches = [p.launch] + ([p.launch_static] if p.info()["workspace_bytes"] <= 8 * 2**20 else [])
+        for launch in launches:
+            dev_in = to_device(ops, ins)
+            outs = [dev_in[0]] + alloc_outputs(ops)[1:]
+            launch(dev_in, outs)
+            torch.cuda.synchronize()
+            for a, b in zip(got, outs):
+                assert np.array_equal(a, b.double().cpu().numpy())
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
