@@ -1061,15 +1061,17 @@ struct Gen {
     return 0;
   }
   // Whether a row of more than twenty elements a lane, with two or more column sums, is a team's rather than a wavefront's.  Two things
-  // decide.  What a wavefront's lane would hold: from about 345 of its 512 registers on (16-bit rows: 420) it is slower at every size.  Below, the
+  // decide.  What a wavefront's lane would hold: from about 345 of its 512 registers on (16-bit rows: 500) it is slower at every size.  Below, the
   // bytes: a team's loads are spread thinner (a chunk a lane, through the caches up to kTeamBytes), which large groups notice, the more so
-  // the narrower their rows and the fewer their sums.  A wavefront's time and a team's in us, a product with its row sum, output and n column sums:
-  //   held       f32 n 3, 264: 8192 x 1300 36.0, 29.4; 8192 x 1536 37.4, 37.9; 16384 x 1536 60.1, 66.0.  352: 16384 x 2048 80.1, 77.0.  n 4, 336: 16384 x
-  //              1536 63.3, 67.6.  n 5, 408: 71.8, 69.0; 544: 16384 x 2048 395, 81.  Backward tail, n 3, 384: 16384 x 1400 121, 95; 8192 x 1300 69.2, 53.3
-  //   16-bit     n 3, 352: 8192 x 2048 34.5, 27.2; 16384 x 2048 48.7, 53.0.  n 5, 408: 16384 x 1536 52.1, 57.5.  n 4, 448: 16384 x 2048 61.8, 57.7
-  //   two sums   (from cold buffers) f32 4096 x 1300 22.7, 22.0; LayerNorm backward over 7000 x 1400 30.9, 33.5.  bf16 1000 x 1500 16.1, 14.5; 2000 x 1300
-  //              14.2, 15.2; 4096 x 1300 17.5, 21.2; 8192 x 1300 22.3, 32.2; up to 32 elements a lane 8192 x 2048 29.1, 28.4
-  //   16-bit     (cold) n 3 4096 x 1300 21.6, 21.9; 8192 x 1300 26.7, 31.6.  n 4 8192 x 1300 31.6, 32.7; 16384 x 1536 42.0, 55.8.  n 5 8192 x 1536 40.7, 34.2
+  // the narrower their rows and the fewer their sums.  Measured in us, a wavefront per row and a team, a product with its row sum, an output and n column sums:
+  //   held     f32 n 3 352: 16384 x 2048 77.5, 76.6.  n 5 544: 245, 80.6.  n 6 480: 16384 x 1536 101, 71.1.  Backward tail, n 3 384: 16384 x 1400 117, 95.0
+  //            16-bit n 5 544: 16384 x 2048 82.3, 62.7.  n 6 624: 191, 66.4.  Just below, f32 n 4 336: 16384 x 1536 60.6, 67.3; 16-bit n 6 480: 45.9, 60.6
+  //   bytes    (from warm and from cold buffers) up to 24 elements a lane, f32 n 2 4096 x 1300 21.0, 16.8 and 21.2, 22.0; 8192 x 1536 33.1, 37.6.  n 3
+  //            4096 x 1536 24.3, 19.1 and 24.4, 23.0; 8192 x 1536 35.4, 38.0
+  //            16-bit n 2 1000 x 1300 13.2, 12.5 and 13.7, 13.6; 2000 x 1300 12.5, 13.0 and 12.8, 15.2.  n 3 2000 x 1300 15.6, 15.0 and 15.7, 16.8; 2000 x 1536
+  //            14.8, 16.9.  n 4 4096 x 1300 22.3, 19.6 and 22.3, 23.3; 8192 x 1536 26.6, 26.9 and 26.5, 32.8.  n 5 4096 x 1536 23.6, 22.4 and 23.5, 24.7
+  //            more elements, f32 n 2 4096 x 2048 27.5, 21.3 and 27.6, 24.6; 16384 x 2048 74.2, 74.7.  16-bit n 2 8192 x 2048 26.4, 24.9 and 26.4, 28.3;
+  //            16384 x 2048 40.9, 48.4
   bool team_is_faster() const {
     if (A.n_col < 2) return false;
     int halves = 2 * (2 * A.n_col + live_values());      // of registers, for each of a lane's elements: sums, values, rows on their way
@@ -1078,9 +1080,9 @@ struct Gen {
       for (int d = 0; d + 1 < A.rank; ++d) if (v.stride[d] != 0) per_row = true;
       if (v.cls == CLS_FULL && per_row) halves += v.dtype == FS_F32 ? 2 : 1;
     }
-    if (A.n_col > 2 && K * W * halves > 2 * (fast ? 420 : 345)) return true;
+    if (A.n_col > 2 && K * W * halves > 2 * (fast ? 500 : 345)) return true;
     int64_t most = kTeamBytes;
-    if (K * W <= 24) most = std::min<int64_t>(most, ((fast ? 16ll : 64ll) << 20) << (A.n_col - 2));
+    if (K * W <= 24) most = std::min<int64_t>(most, ((fast ? 8ll : 64ll) << 20) << (A.n_col - 2));
     return A.g.algorithmic_bytes() <= most;
   }
   bool geometry_rows(std::string* err) {
