@@ -1754,6 +1754,8 @@ struct Gen {
         e.line("    const float wm = exch[%d][threadIdx.x & (T - 1)];", red_index);
         e.line("    r%d = lanes_allreduce<MaxOp, T>(wm);", m);
         e.line("    r%d = lanes_allreduce<SumOp, T>(exch[%d][threadIdx.x & (T - 1)] * %s(fmaxf(wm, -3.402823466e38f) - fmaxf(r%d, -3.402823466e38f)));", q, red_index + 1, ex.c_str(), m);
+        // (a row of nothing but -inf: exp(-inf - -inf) is NaN, as where the two reductions are apart)
+        e.line("    if (r%d == -__builtin_inff()) r%d = __builtin_nanf(\"\");", m, q);
         e.line("  }");
         red_index += 2;
       }

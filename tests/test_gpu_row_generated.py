@@ -748,6 +748,33 @@ def test_maximum_and_sum_in_one_go_beside_other_outputs(cols):
         check_against_oracle(g.ops, ins, what=f"log-sum-exp {cols} {reads_exponentials}")
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("cols", [64, 2048, 2052, 20000, 40001, 45056, 100001])
+def test_sums_of_exponentials_of_infinite_rows(cols, dtype):
+    """The maximum, the sum of exponentials and its logarithm of rows of -inf alone, with one finite element, with +inf and with NaN: the same in every form."""
+    announce(f"log-sum-exp of infinite rows {cols} {dtype}")
+    g = graphs.Graph()
+    x = g.parameter("x", dtype, (6, cols))
+    z = x if dtype == "f32" else g.convert(x, "f32")
+    m = g.reduce_max(z, 1)
+    s = g.reduce_sum(g.exp(g.subtract(z, g.row_broadcast(m, z))), 1)
+    g.output(g.add(m, g.log(s)), "lse")
+    g.output(m, "max")
+    g.output(s, "sum")
+    a = inputs.normal_tensors([(6, cols)], dtype)[0]
+    a[0] = a[1] = -np.inf
+    a[1, cols - 1] = 1.5
+    a[2, cols // 2] = np.inf
+    a[3, 1] = np.nan
+    with np.errstate(invalid="ignore"):
+        want = interp.run(g.ops, [a])
+    lse, top, total = run_gpu(g.ops, [a])
+    assert top[0] == -np.inf and top[1] == lse[1] == 1.5 and total[1] == 1.0 and top[2] == np.inf
+    for v in (lse, total):
+        assert np.isnan(v[[0, 2, 3]]).all(), v
+        assert_close(v[4:], want[0 if v is lse else 2][4:], TOLERANCE[dtype], f"log-sum-exp {cols} {dtype}")
+
+
 def test_maximum_and_sum_in_one_go_in_a_packed_launch():
     announce("log-softmax teams in a packed launch")
     shapes = [((30, 5000), "f32"), ((20, 3001), "f32"), ((7, 4099), "bf16")]
