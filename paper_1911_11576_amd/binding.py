@@ -11,6 +11,7 @@ import ctypes as C
 import os
 from array import array
 from collections import namedtuple
+from math import prod
 
 FS_MAX_RANK = 4
 LIB_PATH = os.environ.get("FS_LIB_PATH") or os.path.join(os.path.dirname(os.path.abspath(__file__)),
@@ -521,6 +522,13 @@ _Launch = namedtuple("_Launch", "plan members inputs outputs extra")
 _OpRecord = namedtuple("_OpRecord", "kind dtype shape operands axis attr")
 
 
+# What a launch is worth in bytes, for a two-step plan that moves more than the launches it replaces (its two kernels both read what a reduced value is
+# made of, where a launch of its own would have written the value once).  y = u / |u|, u the sum of n fp32 tensors, replayed: 2048 x 4096, n 3, 34 MB more
+# and two launches fewer, 38.3 us apart and 37.3 as a two-step plan; n 4, 67 MB more, 43.5 and 46.1; n 8, 201 MB more, 65 and 87; 1024 x 2048, n 8, 42 MB
+# more and three launches fewer, 23.5 and 23.2; 512 x 2048, n 8, 20.1 and 11.0.
+_BYTES_OF_A_LAUNCH = 20e6
+
+
 class FusedProgram:
     """A whole computation graph run as the groups its fusion plan chose: one Plan per group, one per
     several small row groups that do not depend on each other, or one of two kernels for groups that pass scalars reduced
@@ -582,8 +590,23 @@ class FusedProgram:
 
     def _two_steps(self):
         """Launches of two-step plans: a group that reads scalars other groups make, with all that makes them, where nothing else
-        reads what is made on the way.  A group with recorded tuning options keeps its own plan."""
+        reads what is made on the way.  A group with recorded tuning options keeps its own plan; so does one whose two-step plan
+        would move more bytes than the launches saved are worth."""
         groups, ops = self.fusion.groups, self.ops
+
+        def nbytes(values):
+            return sum(prod(ops[i].shape) * (4 if ops[i].dtype == "f32" else 2) for i in values)
+
+        def leaves_below(i, leaves):
+            seen, stack = set(), [i]
+            while stack:
+                k = stack.pop()
+                if k not in seen:
+                    seen.add(k)
+                    if k not in leaves:
+                        stack += ops[k].operands
+            return seen & leaves
+
         used_by = {}
         for k, g in enumerate(groups):
             for i in g["input_of"]:
@@ -618,6 +641,11 @@ class FusedProgram:
                 else:
                     inside.add(i)
                     stack += ops[i].operands
+            # both kernels' reads and the outputs, against what goes in and out of the groups, in as many launches as they have levels
+            more = nbytes(leaves) + sum(nbytes(leaves_below(i, leaves)) for i in inside if ops[i].kind in ("reduce_sum", "reduce_max") and ops[i].shape == ())
+            more += nbytes(outputs) - sum(nbytes(groups[k]["input_of"]) + nbytes(groups[k]["output_of"]) for k in members)
+            if more > (len({self._level[k] for k in members}) - 2) * _BYTES_OF_A_LAUNCH:
+                continue
             inputs = sorted(leaves)
             number, listed = {}, []
             for i in inputs + sorted(inside):

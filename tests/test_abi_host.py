@@ -870,3 +870,28 @@ def test_rows_with_several_column_sums_stay_in_registers(rows, cols, dtype, n):
         assert p.info()["workspace_bytes"] <= 256 * n * cols * 8 and p.info()["lds_bytes"] <= 160 * 1024
     if not torch.cuda.is_available():      # (the buffers are made up)
         assert _in_place_status(ops) == binding.FS_ERR_HIP
+
+
+def _unit_norm(shape, n, dtype="f32"):
+    """y = u / |u|, u the sum of n tensors."""
+    g = Graph()
+    xs = [g.parameter(f"x{k}", dtype, shape) for k in range(n)]
+    xs = xs if dtype == "f32" else [g.convert(x, "f32") for x in xs]
+    u = xs[0]
+    for x in xs[1:]:
+        u = g.add(u, x)
+    y = g.multiply(u, g.broadcast(g.rsqrt(g.reduce_sum(g.reduce_sum(g.multiply(u, u), 1), 0)), shape, 0))
+    g.output(y if dtype == "f32" else g.convert(y, dtype), "y")
+    return g.ops
+
+
+@pytest.mark.parametrize("shape,n,dtype,taken", [((64, 256), 8, "f32", True), ((2048, 4096), 1, "f32", True), ((2048, 4096), 3, "f32", True), ((2048, 4096), 4, "f32", False),
+                                                 ((2048, 4096), 8, "f32", False), ((1024, 2048), 8, "f32", True), ((2048, 4096), 4, "bf16", True), ((2048, 4096), 8, "bf16", False)])
+def test_two_step_plans_are_taken_where_their_bytes_are_worth_it(shape, n, dtype, taken):
+    """A value made of several tensors is read twice by a two-step plan and written once by launches of their own."""
+    from paper_1911_11576_amd import FusedProgram
+    ops = _unit_norm(shape, n, dtype)
+    with Plan.two_step(ops)[0] as p:
+        assert p.info()["n_kernels"] == 2              # (the plan itself is there for who asks for it)
+    with FusedProgram(ops) as prog:
+        assert any(u.extra > 0 for u in prog._launches) == taken
