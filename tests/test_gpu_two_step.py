@@ -62,13 +62,13 @@ def run(ops, dev_in, repeats=1):
 
 
 CASES = [
-    # (a chunk is 4 or 8 elements, a workgroup's run in the first kernel 1024 chunks or more)
+    # (a chunk is 4 or 8 elements, a workgroup's run 256 chunks in small groups and 2048 in the largest)
     ([(1,), (2,), (3,), (4,), (5,)], "f32"),
     ([(7,), (8,), (9,), (15, 17)], "bf16"),
     ([(4096,), (4095,), (4097,)], "f32"),
     ([(8191,), (8193,), (2, 3, 5, 7)], "f16"),
     ([(33, 5000), (9000,), (1, 1, 1)], "f32"),
-    ([(1024, 1024), (1024, 1030), (1021, 1021)], "f32"),      # beyond 1024 runs of 1024 chunks together with the next
+    ([(1024, 1024), (1024, 1030), (1021, 1021)], "f32"),      # runs of 2048 chunks, three tensors that share their code
     ([(2300, 2049)], "f32"),
     ([(1000, 4099)], "bf16"),
     ([(2048, 8197), (5,)], "f32"),                             # more than 1024 partial results of one tensor
@@ -83,6 +83,30 @@ def test_clipping_in_two_kernels(shapes, dtype, kind):
     ins = [inputs.round_to(a, dtype) for a in inputs.normal_tensors(shapes, scale=0.3)]
     for got, want in zip(run(ops, to_device(ops, ins), repeats=2), interp.run(ops, ins)):
         assert_close(got.to(torch.float64).cpu().numpy(), want, TOLERANCE[dtype], f"two-step {shapes} {dtype} {kind}")
+
+
+@pytest.mark.parametrize("kind", ["sum", "max"])
+@pytest.mark.parametrize("shape,dtype", [((1031, 4099), "f32"), ((2300, 4097), "bf16")])
+def test_workgroups_that_go_on_to_a_further_run(shape, dtype, kind):
+    """Beyond 4096 runs a workgroup has two or more, of 256 chunks beside five operands: whole ones, a last one of a few chunks, and a last chunk moved back."""
+    announce(f"two-step, several runs {shape} {dtype} {kind}")
+    g = graphs.Graph()
+    xs = [g.parameter(f"x{k}", dtype, shape) for k in range(5)]
+    u = xs[0] if dtype == "f32" else g.convert(xs[0], "f32")
+    for x in xs[1:]:
+        u = g.add(u, x if dtype == "f32" else g.convert(x, "f32"))
+    reduce = g.reduce_sum if kind == "sum" else g.reduce_max
+    s = reduce(reduce(g.multiply(u, u), 1), 0)
+    y = g.multiply(u, g.broadcast(g.multiply(g.constant(2048.0 if kind == "sum" else 1.0), g.rsqrt(s)), shape, 0))
+    g.output(y if dtype == "f32" else g.convert(y, dtype), "y")
+    chunks = -(-shape[0] * shape[1] // (4 if dtype == "f32" else 8))
+    with Plan.two_step(g.ops)[0] as plan:
+        grid = int(plan.describe().split("cta_num=")[1].split(",")[0])
+        assert -(-chunks // 512) == grid < chunks // 256 and chunks % 512 not in (0, 256)
+    ins = inputs.normal_tensors([shape] * 5, dtype, scale=0.4)
+    want = interp.run(g.ops, ins)[0]
+    got = run(g.ops, to_device(g.ops, ins))[0]
+    assert_close(got.to(torch.float64).cpu().numpy(), want, TOLERANCE[dtype], f"several runs {shape} {dtype} {kind}")
 
 
 def test_dtypes_mixed_scalar_inputs_and_outputs():
