@@ -386,7 +386,8 @@ bool two_step_plan(const Graph& g, TwoStepLaunch* out, std::string* err) {
   // ---- geometry
   // A thread has U chunks in flight, a workgroup U * kThreads chunks of a tensor, in both kernels: eight where that leaves
   // every CU a workgroup, fewer in smaller groups and beside more operands.  A workgroup of the second kernel then works on what the
-  // workgroup of the same number has read in the first, and workgroups of one number run on one XCD: as far as the tensors
+  // workgroup of the same number has read in the first (in fp32 groups; in 16-bit ones, whose reduced value is fp32, the first kernel's chunks are
+  // of four elements), and workgroups of one number run on one XCD: as far as the tensors
   // fit the XCDs' caches they are read from there (4 MB each, 32 in all; the rest comes from the memory-side cache).
   // Bound by memory.  Clipping eight fp32 tensors of width 1024, 42 MB, as a replayed graph: 19.4 us (84 MB read, 42 written);
   // with runs of 1281 chunks in the first kernel and 2048 in the second 23.2, four chunks a
@@ -512,9 +513,8 @@ static __device__ __forceinline__ double wave_max(double v) { UNROLL for (int m 
       const Piece& q = pieces[r];
       const bool mx = reds[q.red].is_max;
       pro.line("        double q%zu = %s;", r, mx ? "-__builtin_inf()" : "0.0");
-      // (sixteen loads in flight at most: all of a large one's at once would take registers from the tensors)
-      pro.line("        %s for (int i = 0; i < %lld; ++i) { const int at = i * 64 + lane; if (at < %lld) q%zu = %s; }", q.count > 1024 ? "_Pragma(\"unroll 8\")" : "UNROLL",
-               (long long)((q.count + 63) / 64), (long long)q.count, r,
+      // (at most sixteen loads in flight: a piece is of 1024 partial results or fewer, kPartials of them being cut into four)
+      pro.line("        UNROLL for (int i = 0; i < %lld; ++i) { const int at = i * 64 + lane; if (at < %lld) q%zu = %s; }", (long long)((q.count + 63) / 64), (long long)q.count, r,
                ((mx ? "fmax(q" + std::to_string(r) + ", ps[" : "q" + std::to_string(r) + " + (ps[") + std::to_string(q.first) + " + at])").c_str());
     }
     for (size_t r : share[w]) pro.line("        q%zu = %s(q%zu);", r, reds[pieces[r].red].is_max ? "wave_max" : "wave_sum", r);
