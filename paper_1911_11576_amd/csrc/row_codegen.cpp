@@ -1149,7 +1149,8 @@ struct Gen {
         while ((int64_t)K * W * A.n_col > 16 && L < 1024) { L *= 2; K = (int)((nvec + L - 1) / L); }
         if ((int64_t)K * W * A.n_col > 16) { *err = "generated row schedule: column reductions over rows too long for their running sums to stay in registers"; return false; }
         exact = (int64_t)K * L == nvec && !ragged;
-      } else if ((int64_t)A.n_col * A.cols * 8 > 96 * 1024) {
+      } else if ((int64_t)A.n_col * A.cols * 8 > 96 * 1024 || (int64_t)A.n_col * K * W * L * 8 > 160 * 1024 - 512) {
+        // (the second is what the kernel declares, whole sets of lanes: with eight outputs at most it is 112 KB where the first passes)
         *err = "generated row schedule: column accumulators exceed the LDS";
         return false;
       }

@@ -872,6 +872,13 @@ def test_rows_with_several_column_sums_stay_in_registers(rows, cols, dtype, n):
         assert _in_place_status(ops) == binding.FS_ERR_HIP
 
 
+@pytest.mark.parametrize("n,cols", [(7, 1752), (7, 520), (5, 1032), (1, 2048)])
+def test_column_sums_meet_in_whole_sets_of_lanes(n, cols):
+    """LDS of the hand-over, a wavefront per row (a fixed grid): 64 lanes times as many 8-element chunks as the row fills, per sum."""
+    with Plan(product_with_column_sums(1024, cols, "bf16", n), grid=100) as p:
+        assert p.info()["lds_bytes"] == n * -(-cols // 512) * 512 * 8 <= 160 * 1024 and "cta_num=100" in p.describe()
+
+
 def _unit_norm(shape, n, dtype="f32"):
     """y = u / |u|, u the sum of n tensors."""
     g = Graph()
