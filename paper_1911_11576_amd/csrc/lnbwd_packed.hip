@@ -185,12 +185,14 @@ void launch(Args a, int grid, int cb, bool aligned, hipStream_t s) {
 }
 }  // namespace
 
-// From 256 to 1024 rows.  A strip goes down all rows in one workgroup, at some 50 GB/s, so its time grows with them; the form
-// over many rows pays for partial rows and a second launch.  Replayed graphs, that form against this: 256 x 256 5.3 and 3.7 us, 400 x 1024 8.3
-// and 4.2, 300 x 1600 9.7 and 4.2, 700 x 1000 8.8 and 6.6, 1000 x 1000 11.2 and 8.0, 1000 x 2048 15.1 and 10.7, 800 x 4096 16.0 and 11.7, 1000 x 200 7.4 and 4.8
-// (and half the time of a call on the host); 1200 x 500 7.1 and 8.4, 1500 x 1280 12.1 and 13.3, 1984 x 256 6.0 and 7.8.  Plans of fewer rows
-// keep the workspace that callers know them by.  A strip of 32 columns (whole lines) where the rows start on lines or are long or few, else of 16:
-// 800 x 1024 6.6 against 7.5 us with 16, 800 x 4096 11.7 against 15.0, 300 x 1600 4.2 against 4.9; 700 x 1000 7.0 and 6.6, 1000 x 1500 10.8 and 10.0.
+// Replayed graphs, the form over many rows and this one, in us.
+//   rows     A strip goes down all rows in one workgroup, at some 50 GB/s, so its time grows with them, where the other form pays for partial rows and a
+//            second launch.  Up to 1024: 1000 x 1000 11.2 and 8.0, 1000 x 2048 15.1 and 10.7; 1200 x 500 7.1 and 8.4, 1500 x 1280 12.1 and 13.3.  Not
+//            below 256, whose plans keep the workspace that callers know them by; it costs those time: 255 x 1024 7.4 and 3.8, 128 x 1024 6.5 and 3.6
+//   columns  Up to 4096, what the widest instance holds (two vectors a lane of 512): 800 x 4096 16.0 and 11.7, 256 x 256 5.3 and 3.7
+//   strips   32 columns (whole lines) where the rows start on lines or are long or few, else 16: 800 x 1024 6.6 against 7.5 with 16, 800 x 4096 11.7 against
+//            15.0, 300 x 1600 4.2 against 4.9; 700 x 1000 7.0 and 6.6, 1000 x 1500 10.8 and 10.0
+//   in place (two launches, against the generated kernel) 300 x 1600 12.8 and 7.1, 1000 x 2048 19.8 and 14.8, 700 x 1001 10.9 and 11.0, 1024 x 4096 16.6 and 17.8
 bool lnbwd_packed_plan(const LnBwdSpec& sp, const LaunchOpts& opt, LnBwdLaunch* out) {
   if (sp.out_dx < 0 || sp.out_dgamma < 0 || sp.out_dbeta < 0 || opt.wg_size || opt.rows_per_wave || opt.grid) return false;
   if (sp.cols < 4 || sp.cols > 4096 || sp.rows < 256 || sp.rows > 1024) return false;

@@ -283,10 +283,15 @@ hipError_t launch_K(const LnBwdArgs& a, bool want_dx, bool want_col, int grid, i
 
 }  // namespace
 
-// Rows of no whole number of vectors: with all three outputs, from 1025 rows of 128 elements on.  The generated kernel, which is what such rows had (single
-// elements or vectors at element alignment, one row ahead), against this one: LayerNorm backward over 2000 x 255 11.5 and 6.4 us, 4407 x 138 8.3 and 7.4, 2000 x
-// 1023 13.9 and 11.1, 20000 x 511 32.3 and 23.9, 10624 x 658 20.0 and 18.9, 32768 x 1023 78.8 and 77.8, 32768 x 159 18.7 and 17.9; the other way round 32768 x
-// 131 16.1 and 17.9, where 33 of a wavefront's lanes hold a vector.  Fewer rows have a launch of their own kind (lnbwd_packed.hip), the fewest the generated kernel.
+// Rows of no whole number of vectors, with all three outputs.  Replayed graphs, the generated kernel, which is what such rows had (single elements or vectors
+// at element alignment, one row ahead), and this one, in us:
+//   taken    2000 x 255 11.5 and 6.4, 4407 x 138 8.3 and 7.4, 2000 x 1023 13.9 and 11.1, 20000 x 511 32.3 and 23.9, 10624 x 658 20.0 and 18.9,
+//            32768 x 1023 78.8 and 77.8
+//   not      from 16385 rows below 160 columns, where 33 to 40 of a wavefront's lanes hold a vector: 32768 x 131 16.1 and 17.9, 32768 x 159 17.6
+//            and 17.9 (17000 x 129 13.2 and 11.9)
+//   not      below 128 columns, which leave half of the lanes idle and where the partial rows (256 of 4 KB) outweigh the group: 32768 x 127 18.2 and
+//            17.9, from cold buffers 20.7 and 21.5; 1100 x 67 0.9 MB, 7.6 and 5.9, 16000 x 99 12.5 and 11.9.  Groups of a few MB would gain by it
+// Up to 1024 rows have a launch of their own kind (lnbwd_packed.hip), the fewest the generated kernel.
 bool lnbwd_takes_ragged(const LnBwdSpec& sp, const LaunchOpts& opt) {
   return opt.codegen && opt.wg_size == 0 && opt.rows_per_wave == 0 && opt.grid == 0 && sp.cols % 4 != 0 && sp.cols >= 128 && sp.cols <= 1024 && sp.rows > 1024 && (sp.cols >= 160 || sp.rows <= 16384) &&
          sp.out_dx >= 0 && sp.out_dgamma >= 0 && sp.out_dbeta >= 0;

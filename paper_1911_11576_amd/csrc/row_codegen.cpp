@@ -637,6 +637,8 @@ template <class Op, int L> static __device__ __forceinline__ float lanes_allredu
 )SRC";
 
 // what a maximum and a sum of exponentials in one go add in fp32 groups
+// (2^(p + r) = 2^p (1 + r ln 2) to first order, with p + r = x log2(e): 1.44269502 is log2(e) rounded to fp32, 1.925963e-8 what that leaves out.
+// Terms below 2^-126 come out as 0, beside a sum of at least 1.)
 const char* kOnlinePreamble = R"SRC(
 // e^x for x <= 0 (or NaN): exp2 of the rounded product, times what the product's rounding and log2(e)'s left out; below -104 e^x is 0 in fp32
 static __device__ __forceinline__ float exp_nonpositive(float x) {
