@@ -384,18 +384,19 @@ bool two_step_plan(const Graph& g, TwoStepLaunch* out, std::string* err) {
   if (g.outputs.size() > 16) return fail("more than 16 outputs");
 
   // ---- geometry
-  // A thread has U chunks in flight, a workgroup U * kThreads chunks of a tensor, in both kernels: eight where that leaves
+  // Bound by memory.  A thread has U chunks in flight, a workgroup U * kThreads chunks of a tensor, in both kernels: eight where that leaves
   // every CU a workgroup, fewer in smaller groups and beside more operands.  A workgroup of the second kernel then works on what the
   // workgroup of the same number has read in the first (in fp32 groups; in 16-bit ones, whose reduced value is fp32, the first kernel's chunks are
   // of four elements), and workgroups of one number run on one XCD: as far as the tensors
   // fit the XCDs' caches they are read from there (4 MB each, 32 in all; the rest comes from the memory-side cache).
-  // Bound by memory.  Clipping eight fp32 tensors of width 1024, 42 MB, as a replayed graph: 19.4 us (84 MB read, 42 written);
-  // with runs of 1281 chunks in the first kernel and 2048 in the second 23.2, four chunks a
-  // thread in the first and eight in the second 22.2; as four launches of packed groups 26.3.  Sixteen of width 1600, 164 MB: 76, four launches
-  // and twelve single scalars 104; 2.6 MB: 6.1 with a workgroup on every CU, 6.8 with two, 8.3 as four launches.  Ordinary loads in the
-  // second kernel: 22.3 and 84; nontemporal ones in the first: 23.3 and 84; the second kernel's workgroups in reverse
-  // order: no gain (19.4 and 76).  Up to 4096 partial results, a workgroup going on to its next run behind the first: 210 MB in two
-  // tensors 95.5 us, up to 8192 109, up to 1024 95.1, as launches of their own 105.8; 335 MB in sixteen 153, 155 and 160.
+  // Replayed graphs, in us; clipping of eight fp32 tensors of width 1024 (42 MB; 84 read, 42 written) and of sixteen of width 1600 (164 MB):
+  //   as here                                      19.4 and 76; as four launches of packed groups 26.3, with twelve single scalars 104
+  //   the same runs in both kernels                19.4; of 1281 chunks in the first and 2048 in the second 23.2; four chunks a thread and eight 22.2
+  //   loads, ordinary and then nontemporal         19.4 and 76; ordinary in the second too 22.3 and 84; nontemporal in the first too 23.3 and 84
+  //   a workgroup on every CU                      2.6 MB: 6.1; two 6.8; as four launches 8.3
+  //   up to 4096 partial results, then further runs of a workgroup behind its first: 210 MB in two tensors 95.5, up to 8192 109, up to 1024 95.1, as launches
+  //                                                of their own 105.8; 335 MB in sixteen 153, 155 and 160
+  // The second kernel's workgroups in reverse order: no gain (19.4 and 76).
   int64_t total = 0, total2 = 0;
   int widest = 1;
   for (const Part& p : first) { total += p.n_chunks; widest = std::max(widest, p.n_full); }

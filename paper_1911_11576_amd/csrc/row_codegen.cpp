@@ -1368,11 +1368,11 @@ struct Gen {
     e.s += kReducePreamble;
     if (mma) e.s += kMmaPreamble;
     if (ragged) e.s += kRaggedPreamble;
-    // Maximum and sum of exponentials in one go.  Measured on log-softmax, apart and in one go (these rows are bound by memory, but a
-    // workgroup of 1024 threads that holds a row is alone on its CU unless 64 registers are enough, and then loads, works and stores in turn):
-    // 512 x 50257 fp32 48.2 and 39.4 us, 300 x 45001 30.1 and 21.4, 64 x 64300 15.4 and 11.4, 1024 x 32768 55.3 and 44.9, 3000 x 9001 40.6 and 40.0;
-    // 1856 x 33152 bf16 49.5 and 43.7, 586 x 17994 8.8 and 8.8, 844 x 10176 bf16 6.3 and 6.6: there an exponential is two instructions, and the running
-    // maximum costs more than it saves up to 16384 columns.
+    // Maximum and sum of exponentials in one go: rows of a team, which are bound by memory, but a workgroup of 1024 threads that holds a row is alone on its
+    // CU unless 64 registers are enough, and then loads, works and stores in turn.  Log-softmax, apart and in one go, in us:
+    //   fp32     512 x 50257 48.2 and 39.4, 300 x 45001 30.1 and 21.4, 64 x 64300 15.4 and 11.4, 1024 x 32768 55.3 and 44.9, 3000 x 9001 40.6 and 40.0
+    //   16 bits  from 16385 columns on: 1856 x 33152 bf16 49.5 and 43.7, 586 x 17994 8.8 and 8.8, but 844 x 10176 6.3 and 6.6: there an exponential is two
+    //            instructions, and the running maximum costs more than it saves
     const Online online = L > 64 && !persistent && !mma && (!fast || A.cols > 16384) ? find_online() : Online();
     in_one_go = online.max_id >= 0 && !fast;
     if (in_one_go) e.s += kOnlinePreamble;
@@ -1455,9 +1455,10 @@ struct Gen {
       } else {
         e.line("  const int rl = threadIdx.x / L;");
         e.line("  const long long first_row = (long long)blockIdx.x * RPW, row_step = (long long)gridDim.x * RPW;");
-        // (Teams too, where the chunks cover the row and a thread has registers for it: no copies of the requests, a barrier a row for all
-        // reductions.  LayerNorm backward over 4096 x 4096 46.8 -> 45.2 us, 2048 x 4096 24.2 -> 22.9, the backward tail of 1024 x 4096 34.3 -> 30.0;
-        // the other way round 8192 x 4096, 403 MB, 79.7 -> 80.2, 8192 x 3001 68.1 -> 69.3, 4096 x 6000 65.6 -> 84.0.  Two and three rows ahead are no faster: 46.2, 46.6.)
+        // Teams too, where the chunks cover the row and a thread has registers for it: no copies of the requests, a barrier a row for all
+        // reductions.  Requests copied and buffers that take turns, in us: LayerNorm backward over 4096 x 4096 46.8 and 45.2, 2048 x 4096 24.2 and 22.9, the
+        // backward tail of 1024 x 4096 34.3 and 30.0; the other way round, hence the bounds, 403 MB of 8192 x 4096 79.7 and 80.2, partial chunks (8192 x 3001)
+        // 68.1 and 69.3, two chunks for each of 1024 threads (4096 x 6000) 65.6 and 84.0.  Two and three rows ahead are no faster: 46.2, 46.6.
         if (L <= 64 || (exact && (L < 1024 || K == 1) && A.g.algorithmic_bytes() <= 2 * kTeamBytes)) {
           // One step of the row loop as a function of the row buffer it works on (ph) and of whether every row
           // of the step exists (ALL): the loop below is unrolled over the buffers, which take turns without
