@@ -5,11 +5,13 @@ import random
 import sys
 
 import pytest
+import torch
 
-from paper_1911_11576_amd import FsError, Plan, binding
-from workloads import graphs, inputs
+from oracle import interp
+from paper_1911_11576_amd import FsError, FusedProgram, Plan, binding
+from workloads import TOLERANCE, graphs, inputs
 
-from gpu_util import check_against_oracle
+from gpu_util import alloc_outputs, assert_close, check_against_oracle, to_device
 
 pytestmark = pytest.mark.gpu
 
@@ -148,3 +150,92 @@ def test_random_groups_around_two_dots(seed):
     with Plan(ops, "generated") as plan:
         assert plan.info()["schedule"] == "block_dot" and plan.info()["n_kernels"] == 1
     check_against_oracle(ops, ins, "generated", what=f"random dot group {seed}")
+
+
+def random_whole_tensor_group(rng):
+    """Tensors of several shapes and dtypes, sums and maxima over whole ones, ops on those scalars, and ops on the tensors that read them."""
+    g = graphs.Graph()
+
+    def f32(v):
+        return v if g.dtype(v) == "f32" else g.convert(v, "f32")
+
+    def mixed(a, b):
+        return rng.choice([g.add, g.subtract, g.multiply, g.maximum])(a, b)
+
+    def bounded(v):
+        return rng.choice([lambda: v, lambda: g.tanh(v), lambda: g.negate(v), lambda: g.multiply(v, g.constant(0.5)), lambda: g.multiply(v, v), lambda: g.logistic(v)])()
+
+    tensors, pshapes, dtypes = [], [], []
+    for k in range(rng.randint(1, 5)):
+        shape = rng.choice([(1,), (3,), (7,), (33, 100), (4095,), (3, 5, 7), (1030,), (257, 129), (2, 3, 4, 5), (64, 64), (9001,)])
+        dt = rng.choice(["f32", "f32", "bf16", "f16"])
+        ps = [g.parameter(f"x{k}_{j}", dt if j == 0 else rng.choice([dt, "f32"]), shape) for j in range(rng.choice([1, 1, 2, 3]))]
+        pshapes += [shape] * len(ps)
+        dtypes += [g.dtype(p) for p in ps]
+        v = bounded(f32(ps[0]))
+        for p in ps[1:]:
+            v = mixed(v, bounded(f32(p)))
+        tensors.append((v, ps, dt))
+    n_inputs = rng.randint(0, 2)
+    scalars = [g.parameter(f"s{k}", "f32", ()) for k in range(n_inputs)]
+    for v, ps, _ in tensors:
+        for _ in range(rng.choice([0, 1, 1, 2]) if v != tensors[0][0] else 1):
+            s, size, total = rng.choice([v, f32(ps[0]), f32(ps[-1])]), 1, rng.random() < 0.6
+            if rng.random() < 0.5:
+                s = bounded(s)
+            for e in g.shape(s):
+                size *= e
+            while len(g.shape(s)) > 0:
+                s = (g.reduce_sum if total else g.reduce_max)(s, rng.choice([0, len(g.shape(s)) - 1]))
+            scalars.append(g.multiply(s, g.constant(1.0 / size)) if total else s)
+    for _ in range(rng.randint(0, 4)):
+        a = mixed(rng.choice(scalars), rng.choice(scalars + [g.constant(0.75)]))
+        scalars.append(rng.choice([lambda: g.tanh(a), lambda: g.sqrt(g.add(g.multiply(a, a), g.constant(1.0))), lambda: g.divide(a, g.sqrt(g.add(g.multiply(a, a), g.constant(0.5))))])())
+    reads = False
+    for v, ps, dt in tensors:
+        y = rng.choice([v, f32(ps[0])])
+        for _ in range(rng.choice([0, 1, 1, 2]) if reads else 1):
+            y = mixed(y, g.broadcast(rng.choice(scalars[n_inputs:]), g.shape(y), 0))
+            reads = True
+        y = g.add(bounded(y), g.constant(0.25))
+        g.output(y if dt == "f32" else g.convert(y, dt))
+        if rng.random() < 0.2:
+            g.output(g.multiply(y, g.constant(2.0)))
+    for s in rng.sample(scalars[n_inputs:], rng.choice([0, 0, 1])):
+        g.output(g.add(s, g.constant(0.5)))
+    # (what no output reads is left out, the inputs apart)
+    read = set()
+    for i in range(len(g.ops) - 1, -1, -1):
+        if g.ops[i].kind in ("output", "parameter") or i in read:
+            read |= {i, *g.ops[i].operands}
+    number = {old: new for new, old in enumerate(sorted(read))}
+    ops = [g.ops[i]._replace(operands=tuple(number[o] for o in g.ops[i].operands)) for i in sorted(read)]
+    return ops, pshapes + [()] * n_inputs, dtypes + ["f32"] * n_inputs
+
+
+@pytest.mark.parametrize("seed", range(24))
+def test_random_whole_tensor_groups(seed):
+    """As one two-step plan where that takes the group, and as a program, whose plan may or may not be one."""
+    rng = random.Random(90210 + seed)
+    ops, pshapes, dtypes = random_whole_tensor_group(rng)
+    announce(f"random whole-tensor group seed {seed}: {len(ops)} ops over {pshapes}")
+    ins = [inputs.normal_tensors([s or (1,)], d, seed_offset=300 + 10 * seed + k)[0].reshape(s) for k, (s, d) in enumerate(zip(pshapes, dtypes))]
+    want = interp.run(ops, ins)
+    dev_in = to_device(ops, ins)
+    results = []
+    try:
+        plan, extra = Plan.two_step(ops)
+        with plan:
+            outs = alloc_outputs(ops)
+            plan.launch(dev_in, outs + [torch.empty(extra, dtype=torch.uint8, device="cuda:0")])
+            torch.cuda.synchronize()
+            results.append(outs)
+    except FsError as e:
+        assert e.status == binding.FS_ERR_UNSUPPORTED
+    with FusedProgram(ops) as prog:
+        results.append(prog.run(dev_in))
+        torch.cuda.synchronize()
+    tol = TOLERANCE["f32" if set(dtypes) == {"f32"} else "bf16"]      # (16-bit groups take the short forms of tanh and exp)
+    for outs in results:
+        for k, (a, b) in enumerate(zip(outs, want)):
+            assert_close(a.double().cpu().numpy(), b, tol, f"random whole-tensor group {seed} output {k}")
