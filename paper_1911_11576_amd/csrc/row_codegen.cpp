@@ -1757,9 +1757,8 @@ struct Gen {
         // (a lane to a wavefront's results: sixteen of each in every lane's registers are what the row's values leave no room for)
         e.line("    const float wm = exch[%d][threadIdx.x & (T - 1)];", red_index);
         e.line("    r%d = lanes_allreduce<MaxOp, T>(wm);", m);
-        e.line("    r%d = lanes_allreduce<SumOp, T>(exch[%d][threadIdx.x & (T - 1)] * %s(fmaxf(wm, -3.402823466e38f) - fmaxf(r%d, -3.402823466e38f)));", q, red_index + 1, ex.c_str(), m);
-        // (a row of nothing but -inf: exp(-inf - -inf) is NaN, as where the two reductions are apart)
-        e.line("    if (r%d == -__builtin_inff()) r%d = __builtin_nanf(\"\");", m, q);
+        // (the row's maximum as it is: nothing but -inf makes the sum 0 times exp(+inf), NaN as exp(-inf - -inf) is where the two reductions are apart)
+        e.line("    r%d = lanes_allreduce<SumOp, T>(exch[%d][threadIdx.x & (T - 1)] * %s(fmaxf(wm, -3.402823466e38f) - r%d));", q, red_index + 1, ex.c_str(), m);
         e.line("  }");
         red_index += 2;
       }
