@@ -98,7 +98,8 @@ int attn_stitch_launch(const AttnSpec& sp, const AttnLaunch& l, const void* cons
   const bool f16 = sp.dtype == DT_F16;
   const hipError_t e = l.decode ? attn_decode_launch(a, f16, l.grid, l.wg, s)
                      : l.nq <= 2 ? (f16 ? attn_launch_f16 : attn_launch_bf16)(a, l.nq, l.nk, s)
-                                 : (f16 ? attn_launch_f16_wide : attn_launch_bf16_wide)(a, l.nq, l.nk, s);
+                     : l.nq == 4 ? (f16 ? attn_launch_f16_wide : attn_launch_bf16_wide)(a, l.nk, s)
+                                 : (f16 ? attn_launch_f16_widest : attn_launch_bf16_widest)(a, l.nk, s);
   if (e != hipSuccess) { *err = std::string("attn_stitch launch: ") + hipGetErrorString(e); return -1; }
   return 0;
 }

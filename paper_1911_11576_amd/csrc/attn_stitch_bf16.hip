@@ -3,6 +3,6 @@
 
 namespace fs {
 hipError_t attn_launch_bf16(const AttnArgs& a, int nq, int nk, hipStream_t s) {
-  return attn_launch_tiles<bf16_t, 1, 2>(a, nq, nk, s);
+  return nq == 1 ? attn_launch_NK<bf16_t, 1>(a, nk, s) : attn_launch_NK<bf16_t, 2>(a, nk, s);
 }
 }  // namespace fs

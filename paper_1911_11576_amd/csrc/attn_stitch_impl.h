@@ -77,11 +77,18 @@ template <class Op> __device__ __forceinline__ float rows_allreduce(float v) {
   return Op::apply(as_f32(r[0]), as_f32(r[1]));
 }
 
+// no mask and no operand; a mask of one row for all queries, through LDS; that or none, with gate, residual or log-sum-exp; a mask
+// value of its own for every score, in registers, with or without the rest
+enum { ATTN_BARE = 0, ATTN_KEY_MASK = 1, ATTN_EPILOGUE = 2, ATTN_FULL_MASK = 3 };
+
 template <int N> struct TileCount { static constexpr int value = N; };   // a compile-time count handed to a generic lambda
 
 // NQ: 16-row tiles of queries (workgroup = NQ wavefronts); NK: 16-key tiles; D: head dim;
-// X: the group has a mask, an epilogue operand or a second output (without any of them those paths
-// are compiled out: on the bare dot-softmax-dot group their run-time tests alone cost 0.15 us of 6);
+// X: what the group has around the dots, one of the four kinds below (run-time tests for what is not there cost 0.15 us of 6 on the
+// bare group, and registers for what is not there cost workgroups on a CU: with one kind for all that is not bare and the key mask in
+// registers, 128 x 128 x 64 held 130, two more than let two workgroups share a CU, and takes 78 with a key mask now; bf16, key mask:
+// 2000 x 128 x 128 x 64 41.2 -> 29.0 us, 1000 x 128 x 128 x 128 36.4 -> 29.3, 359 x 64 x 50 x 128 8.5 -> 7.2; 4096 x 50 x 50 x 64 fp16
+// with every operand 40.9 -> 33.2);
 // E: the lengths are exactly 16 NQ queries and 16 NK keys (NK >= 2), so no row is clamped and no key
 // or query is tested against a length; S: O leaves with nontemporal stores.
 // With two wavefronts per SIMD and a memory phase of one round trip, the kernel's time follows its
@@ -89,8 +96,9 @@ template <int N> struct TileCount { static constexpr int value = N; };   // a co
 // number of key tiles it needs, whether a tile touches the causal diagonal or the end of the keys)
 // is kept in scalar registers and decided by scalar branches, and only tiles that a mask can touch
 // pay for the comparisons.
-template <typename T, int NQ, int NK, int D, bool X, bool E, bool S>
+template <typename T, int NQ, int NK, int D, int X, bool E, bool S>
 __global__ __launch_bounds__(64 * NQ) void attn_stitch_kernel(const AttnArgs a) {
+  constexpr bool KEYS = X == ATTN_KEY_MASK || X == ATTN_EPILOGUE, FULL = X == ATTN_FULL_MASK, OPS = X >= ATTN_EPILOGUE;
   constexpr int KS = D / 32;                 // k-steps of the first dot
   constexpr int NKP = NK < 2 ? 2 : NK;       // key tiles padded to whole 32-key steps
   constexpr int VP = D + (D == 64 ? 8 : 16); // padded row length of V in LDS (halves): the four rows of a
@@ -100,6 +108,8 @@ __global__ __launch_bounds__(64 * NQ) void attn_stitch_kernel(const AttnArgs a) 
   extern __shared__ uint16_t smem[];
   uint16_t* ksh = smem;                      // [NK * 16][KP]  K as stored
   uint16_t* vsh = smem + NK * 16 * KP;       // [NKP * 16][VP]  V as stored, keys beyond the last zero
+  // the key mask in units of log 2, in the padding of K: keys 4m .. 4m+3 behind row 4m
+  auto mask_at = [&](int key) __attribute__((always_inline)) { return reinterpret_cast<float*>(ksh + (key & ~3) * KP + D) + (key & 3); };
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));    // the same in the whole wavefront
   const int c = lane & 15, g = lane >> 4;
@@ -120,8 +130,8 @@ __global__ __launch_bounds__(64 * NQ) void attn_stitch_kernel(const AttnArgs a) 
   if (a.skip_masked_tiles && NQ < wg_tiles) wg_tiles = NQ;
   if (a.skip_masked_tiles && w + 1 < tiles) tiles = w + 1;
 
-  // ---- every global load of the wavefront is issued before the first use: Q, its share of K and
-  // of V (for LDS), the mask values of its scores and the epilogue operands.
+  // ---- every global load of the dots is issued before the first use: Q, its share of K and
+  // of V (for LDS), the mask.
   // Loads behind run-time conditions would each wait out a full memory latency in turn; rows
   // beyond the lengths are clamped to the last row and masked later.
   constexpr int CH = D / 8;                  // 16-byte chunks per row
@@ -130,7 +140,24 @@ __global__ __launch_bounds__(64 * NQ) void attn_stitch_kernel(const AttnArgs a) 
   constexpr bool VFULL = VTOT % (64 * NQ) == 0;   // every lane has a chunk in every round
   u32x4 qf[KS], kf[KT][KS], vreg[NV];
   f32x4 mk[NK];
+  constexpr int NM = (NK * 16 + 64 * NQ - 1) / (64 * NQ);
+  float mkey[NM];
   u32x2 gt[D / 16], rs[D / 16];
+  // gate and residual are requested behind the softmax: up to 32 registers less while scores and K fragments are held, and K and V arrive
+  // sooner.  Against requests at the top (bf16, every operand, warm buffers): 800 x 128 x 128 x 64 causal 19.0 -> 16.4 us, 300 x 100 x
+  // 100 x 64 9.5 -> 8.1, fp16 2000 x 80 x 80 x 128 59.6 -> 53.7
+  auto operands = [&]() __attribute__((always_inline)) {
+    if (OPS && a.gate) {
+      const uint16_t* p = static_cast<const uint16_t*>(a.gate) + ((int64_t)b * sq + qrow) * D + 4 * g;
+#pragma unroll
+      for (int dt = 0; dt < D / 16; ++dt) gt[dt] = *reinterpret_cast<const u32x2*>(p + dt * 16);
+    }
+    if (OPS && a.res) {
+      const uint16_t* p = static_cast<const uint16_t*>(a.res) + ((int64_t)b * sq + qrow) * D + 4 * g;
+#pragma unroll
+      for (int dt = 0; dt < D / 16; ++dt) rs[dt] = *reinterpret_cast<const u32x2*>(p + dt * 16);
+    }
+  };
   {
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks)
@@ -150,7 +177,7 @@ __global__ __launch_bounds__(64 * NQ) void attn_stitch_kernel(const AttnArgs a) 
       const int key = E ? ci / CH : min(ci / CH, sk - 1), d0 = (ci % CH) * 8;
       vreg[i] = *reinterpret_cast<const u32x4*>(vb + (int64_t)key * D + d0);
     }
-    if (X && a.mask) {
+    if (FULL && a.mask) {
       const float* mrow = a.mask + (int64_t)b * a.mask_sb + (int64_t)qrow * a.mask_sq;
 #pragma unroll
       for (int kt = 0; kt < NK; ++kt) {
@@ -166,15 +193,9 @@ __global__ __launch_bounds__(64 * NQ) void attn_stitch_kernel(const AttnArgs a) 
         }
       }
     }
-    if (X && a.gate) {
-      const uint16_t* p = static_cast<const uint16_t*>(a.gate) + ((int64_t)b * sq + qrow) * D + 4 * g;
+    if (KEYS && a.mask) {
 #pragma unroll
-      for (int dt = 0; dt < D / 16; ++dt) gt[dt] = *reinterpret_cast<const u32x2*>(p + dt * 16);
-    }
-    if (X && a.res) {
-      const uint16_t* p = static_cast<const uint16_t*>(a.res) + ((int64_t)b * sq + qrow) * D + 4 * g;
-#pragma unroll
-      for (int dt = 0; dt < D / 16; ++dt) rs[dt] = *reinterpret_cast<const u32x2*>(p + dt * 16);
+      for (int i = 0; i < NM; ++i) mkey[i] = a.mask[(int64_t)b * a.mask_sb + min((int)threadIdx.x + i * 64 * NQ, sk - 1)];
     }
   }
   // the loads stay here: left alone, the compiler moves some down to their use, behind the wait for
@@ -199,7 +220,12 @@ __global__ __launch_bounds__(64 * NQ) void attn_stitch_kernel(const AttnArgs a) 
     const u32x4 t = (E || key < sk) ? vreg[i] : u32x4{0u, 0u, 0u, 0u};
     if (VFULL || cu < VTOT) *reinterpret_cast<u32x4*>(vsh + key * VP + d0) = t;
   }
-  __syncthreads();   // K and V complete
+  if (KEYS && a.mask) {
+#pragma unroll
+    for (int i = 0; i < NM; ++i)
+      if (NK * 16 % (64 * NQ) == 0 || (int)threadIdx.x + i * 64 * NQ < NK * 16) *mask_at(threadIdx.x + i * 64 * NQ) = mkey[i] * 1.4426950408889634f;
+  }
+  __syncthreads();   // K, V and the mask complete
 
   // the A fragment of the second dot for 32-key step kk and head-dim tile dt: keys 32kk+16h+4g+i at
   // k-slot 4h+i, head-dim 16dt+c.  Lane c addresses row (c / 4) and columns 4 (c % 4) .. +3 of the tile.
@@ -264,8 +290,13 @@ __global__ __launch_bounds__(64 * NQ) void attn_stitch_kernel(const AttnArgs a) 
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         float z = acc[kt][i] * sc2;
-        if (X && a.mask) z = fmaf(mk[kt][i], kLog2e, z);
+        if (FULL && a.mask) z = fmaf(mk[kt][i], kLog2e, z);
         acc[kt][i] = z;
+      }
+      if (KEYS && a.mask) {
+        const f32x4 m = *reinterpret_cast<const f32x4*>(mask_at(16 * kt + 4 * g));
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[kt][i] += m[i];
       }
       if (a.causal && 16 * kt + 15 > q0) {             // the tile holds keys right of some row's diagonal
 #pragma unroll
@@ -290,7 +321,7 @@ __global__ __launch_bounds__(64 * NQ) void attn_stitch_kernel(const AttnArgs a) 
       }
     sum = rows_allreduce<SumOp>(sum);
     const float inv = __builtin_amdgcn_rcpf(sum);
-    if (X && a.lse && g == 0 && qi < sq) a.lse[(int64_t)b * sq + qi] = (mx + __builtin_amdgcn_logf(sum)) * kLn2;
+    if (OPS && a.lse && g == 0 && qi < sq) a.lse[(int64_t)b * sq + qi] = (mx + __builtin_amdgcn_logf(sum)) * kLn2;
     // P rounded to the dot's dtype, packed in k-slot order: slots 4h+i of step kk <- tile 2kk+h
     u32x4 pb[KST];                              // P^T, the second dot's B fragments
 #pragma unroll
@@ -307,47 +338,54 @@ __global__ __launch_bounds__(64 * NQ) void attn_stitch_kernel(const AttnArgs a) 
         pb[kk][2 * h + 1] = Mfma<T>::pack(p[2], p[3]);
       }
 
-    // ---- second dot, transposed: O^T(D x 16) = V^T(D x keys) . P^T ---------------------------
-    f32x4 o[D / 16];
+    operands();
+    asm volatile("" ::: "memory");       // (requested here, not at their use)
+    // ---- second dot, transposed: O^T(D x 16) = V^T(D x keys) . P^T, up to 64 columns of O at a time ------
+    constexpr int DH = (D < 64 ? D : 64) / 16;
 #pragma unroll
-    for (int dt = 0; dt < D / 16; ++dt) {
-      if constexpr (PRE) o[dt] = Mfma<T>::run(vpre[dt], pb[0], f32x4{0.f, 0.f, 0.f, 0.f});
-      else o[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
-    }
+    for (int d0 = 0; d0 < D / 16; d0 += DH) {
+      f32x4 o[DH];
 #pragma unroll
-    for (int kk = PRE ? 1 : 0; kk < KST; ++kk) {
-#pragma unroll
-      for (int dt = 0; dt < D / 16; ++dt) o[dt] = Mfma<T>::run(vfrag(kk, dt), pb[kk], o[dt]);
-    }
-    // ---- epilogue on the accumulators: the lane holds O[q0+c][16dt+4g+i], i < 4 -----------------
-    if (X && a.gate) {
-#pragma unroll
-      for (int dt = 0; dt < D / 16; ++dt) {
-        o[dt][0] *= Mfma<T>::lo(gt[dt][0]); o[dt][1] *= Mfma<T>::hi(gt[dt][0]);
-        o[dt][2] *= Mfma<T>::lo(gt[dt][1]); o[dt][3] *= Mfma<T>::hi(gt[dt][1]);
+      for (int dt = 0; dt < DH; ++dt) {
+        if constexpr (PRE) o[dt] = Mfma<T>::run(vpre[dt], pb[0], f32x4{0.f, 0.f, 0.f, 0.f});
+        else o[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
       }
-    }
-    if (X && a.res) {
 #pragma unroll
-      for (int dt = 0; dt < D / 16; ++dt) {
-        o[dt][0] += Mfma<T>::lo(rs[dt][0]); o[dt][1] += Mfma<T>::hi(rs[dt][0]);
-        o[dt][2] += Mfma<T>::lo(rs[dt][1]); o[dt][3] += Mfma<T>::hi(rs[dt][1]);
+      for (int kk = PRE ? 1 : 0; kk < KST; ++kk) {
+#pragma unroll
+        for (int dt = 0; dt < DH; ++dt) o[dt] = Mfma<T>::run(vfrag(kk, d0 + dt), pb[kk], o[dt]);
       }
-    }
-    // ---- 8 bytes per tile.  Lanes g and g^1 trade
-    // one tile of a pair (dt, dt+1) so that each ends up with 8 consecutive values, 16 bytes: after
-    // the row swap lane g holds d = 32(dt/2) + 16(g&1) + 8(g>>1) .. +7 ------------------------
-    uint16_t* orow = ob + (int64_t)qrow * D + 16 * (g & 1) + 8 * (g >> 1);
+      // ---- epilogue on the accumulators: the lane holds O[q0+c][16dt+4g+i], i < 4 -----------------
+      if (OPS && a.gate) {
 #pragma unroll
-    for (int dp = 0; dp < D / 32; ++dp) {
-      const uint32_t a0 = Mfma<T>::pack(o[2 * dp][0], o[2 * dp][1]), a1 = Mfma<T>::pack(o[2 * dp][2], o[2 * dp][3]);
-      const uint32_t b0 = Mfma<T>::pack(o[2 * dp + 1][0], o[2 * dp + 1][1]), b1 = Mfma<T>::pack(o[2 * dp + 1][2], o[2 * dp + 1][3]);
-      // odd rows of the first operand trade places with even rows of the second
-      const auto r0 = __builtin_amdgcn_permlane16_swap(a0, b0, false, false);
-      const auto r1 = __builtin_amdgcn_permlane16_swap(a1, b1, false, false);
-      const u32x4 w4 = {r0[0], r1[0], r0[1], r1[1]};
-      if constexpr (S) { if (E || qi < sq) stream_store16(orow + dp * 32, w4); }
-      else if (E || qi < sq) *reinterpret_cast<u32x4*>(orow + dp * 32) = w4;
+        for (int dt = 0; dt < DH; ++dt) {
+          o[dt][0] *= Mfma<T>::lo(gt[d0 + dt][0]); o[dt][1] *= Mfma<T>::hi(gt[d0 + dt][0]);
+          o[dt][2] *= Mfma<T>::lo(gt[d0 + dt][1]); o[dt][3] *= Mfma<T>::hi(gt[d0 + dt][1]);
+        }
+      }
+      if (OPS && a.res) {
+#pragma unroll
+        for (int dt = 0; dt < DH; ++dt) {
+          o[dt][0] += Mfma<T>::lo(rs[d0 + dt][0]); o[dt][1] += Mfma<T>::hi(rs[d0 + dt][0]);
+          o[dt][2] += Mfma<T>::lo(rs[d0 + dt][1]); o[dt][3] += Mfma<T>::hi(rs[d0 + dt][1]);
+        }
+      }
+      // ---- 8 bytes per tile.  Lanes g and g^1 trade
+      // one tile of a pair (dt, dt+1) so that each ends up with 8 consecutive values, 16 bytes: after
+      // the row swap lane g holds d = 32(dt/2) + 16(g&1) + 8(g>>1) .. +7 ------------------------
+      uint16_t* orow = ob + (int64_t)qrow * D + 16 * d0 + 16 * (g & 1) + 8 * (g >> 1);
+#pragma unroll
+      for (int dp = 0; dp < DH / 2; ++dp) {
+        const uint32_t a0 = Mfma<T>::pack(o[2 * dp][0], o[2 * dp][1]), a1 = Mfma<T>::pack(o[2 * dp][2], o[2 * dp][3]);
+        const uint32_t b0 = Mfma<T>::pack(o[2 * dp + 1][0], o[2 * dp + 1][1]), b1 = Mfma<T>::pack(o[2 * dp + 1][2], o[2 * dp + 1][3]);
+        // odd rows of the first operand trade places with even rows of the second
+        const auto r0 = __builtin_amdgcn_permlane16_swap(a0, b0, false, false);
+        const auto r1 = __builtin_amdgcn_permlane16_swap(a1, b1, false, false);
+        const u32x4 w4 = {r0[0], r1[0], r0[1], r1[1]};
+        if constexpr (S) { if (E || qi < sq) stream_store16(orow + dp * 32, w4); }
+        else if (E || qi < sq) *reinterpret_cast<u32x4*>(orow + dp * 32) = w4;
+      }
+      if constexpr (D > 64) __builtin_amdgcn_sched_barrier(0);      // (the halves' accumulators are not held together)
     }
   };
   if (active) {
@@ -371,7 +409,7 @@ inline int64_t attn_lds_bytes(int NK, int D) {
   return 2 * ((int64_t)NKP * 16 * VP + (int64_t)NK * 16 * (D + 8));
 }
 
-template <typename T, int NQ, int NK, int D, bool X, bool E, bool S>
+template <typename T, int NQ, int NK, int D, int X, bool E, bool S>
 hipError_t attn_launch_form(const AttnArgs& a, hipStream_t s) {
   const size_t lds = (size_t)attn_lds_bytes(NK, D);
   if (lds > 64 * 1024) {     // more dynamic LDS than a kernel may use unasked
@@ -382,17 +420,22 @@ hipError_t attn_launch_form(const AttnArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <typename T, int NQ, int NK, int D>
-hipError_t attn_launch_one(const AttnArgs& a, hipStream_t s) {
-  const bool extras = a.mask || a.gate || a.res || a.lse;
+template <typename T, int NQ, int NK, int D, int X>
+hipError_t attn_launch_class(const AttnArgs& a, hipStream_t s) {
   if constexpr (NK >= 2) {
     if (a.sq == 16 * NQ && a.sk == 16 * NK) {
-      if (!extras) return attn_launch_form<T, NQ, NK, D, false, true, false>(a, s);
-      return a.stream_out ? attn_launch_form<T, NQ, NK, D, true, true, true>(a, s) : attn_launch_form<T, NQ, NK, D, true, true, false>(a, s);
+      if constexpr (X == ATTN_BARE) return attn_launch_form<T, NQ, NK, D, X, true, false>(a, s);
+      else return a.stream_out ? attn_launch_form<T, NQ, NK, D, X, true, true>(a, s) : attn_launch_form<T, NQ, NK, D, X, true, false>(a, s);
     }
   }
-  if (extras) return a.stream_out ? attn_launch_form<T, NQ, NK, D, true, false, true>(a, s) : attn_launch_form<T, NQ, NK, D, true, false, false>(a, s);
-  return a.stream_out ? attn_launch_form<T, NQ, NK, D, false, false, true>(a, s) : attn_launch_form<T, NQ, NK, D, false, false, false>(a, s);
+  return a.stream_out ? attn_launch_form<T, NQ, NK, D, X, false, true>(a, s) : attn_launch_form<T, NQ, NK, D, X, false, false>(a, s);
+}
+
+template <typename T, int NQ, int NK, int D>
+hipError_t attn_launch_one(const AttnArgs& a, hipStream_t s) {
+  if (a.mask && a.mask_sq != 0) return attn_launch_class<T, NQ, NK, D, ATTN_FULL_MASK>(a, s);
+  if (a.gate || a.res || a.lse) return attn_launch_class<T, NQ, NK, D, ATTN_EPILOGUE>(a, s);
+  return a.mask ? attn_launch_class<T, NQ, NK, D, ATTN_KEY_MASK>(a, s) : attn_launch_class<T, NQ, NK, D, ATTN_BARE>(a, s);
 }
 
 template <typename T, int NQ, int NK>
@@ -414,16 +457,13 @@ hipError_t attn_launch_NK(const AttnArgs& a, int nk, hipStream_t s) {
   }
 }
 
-// one translation unit per dtype and pair of query tile counts
-template <typename T, int NQ0, int NQ1>
-hipError_t attn_launch_tiles(const AttnArgs& a, int nq, int nk, hipStream_t s) {
-  return nq == NQ0 ? attn_launch_NK<T, NQ0>(a, nk, s) : attn_launch_NK<T, NQ1>(a, nk, s);
-}
-
 hipError_t attn_decode_launch(const AttnArgs& a, bool f16, int grid, int wg, hipStream_t s);      // one query per batch element
+// one translation unit per dtype and number of query tiles (1 and 2 share one)
 hipError_t attn_launch_f16(const AttnArgs& a, int nq, int nk, hipStream_t s);             // 1 or 2 query tiles
-hipError_t attn_launch_f16_wide(const AttnArgs& a, int nq, int nk, hipStream_t s);        // 4 or 8
+hipError_t attn_launch_f16_wide(const AttnArgs& a, int nk, hipStream_t s);                // 4
+hipError_t attn_launch_f16_widest(const AttnArgs& a, int nk, hipStream_t s);              // 8
 hipError_t attn_launch_bf16(const AttnArgs& a, int nq, int nk, hipStream_t s);
-hipError_t attn_launch_bf16_wide(const AttnArgs& a, int nq, int nk, hipStream_t s);
+hipError_t attn_launch_bf16_wide(const AttnArgs& a, int nk, hipStream_t s);
+hipError_t attn_launch_bf16_widest(const AttnArgs& a, int nk, hipStream_t s);
 
 }  // namespace fs

@@ -500,6 +500,11 @@ DECODE_CASES += [(b, 1, sk, d, dt, kw) for b, sk, d, dt, kw in [
     (767, 64, 64, "f16", dict()), (769, 64, 64, "f16", dict()),                          # (12 MB lie between them)
     (1031, 128, 128, "bf16", dict()), (1030, 100, 128, "f16", dict(mask="shared", lse=True)), (1033, 70, 128, "bf16", dict()), (4100, 100, 32, "f16", dict(mask="key"))]]
 ATTN_BLOCK_CASES += DECODE_CASES
+# a mask of keys in the padding of K: more keys than a workgroup has lanes, a single key, partial groups of four, with and without operands
+ATTN_BLOCK_CASES += [(2, 16, 128, 64, "f16", dict(mask="key")), (3, 9, 70, 32, "bf16", dict(mask="key", residual=True)), (2, 128, 1, 64, "f16", dict(mask="key")),
+                     (3, 20, 17, 32, "f16", dict(mask="key", lse=True)), (2, 65, 33, 128, "bf16", dict(mask="key", gate=True)), (2, 128, 128, 128, "f16", dict(mask="key")),
+                     (2, 100, 100, 64, "bf16", dict(causal=True, mask="key", gate=True, residual=True, lse=True)), (3, 64, 113, 128, "f16", dict(mask="key", residual=True)),
+                     (2, 128, 128, 64, "bf16", dict(causal=True, mask="key", residual=True)), (3, 50, 128, 128, "bf16", dict(mask="shared", gate=True, residual=True))]
 
 
 @pytest.mark.parametrize("case", ATTN_BLOCK_CASES, ids=lambda c: f"{c[0]}x{c[1]}x{c[2]}x{c[3]}-{c[4]}-" + "+".join(sorted(c[5])))
