@@ -123,6 +123,11 @@ __global__ __launch_bounds__(64 * NQ) void attn_stitch_kernel(const AttnArgs a) 
   const bool active = E || q0 < sq;
   const int qi = q0 + c;                     // the lane's query row
   const int qrow = E ? qi : min(qi, sq - 1);
+  // a wavefront's addresses: a base in scalar registers and 32 bits of offset a lane
+  const uint32_t qoff = (uint32_t)(qrow * D + 8 * g) * 2, goff = (uint32_t)(qrow * D + 4 * g) * 2;
+  auto at16 = [](const uint16_t* base, uint32_t off, int more) __attribute__((always_inline)) {
+    return *reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(base) + off + more);
+  };
   // key tiles this wavefront needs: all that hold a valid key, cut at the diagonal when
   // masked scores are exactly -inf
   int tiles = (sk + 15) / 16;
@@ -146,36 +151,39 @@ __global__ __launch_bounds__(64 * NQ) void attn_stitch_kernel(const AttnArgs a) 
   // gate and residual are requested behind the softmax: up to 32 registers less while scores and K fragments are held, and K and V arrive
   // sooner.  Against requests at the top (bf16, every operand, warm buffers): 800 x 128 x 128 x 64 causal 19.0 -> 16.4 us, 300 x 100 x
   // 100 x 64 9.5 -> 8.1, fp16 2000 x 80 x 80 x 128 59.6 -> 53.7
+  // ... but at the top where a mask value per score fills the registers either way: 4096 x 64 x 64 x 64 full mask, causal 48.4 against 47.5, 1536 x 100
+  // x 100 x 64 34.8 against 34.2 (3000 x 50 x 50 x 64 36.2 against 37.5, 800 x 128 x 128 x 64 23.4 against 23.8, 1000 x 128 x 128 x 128 51.3 against 53.9)
+  constexpr bool LATE = !(FULL && D == 64 && ((NQ == 4 && NK == 4 && E) || (NQ == 8 && NK == 8 && !E)));
   auto operands = [&]() __attribute__((always_inline)) {
     if (OPS && a.gate) {
-      const uint16_t* p = static_cast<const uint16_t*>(a.gate) + ((int64_t)b * sq + qrow) * D + 4 * g;
+      const char* p = static_cast<const char*>(a.gate) + (int64_t)b * sq * D * 2 + goff;
 #pragma unroll
-      for (int dt = 0; dt < D / 16; ++dt) gt[dt] = *reinterpret_cast<const u32x2*>(p + dt * 16);
+      for (int dt = 0; dt < D / 16; ++dt) gt[dt] = *reinterpret_cast<const u32x2*>(p + dt * 32);
     }
     if (OPS && a.res) {
-      const uint16_t* p = static_cast<const uint16_t*>(a.res) + ((int64_t)b * sq + qrow) * D + 4 * g;
+      const char* p = static_cast<const char*>(a.res) + (int64_t)b * sq * D * 2 + goff;
 #pragma unroll
-      for (int dt = 0; dt < D / 16; ++dt) rs[dt] = *reinterpret_cast<const u32x2*>(p + dt * 16);
+      for (int dt = 0; dt < D / 16; ++dt) rs[dt] = *reinterpret_cast<const u32x2*>(p + dt * 32);
     }
   };
   {
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks)
-      qf[ks] = *reinterpret_cast<const u32x4*>(qb + (int64_t)qrow * D + ks * 32 + 8 * g);
+      qf[ks] = at16(qb, qoff, ks * 64);
 #pragma unroll
     for (int j = 0; j < KT; ++j) {
-      const int kt = w + j * NQ;               // the same for the whole wavefront
-      const int krow = E ? kt * 16 + c : min(kt * 16 + c, sk - 1);
+      // (a tile beyond the last asks for the last row again: with a branch around every load the compiler waited out one behind the other:
+      // bf16 key mask 359 x 64 x 50 x 128 7.2 -> 6.4 us, 4288 x 64 x 24 x 64 17.7 -> 16.4, 1000 x 128 x 128 x 128 29.3 -> 26.8)
+      const int kt = w + j * NQ;
+      const int krow = E && NK % NQ == 0 ? kt * 16 + c : min(kt * 16 + c, sk - 1);
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        if (kt < wg_tiles) kf[j][ks] = *reinterpret_cast<const u32x4*>(kb + (int64_t)krow * D + ks * 32 + 8 * g);
-      }
+      for (int ks = 0; ks < KS; ++ks) kf[j][ks] = at16(kb, (uint32_t)(krow * D + 8 * g) * 2, ks * 64);
     }
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
       const int ci = VFULL ? (int)threadIdx.x + i * 64 * NQ : min((int)threadIdx.x + i * 64 * NQ, VTOT - 1);
       const int key = E ? ci / CH : min(ci / CH, sk - 1), d0 = (ci % CH) * 8;
-      vreg[i] = *reinterpret_cast<const u32x4*>(vb + (int64_t)key * D + d0);
+      vreg[i] = at16(vb, (uint32_t)(key * D + d0) * 2, 0);
     }
     if (FULL && a.mask) {
       const float* mrow = a.mask + (int64_t)b * a.mask_sb + (int64_t)qrow * a.mask_sq;
@@ -193,9 +201,11 @@ __global__ __launch_bounds__(64 * NQ) void attn_stitch_kernel(const AttnArgs a) 
         }
       }
     }
-    if (KEYS && a.mask) {
+    if constexpr (!LATE) operands();
+    if constexpr (KEYS) {
+      const float* mrow = X == ATTN_KEY_MASK || a.mask ? a.mask + (int64_t)b * a.mask_sb : reinterpret_cast<const float*>(kb);      // (no mask: any sk values)
 #pragma unroll
-      for (int i = 0; i < NM; ++i) mkey[i] = a.mask[(int64_t)b * a.mask_sb + min((int)threadIdx.x + i * 64 * NQ, sk - 1)];
+      for (int i = 0; i < NM; ++i) mkey[i] = mrow[min((int)threadIdx.x + i * 64 * NQ, sk - 1)];
     }
   }
   // the loads stay here: left alone, the compiler moves some down to their use, behind the wait for
@@ -220,10 +230,10 @@ __global__ __launch_bounds__(64 * NQ) void attn_stitch_kernel(const AttnArgs a) 
     const u32x4 t = (E || key < sk) ? vreg[i] : u32x4{0u, 0u, 0u, 0u};
     if (VFULL || cu < VTOT) *reinterpret_cast<u32x4*>(vsh + key * VP + d0) = t;
   }
-  if (KEYS && a.mask) {
+  if constexpr (KEYS) {
 #pragma unroll
     for (int i = 0; i < NM; ++i)
-      if (NK * 16 % (64 * NQ) == 0 || (int)threadIdx.x + i * 64 * NQ < NK * 16) *mask_at(threadIdx.x + i * 64 * NQ) = mkey[i] * 1.4426950408889634f;
+      if (NK * 16 % (64 * NQ) == 0 || (int)threadIdx.x + i * 64 * NQ < NK * 16) *mask_at(threadIdx.x + i * 64 * NQ) = X == ATTN_KEY_MASK || a.mask ? mkey[i] * 1.4426950408889634f : 0.f;
   }
   __syncthreads();   // K, V and the mask complete
 
@@ -293,7 +303,7 @@ __global__ __launch_bounds__(64 * NQ) void attn_stitch_kernel(const AttnArgs a) 
         if (FULL && a.mask) z = fmaf(mk[kt][i], kLog2e, z);
         acc[kt][i] = z;
       }
-      if (KEYS && a.mask) {
+      if constexpr (KEYS) {
         const f32x4 m = *reinterpret_cast<const f32x4*>(mask_at(16 * kt + 4 * g));
 #pragma unroll
         for (int i = 0; i < 4; ++i) acc[kt][i] += m[i];
@@ -338,7 +348,7 @@ __global__ __launch_bounds__(64 * NQ) void attn_stitch_kernel(const AttnArgs a) 
         pb[kk][2 * h + 1] = Mfma<T>::pack(p[2], p[3]);
       }
 
-    operands();
+    if constexpr (LATE) operands();
     asm volatile("" ::: "memory");       // (requested here, not at their use)
     // ---- second dot, transposed: O^T(D x 16) = V^T(D x keys) . P^T, up to 64 columns of O at a time ------
     constexpr int DH = (D < 64 ? D : 64) / 16;
@@ -373,7 +383,7 @@ __global__ __launch_bounds__(64 * NQ) void attn_stitch_kernel(const AttnArgs a) 
       // ---- 8 bytes per tile.  Lanes g and g^1 trade
       // one tile of a pair (dt, dt+1) so that each ends up with 8 consecutive values, 16 bytes: after
       // the row swap lane g holds d = 32(dt/2) + 16(g&1) + 8(g>>1) .. +7 ------------------------
-      uint16_t* orow = ob + (int64_t)qrow * D + 16 * d0 + 16 * (g & 1) + 8 * (g >> 1);
+      char* orow = reinterpret_cast<char*>(ob) + (uint32_t)(qrow * D + 16 * (g & 1) + 8 * (g >> 1)) * 2 + 32 * d0;
 #pragma unroll
       for (int dp = 0; dp < DH / 2; ++dp) {
         const uint32_t a0 = Mfma<T>::pack(o[2 * dp][0], o[2 * dp][1]), a1 = Mfma<T>::pack(o[2 * dp][2], o[2 * dp][3]);
@@ -382,8 +392,8 @@ __global__ __launch_bounds__(64 * NQ) void attn_stitch_kernel(const AttnArgs a) 
         const auto r0 = __builtin_amdgcn_permlane16_swap(a0, b0, false, false);
         const auto r1 = __builtin_amdgcn_permlane16_swap(a1, b1, false, false);
         const u32x4 w4 = {r0[0], r1[0], r0[1], r1[1]};
-        if constexpr (S) { if (E || qi < sq) stream_store16(orow + dp * 32, w4); }
-        else if (E || qi < sq) *reinterpret_cast<u32x4*>(orow + dp * 32) = w4;
+        if constexpr (S) { if (E || qi < sq) stream_store16(orow + dp * 64, w4); }
+        else if (E || qi < sq) *reinterpret_cast<u32x4*>(orow + dp * 64) = w4;
       }
       if constexpr (D > 64) __builtin_amdgcn_sched_barrier(0);      // (the halves' accumulators are not held together)
     }
