@@ -9,7 +9,6 @@ from __future__ import annotations
 
 import ctypes as C
 import os
-from array import array
 from collections import namedtuple
 from math import prod
 
@@ -55,13 +54,12 @@ class FsError(RuntimeError):
 
 
 _lib = None
-_raw_launch = None          # fs_launch and fs_launch_static taking plain addresses, with lib()
-_raw_launch_static = None
+_native = None              # the launch entry points on Python lists (csrc/py_launch.cpp), with lib()
 
 
 def lib():
     """The loaded shared library (loaded on first use)."""
-    global _lib, _raw_launch, _raw_launch_static
+    global _lib, _native
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise ImportError(
@@ -132,13 +130,9 @@ def lib():
         L.fs_fusion_pattern_group_size.restype = i32
         L.fs_fusion_pattern_group.argtypes = [vp, i32, C.POINTER(fs_op_desc), C.POINTER(i32), C.POINTER(i32)]
         L.fs_fusion_pattern_group.restype = i32
-        # the two launch entry points once more, on a handle of their own: ints in place of typed pointers cost a
-        # call a microsecond less
-        raw = C.CDLL(LIB_PATH)
-        for f in (raw.fs_launch, raw.fs_launch_static):
-            f.argtypes = [vp, vp, i32, vp, i32, vp]
-            f.restype = i32
-        _raw_launch, _raw_launch_static = raw.fs_launch, raw.fs_launch_static
+        from . import _launch
+        _launch.bind(C.cast(L.fs_launch, C.c_void_p).value, C.cast(L.fs_launch_static, C.c_void_p).value, _stream_source)
+        _native = _launch
         _lib = L
     return _lib
 
@@ -206,48 +200,37 @@ def _pointers(tensors):
     return arr
 
 
-_torch_stream = None
+def _stream_source():
+    """Where the handle of torch's current stream comes from (without the stream object that torch.cuda.current_stream()
+    makes): a function of the device's ordinal and the one that gives the ordinal, or a function of nothing and None."""
+    import torch
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is None:
+        return (lambda: torch.cuda.current_stream().cuda_stream), None
+    return raw, torch.cuda.current_device
 
 
 def _current_stream():
-    """The handle of torch's current stream (without the stream object that torch.cuda.current_stream() makes)."""
-    global _torch_stream
-    if _torch_stream is None:
-        import torch
-        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
-        if raw is None:
-            _torch_stream = lambda: torch.cuda.current_stream().cuda_stream
-        else:
-            device = torch.cuda.current_device
-            _torch_stream = lambda: raw(device())
-    return _torch_stream()
-
-
-def _addresses(tensors):
-    return array("Q", [t if isinstance(t, int) else t.data_ptr() for t in tensors] or [0])
+    if _native is None:
+        lib()
+    return _native.current_stream()
 
 
 def fs_launch(plan, inputs, outputs, stream=None):
     """inputs/outputs: device tensors (anything with .data_ptr()) or raw addresses.
     stream: a hipStream_t address; None = torch's current stream."""
-    if stream is None:
-        stream = _current_stream()
-    if _raw_launch is None:
+    if _native is None:
         lib()
-    ins, outs = _addresses(inputs), _addresses(outputs)
-    status = _raw_launch(plan, ins.buffer_info()[0], len(inputs), outs.buffer_info()[0], len(outputs), stream)
+    status = _native.launch(plan, inputs, outputs, stream)
     if status != FS_OK:
         raise FsError(status, fs_last_error())
 
 
 def fs_launch_static(plan, inputs, outputs, stream=None):
     """fs_launch without any allocation: the plan's scratch memory is the library's static device array."""
-    if stream is None:
-        stream = _current_stream()
-    if _raw_launch_static is None:
+    if _native is None:
         lib()
-    ins, outs = _addresses(inputs), _addresses(outputs)
-    _check(_raw_launch_static(plan, ins.buffer_info()[0], len(inputs), outs.buffer_info()[0], len(outputs), stream))
+    _check(_native.launch_static(plan, inputs, outputs, stream))
 
 
 def fs_plan_tune(ops, inputs, outputs, stream=None, trials=20):
@@ -392,14 +375,16 @@ class Plan:
         return plan
 
     def launch(self, inputs, outputs, stream=None):
-        fs_launch(self._h, inputs, outputs, stream)
+        st = _native.launch(self._h, inputs, outputs, stream)
+        if st != FS_OK:
+            raise FsError(st, fs_last_error())
 
     def launch_static(self, inputs, outputs, stream=None):
         fs_launch_static(self._h, inputs, outputs, stream)
 
     def launch_bound(self, bound, stream):
         """Launch with pre-marshalled arguments (see BoundArgs) on an explicit stream handle."""
-        st = _raw_launch(self._h, bound.in_addr, bound.n_in, bound.out_addr, bound.n_out, stream)
+        st = _native.launch_arrays(self._h, bound.in_addr, bound.n_in, bound.out_addr, bound.n_out, stream)
         if st != FS_OK:
             raise FsError(st, fs_last_error())
 

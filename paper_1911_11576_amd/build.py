@@ -2,19 +2,23 @@
 
 Every source under csrc/ is compiled with hipcc (device code for gfx950 only) and linked
 into libfusionstitch.so next to this file, together with the HIP run-time compiler that
-the kernel generator of the elementwise schedule uses.  hipcc cross-compiles without a GPU.
+the kernel generator of the elementwise schedule uses.  The launch calls of the Python binding are a module
+of their own beside it.  hipcc cross-compiles without a GPU.
 """
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.environ.get("FS_OBJ_DIR", os.path.join(HERE, "_build"))
 LIB = os.environ.get("FS_LIB_OUT", os.path.join(HERE, "libfusionstitch.so"))
+
+PY_LIB = os.path.join(HERE, "_launch" + sysconfig.get_config_var("EXT_SUFFIX"))
 
 SOURCES = ["attn_stitch_bf16_widest.hip", "attn_stitch_f16_widest.hip", "attn_stitch_bf16_wide.hip", "attn_stitch_f16_wide.hip", "attn_stitch_bf16.hip", "attn_stitch_f16.hip",      # (these take longest)
            "api.cpp", "graph.cpp", "match.cpp", "row_stitch.hip", "row_stitch_f32.hip", "row_stitch_f16.hip", "row_stitch_bf16.hip", "row_team.hip", "row_block.hip", "lnbwd_stitch.hip", "lnbwd_packed.hip", "attn_stitch.hip", "attn_decode.hip", "per_op.hip", "ew_stitch.hip", "ew_codegen.cpp", "row_codegen.cpp", "grid_codegen.cpp", "shared_plan.cpp", "fusion_plan.cpp", "util.hip", "launch_static.hip"]
@@ -50,7 +54,17 @@ def build(verbose=False, jobs=None):
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError("link failed:\n" + r.stdout + r.stderr)
+    _build_python_calls()
     return LIB
+
+
+def _build_python_calls():
+    """csrc/py_launch.cpp, host code alone: the module _launch of this package, for the Python that builds it."""
+    cmd = [HIPCC, "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall", "-Wno-cast-function-type", "-x", "c++", "-I", sysconfig.get_paths()["include"],
+           os.path.join(CSRC, "py_launch.cpp"), "-o", PY_LIB]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("hipcc failed on py_launch.cpp:\n" + r.stdout + r.stderr)
 
 
 if __name__ == "__main__":

@@ -1,0 +1,74 @@
+"""The launch calls of the Python binding (csrc/py_launch.cpp): what they take as tensors, plans and streams, on a group
+without rows, which launches nothing."""
+import ctypes as C
+from collections import deque
+
+import pytest
+
+from paper_1911_11576_amd import BoundArgs, FsError, Plan, binding
+from workloads import graphs
+
+
+class Tensor:
+    def __init__(self, address):
+        self.address = address
+
+    def data_ptr(self):
+        return self.address
+
+
+@pytest.fixture(scope="module")
+def plan():
+    with Plan(graphs.layernorm_fwd(0, 768, "f32", 1e-5)) as p:
+        yield p
+
+
+TENSORS = [[4096, 8192, 16384], (Tensor(4096), 8192, Tensor(16384)), deque([Tensor(4096)] * 3), range(4096, 4096 * 4, 4096)]
+
+
+@pytest.mark.parametrize("ins", TENSORS, ids=lambda t: type(t).__name__)
+@pytest.mark.parametrize("stream", [0, C.c_void_p(0), C.c_void_p(64)], ids=["int", "null", "c_void_p"])
+def test_accepted(plan, ins, stream):
+    plan.launch(ins, [32768], stream)
+    binding.fs_launch(plan._h, ins, (Tensor(32768),), stream)
+    binding.fs_launch(C.c_void_p(plan._h), ins, [32768], stream)
+    plan.launch_static(ins, [32768], stream)
+    plan.launch_bound(BoundArgs(ins, [32768]), stream)
+    plan.launch_bound(BoundArgs(ins, [32768]), None)
+
+
+@pytest.mark.parametrize("ins, outs, error", [
+    ([4096, 8192], [32768], FsError),                    # counts
+    ([4096, 8196, 16384], [32768], FsError),             # alignment of gamma, which has elements
+    ([4096] * 100, [32768], FsError),                    # more than the local array holds
+    ([4096, 8192, -1], [32768], OverflowError),
+    ([4096, 8192, 1 << 64], [32768], OverflowError),
+    ([4096, 8192, 1.5], [32768], AttributeError),
+    ([4096, 8192, Tensor(1.5)], [32768], TypeError),
+    ([4096, 8192, None], [32768], AttributeError),
+    (iter([4096, 8192, 16384]), [32768], TypeError),     # no length
+    (None, [32768], TypeError),
+])
+def test_refused(plan, ins, outs, error):
+    with pytest.raises(error):
+        plan.launch(ins, outs, 0)
+    with pytest.raises(error):
+        plan.launch_static(ins, outs, 0)
+
+
+def test_a_list_that_shrinks_while_it_is_read(plan):
+    class Shrinks(Tensor):
+        def data_ptr(self):
+            ins.clear()
+            return self.address
+    ins = [4096, Shrinks(8192), 16384]
+    with pytest.raises((RuntimeError, IndexError)):
+        plan.launch(ins, [32768], 0)
+
+
+def test_a_closed_plan_is_refused():
+    p = Plan(graphs.layernorm_fwd(0, 768, "f32", 1e-5))
+    p.close()
+    for call in (lambda: p.launch([4096] * 3, [32768], 0), lambda: p.launch_bound(BoundArgs([4096] * 3, [32768]), 0)):
+        with pytest.raises(FsError):
+            call()
