@@ -21,7 +21,7 @@ LIB = os.environ.get("FS_LIB_OUT", os.path.join(HERE, "libfusionstitch.so"))
 PY_LIB = os.path.join(HERE, "_launch" + sysconfig.get_config_var("EXT_SUFFIX"))
 
 SOURCES = ["attn_stitch_bf16_widest.hip", "attn_stitch_f16_widest.hip", "attn_stitch_bf16_wide.hip", "attn_stitch_f16_wide.hip", "attn_stitch_bf16.hip", "attn_stitch_f16.hip",      # (these take longest)
-           "api.cpp", "graph.cpp", "match.cpp", "row_stitch.hip", "row_stitch_f32.hip", "row_stitch_f16.hip", "row_stitch_bf16.hip", "row_team.hip", "row_block.hip", "lnbwd_stitch.hip", "lnbwd_packed.hip", "attn_stitch.hip", "attn_decode.hip", "per_op.hip", "ew_stitch.hip", "ew_codegen.cpp", "row_codegen.cpp", "grid_codegen.cpp", "shared_plan.cpp", "fusion_plan.cpp", "util.hip", "launch_static.hip"]
+           "api.cpp", "graph.cpp", "match.cpp", "row_stitch.hip", "row_stitch_f32.hip", "row_stitch_f16.hip", "row_stitch_bf16.hip", "row_team.hip", "row_block.hip", "lnbwd_stitch.hip", "lnbwd_packed.hip", "lnbwd_team.hip", "attn_stitch.hip", "attn_decode.hip", "per_op.hip", "ew_stitch.hip", "ew_codegen.cpp", "row_codegen.cpp", "grid_codegen.cpp", "shared_plan.cpp", "fusion_plan.cpp", "util.hip", "launch_static.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950",

@@ -418,6 +418,15 @@ fs_status plan_create_impl(const fs_op_desc* ops, int32_t n_ops, const fs_plan_o
             p->description = fs::lnbwd_packed_describe(p->lnbwd);
             break;
           }
+          if (!want_generated && fs::lnbwd_team_plan(p->match.lnbwd, lo, &p->lnbwd)) {
+            p->schedule = FS_SCHED_ROW_COL;
+            p->lds_bytes = p->lnbwd.lds_bytes;
+            p->workspace_bytes = p->lnbwd.workspace_bytes;
+            p->n_kernels = p->lnbwd.n_kernels;
+            p->moved_bytes = algo + 2 * p->lnbwd.workspace_bytes;
+            p->description = fs::lnbwd_team_describe(p->lnbwd);
+            break;
+          }
           if (!fs::lnbwd_stitch_plan(p->match.lnbwd, lo, &p->lnbwd, &err)) {
             const bool bad_opt = err.find("wg_size") != std::string::npos;
             if (!bad_opt && fall_back_to_generated()) break;
@@ -527,6 +536,7 @@ fs_status fs::enqueue_plan(fs_plan* p, const void* const* inputs, void* const* o
       case FS_SCHED_ROW_COL:
         rc = p->row_form == 3  ? fs::row_gen_launch(p->row_gen, inputs, outputs, n_out, workspace, hip_stream, &err)
              : p->lnbwd.packed ? fs::lnbwd_packed_launch(p->match.lnbwd, p->lnbwd, inputs, outputs, hip_stream, &err)
+             : p->lnbwd.teams  ? fs::lnbwd_team_launch(p->match.lnbwd, p->lnbwd, inputs, outputs, workspace, hip_stream, &err)
                                : fs::lnbwd_stitch_launch(p->match.lnbwd, p->lnbwd, inputs, outputs, workspace, hip_stream, &err);
         break;
       case FS_SCHED_BLOCK_DOT: rc = fs::row_gen_launch(p->row_gen, inputs, outputs, n_out, workspace, hip_stream, &err); break;

@@ -30,13 +30,18 @@ int row_block_launch(const RowSpec&, const RowBlockLaunch&, const void* const* i
                      void* stream, std::string* err);
 
 // LayerNorm backward: row path for dx packed with the column path for dgamma/dbeta.
-struct LnBwdLaunch { int K = 1, wg = 256, grid = 1, n_kernels = 1; int64_t lds_bytes = 0, workspace_bytes = 0; bool packed = false, in_place = false; int T = 1, strip = 32; };   // packed: one launch; T wavefronts to a row, strips of columns; in_place: dx may take the buffer of dy or x
+struct LnBwdLaunch { int K = 1, wg = 256, grid = 1, n_kernels = 1; int64_t lds_bytes = 0, workspace_bytes = 0; bool packed = false, in_place = false; int T = 1, strip = 32, teams = 0; };   // packed: one launch; T wavefronts to a row, strips of columns; teams: rows of teams of T wavefronts, so many to a workgroup; in_place: dx may take the buffer of dy or x
 inline bool lnbwd_broadcasts(const LnBwdSpec& sp, int param) { return param == sp.in_gamma || param == sp.in_mean || param == sp.in_rstd; }
 bool lnbwd_takes_ragged(const LnBwdSpec&, const LaunchOpts&);      // rows of no whole number of vectors that the hand-written kernel takes
 bool lnbwd_stitch_plan(const LnBwdSpec&, const LaunchOpts&, LnBwdLaunch*, std::string* err);
 std::string lnbwd_stitch_describe(const LnBwdSpec&, const LnBwdLaunch&);
 int lnbwd_stitch_launch(const LnBwdSpec&, const LnBwdLaunch&, const void* const* in, void* const* out,
                         void* workspace, void* stream, std::string* err);
+
+// The same over rows of 1025 to 4096 columns: several wavefronts to a row.
+bool lnbwd_team_plan(const LnBwdSpec&, const LaunchOpts&, LnBwdLaunch*);
+std::string lnbwd_team_describe(const LnBwdLaunch&);
+int lnbwd_team_launch(const LnBwdSpec&, const LnBwdLaunch&, const void* const* in, void* const* out, void* workspace, void* stream, std::string* err);
 
 // The same over few rows as one launch: row path and column path as workgroups of their own.
 bool lnbwd_packed_plan(const LnBwdSpec&, const LaunchOpts&, LnBwdLaunch*);
@@ -82,6 +87,6 @@ int stream_copy_launch(void* dst, const void* src, int64_t bytes, void* stream, 
 // out[r][s][c] = sum over g of partial[r][s * groups + g][c] (doubles), stored in dtype[r]; r < n_red <= 8;
 // s < n_seg runs of rows (1: sums over all rows)
 int col_combine_launch(const void* partial, int groups, int64_t cols, int n_red, void* const* out, const int* dtype,
-                       void* stream, std::string* err, int64_t n_seg = 1, const int* is_max = nullptr);   // is_max[r]: a maximum, not a sum
+                       void* stream, std::string* err, int64_t n_seg = 1, const int* is_max = nullptr, int64_t stride = 0);   // is_max[r]: a maximum, not a sum; stride: doubles from one partial row to the next, 0: cols
 
 }  // namespace fs

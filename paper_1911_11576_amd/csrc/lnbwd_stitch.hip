@@ -200,7 +200,7 @@ void lnbwd_rows_kernel(const LnBwdArgs a) {
 // Second kernel of the plan: out[col(slot)] = sum over the workgroups' partial rows, in a fixed order
 // (256 / SL interleaved slices of partial rows, then the slices in order).  A block owns SL consecutive slots:
 // with 16 the 16 lanes of a slice read one whole 128-byte line of a partial row.
-template <int SL, int NT = 256, int NL = 8>
+template <int SL, int NT = 256>
 __global__ __launch_bounds__(NT)
 void lnbwd_combine_kernel(const double* __restrict__ part, int groups, int K, int nvec, int cols, float* dgamma, float* dbeta) {
   constexpr int NS = NT / SL;           // slices
@@ -209,17 +209,7 @@ void lnbwd_combine_kernel(const double* __restrict__ part, int groups, int K, in
   const int j = threadIdx.x % SL, slice = threadIdx.x / SL;
   const int s = blockIdx.x * SL + j;
   const double* p = part + s;
-  double acc = 0.0;
-  int g = slice;
-  // NL partial rows requested at a time (the loads are independent, the additions keep their order)
-  for (; g + (NL - 1) * NS < groups; g += NL * NS) {
-    double v[NL];
-#pragma unroll
-    for (int i = 0; i < NL; ++i) v[i] = p[(int64_t)(g + i * NS) * n2];
-#pragma unroll
-    for (int i = 0; i < NL; ++i) acc += v[i];
-  }
-  for (; g < groups; g += NS) acc += p[(int64_t)g * n2];
+  const double acc = combine_partials<NS>(p, n2, slice, groups, 0.0, [](double a, double b) { return a + b; });
   stage[slice][j] = acc;
   __syncthreads();
   if (slice == 0) {

@@ -39,7 +39,7 @@ struct ColCombineArgs {
 // 0.8 us faster than 1024 on 256 partial rows of 2048 columns), 1024 beyond.
 template <int NT>
 __global__ __launch_bounds__(NT) void col_combine_kernel(const double* __restrict__ partial, int groups, int64_t total_groups,
-                                                         int64_t cols, const ColCombineArgs args) {
+                                                         int64_t cols, int64_t stride, const ColCombineArgs args) {
   constexpr int NS = NT / 16;
   __shared__ double part[NS][17];
   const int64_t col_blocks = (cols + 15) / 16;
@@ -49,21 +49,9 @@ __global__ __launch_bounds__(NT) void col_combine_kernel(const double* __restric
   const bool is_max = args.is_max[r] != 0;
   double s = is_max ? -__builtin_inf() : 0.0;
   if (c < cols) {
-    const double* p = partial + ((int64_t)r * total_groups + seg * groups) * cols + c;
-    if (is_max) {
-      for (int g = slice; g < groups; g += NS) s = fmax(s, p[(int64_t)g * cols]);
-    } else {
-      // eight partial rows requested at a time (the loads are independent, the additions keep their order)
-      int g = slice;
-      for (; g + 7 * NS < groups; g += 8 * NS) {
-        double v[8];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) v[i] = p[(int64_t)(g + i * NS) * cols];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) s += v[i];
-      }
-      for (; g < groups; g += NS) s += p[(int64_t)g * cols];
-    }
+    const double* p = partial + ((int64_t)r * total_groups + seg * groups) * stride + c;
+    s = is_max ? combine_partials<NS>(p, stride, slice, groups, s, [](double a, double b) { return fmax(a, b); })
+               : combine_partials<NS>(p, stride, slice, groups, s, [](double a, double b) { return a + b; });
   }
   part[slice][j] = s;
   __syncthreads();
@@ -83,10 +71,10 @@ __global__ __launch_bounds__(NT) void col_combine_kernel(const double* __restric
   }
 }
 
-// partial: [n_red][n_seg * groups][cols] doubles -- for every reduction and every run of rows, `groups`
+// partial: [n_red][n_seg * groups][stride, or cols] doubles -- for every reduction and every run of rows, `groups`
 // partial rows, added in a fixed order into out[r][n_seg][cols].  n_seg = 1: sums over all rows.
 int col_combine_launch(const void* partial, int groups, int64_t cols, int n_red, void* const* out, const int* dtype,
-                       void* stream, std::string* err, int64_t n_seg, const int* is_max) {
+                       void* stream, std::string* err, int64_t n_seg, const int* is_max, int64_t stride) {
   if (n_red <= 0 || cols <= 0 || n_seg <= 0) return 0;
   const int64_t blocks = n_seg * ((cols + 15) / 16);
   if (blocks > 0x7fffffffLL) { *err = "col_combine launch: too many runs of rows for one grid"; return -1; }
@@ -95,10 +83,10 @@ int col_combine_launch(const void* partial, int groups, int64_t cols, int n_red,
   const dim3 grid((unsigned)blocks, (unsigned)n_red);
   if (groups <= 512)
     hipLaunchKernelGGL(col_combine_kernel<256>, grid, dim3(256), 0, static_cast<hipStream_t>(stream),
-                       static_cast<const double*>(partial), groups, n_seg * (int64_t)groups, cols, a);
+                       static_cast<const double*>(partial), groups, n_seg * (int64_t)groups, cols, stride ? stride : cols, a);
   else
     hipLaunchKernelGGL(col_combine_kernel<1024>, grid, dim3(1024), 0, static_cast<hipStream_t>(stream),
-                       static_cast<const double*>(partial), groups, n_seg * (int64_t)groups, cols, a);
+                       static_cast<const double*>(partial), groups, n_seg * (int64_t)groups, cols, stride ? stride : cols, a);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) { *err = std::string("col_combine launch: ") + hipGetErrorString(e); return -1; }
   return 0;

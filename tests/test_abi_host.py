@@ -849,6 +849,17 @@ def test_layernorm_bwd_plans_name_the_update_in_place_and_hide_no_workspace():
             assert (p.info()["workspace_bytes"] == 0) == free
 
 
+@pytest.mark.parametrize("rows,cols", [(1025, 1025), (1025, 4096), (1500, 3999), (2564, 2316), (2730, 3072), (3000, 3072), (4095, 4096), (4096, 4096), (16384, 2048), (30000, 1100)])
+def test_layernorm_bwd_teams_need_no_more_scratch_memory(rows, cols):
+    """fs_launch_static takes LayerNorm backward wherever sixteen rows to a workgroup, or a wavefront to a row, would fit its array."""
+    with Plan(graphs.layernorm_bwd(rows, cols)) as p:
+        assert "wavefronts to a row" in p.describe() and "in place of dy or x" in p.describe()
+        groups = 256 if cols <= 2048 else min(256, -(-rows // 16))
+        assert p.info()["workspace_bytes"] <= max(8 << 20, groups * 2 * -(-cols // 16) * 16 * 8)
+        if groups * 2 * cols * 8 <= 8 << 20:
+            assert p.info()["workspace_bytes"] <= 8 << 20
+
+
 def _in_place_status(ops):
     """Status of a launch with the first output in the first parameter's buffer, by its arguments alone: FS_ERR_HIP where they pass, as there is no GPU."""
     with Plan(ops) as p:

@@ -346,6 +346,38 @@ def test_layernorm_bwd_rows_of_no_whole_vectors(rows, cols):
                 assert_close(a.double().cpu().numpy(), b, 1e-5, f"lnbwd in place {rows}x{cols}")
 
 
+@pytest.mark.parametrize("rows,cols", [(1025, 1025), (1026, 1028), (1100, 1537), (1500, 1536), (2049, 2048), (1030, 2049), (1031, 3072), (1200, 3075), (1027, 4095), (1300, 4096),
+                                       (4099, 1100), (7300, 1540)])
+def test_layernorm_bwd_with_teams_of_wavefronts(rows, cols):
+    """Two and four wavefronts to a row: edges of the lanes' vectors, rows at element alignment, trips of odd length, workgroups whose second team has no row
+    left, the loads of large groups; bit-reproducible, updates in place of dy and of x as by the generated form, the prebuilt mode as before.
+    dgamma over more than 2048 rows has the room of a sum of so many fp32 terms t, each with the rounding of the chain that made it: 4 * 2^-24 * sqrt(sum t^2)."""
+    announce(f"layernorm_bwd teams {rows}x{cols}")
+    ops, ins = graphs.layernorm_bwd(rows, cols), inputs.layernorm_bwd(rows, cols)
+    dy, x, _, mean, rstd = (np.asarray(a, dtype=np.float64) for a in ins)
+    terms = dy * (x - mean.reshape(-1, 1)) * rstd.reshape(-1, 1)
+    slack = [None, 4.0 * 2.0 ** -24 * np.sqrt((terms * terms).sum(axis=0)) if rows > 2048 else None, None]
+    assert [op.shape for op in ops if op.kind == "output"] == [(rows, cols), (cols,), (cols,)]
+    with Plan(ops) as p:
+        assert "wavefronts to a row" in p.describe() and p.info()["n_kernels"] == 2
+    with pytest.raises(FsError):
+        Plan(ops, "prebuilt")
+    got, want = run_gpu(ops, ins), interp.run(ops, ins)
+    for i in range(3):
+        assert_close(got[i], want[i], 1e-5, f"lnbwd {rows}x{cols} output {i}", slack[i])
+    for a, b in zip(got, run_gpu(ops, ins, launches=2)):
+        assert np.array_equal(a, b)
+    with Plan(ops) as p:
+        launches = [p.launch] + ([p.launch_static] if p.info()["workspace_bytes"] <= 8 << 20 else [])
+        for k in (0, 1):
+            for launch in launches:
+                dev_in, outs = to_device(ops, ins), alloc_outputs(ops)
+                outs[0] = dev_in[k]
+                launch(dev_in, outs)
+                torch.cuda.synchronize()
+                assert all(np.array_equal(a.double().cpu().numpy(), b) for a, b in zip(outs, got)), (k, launch.__name__)
+
+
 @pytest.mark.parametrize("rows,cols", [(300, 31), (700, 1600), (301, 1027), (256, 4095), (1027, 1023)])
 def test_layernorm_bwd_in_place_beside_other_launches(rows, cols):
     """Updates in place need no more than the plan reports: bit for bit what a launch with buffers of its own gives, in dy's buffer and in x's, captured after
