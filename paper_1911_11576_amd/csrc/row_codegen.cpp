@@ -2518,6 +2518,166 @@ struct Stream {
       }
     }
     e.line("}");
+    name_kernel(kernel_name);
+  }
+  // Whether a row of one tensor is read once and kept by a workgroup as it was loaded, chunk by chunk of 16 bytes, for groups of its maximum, the sum of its
+  // exponentials (log-softmax, log-sum-exp) and elementwise ops on it and on those.  Registers and LDS together hold up to 118784 fp32 elements, twice as many
+  // of 16 bits; up to eight more chunks a thread are read a second time, for want of room.  Log-softmax, us, the form it would have and this one:
+  //   beyond the register templates, streamed in three passes: fp32 256 x 94000 54.5 and 32.2, 339 x 104576 89.3 and 54.8, 100 x 131071 45.7 and 29.0,
+  //               390 x 131072 118 and 97.6; bf16 64 x 117566 18.5 and 10.9, 700 x 120001 121 and 79, 1600 x 93001 209 and 141
+  //   16-bit rows of more than 57344 elements, whose values as floats leave a CU one workgroup: 512 x 65536 24.4 and 20.1, 557 x 78776 37.7 and 33.8, 1600 x
+  //               62000 76.4 and 74.7, 1194 x 82944 71.9 and 72.1; not below, where two fit: 1500 x 50000 55.0 and 56.5, 2000 x 33000 46.7 and 47.9.  fp32 rows
+  //               of that kind are held either way: 512 x 88001 74.1 and 74.1
+  // One workgroup to a CU and no more than half of its time on the memory: two of them with half the registers each, and more LDS, are no faster (bf16 700 x
+  // 120001 93, 512 x 131072 57).  Up to three rows of whole chunks keep the form they have, see Gen::long_row_fits.
+  bool can_hold(bool in_registers, int per_thread, Gen::Online* online) {
+    std::string why;
+    if (A.n_col > 0 || A.n_reduce != 2 || A.views.size() != 1 || A.has_causal || A.mma_in >= 0 || !geometry(1024, &why)) return false;
+    const RView& v = A.views[0];
+    if ((A.rows < 4 && !ragged) || splat_view(0) || v.cls != CLS_FULL || W * (v.dtype == FS_F32 ? 4 : 2) != 16) return false;
+    if (in_registers && (v.dtype == FS_F32 || per_thread <= 56)) return false;
+    schedule();
+    *online = Gen(A).find_online();
+    if (online->max_id < 0 || A.nodes[idx_of[online->max_id]].o[0].kind != OP_VIEW) return false;
+    for (const RNode& x : A.nodes) {
+      if (x.op == ROP_DOT_OUTER || x.op == ROP_DOT_REDUCE) return false;
+      if (is_red(x) && x.id != online->max_id && x.id != online->sum_id) return false;
+    }
+    return n_iter() <= kHeldChunks + kKeptChunks + kAgainChunks;
+  }
+  static constexpr int kHeldChunks = 20, kKeptChunks = 9, kAgainChunks = 8;      // a thread's, in registers (80 of its 128), in LDS (144 KB of a workgroup's 160), read again
+
+  void emit_held(const Gen::Online& online, std::string* kernel_name) {
+    const int n = (int)A.nodes.size(), nit = n_iter(), held = std::min(nit, kHeldChunks), kept = std::min(nit - held, kKeptChunks), again = nit - held - kept;
+    std::vector<int> outputs;
+    for (int i = 0; i < n; ++i) if (A.nodes[i].cls == CLS_FULL && A.nodes[i].out_ord >= 0) outputs.push_back(i);
+    const RView& v = A.views[0];
+    const char* ty = v.dtype == FS_F32 ? "float" : "unsigned short";
+    const char* ex = fast ? "exp_fast" : "exp_nonpositive";
+    splat.assign(1, 0);
+    roff.assign(1, "");
+    Gen helper(A);
+    roff[0] = helper.row_offset(v, &coords);
+    std::vector<char> is_divisor(A.g.size(), 0);
+    for (const RNode& x : A.nodes) if (x.op == FS_DIVIDE && x.cls == CLS_FULL && x.o[1].kind == OP_ROWB) is_divisor[x.o[1].index] = 1;
+    e.s = ew_preamble();
+    e.s += kReducePreamble;
+    if (!fast) e.s += kOnlinePreamble;
+    e.s += kRaggedPreamble;
+    const char* if_counts = ragged ? "if (j >= lo) " : "";
+    lds_kept = (int64_t)kept * wg * 16;
+    e.line("extern \"C\" __global__ __launch_bounds__(%d) void FS_ROW_NAME(const Args a) {", wg);
+    e.line("  constexpr int W = %d, NVEC = %lld, WG = %d, T = %d, NIT = %d, HELD = %d, KEPT = %d, AGAIN = %d;", W, (long long)n_chunks(), wg, wg / 64, nit, held, kept, again);
+    e.line("  __shared__ float exch[2][T];");
+    if (kept > 0) e.line("  __shared__ u32x4 keep[KEPT][WG];");
+    e.line("  const int mine = (int)threadIdx.x * W, c = (int)threadIdx.x + (NIT - 1) * WG;");
+    // (all of a thread's chunks but the last are there and whole)
+    e.line("  const bool there = c < NVEC;");
+    e.line("  const int last = %s(there ? c : 0) * W, lost = %s;", ragged ? ("c == NVEC - 1 ? " + std::to_string(A.cols - W) + " : ").c_str() : "",
+           ragged ? ("c == NVEC - 1 ? " + std::to_string(n_chunks() * W - A.cols) + " : 0").c_str() : "0");
+    e.line("  for (long long row = blockIdx.x; row < %lldll; row += gridDim.x) {", (long long)A.rows);
+    if (coords) {
+      const int nrow = A.rank - 1;
+      e.line("    unsigned long long rr = (unsigned long long)row;");
+      for (int d = nrow - 1; d >= 0; --d) {
+        if (A.S[d] == 1) { e.line("    const long long i%d = 0;", d); continue; }
+        e.line("    const long long i%d = rr %% %lldull; rr /= %lldull;", d, (long long)A.S[d], (long long)A.S[d]);
+      }
+    }
+    // a chunk's start in scalar registers: one lane offset serves all chunks but the last
+    e.line("    auto request = [&](int it) __attribute__((always_inline)) {");
+    e.line("      long long at = (%s) + (it + 1 < NIT ? it * WG * W : 0);", roff[0].c_str());
+    e.line("      asm(\"\" : \"+s\"(at));");
+    e.line("      return (u32x4)*reinterpret_cast<const u32x4%s*>(static_cast<const %s*>(a.in[0]) + at + (it + 1 < NIT ? mine : last));", ragged ? "e" : "", ty);
+    e.line("    };");
+    auto unpack = [&]() {
+      e.line("      float v0[W];");
+      if (v.dtype == FS_F32) e.line("      UNROLL for (int j = 0; j < W; ++j) v0[j] = bits_f32(x[j]);");
+      else {
+        const char* h = v.dtype == FS_F16 ? "f16" : "bf16";
+        e.line("      UNROLL for (int j = 0; j < W / 2; ++j) { v0[2 * j] = %s_lo(x[j]); v0[2 * j + 1] = %s_hi(x[j]); }", h, h);
+      }
+    };
+    const int m = online.max_id, q = online.sum_id;
+    // A thread's running maximum and sum, see Gen: maxima of -inf stand for the least finite value in exponents.
+    e.line("    float r%d = -__builtin_inff(), r%d = 0.0f;", m, q);
+    e.line("    auto take = [&](const u32x4 x, int it) __attribute__((always_inline)) {");
+    e.line("      __builtin_amdgcn_sched_barrier(0);");
+    // (branches the compiler cannot see through keep what is behind a run of chunks from being mixed with it: 16 to 61 spilled registers without)
+    e.line("      if (it + 1 == HELD || it + 1 == HELD + KEPT || it + 1 == NIT) { int go = 1; asm volatile(\"\" : \"+s\"(go)); if (!go || (it + 1 == NIT && !there)) return; }");
+    if (ragged) e.line("      const int lo = it + 1 == NIT ? lost : 0;");
+    unpack();
+    e.line("      float m = r%d;", m);
+    e.line("      UNROLL for (int j = 0; j < W; ++j) %sm = fmaxf(m, v0[j]);", if_counts);
+    e.line("      const float mf = fmaxf(m, -3.402823466e38f);");
+    e.line("      r%d = r%d * %s(fmaxf(r%d, -3.402823466e38f) - mf);", q, q, ex, m);
+    e.line("      UNROLL for (int j = 0; j < W; ++j) %sr%d = r%d + %s(v0[j] - mf);", if_counts, q, q, ex);
+    e.line("      r%d = m;", m);
+    e.line("    };");
+    // What goes to LDS first, with half of the rest requested behind it.
+    e.line("    u32x4 held[HELD];");
+    if (kept > 0) {
+      e.line("    {");
+      e.line("      u32x4 x[KEPT];");
+      e.line("      UNROLL for (int i = 0; i < KEPT; ++i) x[i] = request(HELD + i);");
+      e.line("      UNROLL for (int i = 0; i < HELD / 2; ++i) held[i] = request(i);");
+      e.line("      UNROLL for (int i = 0; i < KEPT; ++i) { keep[i][threadIdx.x] = x[i]; take(x[i], HELD + i); }");
+      e.line("      UNROLL for (int i = HELD / 2; i < HELD; ++i) held[i] = request(i);");
+      e.line("    }");
+    } else {
+      e.line("    UNROLL for (int i = 0; i < HELD; ++i) held[i] = request(i);");
+    }
+    e.line("    UNROLL for (int i = 0; i < HELD; ++i) take(held[i], i);");
+    if (again > 0) e.line("    UNROLL for (int i = HELD + KEPT; i < NIT; ++i) take(request(i), i);");
+    e.line("    {");
+    e.line("      const float own = fmaxf(r%d, -3.402823466e38f);", m);
+    e.line("      r%d = lanes_allreduce<MaxOp, 64>(r%d);", m, m);
+    e.line("      r%d = lanes_allreduce<SumOp, 64>(r%d * %s(own - fmaxf(r%d, -3.402823466e38f)));", q, q, ex, m);
+    e.line("      if ((threadIdx.x & 63) == 0) { exch[0][threadIdx.x >> 6] = r%d; exch[1][threadIdx.x >> 6] = r%d; }", m, q);
+    e.line("      __syncthreads();");
+    e.line("      const float wm = exch[0][threadIdx.x & (T - 1)];");
+    e.line("      r%d = lanes_allreduce<MaxOp, T>(wm);", m);
+    e.line("      r%d = lanes_allreduce<SumOp, T>(exch[1][threadIdx.x & (T - 1)] * %s(fmaxf(wm, -3.402823466e38f) - r%d));", q, ex, m);
+    e.line("    }");
+    for (const RNode& x : A.nodes) {
+      if (x.cls != CLS_ROW) continue;
+      if (!is_red(x)) e.line("    const float r%d = %s;", x.id, expr(x).c_str());
+      if (is_divisor[x.id]) e.line("    const float inv%d = 1.0f / r%d;", x.id, x.id);
+      row_out(x);
+    }
+    if (!outputs.empty()) {
+      e.line("    auto give = [&](const u32x4 x, int it) __attribute__((always_inline)) {");
+      e.line("      __builtin_amdgcn_sched_barrier(0);");
+      e.line("      if (it + 1 == NIT && !there) return;");
+      e.line("      int col = it + 1 < NIT ? mine + it * WG * W : last;");
+      if (ragged) e.line("      const int lo = it + 1 == NIT ? lost : 0;");
+      unpack();
+      std::vector<char> have(n, 0);
+      std::function<void(int)> need = [&](int k) {
+        if (have[k]) return;
+        have[k] = 1;
+        const RNode& x = A.nodes[k];
+        for (int j = 0; j < x.nop; ++j) if (x.o[j].kind == OP_NODE && A.nodes[idx_of[x.o[j].index]].cls == CLS_FULL) need(idx_of[x.o[j].index]);
+        e.line("        float t%d[W];", x.id);
+        e.line("        UNROLL for (int j = 0; j < W; ++j) t%d[j] = %s;", x.id, expr(x).c_str());
+      };
+      for (int t : outputs) need(t);
+      for (int t : outputs) store_global(A.nodes[t]);
+      e.line("    };");
+      // (a chunk is unpacked anew: its values as floats would take twice the registers of a 16-bit row)
+      e.line("    UNROLL for (int i = 0; i < HELD; ++i) { asm volatile(\"\" : \"+v\"(held[i]) :: \"memory\"); give(held[i], i); }");
+      if (kept > 0) e.line("    UNROLL for (int i = 0; i < KEPT; ++i) give(keep[i][threadIdx.x], HELD + i);");
+      if (again > 0) e.line("    UNROLL for (int i = HELD + KEPT; i < NIT; ++i) give(request(i), i);");
+    }
+    e.line("    __syncthreads();      // the exchange slots are reused by the next row");
+    e.line("  }");
+    e.line("}");
+    name_kernel(kernel_name);
+  }
+  int64_t lds_kept = 0;
+
+  // the kernel's name: a hash of its source
+  void name_kernel(std::string* kernel_name) {
     uint64_t h = 1469598103934665603ull;
     for (unsigned char c : e.s) { h ^= c; h *= 1099511628211ull; }
     char name[32];
@@ -2609,7 +2769,11 @@ bool row_gen_plan(const Graph& g, const LaunchOpts& opt, RowGenLaunch* out, int*
   gen.wg = opt.wg_size && (opt.wg_size <= 256 || A.n_col > 0) ? opt.wg_size : 256;
   if (gen.wg & (gen.wg - 1)) gen.wg = gen.wg > 512 ? 512 : gen.wg > 256 ? 256 : 128;   // lanes per row divide the workgroup
   std::string gerr;
-  if (!want_stream && gen.geometry(&gerr)) {
+  const bool in_registers = !want_stream && gen.geometry(&gerr);
+  Stream holder(A);
+  Gen::Online online;
+  const bool held = gen.default_shape && (!in_registers || gen.long_row) && holder.can_hold(in_registers, gen.K * gen.W, &online);
+  if (in_registers && !held) {
     // the row lives in registers
     int64_t n_seg = 0;
     if (A.seg_rows > 0) {
@@ -2703,10 +2867,24 @@ bool row_gen_plan(const Graph& g, const LaunchOpts& opt, RowGenLaunch* out, int*
     return true;
   }
   const bool too_long = gerr.find("row longer") != std::string::npos || gerr.find("running sums to stay in registers") != std::string::npos;
-  if (!want_stream && (opt.rows_per_wave || !too_long)) { *err = gerr; return false; }
+  if (!want_stream && !in_registers && (opt.rows_per_wave || !too_long)) { *err = gerr; return false; }
   if (A.mma_in >= 0) { *err = gerr.empty() ? "generated row schedule: dots on the matrix unit have no streamed form" : gerr; return false; }
   if (A.n_col > 0 && A.seg_rows > 0) { *err = "generated row schedule: column reductions per run of rows over rows longer than the register templates hold"; return false; }
 
+  if (held) {
+    // the row is read once and kept by one workgroup
+    holder.emit_held(online, &l.kernel_name);
+    dump_source(holder.e.s);
+    std::string cerr;
+    if (!ew_compile_source(holder.e.s, &l.code_object, &cerr)) { *err = "generated row schedule: " + cerr; return false; }
+    l.streamed = l.held = true;
+    l.W = holder.W; l.L = l.wg = holder.wg; l.K = 0;
+    l.lds_bytes = holder.lds_kept + (int64_t)A.n_reduce * (holder.wg / 64) * 4;
+    l.grid = (int)std::min<int64_t>(A.rows, 1 << 22);
+    *out = l;
+    *status = FS_OK;
+    return true;
+  }
   // the row is streamed in passes by one workgroup
   Stream st(A);
   if (A.n_col > 0) {
@@ -2902,6 +3080,11 @@ std::string row_gen_describe(const RowGenLaunch& l) {
   if (l.parts > 1) {
     snprintf(buf, sizeof buf, "reduce x%d + elementwise x%d packed in %d independent row groups, a run of workgroups each (generated kernel %s, %zu bytes of code); cta_num=%d, cta_size=%d, lds=%lld",
              l.n_reduce, l.n_ops - l.n_reduce, l.parts, l.kernel_name.c_str(), l.code_object.size(), l.grid, l.wg, (long long)l.lds_bytes);
+    return buf;
+  }
+  if (l.held) {
+    snprintf(buf, sizeof buf, "reduce x%d[GRID,CTA-S] + elementwise x%d[GRID,CTA-THREAD_%d] streamed in 1 pass, the row held in registers and LDS (generated kernel %s, %zu bytes of code); cta_num=%d, cta_size=%d, lds=%lld",
+             l.n_reduce, l.n_ops - l.n_reduce, l.W, l.kernel_name.c_str(), l.code_object.size(), l.grid, l.wg, (long long)l.lds_bytes);
     return buf;
   }
   if (l.streamed) {

@@ -17,6 +17,7 @@ struct RowGenLaunch {
   int L = 64, K = 1, W = 4;           // lanes per row, chunks per lane, elements per chunk
   int n_ops = 0, n_reduce = 0;
   bool streamed = false;              // one workgroup walks the row in passes
+  bool held = false;                  // ... of which the first keeps it, in registers and LDS
   bool persistent = false;            // a fixed grid loops over register-resident rows
   int passes = 1, row_buffers = 0, buffers_shared = 0;
   bool inputs_cached = true;

@@ -445,6 +445,34 @@ def test_long_rows_of_any_length(rows, cols):
     assert_close(np.where(np.isfinite(got), got, 0.0), np.where(np.isfinite(want), want, 0.0), 1e-5, "log_softmax with -inf")
 
 
+@pytest.mark.parametrize("rows,cols,dtype", [(5, 90113, "f32"), (4, 94208, "f32"), (6, 114689, "f32"), (4, 118784, "f32"), (7, 118785, "f32"), (3, 131071, "f32"), (300, 122884, "f32"),
+                                             (4, 151552, "f32"), (4, 57352, "bf16"), (5, 65537, "f16"), (270, 81928, "bf16"), (4, 131072, "f16"), (4, 163848, "bf16"), (4, 237569, "f16"),
+                                             (4, 303104, "bf16")])
+def test_rows_held_in_registers_and_lds(rows, cols, dtype):
+    """Log-softmax and log-sum-exp of rows that are read once: edges of the chunks in registers, in LDS and read again, last chunks that are whole, begun or one
+    element, more rows than workgroups at a time; infinities; bit-reproducible; no update in place, as in the streamed form."""
+    announce(f"held rows {rows}x{cols} {dtype}")
+    ops, ins = graphs.log_softmax((rows, cols), dtype), inputs.normal_tensors([(rows, cols)], dtype, scale=3.0)
+    with Plan(ops) as p:
+        assert "held in registers and LDS" in p.describe() and p.info()["lds_bytes"] <= 160 * 1024 and p.info()["n_kernels"] == 1
+        dev = to_device(ops, ins)
+        with pytest.raises(FsError):
+            p.launch(dev, dev)
+    got, _ = check_against_oracle(ops, ins, what="log_softmax held")
+    assert np.array_equal(got[0], run_gpu(ops, ins, launches=2)[0])
+    if rows <= 7:
+        x = [np.array(a) for a in ins]
+        x[0][0, ::3] = -np.inf
+        x[0][-1, :-1] = -np.inf
+        x[0][1, -1] = np.inf
+        with np.errstate(divide="ignore", invalid="ignore"):
+            (want,) = interp.run(ops, x)
+        got = run_gpu(ops, x)[0]
+        assert np.array_equal(np.isnan(got), np.isnan(want)) and np.array_equal(got == -np.inf, want == -np.inf)
+        fine = np.isfinite(want)
+        assert_close(np.where(fine, got, 0.0), np.where(fine, want, 0.0), TOLERANCE[dtype], "log_softmax with infinities")
+
+
 def test_layernorm_backward_generated_at_full_size():
     announce("generated LN backward full size")
     ops, ins = BY_NAME["layernorm_bwd"].build("full")
