@@ -46,9 +46,10 @@ struct LnBwdArgs {
 // PF: row steps requested ahead of the one being worked on
 // MAXWG: largest workgroup the instance is launched with (256: one wavefront per SIMD may use the
 // whole register file; 512: two share it)
+// NT: nontemporal loads, where the rows are of whole vectors
 // WHOLE: rows of whole vectors.  Otherwise vectors are read and written at element alignment, through the caches (neighbouring rows share
 // lines), and the first elements of a row's last vector, its neighbour's too, count in nothing.
-template <int K, bool WANT_DX, int COL, bool EXACT, int PF, int MAXWG, bool WHOLE = true>
+template <int K, bool WANT_DX, int COL, bool EXACT, int PF, int MAXWG, bool WHOLE = true, bool NT = true>
 __global__ __launch_bounds__(MAXWG)
 void lnbwd_rows_kernel(const LnBwdArgs a) {
   extern __shared__ double lds[];   // [waves][2*K*256] slots
@@ -98,8 +99,9 @@ void lnbwd_rows_kernel(const LnBwdArgs a) {
     if constexpr (NEED_X) { rmu[b] = a.mean[r]; rrs[b] = a.rstd[r]; }
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-      rdy[b][k] = stream_load<float, WHOLE>(a.dy + r * a.cols + voff[k]);
-      if constexpr (NEED_X) rx[b][k] = stream_load<float, WHOLE>(a.x + r * a.cols + voff[k]);
+      auto load = [](const float* p) { return NT ? stream_load<float, WHOLE>(p) : cached_load<float, WHOLE>(p); };
+      rdy[b][k] = load(a.dy + r * a.cols + voff[k]);
+      if constexpr (NEED_X) rx[b][k] = load(a.x + r * a.cols + voff[k]);
     }
   };
 #pragma unroll
@@ -230,6 +232,10 @@ namespace {
 
 constexpr int kKs[] = {1, 2, 3, 4};
 constexpr int kPrefetch = 2;
+// Groups up to here load through the caches.  Nontemporally and so, us, from buffers that were in use a pass before and from others: 4096 x 1024 14.9, 12.7 and
+// 15.6, 15.1; 5248 x 192 7.9, 7.0 and 9.0, 8.4; 9268 x 192 9.7, 8.5 and 9.9, 9.7; 24832 x 128 14.2, 12.8 and 14.6, 15.1; 2496 x 832 11.2, 11.2 and 12.0, 12.3.  Beyond,
+// what the caches hold is not worth what new buffers lose: 8768 x 576 15.9, 14.3 and 16.6, 17.0; 16384 x 768 29.8, 30.6 and 30.2, 31.8.
+constexpr int64_t kCachedBytes = 48ll << 20;
 
 // more than 64 KB of dynamic LDS has to be enabled once per kernel
 template <typename Kern>
@@ -253,6 +259,9 @@ template <int K, bool EXACT, int MAXWG>
 hipError_t launch_KEW(const LnBwdArgs& a, bool want_dx, bool want_col, int grid, int wg, size_t lds,
                       hipStream_t s) {
   const bool need_x_cols = a.dgamma != nullptr;
+  if constexpr (MAXWG == 256)
+    if (want_dx && want_col && 12 * a.rows * a.cols <= kCachedBytes)
+      return launch_with_lds(lnbwd_rows_kernel<K, true, 2, EXACT, kPrefetch, MAXWG, true, false>, a, grid, wg, lds, s);
   if (want_dx && want_col)   // with dx the row is loaded anyway: always the full column path
     return launch_with_lds(lnbwd_rows_kernel<K, true, 2, EXACT, kPrefetch, MAXWG>, a, grid, wg, lds, s);
   if (want_dx) return launch_with_lds(lnbwd_rows_kernel<K, true, 0, EXACT, kPrefetch, MAXWG>, a, grid, wg, 0, s);

@@ -296,6 +296,13 @@ def test_layernorm_bwd_shapes(rows, cols, mode):
     check_against_oracle(graphs.layernorm_bwd(rows, cols), inputs.layernorm_bwd(rows, cols), mode, what=f"lnbwd {rows}x{cols}")
 
 
+@pytest.mark.parametrize("rows,cols", [(1025, 128), (1030, 260), (1100, 772), (4096, 1024), (4097, 1024)])
+def test_layernorm_bwd_through_the_caches(rows, cols):
+    """A wavefront to a row, up to 48 MiB with ordinary loads: one to four vectors a lane, whole sets of lanes and not, the largest such group and the next."""
+    announce(f"layernorm_bwd cached {rows}x{cols}")
+    check_against_oracle(graphs.layernorm_bwd(rows, cols), inputs.layernorm_bwd(rows, cols), what=f"lnbwd {rows}x{cols}")
+
+
 @pytest.mark.parametrize("rows,cols", [(256, 4), (257, 5), (300, 31), (1024, 33), (401, 255), (400, 257), (999, 511), (1024, 1024), (513, 1025), (301, 1027), (260, 2048), (450, 2049), (258, 4095), (256, 4096)])
 def test_layernorm_bwd_in_one_launch(rows, cols):
     """Few rows: the row path and strips of columns as workgroups of one launch; edges of vectors, strips, wavefronts and teams, the rule's
