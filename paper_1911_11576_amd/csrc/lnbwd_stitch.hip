@@ -259,7 +259,7 @@ template <int K, bool EXACT, int MAXWG>
 hipError_t launch_KEW(const LnBwdArgs& a, bool want_dx, bool want_col, int grid, int wg, size_t lds,
                       hipStream_t s) {
   const bool need_x_cols = a.dgamma != nullptr;
-  if constexpr (MAXWG == 256)
+  if constexpr (MAXWG == 256 || K == 1)
     if (want_dx && want_col && 12 * a.rows * a.cols <= kCachedBytes)
       return launch_with_lds(lnbwd_rows_kernel<K, true, 2, EXACT, kPrefetch, MAXWG, true, false>, a, grid, wg, lds, s);
   if (want_dx && want_col)   // with dx the row is loaded anyway: always the full column path
@@ -306,7 +306,9 @@ bool lnbwd_stitch_plan(const LnBwdSpec& sp, const LaunchOpts& opt, LnBwdLaunch* 
   for (int k : kKs) if (k >= need) { l.K = k; break; }
   // 4 wavefronts per workgroup and one workgroup per CU: one wavefront per SIMD has the whole
   // register file for its running sums and three row buffers; more wavefronts measured slower
-  l.wg = opt.wg_size ? opt.wg_size : 256;
+  // ... but for many rows of less than 256 columns, whose steps are too short to hide a row's latency behind: eight wavefronts 24832 x 128 12.9 -> 11.5 us (from
+  // buffers not in the caches 15.3 -> 13.1), 32768 x 192 18.8 -> 17.6; 12000 x 240 10.2 and 10.0, 9268 x 192 8.4 and 8.6, 32768 x 256 21.0 and 21.3
+  l.wg = opt.wg_size ? opt.wg_size : sp.cols % 4 == 0 && sp.cols < 256 && sp.rows >= 12288 ? 512 : 256;
   if (l.wg < 64 || l.wg > 512 || l.wg % 64) { *err = "LayerNorm-backward schedule: wg_size must be a multiple of 64 in [64,512]"; return false; }
   const int waves = l.wg / 64;
   int64_t grid = opt.grid > 0 ? opt.grid : 256;
