@@ -407,7 +407,7 @@ fs_status plan_create_impl(const fs_op_desc* ops, int32_t n_ops, const fs_plan_o
         case fs::MATCH_LNBWD:
           // The hand-written kernel (rows requested two steps ahead, per-wavefront LDS arrays) measured
           // faster than the generated one on config 5 (69.0 against 71.2 us): it is the default where it
-          // takes the shape (fp32, up to 1024 columns); the generated kernel serves the other shapes and
+          // takes the shape (fp32, up to 1024 columns, with teams of wavefronts up to 4096); the generated kernel serves the other shapes and
           // FS_MODE_STITCHED_GENERATED.
           if (want_generated && fall_back_to_generated()) break;
           // Few rows: one launch.
