@@ -2528,7 +2528,7 @@ struct Stream {
   //   16-bit rows of more than 57344 elements, whose values as floats leave a CU one workgroup: 512 x 65536 24.4 and 20.1, 557 x 78776 37.7 and 33.8, 1600 x
   //               62000 76.4 and 74.7, 1194 x 82944 71.9 and 72.1; not below, where two fit: 1500 x 50000 55.0 and 56.5, 2000 x 33000 46.7 and 47.9.  fp32 rows
   //               of that kind are held either way: 512 x 88001 74.1 and 74.1
-  // One workgroup to a CU and no more than half of its time on the memory: two of them with half the registers each, and more LDS, are no faster (bf16 700 x
+  // A CU has one workgroup, which loads and then stores; two of them with half the registers each, and more LDS, are no faster (bf16 700 x
   // 120001 93, 512 x 131072 57).  Up to three rows of whole chunks keep the form they have, see Gen::long_row_fits.
   bool can_hold(bool in_registers, int per_thread, Gen::Online* online) {
     std::string why;
