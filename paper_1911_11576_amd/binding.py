@@ -131,7 +131,8 @@ def lib():
         L.fs_fusion_pattern_group.argtypes = [vp, i32, C.POINTER(fs_op_desc), C.POINTER(i32), C.POINTER(i32)]
         L.fs_fusion_pattern_group.restype = i32
         from . import _launch
-        _launch.bind(C.cast(L.fs_launch, C.c_void_p).value, C.cast(L.fs_launch_static, C.c_void_p).value, _stream_source)
+        _launch.bind(C.cast(L.fs_launch, C.c_void_p).value, C.cast(L.fs_launch_static, C.c_void_p).value, _stream_source,
+                     C.c_void_p, lambda o: C.cast(o, C.c_void_p).value)
         _native = _launch
         _lib = L
     return _lib

@@ -20,9 +20,12 @@ LaunchFn g_launch = nullptr, g_launch_static = nullptr;     // of the library th
 PyObject* g_source = nullptr;                               // gives the next two, asked once
 PyObject* g_raw_stream = nullptr;                           // device ordinal -> handle of torch's current stream there
 PyObject* g_device = nullptr;                               // -> torch's current device; None: the one above takes no ordinal
+PyObject* g_c_void_p = nullptr;                             // ctypes.c_void_p
+PyObject* g_address_of = nullptr;                           // anything that ctypes takes for a c_void_p -> its address, or None
 PyObject* g_data_ptr = nullptr;                             // "data_ptr"
 
-// What ctypes makes of a c_void_p argument: None is NULL, an int is the address, a c_void_p its value.
+// What ctypes makes of a c_void_p argument: None is NULL, an int is the address, a c_void_p its value; whatever else it
+// takes (an object with _as_parameter_ such as a torch stream, an array, a reference) or refuses, ctypes itself is asked.
 bool as_handle(PyObject* o, void** out) {
   if (o == Py_None) { *out = nullptr; return true; }
   if (PyLong_Check(o)) {
@@ -31,11 +34,12 @@ bool as_handle(PyObject* o, void** out) {
     *out = reinterpret_cast<void*>(static_cast<uintptr_t>(v));
     return true;
   }
-  PyObject* value = PyObject_GetAttrString(o, "value");
+  if (!g_address_of) { PyErr_SetString(PyExc_RuntimeError, "bind() has not been called"); return false; }
+  PyObject* value = (PyObject*)Py_TYPE(o) == g_c_void_p ? PyObject_GetAttrString(o, "value") : PyObject_CallOneArg(g_address_of, o);
   if (!value) return false;
   bool ok = false;
   if (value == Py_None || PyLong_Check(value)) ok = as_handle(value, out);
-  else PyErr_SetString(PyExc_TypeError, "a handle is an int, None or a c_void_p");
+  else PyErr_SetString(PyExc_TypeError, "an address is an int or None");
   Py_DECREF(value);
   return ok;
 }
@@ -170,15 +174,20 @@ PyObject* launch_arrays(PyObject*, PyObject* const* args, Py_ssize_t n) {
   return PyLong_FromLong(st);
 }
 
-// (address of fs_launch, address of fs_launch_static, function that says where the current stream comes from)
+// (address of fs_launch, address of fs_launch_static, function that says where the current stream comes from, c_void_p,
+// function that gives the address of what ctypes takes for one)
 PyObject* bind(PyObject*, PyObject* const* args, Py_ssize_t n) {
   void *a, *b;
-  if (n != 3) { PyErr_SetString(PyExc_TypeError, "bind(fs_launch, fs_launch_static, stream_source)"); return nullptr; }
+  if (n != 5) { PyErr_SetString(PyExc_TypeError, "bind(fs_launch, fs_launch_static, stream_source, c_void_p, address_of)"); return nullptr; }
   if (!as_handle(args[0], &a) || !as_handle(args[1], &b)) return nullptr;
   g_launch = reinterpret_cast<LaunchFn>(a);
   g_launch_static = reinterpret_cast<LaunchFn>(b);
   Py_INCREF(args[2]);
   Py_XSETREF(g_source, args[2]);
+  Py_INCREF(args[3]);
+  Py_XSETREF(g_c_void_p, args[3]);
+  Py_INCREF(args[4]);
+  Py_XSETREF(g_address_of, args[4]);
   Py_RETURN_NONE;
 }
 
@@ -189,7 +198,7 @@ PyObject* current_stream_handle(PyObject*, PyObject*) {
 
 #define FASTCALL(f) reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(f)), METH_FASTCALL
 PyMethodDef methods[] = {
-    {"bind", FASTCALL(bind), "bind(fs_launch, fs_launch_static, stream_source): the library's entry points"},
+    {"bind", FASTCALL(bind), "bind(fs_launch, fs_launch_static, stream_source, c_void_p, address_of): the library's entry points"},
     {"current_stream", current_stream_handle, METH_NOARGS, "the handle of torch's current stream"},
     {"launch", FASTCALL(launch), "launch(plan, inputs, outputs, stream) -> fs_status"},
     {"launch_static", FASTCALL(launch_static), "launch_static(plan, inputs, outputs, stream) -> fs_status"},

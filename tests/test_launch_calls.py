@@ -56,6 +56,26 @@ def test_refused(plan, ins, outs, error):
         plan.launch_static(ins, outs, 0)
 
 
+class Stream:
+    """What a torch.cuda.Stream is to ctypes."""
+    _as_parameter_ = C.c_void_p(64)
+
+
+@pytest.mark.parametrize("stream", [Stream(), C.byref(C.c_uint64()), (C.c_uint64 * 4)(), C.pointer(C.c_uint64())], ids=lambda s: type(s).__name__)
+def test_streams_that_ctypes_takes(plan, stream):
+    plan.launch([4096, 8192, 16384], [32768], stream)
+    plan.launch_static([4096, 8192, 16384], [32768], stream)
+    plan.launch_bound(BoundArgs([4096, 8192, 16384], [32768]), stream)
+
+
+@pytest.mark.parametrize("stream", [C.c_int(3), 1.5, [], Tensor(64)], ids=lambda s: type(s).__name__)
+def test_streams_that_ctypes_refuses(plan, stream):
+    for call in (lambda: plan.launch([4096, 8192, 16384], [32768], stream), lambda: plan.launch_static([4096, 8192, 16384], [32768], stream),
+                 lambda: plan.launch_bound(BoundArgs([4096, 8192, 16384], [32768]), stream)):
+        with pytest.raises(C.ArgumentError):
+            call()
+
+
 def test_a_list_that_shrinks_while_it_is_read(plan):
     class Shrinks(Tensor):
         def data_ptr(self):
