@@ -1,4 +1,5 @@
-"""ctypes binding of include/fs.h: same entry points, argument marshalling only.
+"""Binding of include/fs.h: same entry points, argument marshalling only, by ctypes; the launch calls by the module
+_launch (csrc/py_launch.cpp) where it was built for this interpreter, else by ctypes too, a microsecond a call slower.
 
 Every step of the path runs in the HIP library.  PyTorch appears here only as the
 owner of device memory and streams (`tensor.data_ptr()`, the current stream's
@@ -9,6 +10,7 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+from array import array
 from collections import namedtuple
 from math import prod
 
@@ -54,7 +56,7 @@ class FsError(RuntimeError):
 
 
 _lib = None
-_native = None              # the launch entry points on Python lists (csrc/py_launch.cpp), with lib()
+_native = None              # the launch entry points on Python lists (_launch or _CtypesCalls), with lib()
 
 
 def lib():
@@ -130,12 +132,55 @@ def lib():
         L.fs_fusion_pattern_group_size.restype = i32
         L.fs_fusion_pattern_group.argtypes = [vp, i32, C.POINTER(fs_op_desc), C.POINTER(i32), C.POINTER(i32)]
         L.fs_fusion_pattern_group.restype = i32
-        from . import _launch
-        _launch.bind(C.cast(L.fs_launch, C.c_void_p).value, C.cast(L.fs_launch_static, C.c_void_p).value, _stream_source,
-                     C.c_void_p, lambda o: C.cast(o, C.c_void_p).value)
-        _native = _launch
+        _native = _launch_calls(L)
         _lib = L
     return _lib
+
+
+class _CtypesCalls:
+    """The calls of the module _launch by ctypes, for an interpreter that it was not built for."""
+
+    def __init__(self):
+        raw = C.CDLL(LIB_PATH)          # a handle of its own: plain addresses in place of lib()'s typed pointers
+        for f in (raw.fs_launch, raw.fs_launch_static):
+            f.argtypes = [C.c_void_p, C.c_void_p, C.c_int32, C.c_void_p, C.c_int32, C.c_void_p]
+            f.restype = C.c_int32
+        self.launch_arrays, self._launch_static, self._stream = raw.fs_launch, raw.fs_launch_static, None
+
+    def current_stream(self):
+        if self._stream is None:
+            self._stream = _stream_source()
+        raw, device = self._stream
+        return raw(device()) if device else raw()
+
+    def _call(self, f, plan, inputs, outputs, stream):
+        if stream is None:
+            stream = self.current_stream()
+        ins, n_in = self._addresses(inputs)
+        outs, n_out = self._addresses(outputs)
+        return f(plan, ins.buffer_info()[0], n_in, outs.buffer_info()[0], n_out, stream)
+
+    @staticmethod
+    def _addresses(tensors):
+        len(tensors)                    # an iterator has no length: refused
+        taken = [t if isinstance(t, int) else t.data_ptr() for t in tensors]
+        return array("Q", taken or [0]), len(taken)
+
+    def launch(self, plan, inputs, outputs, stream):
+        return self._call(self.launch_arrays, plan, inputs, outputs, stream)
+
+    def launch_static(self, plan, inputs, outputs, stream):
+        return self._call(self._launch_static, plan, inputs, outputs, stream)
+
+
+def _launch_calls(L):
+    try:
+        from . import _launch
+    except ImportError:
+        return _CtypesCalls()
+    _launch.bind(C.cast(L.fs_launch, C.c_void_p).value, C.cast(L.fs_launch_static, C.c_void_p).value, _stream_source,
+                 C.c_void_p, lambda o: C.cast(o, C.c_void_p).value)
+    return _launch
 
 
 def fs_last_error():

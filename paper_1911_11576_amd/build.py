@@ -3,7 +3,10 @@
 Every source under csrc/ is compiled with hipcc (device code for gfx950 only) and linked
 into libfusionstitch.so next to this file, together with the HIP run-time compiler that
 the kernel generator of the elementwise schedule uses.  The launch calls of the Python binding are a module
-of their own beside it.  hipcc cross-compiles without a GPU.
+of their own beside it, for the interpreter that builds it and only where its headers are installed (the binding makes
+the calls by ctypes elsewhere).  hipcc cross-compiles without a GPU.
+
+FS_LIB_OUT names another place for the library; nothing is written beside this file then (the module takes any library).
 """
 from __future__ import annotations
 
@@ -46,6 +49,7 @@ def build(verbose=False, jobs=None):
     os.makedirs(OBJ, exist_ok=True)
     jobs = jobs or min(8, os.cpu_count() or 1)
     with ThreadPoolExecutor(jobs) as ex:
+        calls = ex.submit(_build_python_calls) if "FS_LIB_OUT" not in os.environ else None
         results = list(ex.map(_compile, SOURCES))
     for (obj, log), src in zip(results, SOURCES):
         if verbose and log.strip():
@@ -54,13 +58,21 @@ def build(verbose=False, jobs=None):
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError("link failed:\n" + r.stdout + r.stderr)
-    _build_python_calls()
+    if calls:
+        calls.result()
     return LIB
 
 
 def _build_python_calls():
-    """csrc/py_launch.cpp, host code alone: the module _launch of this package, for the Python that builds it."""
-    cmd = [HIPCC, "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall", "-Wno-cast-function-type", "-x", "c++", "-I", sysconfig.get_paths()["include"],
+    """csrc/py_launch.cpp, host code alone: the module _launch of this package, for the Python that builds it.
+    Without that Python's headers there is none, and none of an earlier build is left."""
+    include = sysconfig.get_paths()["include"]
+    if not os.path.exists(os.path.join(include, "Python.h")):
+        if os.path.exists(PY_LIB):
+            os.remove(PY_LIB)
+        print(f"no Python.h in {include}: launch calls by ctypes")
+        return
+    cmd = [HIPCC, "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall", "-Wno-cast-function-type", "-x", "c++", "-I", include,
            os.path.join(CSRC, "py_launch.cpp"), "-o", PY_LIB]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:

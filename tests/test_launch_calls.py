@@ -1,11 +1,15 @@
-"""The launch calls of the Python binding (csrc/py_launch.cpp): what they take as tensors, plans and streams, on a group
-without rows, which launches nothing."""
+"""The launch calls of the Python binding (csrc/py_launch.cpp, and ctypes where that is not built): what they take as
+tensors, plans and streams, on a group without rows, which launches nothing."""
 import ctypes as C
+import os
+import subprocess
+import sys
+import sysconfig
 from collections import deque
 
 import pytest
 
-from paper_1911_11576_amd import BoundArgs, FsError, Plan, binding
+from paper_1911_11576_amd import BoundArgs, FsError, Plan, binding, build
 from workloads import graphs
 
 
@@ -17,8 +21,20 @@ class Tensor:
         return self.address
 
 
+@pytest.fixture(scope="module", autouse=True, params=["native", "ctypes"])
+def calls(request):
+    binding.lib()
+    kept = binding._native
+    if request.param == "ctypes":
+        binding._native = binding._CtypesCalls()
+    elif isinstance(kept, binding._CtypesCalls):
+        pytest.skip("_launch is not built for this interpreter")
+    yield
+    binding._native = kept
+
+
 @pytest.fixture(scope="module")
-def plan():
+def plan(calls):
     with Plan(graphs.layernorm_fwd(0, 768, "f32", 1e-5)) as p:
         yield p
 
@@ -92,3 +108,37 @@ def test_a_closed_plan_is_refused():
     for call in (lambda: p.launch([4096] * 3, [32768], 0), lambda: p.launch_bound(BoundArgs([4096] * 3, [32768]), 0)):
         with pytest.raises(FsError):
             call()
+
+
+def test_an_interpreter_that_launch_was_not_built_for():
+    code = ("import sys; sys.modules['paper_1911_11576_amd._launch'] = None\n"
+            "from paper_1911_11576_amd import Plan, binding\n"
+            "from workloads import graphs\n"
+            "with Plan(graphs.layernorm_fwd(0, 768, 'f32', 1e-5)) as p:\n"
+            "    p.launch([4096] * 3, [32768], 0)\n"
+            "assert isinstance(binding._native, binding._CtypesCalls)\n")
+    subprocess.run([sys.executable, "-c", code], check=True, timeout=120, cwd=os.path.dirname(build.HERE))
+
+
+def built(tmp_path, monkeypatch, environ):
+    """What a build in this environment runs and writes, with the compiler left out."""
+    commands = []
+    monkeypatch.setattr(build, "OBJ", str(tmp_path / "obj"))
+    monkeypatch.setattr(build, "PY_LIB", str(tmp_path / "_launch.so"))
+    monkeypatch.setattr(build.subprocess, "run", lambda cmd, **_: commands.append(cmd) or subprocess.CompletedProcess(cmd, 0, "", ""))
+    monkeypatch.delenv("FS_LIB_OUT", raising=False)
+    for name, value in environ.items():
+        monkeypatch.setenv(name, value)
+    build.build()
+    return [cmd[cmd.index("-o") + 1] for cmd in commands]
+
+
+def test_a_library_built_elsewhere_leaves_the_package_alone(tmp_path, monkeypatch):
+    assert str(tmp_path / "_launch.so") in built(tmp_path, monkeypatch, {})
+    assert str(tmp_path / "_launch.so") not in built(tmp_path, monkeypatch, {"FS_LIB_OUT": str(tmp_path / "lib.so")})
+
+
+def test_a_build_without_python_headers(tmp_path, monkeypatch):
+    monkeypatch.setattr(sysconfig, "get_paths", lambda: {"include": str(tmp_path)})
+    (tmp_path / "_launch.so").write_text("of an earlier build")
+    assert str(tmp_path / "_launch.so") not in built(tmp_path, monkeypatch, {}) and not (tmp_path / "_launch.so").exists()
