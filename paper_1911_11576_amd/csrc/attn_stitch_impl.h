@@ -170,14 +170,20 @@ __global__ __launch_bounds__(64 * NQ) void attn_stitch_kernel(const AttnArgs a) 
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks)
       qf[ks] = at16(qb, qoff, ks * 64);
-#pragma unroll
-    for (int j = 0; j < KT; ++j) {
-      // (a tile beyond the last asks for the last row again: with a branch around every load the compiler waited out one behind the other:
-      // bf16 key mask 359 x 64 x 50 x 128 7.2 -> 6.4 us, 4288 x 64 x 24 x 64 17.7 -> 16.4, 1000 x 128 x 128 x 128 29.3 -> 26.8)
+    // (a tile beyond the last asks for the last row again: with a branch around every load the compiler waited out one behind the other:
+    // bf16 key mask 359 x 64 x 50 x 128 7.2 -> 6.4 us, 4288 x 64 x 24 x 64 17.7 -> 16.4, 1000 x 128 x 128 x 128 29.3 -> 26.8)
+    auto request_k = [&](int j) __attribute__((always_inline)) {
       const int kt = w + j * NQ;
       const int krow = E && NK % NQ == 0 ? kt * 16 + c : min(kt * 16 + c, sk - 1);
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) kf[j][ks] = at16(kb, (uint32_t)(krow * D + 8 * g) * 2, ks * 64);
+    };
+    request_k(0);
+    // (K's tiles beyond the first for each wavefront lie right of the diagonal for all queries where tiles are skipped: one branch around all of them,
+    // causal bf16 8192 x 16 x 128 x 64 33.9 us, all tiles requested 53.5; 4096 x 16 x 128 x 128 35.2 and 52.9; without a mask 55.0 and 54.7)
+    if (wg_tiles > NQ) {
+#pragma unroll
+      for (int j = 1; j < KT; ++j) request_k(j);
     }
 #pragma unroll
     for (int i = 0; i < NV; ++i) {

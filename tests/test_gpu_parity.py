@@ -565,6 +565,33 @@ def test_attention_with_prologue_and_epilogue(case):
         assert got[1].shape == (B, sq)
 
 
+@pytest.mark.parametrize("B,sq,sk,d,dtype", [(8192, 16, 128, 64, "bf16"), (8192, 30, 127, 64, "f16"), (4096, 16, 128, 128, "f16")])
+def test_causal_attention_requests_the_keys_it_needs(B, sq, sk, d, dtype):
+    """With fewer queries than keys and a fill of -inf most rows of K are read by no one: by the bytes the causal group takes 0.60 (16 x 128) to 0.65 of
+    the time of the same group without the mask (0.98 if all of K is read), and what K holds there counts in nothing."""
+    announce(f"causal attention {B}x{sq}x{sk}x{d} {dtype}")
+    groups = [graphs.attention_block(B, sq, sk, d, dtype, causal=causal) for causal in (True, False)]
+    ins = inputs.attention_block(4, sq, sk, d, dtype, causal=True)
+    tail = [np.array(a) for a in ins]
+    tail[1][:, (sq + 15) // 16 * 16:, :] = np.nan
+    small = graphs.attention_block(4, sq, sk, d, dtype, causal=True)
+    assert np.array_equal(run_gpu(small, ins)[0], run_gpu(small, tail)[0])
+    dev_in = [t.repeat(B // 4, 1, 1) for t in to_device(small, ins)]
+    outs = alloc_outputs(groups[0])
+    times = [[], []]
+    with Plan(groups[0]) as causal, Plan(groups[1]) as full:
+        for _ in range(12):
+            for plan, took in ((causal, times[0]), (full, times[1])):
+                start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+                start.record()
+                for _ in range(8):
+                    plan.launch(dev_in, outs)
+                end.record()
+                end.synchronize()
+                took.append(start.elapsed_time(end))
+    assert np.median(times[0]) < 0.8 * np.median(times[1]), [np.median(t) for t in times]
+
+
 # ---------------------------------------------------------------- full-size configs, bench launch shape
 
 def test_full_size_layernorm_fwd():
