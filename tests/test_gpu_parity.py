@@ -592,6 +592,27 @@ def test_causal_attention_requests_the_keys_it_needs(B, sq, sk, d, dtype):
     assert np.median(times[0]) < 0.8 * np.median(times[1]), [np.median(t) for t in times]
 
 
+@pytest.mark.parametrize("sq,sk,d,dtype,mask", [(64, 64, 64, "f16", "key"), (100, 100, 64, "bf16", "key"), (33, 70, 32, "f16", "key"), (16, 128, 128, "bf16", "key"),
+                                                (64, 64, 64, "f16", "full"), (33, 70, 32, "bf16", "full")])
+def test_attention_rounds_a_mask_with_the_score(sq, sk, d, dtype, mask):
+    """A bias counts unrounded: one rounding at the size of the score times the scale, one of its sum with the bias, both in units of log 2.  The dots are
+    of whole numbers, and one key's bias lies so far above the others that its score alone is the log-sum-exp: bit for bit."""
+    announce(f"attention mask rounding {sq}x{sk}x{d} {dtype} {mask}")
+    B, scale, f32 = 16, 0.01, np.float32
+    rng = np.random.default_rng(sq * sk + d)
+    q, k = (rng.integers(-2, 3, (B, n, d)).astype(np.float64) for n in (sq, sk))
+    bias = rng.uniform(-64, 0, (B, 1, sk))
+    bias[np.arange(B), 0, rng.integers(0, sk, B)] = rng.uniform(66, 90, B)
+    bias = inputs.round_to(bias, "f32")
+    log2e, ln2 = float(f32(1.4426950408889634)), f32(0.6931471805599453)
+    z = (q @ k.transpose(0, 2, 1) * float(f32(scale) * f32(log2e))).astype(f32).astype(np.float64)
+    want = (z + bias * log2e).max(axis=-1).astype(f32) * ln2
+    full = np.broadcast_to(bias, (B, sq, sk)).copy()
+    ops = graphs.attention_block(B, sq, sk, d, dtype, scale=scale, mask=mask, lse=True)
+    got = run_gpu(ops, [q, k, rng.normal(size=(B, sk, d)), bias if mask == "key" else full])[1]
+    assert np.array_equal(got.reshape(B, sq), want)
+
+
 # ---------------------------------------------------------------- full-size configs, bench launch shape
 
 def test_full_size_layernorm_fwd():
