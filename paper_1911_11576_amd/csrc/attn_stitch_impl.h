@@ -151,9 +151,6 @@ __global__ __launch_bounds__(64 * NQ) void attn_stitch_kernel(const AttnArgs a) 
   // gate and residual are requested behind the softmax: up to 32 registers less while scores and K fragments are held, and K and V arrive
   // sooner.  Against requests at the top (bf16, every operand, warm buffers): 800 x 128 x 128 x 64 causal 19.0 -> 16.4 us, 300 x 100 x
   // 100 x 64 9.5 -> 8.1, fp16 2000 x 80 x 80 x 128 59.6 -> 53.7
-  // ... but at the top where a mask value per score fills the registers either way: 4096 x 64 x 64 x 64 full mask, causal 48.4 against 47.5, 1536 x 100
-  // x 100 x 64 34.8 against 34.2 (3000 x 50 x 50 x 64 36.2 against 37.5, 800 x 128 x 128 x 64 23.4 against 23.8, 1000 x 128 x 128 x 128 51.3 against 53.9)
-  constexpr bool LATE = !(FULL && D == 64 && ((NQ == 4 && NK == 4 && E) || (NQ == 8 && NK == 8 && !E)));
   auto operands = [&]() __attribute__((always_inline)) {
     if (OPS && a.gate) {
       const char* p = static_cast<const char*>(a.gate) + (int64_t)b * sq * D * 2 + goff;
@@ -207,7 +204,6 @@ __global__ __launch_bounds__(64 * NQ) void attn_stitch_kernel(const AttnArgs a) 
         }
       }
     }
-    if constexpr (!LATE) operands();
     if constexpr (KEYS) {
       const float* mrow = X == ATTN_KEY_MASK || a.mask ? a.mask + (int64_t)b * a.mask_sb : reinterpret_cast<const float*>(kb);      // (no mask: any sk values)
 #pragma unroll
@@ -358,7 +354,7 @@ __global__ __launch_bounds__(64 * NQ) void attn_stitch_kernel(const AttnArgs a) 
         pb[kk][2 * h + 1] = Mfma<T>::pack(p[2], p[3]);
       }
 
-    if constexpr (LATE) operands();
+    operands();
     asm volatile("" ::: "memory");       // (requested here, not at their use)
     // ---- second dot, transposed: O^T(D x 16) = V^T(D x keys) . P^T, up to 64 columns of O at a time ------
     constexpr int DH = (D < 64 ? D : 64) / 16;
