@@ -306,9 +306,17 @@ bool lnbwd_stitch_plan(const LnBwdSpec& sp, const LaunchOpts& opt, LnBwdLaunch* 
   for (int k : kKs) if (k >= need) { l.K = k; break; }
   // 4 wavefronts per workgroup and one workgroup per CU: one wavefront per SIMD has the whole
   // register file for its running sums and three row buffers; more wavefronts measured slower
-  // ... but for many rows of less than 256 columns, whose steps are too short to hide a row's latency behind: eight wavefronts 24832 x 128 12.9 -> 11.5 us (from
-  // buffers not in the caches 15.3 -> 13.1), 32768 x 192 18.8 -> 17.6; 12000 x 240 10.2 and 10.0, 9268 x 192 8.4 and 8.6, 32768 x 256 21.0 and 21.3
-  l.wg = opt.wg_size ? opt.wg_size : sp.cols % 4 == 0 && sp.cols < 256 && sp.rows >= 12288 ? 512 : 256;
+  // ... but for many rows of up to 224 columns, whose steps are too short to hide a row's latency behind.  Four and eight wavefronts, us from buffers in use a
+  // pass before (from others):
+  //   all outputs  24832 x 128 12.9 and 11.3 (15.3 and 13.1), 50000 x 64 17.7 and 13.9 (21.8 and 16.7), 32768 x 224 19.7 and 19.1, 60000 x 224 31.0 and 30.3
+  //   dx alone     20000 x 128 9.0 and 7.3 (9.5 and 8.2), 60000 x 224 27.4 and 26.9 (28.3 and 28.2), 12288 x 224 7.8 and 7.5 (8.3 and 8.4)
+  //   column sums  50000 x 128 16.1 and 12.5 (16.8 and 13.5), 60000 x 224 20.6 and 20.1 (21.5 and 21.5), 12288 x 224 8.5 and 8.3 (9.2 and 9.5)
+  //   not          9268 x 192 8.4 and 8.6; 32768 x 256 21.0 and 21.3
+  // Up to 252 columns with dx and column sums and up to 24576 rows: 12288 x 252 10.5 and 10.3 (12.2 and 12.1), 20000 x 244 14.8 and 14.8; not 60000 x 252 34.2 and
+  // 35.7, 60000 x 240 32.2 and 32.5, nor dx alone 20000 x 240 11.4 and 11.3 (12.0 and 12.4), 60000 x 252 30.6 and 32.1, nor sums alone 20000 x 240 10.5 and 10.5 (11.3 and 11.5)
+  const bool want_col = sp.out_dgamma >= 0 || sp.out_dbeta >= 0;
+  const bool eight = sp.cols % 4 == 0 && sp.rows >= 12288 && (sp.cols <= 224 || (sp.cols < 256 && sp.rows <= 24576 && sp.out_dx >= 0 && want_col));
+  l.wg = opt.wg_size ? opt.wg_size : eight ? 512 : 256;
   if (l.wg < 64 || l.wg > 512 || l.wg % 64) { *err = "LayerNorm-backward schedule: wg_size must be a multiple of 64 in [64,512]"; return false; }
   const int waves = l.wg / 64;
   int64_t grid = opt.grid > 0 ? opt.grid : 256;
@@ -317,7 +325,6 @@ bool lnbwd_stitch_plan(const LnBwdSpec& sp, const LaunchOpts& opt, LnBwdLaunch* 
   if (grid < 1) grid = 1;
   if (grid > 4096) grid = 4096;
   l.grid = (int)grid;
-  const bool want_col = sp.out_dgamma >= 0 || sp.out_dbeta >= 0;
   l.n_kernels = want_col ? 2 : 1;
   // (a row is read by the one wavefront that writes it, before it does; whole vectors have never taken updates in place)
   l.in_place = sp.cols % 4 != 0;

@@ -86,3 +86,16 @@ def product_with_column_sums(rows, cols, dtype, n):
     for k, v in enumerate([p, a, b, g.multiply(a, a), g.multiply(b, b), g.add(a, b), g.subtract(a, b)][:n]):
         g.output(g.reduce_sum(v, 0), f"sum{k}")
     return g.ops
+
+
+def with_outputs(ops, keep):
+    """The ops that the outputs number `keep` need, and those outputs."""
+    outs = [i for i, op in enumerate(ops) if op.kind == "output"]
+    need, todo = set(), [outs[k] for k in keep]
+    while todo:
+        i = todo.pop()
+        if i not in need:
+            need.add(i)
+            todo += ops[i].operands
+    order = sorted(need)
+    return [ops[i]._replace(operands=tuple(order.index(j) for j in ops[i].operands)) for i in order]

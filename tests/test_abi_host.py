@@ -11,7 +11,7 @@ from paper_1911_11576_amd import FsError, Plan, binding
 from workloads import BY_NAME, CONFIGS, algorithmic_bytes, graphs
 from workloads.graphs import Graph, Op
 
-from gpu_util import product_with_column_sums
+from gpu_util import product_with_column_sums, with_outputs
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -858,6 +858,17 @@ def test_layernorm_bwd_teams_need_no_more_scratch_memory(rows, cols):
         assert p.info()["workspace_bytes"] <= max(8 << 20, groups * 2 * -(-cols // 16) * 16 * 8)
         if groups * 2 * cols * 8 <= 8 << 20:
             assert p.info()["workspace_bytes"] <= 8 << 20
+
+
+@pytest.mark.parametrize("rows,cols,keep,threads", [
+    (12287, 128, (0, 1, 2), 256), (12288, 128, (0, 1, 2), 512), (60000, 224, (0, 1, 2), 512), (60000, 224, (0,), 512), (60000, 224, (1, 2), 512),
+    (20000, 252, (0, 1, 2), 512), (24576, 228, (0, 2), 512), (24577, 228, (0, 1, 2), 256), (60000, 252, (0, 1, 2), 256), (60000, 256, (0, 1, 2), 256),
+    (20000, 252, (0,), 256), (60000, 252, (0,), 256), (20000, 228, (1, 2), 256), (60000, 252, (1, 2), 256)])
+def test_layernorm_bwd_wavefronts_to_a_workgroup(rows, cols, keep, threads):
+    """Eight where they were measured to be faster: many rows of up to 224 columns, and of up to 252 with dx and column sums and not too many rows."""
+    ops = with_outputs(graphs.layernorm_bwd(rows, cols), keep)
+    with Plan(ops) as p:
+        assert "hand-written" in p.describe() and f"cta_size={threads}" in p.describe(), p.describe()
 
 
 def _in_place_status(ops):
