@@ -15,7 +15,7 @@ from paper_1911_11576_amd import binding
 from workloads import BY_NAME, CONFIGS, TOLERANCE, graphs, inputs
 
 from gpu_util import (alloc_outputs, assert_close, check_against_oracle, run_gpu,
-                      to_device)
+                      to_device, with_outputs)
 
 pytestmark = pytest.mark.gpu
 
@@ -309,6 +309,31 @@ def test_layernorm_bwd_through_the_caches(rows, cols):
     check_against_oracle(graphs.layernorm_bwd(rows, cols), inputs.layernorm_bwd(rows, cols), what=f"lnbwd {rows}x{cols}")
 
 
+@pytest.mark.parametrize("rows,cols,threads,keep", [
+    (21001, 200, 512, (0, 1, 2)), (32769, 132, 512, (0, 1, 2)), (18001, 244, 512, (0, 1, 2)), (24601, 228, 256, (0, 1, 2)), (16500, 256, 256, (0, 1, 2)),
+    (9001, 500, 256, (0, 1, 2)), (8200, 512, 256, (0, 1, 2)), (5701, 740, 256, (0, 1, 2)), (5500, 768, 256, (0, 1, 2)), (4301, 1000, 256, (0, 1, 2)),
+    (12290, 128, 512, (0,)), (12297, 128, 512, (1, 2)), (12289, 220, 512, (2,)), (12288, 64, 512, (0, 1)), (1500, 1000, 256, (0,)), (1501, 768, 256, (2,))])
+def test_layernorm_bwd_nontemporally(rows, cols, threads, keep):
+    """A wavefront to a row with nontemporal loads: all outputs beyond 48 MiB and some of them at any size, one to four vectors a lane, whole sets of lanes and
+    not, four and eight wavefronts to a workgroup; bit-reproducible.  Column sums have the room of a sum of fp32 terms t, each with the rounding of the chain
+    that made it: 4 * 2^-24 * sqrt(sum t^2)."""
+    announce(f"layernorm_bwd nontemporal {rows}x{cols} {keep}")
+    assert len(keep) < 3 or 12 * rows * cols > 48 << 20
+    ops, ins = graphs.layernorm_bwd(rows, cols), inputs.layernorm_bwd(rows, cols)
+    dy, x, _, mean, rstd = (np.asarray(a, dtype=np.float64) for a in ins)
+    terms = [dy * (x - mean.reshape(-1, 1)) * rstd.reshape(-1, 1), dy]
+    slack = [None] + [4.0 * 2.0 ** -24 * np.sqrt((t * t).sum(axis=0)) for t in terms]
+    ops = with_outputs(ops, keep)
+    ins = [ins[["dy", "x", "gamma", "mean", "rstd"].index(op.name)] for op in ops if op.kind == "parameter"]
+    with Plan(ops) as p:
+        assert "hand-written" in p.describe() and f"cta_size={threads}" in p.describe()
+    got, want = run_gpu(ops, ins), interp.run(ops, ins)
+    for k, a, b in zip(keep, got, want):
+        assert_close(a, b, 1e-5, f"lnbwd {rows}x{cols} output {k}", slack[k])
+    for a, b in zip(got, run_gpu(ops, ins, launches=2)):
+        assert np.array_equal(a, b)
+
+
 @pytest.mark.parametrize("rows,cols", [(256, 4), (257, 5), (300, 31), (1024, 33), (401, 255), (400, 257), (999, 511), (1024, 1024), (513, 1025), (301, 1027), (260, 2048), (450, 2049), (258, 4095), (256, 4096)])
 def test_layernorm_bwd_in_one_launch(rows, cols):
     """Few rows: the row path and strips of columns as workgroups of one launch; edges of vectors, strips, wavefronts and teams, the rule's
@@ -360,10 +385,10 @@ def test_layernorm_bwd_rows_of_no_whole_vectors(rows, cols):
 
 
 @pytest.mark.parametrize("rows,cols", [(1025, 1025), (1026, 1028), (1100, 1537), (1500, 1536), (2049, 2048), (1030, 2049), (1031, 3072), (1200, 3075), (1027, 4095), (1300, 4096),
-                                       (4099, 1100), (7300, 1540)])
+                                       (4099, 1100), (7300, 1540), (12001, 1280), (7203, 2048), (4703, 3072), (3502, 4096)])
 def test_layernorm_bwd_with_teams_of_wavefronts(rows, cols):
     """Two and four wavefronts to a row: edges of the lanes' vectors, rows at element alignment, trips of odd length, workgroups whose second team has no row
-    left, the loads of large groups; bit-reproducible, updates in place of dy and of x as by the generated form, the prebuilt mode as before.
+    left, nontemporal loads (beyond 160 MiB, every number of vectors a lane); bit-reproducible, updates in place of dy and of x as by the generated form, the prebuilt mode as before.
     dgamma over more than 2048 rows has the room of a sum of so many fp32 terms t, each with the rounding of the chain that made it: 4 * 2^-24 * sqrt(sum t^2)."""
     announce(f"layernorm_bwd teams {rows}x{cols}")
     ops, ins = graphs.layernorm_bwd(rows, cols), inputs.layernorm_bwd(rows, cols)

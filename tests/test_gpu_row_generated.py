@@ -449,7 +449,7 @@ def test_long_rows_of_any_length(rows, cols):
                                              (4, 151552, "f32"), (4, 57352, "bf16"), (5, 65537, "f16"), (270, 81928, "bf16"), (4, 131072, "f16"), (4, 163848, "bf16"), (4, 237569, "f16"),
                                              (4, 303104, "bf16")])
 def test_rows_held_in_registers_and_lds(rows, cols, dtype):
-    """Log-softmax and log-sum-exp of rows that are read once: edges of the chunks in registers, in LDS and read again, last chunks that are whole, begun or one
+    """Log-softmax of rows that are read once: edges of the chunks in registers, in LDS and read again, last chunks that are whole, begun or one
     element, more rows than workgroups at a time; infinities; bit-reproducible; no update in place, as in the streamed form."""
     announce(f"held rows {rows}x{cols} {dtype}")
     ops, ins = graphs.log_softmax((rows, cols), dtype), inputs.normal_tensors([(rows, cols)], dtype, scale=3.0)
@@ -471,6 +471,58 @@ def test_rows_held_in_registers_and_lds(rows, cols, dtype):
         assert np.array_equal(np.isnan(got), np.isnan(want)) and np.array_equal(got == -np.inf, want == -np.inf)
         fine = np.isfinite(want)
         assert_close(np.where(fine, got, 0.0), np.where(fine, want, 0.0), TOLERANCE[dtype], "log_softmax with infinities")
+
+
+def _held(shape, dtype, outputs, of=None):
+    """Log-softmax "y", the row's maximum "max" and log-sum-exp "lse", those named; of: the input's shape, with dims of one for those it is repeated over."""
+    g = graphs.Graph()
+    x = g.parameter("x", dtype, of or shape)
+    if dtype != "f32":
+        x = g.convert(x, "f32")
+    if of:
+        x = g.broadcast(x, shape, 0)
+    m = g.reduce_max(x, -1)
+    c = g.subtract(x, g.row_broadcast(m, x))
+    log_sum = g.log(g.reduce_sum(g.exp(c), -1))
+    for name in outputs:
+        if name == "y":
+            y = g.subtract(c, g.row_broadcast(log_sum, c))
+            g.output(y if dtype == "f32" else g.convert(y, dtype), "y")
+        else:
+            g.output(m if name == "max" else g.add(log_sum, m), name)
+    return g.ops
+
+
+@pytest.mark.parametrize("outputs", [("lse",), ("max", "lse"), ("y", "lse"), ("y", "max", "lse")], ids="+".join)
+@pytest.mark.parametrize("rows,cols,dtype", [(5, 90113, "f32"), (4, 118784, "f32"), (7, 118785, "f32"), (4, 151552, "f32"), (4, 57352, "bf16"), (5, 65537, "f16"), (4, 237569, "bf16")])
+def test_held_rows_with_row_outputs(rows, cols, dtype, outputs):
+    """Log-sum-exp and maximum of held rows, alone and beside log-softmax: chunks in registers, in LDS and read again, whole and ragged; infinities."""
+    announce(f"held rows {rows}x{cols} {dtype} {outputs}")
+    ops, (x,) = _held((rows, cols), dtype, outputs), inputs.normal_tensors([(rows, cols)], dtype, scale=3.0)
+    with Plan(ops) as p:
+        assert "held in registers and LDS" in p.describe() and p.info()["n_kernels"] == 1
+    check_against_oracle(ops, [x], what="held rows")
+    x = np.array(x)
+    x[0, ::3] = -np.inf
+    x[1, -1] = np.inf
+    x[2, :] = -np.inf
+    x[-1, :-1] = -np.inf
+    with np.errstate(divide="ignore", invalid="ignore"):
+        want = interp.run(ops, [x])
+    for name, a, b in zip(outputs, run_gpu(ops, [x]), want):
+        fine = np.isfinite(b)
+        assert np.array_equal(np.isnan(a), np.isnan(b)) and np.array_equal(a[~fine & ~np.isnan(b)], b[~fine & ~np.isnan(b)]), name
+        assert_close(np.where(fine, a, 0.0), np.where(fine, b, 0.0), TOLERANCE[dtype], f"held rows with infinities, {name}")
+
+
+@pytest.mark.parametrize("shape,of,dtype", [((4, 5, 100000), (4, 1, 100000), "f32"), ((2, 3, 2, 65537), (2, 1, 2, 65537), "bf16"), ((3, 2, 118785), (1, 2, 118785), "f32")])
+def test_held_rows_of_a_repeated_input(shape, of, dtype):
+    """Rows found by their coordinates: one row of the input is several of the group."""
+    announce(f"held rows {shape} of {of} {dtype}")
+    ops = _held(shape, dtype, ("y", "lse"), of)
+    with Plan(ops) as p:
+        assert "held in registers and LDS" in p.describe()
+    check_against_oracle(ops, inputs.normal_tensors([of], dtype, scale=3.0), what="held rows of a repeated input")
 
 
 def test_layernorm_backward_generated_at_full_size():
