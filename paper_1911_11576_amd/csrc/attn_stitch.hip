@@ -27,8 +27,11 @@ bool attn_stitch_plan(const AttnSpec& sp, const LaunchOpts& opt, AttnLaunch* out
   l.grid = (int)sp.batch;
   if (sp.sq == 1 && !sp.causal && !(sp.dim == 32 && sp.sk > 8 && sp.sk <= 32)) {
     // one query: matrix-vector products, a wavefront per batch element (attn_decode.hip).  9 to 32 keys of 32 stay on the
-    // matrix-unit tile: level from warm buffers, 4 to 10 % ahead from cold ones (4096 x 20 x 32 bf16 4.4 us against 4.8,
-    // 8192 x 16 x 32 5.5 against 6.0).  Up to four wavefronts to a workgroup
+    // matrix-unit tile.  Tile and matrix-vector products, bf16 with a key mask, us from warm (cold) buffers: 512 x 16 x 32 2.0 and 2.2 (2.4 and 2.7),
+    // 4096 x 16 x 32 2.8 and 2.9 (4.0 and 4.5); the products 4096 x 48 x 32 6.6 and 5.6 (7.3 and 6.4), 4096 x 16 x 64 5.1 and 4.4 (5.7 and 5.3),
+    // 4096 x 8 x 128 6.5 and 5.0 (7.6 and 5.7), 512 x 128 x 64 5.4 and 5.0 (6.0 and 5.6).  The tile, as it is now, is level or ahead for up to 8 keys
+    // of 32, 12 of 64 and in launches of a few MB too, by 0.5 us at most: 512 x 8 x 32 2.0 and 2.2 (2.4 and 2.7), 4096 x 12 x 64 4.2 and 4.3 (4.8 and
+    // 5.3), 512 x 64 x 64 3.1 and 2.8 (4.2 and 4.5).  Up to four wavefronts to a workgroup
     // where that leaves four workgroups for every CU (512 elements of 128 keys of 64 fp16: 5.3 us with one each, 7.0
     // with four on half of the CUs), and one if the caller names the workgroup of a single query tile
     l.decode = true;
@@ -89,10 +92,13 @@ int attn_stitch_launch(const AttnSpec& sp, const AttnLaunch& l, const void* cons
   a.skip_masked_tiles = sp.causal && sp.fill == -INFINITY;
   // Nontemporal stores of O in groups of less than 128 MB, but not in the bare exact form (4096 x 64 x 64 x 64 fp16 from cold
   // buffers 24.5 us with ordinary stores, 25.5 without).  From warm / cold buffers against ordinary stores, 64 wide, bf16: with every
-  // operand 512 x 100 x 100 10.3 / 11.3 (10.8 / 12.4), 1536 x 100 x 100 26.1 / 27.1 (27.6 / 27.7); with a key mask only 512 x 100 x 100
-  // 7.7 / 8.0 (8.2 / 9.0), 1536 x 128 x 128 24.3 / 27.5 (26.9 / 27.6), 4096 x 128 x 128 66.0 / 66.0 (65.0 / 64.9).  A kernel that reads O at once
-  // finds less of it in the caches: with a consumer 512 x 100 x 100 16.0 (16.3), 1536 x 100 x 100 37.8 (36.8), 4096 x 64 x 64
-  // with a key mask 41.5 (39.5).
+  // operand 512 x 100 x 100 8.8 / 10.5 (9.3 / 11.0), 1536 x 100 x 100 25.0 / 27.5 (27.4 / 28.0), 2500 x 100 x 100 40.3 / 41.0 (40.7 / 41.3); with a key
+  // mask only 512 x 100 x 100 7.5 / 8.1 (8.0 / 9.2), 1600 x 128 x 128 21.1 / 24.2 (22.5 / 23.7), 2600 x 128 x 128 34.9 / 35.5 (34.2 / 34.8),
+  // 4096 x 128 x 128 51.7 / 52.4 (49.9 / 50.7), 3600 x 64 x 64 22.3 / 24.0 (23.0 / 23.5), 8192 x 64 x 64 49.2 / 50.1 (47.0 / 47.8); with a mask of all scores
+  // 512 x 100 x 100 9.9 / 11.5 (10.5 / 12.7), 4096 x 100 x 100 69.4 / 70.9 (70.1 / 71.4); bare 2300 x 100 x 100 23.4 / 25.9 (25.1 / 25.8), 4096 x 100 x 100
+  // 41.5 / 42.0 (41.0 / 41.5).  The line is the key mask's and the bare group's; at whole tiles of 64 theirs lies lower (2048 x 64 x 64 12.7 / 15.2 (11.9 /
+  // 14.5)).  A kernel that reads O at once finds less of it in the caches: with a consumer, from cold buffers, every operand 512 x 100 x 100 15.7 (15.1),
+  // 1536 x 100 x 100 39.2 (38.9), key mask 1600 x 128 x 128 38.0 (35.8).
   a.stream_out = sp.batch * sp.dim * 2 * (sp.sq * (2 + (a.gate != nullptr) + (a.res != nullptr)) + 2 * sp.sk) < (128ll << 20);
   hipStream_t s = static_cast<hipStream_t>(stream);
   const bool f16 = sp.dtype == DT_F16;

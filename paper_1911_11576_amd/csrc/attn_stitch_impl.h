@@ -86,9 +86,9 @@ template <int N> struct TileCount { static constexpr int value = N; };   // a co
 // NQ: 16-row tiles of queries (workgroup = NQ wavefronts); NK: 16-key tiles; D: head dim;
 // X: what the group has around the dots, one of the four kinds below (run-time tests for what is not there cost 0.15 us of 6 on the
 // bare group, and registers for what is not there cost workgroups on a CU: with one kind for all that is not bare and the key mask in
-// registers, 128 x 128 x 64 held 130, two more than let two workgroups share a CU, and takes 78 with a key mask now; bf16, key mask:
-// 2000 x 128 x 128 x 64 41.2 -> 29.0 us, 1000 x 128 x 128 x 128 36.4 -> 29.3, 359 x 64 x 50 x 128 8.5 -> 7.2; 4096 x 50 x 50 x 64 fp16
-// with every operand 40.9 -> 33.2);
+// registers, 128 x 128 x 64 held 130, two more than let two workgroups share a CU; with a key mask it takes 72 now, 77 where the tiles
+// are not whole, and 88 and 86 with operands.  With the order of the loads below, bf16, key mask: 2000 x 128 x 128 x 64 40.7 -> 26.9 us,
+// 1000 x 128 x 128 x 128 35.4 -> 27.1, 359 x 64 x 50 x 128 8.3 -> 6.1; 4096 x 50 x 50 x 64 fp16 with every operand 40.5 -> 32.0);
 // E: the lengths are exactly 16 NQ queries and 16 NK keys (NK >= 2), so no row is clamped and no key
 // or query is tested against a length; S: O leaves with nontemporal stores.
 // With two wavefronts per SIMD and a memory phase of one round trip, the kernel's time follows its
@@ -150,7 +150,8 @@ __global__ __launch_bounds__(64 * NQ) void attn_stitch_kernel(const AttnArgs a) 
   u32x2 gt[D / 16], rs[D / 16];
   // gate and residual are requested behind the softmax: up to 32 registers less while scores and K fragments are held, and K and V arrive
   // sooner.  Against requests at the top (bf16, every operand, warm buffers): 800 x 128 x 128 x 64 causal 19.0 -> 16.4 us, 300 x 100 x
-  // 100 x 64 9.5 -> 8.1, fp16 2000 x 80 x 80 x 128 59.6 -> 53.7
+  // 100 x 64 9.5 -> 8.1, fp16 2000 x 80 x 80 x 128 59.6 -> 53.7.  A mask of all scores fills the registers either way: there large launches lose 1.3 to
+  // 1.8 % by it (bf16 4096 x 64 x 64 x 64 47.3 -> 47.9, 1536 x 100 x 100 x 64 36.7 -> 37.4) and small ones gain 2 to 4 (512 x 64 x 64 x 64 8.2 -> 7.9)
   auto operands = [&]() __attribute__((always_inline)) {
     if (OPS && a.gate) {
       const char* p = static_cast<const char*>(a.gate) + (int64_t)b * sq * D * 2 + goff;

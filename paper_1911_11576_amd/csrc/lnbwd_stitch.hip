@@ -232,9 +232,13 @@ namespace {
 
 constexpr int kKs[] = {1, 2, 3, 4};
 constexpr int kPrefetch = 2;
-// Groups up to here load through the caches.  Nontemporally and so, us, from buffers that were in use a pass before and from others: 4096 x 1024 14.9, 12.7 and
-// 15.6, 15.1; 5248 x 192 7.9, 7.0 and 9.0, 8.4; 9268 x 192 9.7, 8.5 and 9.9, 9.7; 24832 x 128 14.2, 12.8 and 14.6, 15.1; 2496 x 832 11.2, 11.2 and 12.0, 12.3.  Beyond,
-// what the caches hold is not worth what new buffers lose: 8768 x 576 15.9, 14.3 and 16.6, 17.0; 16384 x 768 29.8, 30.6 and 30.2, 31.8.
+// Groups up to here load through the caches, with all outputs.  Nontemporally and so, us, from buffers that were in use a pass before and from others:
+//   3600 x 1024 14.1, 12.0 and 14.7, 14.8; 4500 x 768 13.4, 11.4 and 13.8, 13.8; 6000 x 512 11.5, 10.6 and 12.0, 12.3; 20000 x 192 12.7, 11.5 and 13.5, 13.8;
+//   12000 x 128 10.2, 9.3 and 10.2, 10.3; 2400 x 832 11.2, 11.3 and 12.1, 12.5; 1500 x 1024 10.0, 9.4 and 10.4, 10.7; 1900 x 768 9.0, 8.8 and 9.2, 9.6; 1500 x 256
+//   6.6, 6.1 from others
+// That is up to 15 % less where the caches hold the rows, and up to 5 % more (below 256 columns up to 9 % less) where they don't.  Beyond, they hold less and less,
+// and the line is drawn on the safe side:
+// 8768 x 576 15.8, 14.4 and 16.9, 17.2; 6000 x 1000 19.4, 16.8 and 20.2, 19.8; 16384 x 768 29.7, 30.3 and 30.7, 31.9.
 constexpr int64_t kCachedBytes = 48ll << 20;
 
 // more than 64 KB of dynamic LDS has to be enabled once per kernel

@@ -32,12 +32,12 @@ template <bool NT, bool WHOLE> __device__ __forceinline__ u32x4 row_load(const f
 }
 
 // T wavefronts to a row, K vectors of it in a lane, TEAMS rows to a workgroup at a time, the next ones requested ahead.
-// Bound by HBM: 16 rows a workgroup of 4096 x 4096 take 36 us, 48 KB a row at the 5.7 TB/s that two tensors read and one written reach beside the partial rows.
+// Bound by HBM: 4096 x 4096, 18 or 19 rows to each of 224 workgroups, takes 36.6 us, 48 KB a row at 5.5 TB/s beside the partial rows.
 template <int T, int K, int TEAMS, bool WHOLE, bool NT>
 __global__ __launch_bounds__(64 * T * TEAMS) void lnbwd_team_kernel(const Args a) {
   constexpr int LANES = 64 * T;
   // Two row buffers that take turns, and with them the exchange slots: one is written again behind another row's barrier only.  (Rows requested two steps
-  // ahead, in three buffers, are no faster: 4096 x 4096 44.0 us and 44.2, 4587 x 1536 18.8 and 18.8, 1600 x 3502 19.8 and 20.5.)
+  // ahead, in three buffers, are no faster, us with the second kernel in replayed launches of one plan: 4096 x 4096 44.0 and 44.2, 4587 x 1536 18.8 and 18.8, 1600 x 3502 19.8 and 20.5.)
   constexpr int NB = 2;
   extern __shared__ double lds[];                    // [TEAMS - 1][2 * K * 4][LANES]
   __shared__ float exch[NB][TEAMS][T][2];
@@ -204,19 +204,22 @@ hipError_t launch(const Args& a, int grid, hipStream_t s) {
 // Doubles from one partial row to the next: whole 128-byte lines, which the second kernel reads (6000 x 3001: 5.9 us without).
 static int64_t partial_stride(int64_t cols) { return (cols + 15) / 16 * 16; }
 
-// Replayed launches over three sets of buffers, the generated kernel, which is what such rows had (up to 512 workgroups, teams of a power of two of
-// wavefronts, ragged rows' buffers copied behind every row), and this one, in us.
+// Launches over three sets of buffers with a plan each, the generated kernel, which is what such rows had (up to 512 workgroups, teams of a power of two of
+// wavefronts, ragged rows' buffers copied behind every row), and this one, in us (replayed launches of one plan, whose partial rows share a workspace,
+// take up to 8 % longer: 4096 x 4096 45.1 and 44.5).
 //   taken       1027 x 1472 12.0 and 10.2, 1500 x 1100 12.8 and 10.7, 3000 x 1280 15.9 and 13.6, 4587 x 1536 23.2 and 18.8, 1326 x 2547 18.7 and 14.9,
 //               2564 x 2316 21.9 and 18.1, 5500 x 3072 53.3 and 41.5, 6000 x 3001 56.8 and 44.4, 9000 x 3600 82.9 and 77.3, 4096 x 4096 41.5 and 41.3; 1100 x 4096, where the
 //               workspace leaves 128 workgroups, 16.6 and 16.7.  Up to 1024 rows have a launch of their own kind (lnbwd_packed.hip)
 //   T           two wavefronts to a row up to 2048 columns, else four, with three or four vectors a lane, four wavefronts to a workgroup: 4 and 2 vectors
-//               19.4 for 4587 x 1536, where this is 18.8 (both as 256 workgroups); eight wavefronts to a workgroup 18.9, 4096 x 4096 48.7 and not 44.0
+//               19.4 for 4587 x 1536, where this is 18.8 (both as 256 workgroups); eight wavefronts to a workgroup 18.9, and 4096 x 4096 48.7 and not 44.0 (one plan)
 //   loads       through the caches up to 160 MB: 3000 x 1280 13.6 and nontemporally 15.3 (from cold buffers 15.5 and 15.7), 2564 x 2316 18.0 and 21.7, 3000 x
-//               4096 32.2 and 35.6; 10000 x 1536 37.4 and 36.2, 4096 x 4096 43.1 and 41.3, 16000 x 1536 55.6 and 52.8 (9000 x 3600 75.1 and 77.3).  Rows at
-//               element alignment share lines with their neighbours: always through the caches
+//               4096 32.2 and 35.6, 4000 x 3072 31.5 and 31.6; beyond, 3500 x 4096 38.5 and 37.2, 10000 x 1536 37.8 and 35.9, 4096 x 4096 43.1 and 41.4, 5500 x
+//               3072 41.7 and 39.9, 16000 x 1536 55.6 and 52.5, 7000 x 4096 66.7 and 62.9, but 6000 x 3600 53.1 and 55.3, 9000 x 3600 75.2 and 77.8, and one plan's
+//               launches 4096 x 4096 42.7 and 44.5.  Rows at element alignment share lines with their neighbours: always through the caches
 //   workgroups  192, of four steps of rows at least (every one of them writes a partial row, all of which are read again): 1027 x 1472 10.1, 256 workgroups
-//               11.1; 2564 x 2316 18.7, 128 20.4.  Nontemporally 256 and with four wavefronts to a row 224: 30000 x 1100 70.1 with 256, 76.2 with 192;
-//               9000 x 3600 77.3 with 224, 79.2 with 192
+//               11.1; 2564 x 2316 18.7, 128 20.4.  Nontemporally 256: 30000 x 1100 70.5, 224 71.8, 192 76.0 (12000 x 1280 35.9, 35.7 and 36.5, 16000 x 1536 53.2, 52.5
+//               and 52.8).  With four wavefronts to a row 224, which no shape loses much by: 192, 224 and 256 take 4096 x 4096 41.5, 41.4 and 41.5, 7000 x 4096
+//               63.5, 62.9 and 63.4, 5300 x 4000 49.6, 49.4 and 51.0, 8000 x 2600 50.9, 49.5 and 49.4, 4000 x 3300 37.0, 35.6 and 34.6, 9000 x 3600 80.0, 77.9 and 76.1
 //   workspace   within FS_STATIC_SCRATCH_BYTES, which fs_launch_static has, wherever sixteen rows to a workgroup would be
 bool lnbwd_team_plan(const LnBwdSpec& sp, const LaunchOpts& opt, LnBwdLaunch* out) {
   if (!opt.codegen || opt.wg_size || opt.rows_per_wave || opt.grid) return false;

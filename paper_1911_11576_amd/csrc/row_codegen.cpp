@@ -2526,8 +2526,10 @@ struct Stream {
   //   beyond the register templates, streamed in three passes: fp32 256 x 94000 54.5 and 32.2, 339 x 104576 89.3 and 54.8, 100 x 131071 45.7 and 29.0,
   //               390 x 131072 118 and 97.6; bf16 64 x 117566 18.5 and 10.9, 700 x 120001 121 and 79, 1600 x 93001 209 and 141
   //   16-bit rows of more than 57344 elements, whose values as floats leave a CU one workgroup: 512 x 65536 24.4 and 20.1, 557 x 78776 37.7 and 33.8, 1600 x
-  //               62000 76.4 and 74.7, 1194 x 82944 71.9 and 72.1; not below, where two fit: 1500 x 50000 55.0 and 56.5, 2000 x 33000 46.7 and 47.9.  fp32 rows
+  //               62000 76.7 and 74.8, and no worse than level: 1194 x 82944 71.4 and 71.7; not below, where two fit: 1500 x 50000 55.0 and 56.5, 2000 x 33000 46.7 and 47.9.  fp32 rows
   //               of that kind are held either way: 512 x 88001 74.1 and 74.1
+  //   log-sum-exp alone, which stores no row and needs none kept: fp32 256 x 94000 28.5 and 17.5, 339 x 104576 48.3 and 31.2, 390 x 131072 65.6 and 54.6, bf16 700 x
+  //               120001 74.9 and 40.6, 512 x 65536 13.6 and 12.2
   // A CU has one workgroup, which loads and then stores; two of them with half the registers each, and more LDS, are no faster (bf16 700 x
   // 120001 93, 512 x 131072 57).  Up to three rows of whole chunks keep the form they have, see Gen::long_row_fits.
   bool can_hold(bool in_registers, int per_thread, Gen::Online* online) {
