@@ -197,31 +197,37 @@ template <class Op, int L> __device__ __forceinline__ float group_allreduce(floa
 
 // One thread's part of adding up partial rows (of column reductions): rows slice, slice + NS, .. of `groups`, in that order.
 // The rows lie in memory that another kernel has just written, a microsecond away, and that latency is what bounds the
-// kernels that do this: up to sixteen rows are requested at a time without a branch, the rest in halves of that, with the
-// last row asked for again in place of rows there are none of.  (Batches of eight, and what is no multiple of
-// them row after row, cost 5.9 us over 226 rows of 2316 values and two sums; now 4.6.  Over 256 rows both take the same.)
+// kernels that do this: MOST rows are requested at a time without a branch, the rest in halves of that down to two, with the
+// last row asked for again in place of rows there are none of.  (Batches of eight, and what is no multiple of them row after
+// row, cost 5.9 us over 226 rows of 2316 values and two sums; now 4.6.  Addresses are stepped: a 64-bit product for every row, which the
+// test against the last row had made of them, cost 0.15 us where eight rows a thread are all there are.)
 template <int N, int NS, class Op>
 __device__ __forceinline__ double combine_batch(double acc, const double* p, int64_t stride, int first, int groups, double neutral, Op op) {
+  const double *at = p + first * stride, *last = p + (groups - 1) * stride;
   double v[N];
 #pragma unroll
   for (int i = 0; i < N; ++i) {
-    const int g = first + i * NS;
-    v[i] = p[(int64_t)(g < groups ? g : groups - 1) * stride];
+    v[i] = *(first + i * NS < groups ? at : last);
+    at += NS * stride;
   }
 #pragma unroll
   for (int i = 0; i < N; ++i) acc = op(acc, first + i * NS < groups ? v[i] : neutral);
   return acc;
 }
 
-template <int NS, class Op>
+// MOST = 1: no more rows than slices.
+template <int MOST, int NS, class Op>
 __device__ __forceinline__ double combine_partials(const double* p, int64_t stride, int slice, int groups, double neutral, Op op) {
+  if constexpr (MOST == 1) return slice < groups ? op(neutral, p[slice * stride]) : neutral;
   double acc = neutral;
   int base = 0;
-  for (; base + 8 * NS < groups; base += 16 * NS) acc = combine_batch<16, NS>(acc, p, stride, base + slice, groups, neutral, op);
+  for (; base + MOST / 2 * NS < groups; base += MOST * NS) acc = combine_batch<MOST, NS>(acc, p, stride, base + slice, groups, neutral, op);
   const int left = groups - base;
-  if (left > 4 * NS) acc = combine_batch<8, NS>(acc, p, stride, base + slice, groups, neutral, op);
-  else if (left > 2 * NS) acc = combine_batch<4, NS>(acc, p, stride, base + slice, groups, neutral, op);
-  else if (left > 0) acc = combine_batch<2, NS>(acc, p, stride, base + slice, groups, neutral, op);
+  if (MOST > 8 && left > 4 * NS) acc = combine_batch<8, NS>(acc, p, stride, base + slice, groups, neutral, op);
+  else if (MOST > 4 && left > 2 * NS) acc = combine_batch<4, NS>(acc, p, stride, base + slice, groups, neutral, op);
+  else if (MOST > 2 && left > NS) acc = combine_batch<2, NS>(acc, p, stride, base + slice, groups, neutral, op);
+  // (one row or none for a thread: with none it asks for none)
+  else if (base + slice < groups) acc = op(acc, p[(base + slice) * stride]);
   return acc;
 }
 

@@ -211,7 +211,7 @@ void lnbwd_combine_kernel(const double* __restrict__ part, int groups, int K, in
   const int j = threadIdx.x % SL, slice = threadIdx.x / SL;
   const int s = blockIdx.x * SL + j;
   const double* p = part + s;
-  const double acc = combine_partials<NS>(p, n2, slice, groups, 0.0, [](double a, double b) { return a + b; });
+  const double acc = combine_partials<16, NS>(p, n2, slice, groups, 0.0, [](double a, double b) { return a + b; });
   stage[slice][j] = acc;
   __syncthreads();
   if (slice == 0) {

@@ -36,8 +36,11 @@ struct ColCombineArgs {
 
 // NT threads: a block owns 16 columns of one run of rows (one 128-byte line of every partial row); its
 // threads are NT / 16 slices of that run's partial rows.  256 threads for up to 512 partial rows (measured
-// 0.8 us faster than 1024 on 256 partial rows of 2048 columns), 1024 beyond.
-template <int NT>
+// 0.8 us faster than 1024 on 256 partial rows of 2048 columns), 1024 beyond, 64 for four and fewer (256 runs of 4 rows of 1024
+// values, both kernels of the plan: 28.4 us, with 256 threads 35.3).  MOST rows are requested at a time, see combine_partials; one where
+// there is one for a slice at most (sixteen: 36.3 us there), eight from 768 blocks on, which hide the latency by themselves (257 rows of 12000 values and
+// two sums 30.3 and 30.8, 16 runs of 1024 x 768 13.9 and 14.2; fewer blocks 226 rows of 520 9.6 and 9.4, 2000 x 3000 18.4 and 18.2).
+template <int NT, int MOST>
 __global__ __launch_bounds__(NT) void col_combine_kernel(const double* __restrict__ partial, int groups, int64_t total_groups,
                                                          int64_t cols, int64_t stride, const ColCombineArgs args) {
   constexpr int NS = NT / 16;
@@ -50,8 +53,8 @@ __global__ __launch_bounds__(NT) void col_combine_kernel(const double* __restric
   double s = is_max ? -__builtin_inf() : 0.0;
   if (c < cols) {
     const double* p = partial + ((int64_t)r * total_groups + seg * groups) * stride + c;
-    s = is_max ? combine_partials<NS>(p, stride, slice, groups, s, [](double a, double b) { return fmax(a, b); })
-               : combine_partials<NS>(p, stride, slice, groups, s, [](double a, double b) { return a + b; });
+    s = is_max ? combine_partials<MOST, NS>(p, stride, slice, groups, s, [](double a, double b) { return fmax(a, b); })
+               : combine_partials<MOST, NS>(p, stride, slice, groups, s, [](double a, double b) { return a + b; });
   }
   part[slice][j] = s;
   __syncthreads();
@@ -81,12 +84,15 @@ int col_combine_launch(const void* partial, int groups, int64_t cols, int n_red,
   ColCombineArgs a{};
   for (int r = 0; r < n_red && r < 8; ++r) { a.out[r] = out[r]; a.dtype[r] = dtype[r]; a.is_max[r] = is_max ? is_max[r] : 0; }
   const dim3 grid((unsigned)blocks, (unsigned)n_red);
-  if (groups <= 512)
-    hipLaunchKernelGGL(col_combine_kernel<256>, grid, dim3(256), 0, static_cast<hipStream_t>(stream),
-                       static_cast<const double*>(partial), groups, n_seg * (int64_t)groups, cols, stride ? stride : cols, a);
-  else
-    hipLaunchKernelGGL(col_combine_kernel<1024>, grid, dim3(1024), 0, static_cast<hipStream_t>(stream),
-                       static_cast<const double*>(partial), groups, n_seg * (int64_t)groups, cols, stride ? stride : cols, a);
+  auto launch = [&](auto kernel, int threads) {
+    hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, static_cast<hipStream_t>(stream), static_cast<const double*>(partial), groups, n_seg * (int64_t)groups, cols,
+                       stride ? stride : cols, a);
+  };
+  if (groups <= 4) launch(col_combine_kernel<64, 1>, 64);
+  else if (groups <= 16) launch(col_combine_kernel<256, 1>, 256);
+  else if (groups > 512) launch(col_combine_kernel<1024, 16>, 1024);
+  else if (blocks * n_red >= 768) launch(col_combine_kernel<256, 8>, 256);
+  else launch(col_combine_kernel<256, 16>, 256);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) { *err = std::string("col_combine launch: ") + hipGetErrorString(e); return -1; }
   return 0;

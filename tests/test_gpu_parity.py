@@ -309,6 +309,24 @@ def test_layernorm_bwd_through_the_caches(rows, cols):
     check_against_oracle(graphs.layernorm_bwd(rows, cols), inputs.layernorm_bwd(rows, cols), what=f"lnbwd {rows}x{cols}")
 
 
+PARTIAL_ROWS = (1, 2, 3, 4, 5, 15, 16, 17, 31, 32, 33, 47, 48, 64, 65, 80, 128, 129, 256, 257)
+
+
+@pytest.mark.parametrize("mode,rows,cols,groups", [("stitched", 2048, 520, PARTIAL_ROWS + (272, 273, 400, 511, 512)), ("generated", 2048, 520, PARTIAL_ROWS),
+                                                   ("generated", 520, 6200, (4, 16, 17, 32, 33, 65, 128, 129, 257, 513))])
+def test_any_number_of_partial_rows_is_added_up(mode, rows, cols, groups):
+    """The second kernel reads up to sixteen partial rows a thread at a time, eight where it has many blocks, the rest in batches of half as many down to one, and has
+    a form for four rows and for sixteen: the edges of them all, through the workgroups that a launch option names."""
+    announce(f"partial rows {mode} {rows}x{cols}")
+    ops, ins = graphs.layernorm_bwd(rows, cols), inputs.layernorm_bwd(rows, cols)
+    want = interp.run(ops, ins)
+    for n in groups:
+        with Plan(ops, mode, grid=n) as p:
+            assert f" {n} partial rows" in p.describe()
+        for k, (a, b) in enumerate(zip(run_gpu(ops, ins, mode, grid=n), want)):
+            assert_close(a, b, 1e-5, f"{n} partial rows, output {k}")
+
+
 @pytest.mark.parametrize("rows,cols,threads,keep", [
     (21001, 200, 512, (0, 1, 2)), (32769, 132, 512, (0, 1, 2)), (18001, 244, 512, (0, 1, 2)), (24601, 228, 256, (0, 1, 2)), (16500, 256, 256, (0, 1, 2)),
     (9001, 500, 256, (0, 1, 2)), (8200, 512, 256, (0, 1, 2)), (5701, 740, 256, (0, 1, 2)), (5500, 768, 256, (0, 1, 2)), (4301, 1000, 256, (0, 1, 2)),
